@@ -16,15 +16,12 @@ constexpr int kSelThreads = 256;       // select / compact-plan workgroup
 constexpr int kMoveThreads = 256;
 constexpr int kMaxChunks = 16;         // a list is split over at most this many workgroups
 
-// Attend launch plan: a workgroup handles (sequence, head group, token chunk).
+// Attend launch plan: a workgroup handles (sequence, head, token chunk).
 struct AttendPlan {
-  int lanes_per_row;    // lanes that cover one (token, head) row with 16-byte loads
-  bool head_major;      // [head][slot][D] cache: a wave-load takes consecutive tokens of ONE head
-  int heads_per_group;  // heads one workgroup covers: 1 (head-major) or rows-per-wave-load (slot-major)
-  int n_head_groups;    // ceil(n_heads / heads_per_group)
-  int n_chunks;         // token chunks per sequence (grid.x); every sequence splits its own count evenly
+  int n_chunks;         // token chunks per list; every sequence splits its own count evenly
   int chunk_max;        // upper bound of tokens in one chunk, + 1
-  int waves;            // waves per attend workgroup: 4, 8 or 16
+  int reserved_chunks;  // chunks per list the workspace has room for (>= n_chunks)
+  int waves;            // waves per attend workgroup: 4 or 8
 };
 
 // Rows of adsa_seq.score: one accumulator per head for ATTN_MASS (the rank of a slot is their sum),
@@ -41,7 +38,7 @@ constexpr int kVcosTags = 4;      // floats after u in adsa_seq.vcos_u: [0] 1 + 
 
 // Workspace layout (byte offsets from a 256-byte aligned base).
 struct Workspace {
-  size_t counters_off;     // int32 [n_seq][n_head_groups]  arrival counters (zero between launches)
+  size_t counters_off;     // int32 [n_seq][head groups]  arrival counters of split grouped-query launches (zero between launches)
   size_t persistent_bytes; // leading bytes that adsa_workspace_init zeroes and every launch leaves zero
   size_t logits_off;       // float [n_seq][n_heads][lg_stride]  scaled logits in log2 units
   size_t part_ml_off;      // float [n_seq][n_heads][n_chunks][2]   (m, l) per chunk
