@@ -12,7 +12,6 @@
 namespace adsa {
 
 constexpr int kWave = 64;
-constexpr int kSelThreads = 256;       // select / compact-plan workgroup
 constexpr int kMoveThreads = 256;
 constexpr int kMaxChunks = 16;         // a list is split over at most this many workgroups
 

@@ -11,27 +11,29 @@
 //                    the hole in order or leaving it to the incoming token.
 //  k_compact_move  : in-place, order-preserving move of the surviving K and V rows.
 //
-// One workgroup of 256 threads owns one sequence in the first two kernels; everything it ranks
-// lives in LDS (keys 4 B/slot), so the score array is read from HBM exactly once.
+// One workgroup owns one sequence in the first two kernels.  Its slots live in registers, S per thread (slot = u * NT +
+// thread), from the one read of the score array to the last write: what crosses threads is a histogram, at most 64
+// keys and one pair of counts per wave.  Both kernels are chains of dependent latencies (record -> scores -> a handful
+// of barriers -> stores) rather than work, so the number of barriers and of memory round trips is what they are built around.
+#include "adsa_device.h"
 #include "adsa_internal.h"
 #include "adsa_partition.h"
 
 namespace adsa {
 namespace {
 
-constexpr uint8_t kFixed = 0;      // prefix / local / protected row: always kept
-constexpr uint8_t kSkip = 1;       // a freed slot (ADSA_EVICT_REUSE_SLOT): in no list
-constexpr uint8_t kCand = 2;       // competes for the budget
+constexpr int kBins = 512, kBinBits = 9;
 
-// LDS of one ranking workgroup.  key[] and cls[] are sized by the launch's cap (dynamic LDS:
-// 5 bytes per slot), so small caches leave room for many workgroups per CU.
+// LDS of one ranking workgroup (9 KB).
 struct RankShared {
-  uint32_t hist[256];
-  uint32_t wave_tot[kSelThreads / kWave];
-  uint32_t bcast[4];
+  uint32_t hist[4][kBins];           // one histogram per narrowing step: 32-bit keys, 9 bits a step
+  uint32_t list[kWave];              // the keys of the bin the threshold lies in, once they fit a wave
+  uint32_t list_n;
+  uint32_t red[2][3][16];            // per wave: candidates (bit 31: malformed entry), largest key, largest ~key
+  uint32_t newest[16];               // per wave: 1 + newest position among the candidates with the smallest key
+  uint32_t tot[128];                 // per (u, wave): kept | equal << 16
+  uint32_t first;                    // first slot that is not kept
 };
-
-static size_t rank_lds_bytes(int cap) { return (size_t)cap * 4 + (((size_t)cap + 15) / 16) * 16; }
 
 // Larger key == kept first.  -0 is folded into +0 so that they tie (IEEE equality).
 __device__ __forceinline__ uint32_t order_key(float x, bool keep_largest) {
@@ -41,80 +43,177 @@ __device__ __forceinline__ uint32_t order_key(float x, bool keep_largest) {
   return keep_largest ? u : ~u;
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t x) {       // lanes without a source (or masked out) get 0
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+// row_shr:1, 2, 4, 8 inside the 16-lane rows, then lane 15 -> next row, lane 31 -> upper half
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint32_t o = __shfl_up(v, d, kWave);
-    if (lane >= d) v += o;
-  }
+  v += dpp_u<0x111, 0xF>(v); v += dpp_u<0x112, 0xF>(v); v += dpp_u<0x114, 0xF>(v); v += dpp_u<0x118, 0xF>(v);
+  v += dpp_u<0x142, 0xA>(v); v += dpp_u<0x143, 0xC>(v);
   return v;
 }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {     // of unsigned values; uniform result
+  v = max(v, dpp_u<0x111, 0xF>(v)); v = max(v, dpp_u<0x112, 0xF>(v)); v = max(v, dpp_u<0x114, 0xF>(v)); v = max(v, dpp_u<0x118, 0xF>(v));
+  v = max(v, dpp_u<0x142, 0xA>(v)); v = max(v, dpp_u<0x143, 0xC>(v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+__device__ __forceinline__ uint32_t lane_of(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); }
 
-// Exclusive prefix sum of one value per thread over the 256-thread workgroup; *total gets the sum.
-__device__ __forceinline__ uint32_t block_excl_scan(RankShared& sh, uint32_t v, uint32_t* total) {
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  uint32_t incl = wave_incl_scan(v);
-  __syncthreads();                                   // wave_tot may still be read from a previous scan
-  if (lane == kWave - 1) sh.wave_tot[wave] = incl;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kSelThreads / kWave; ++w) {
-    uint32_t t = sh.wave_tot[w];
-    if (w < wave) base += t;
-    tot += t;
-  }
-  *total = tot;
-  return base + incl - v;
+// zeroes what the ranking adds to; the barrier inside block_stats orders it before the first addition
+template <int NT>
+__device__ __forceinline__ void rank_clear(RankShared& sh) {
+  uint4* const h = reinterpret_cast<uint4*>(&sh.hist[0][0]);
+  for (int i = threadIdx.x; i < 4 * kBins / 4; i += NT) h[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (threadIdx.x == 0) { sh.list_n = 0u; sh.first = 0xFFFFFFFFu; }
 }
 
-// Eq. 4 as a threshold: returns T and need_eq such that {key > T} plus the first need_eq slots
-// with key == T (ascending slot) are exactly the `want` best candidates.
-__device__ void radix_threshold(RankShared& sh, const uint32_t* key, const uint8_t* cls, int n, uint32_t n_cand,
-                                uint32_t want, uint32_t* T_out, uint32_t* need_eq_out) {
-  if (want == 0) { *T_out = 0xFFFFFFFFu; *need_eq_out = 0; return; }
-  if (want >= n_cand) { *T_out = 0u; *need_eq_out = 0xFFFFFFFFu; return; }
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  uint32_t prefix = 0, mask = 0, remaining = want;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    sh.hist[tid] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += kSelThreads) {
-      uint32_t k = key[i];
-      if (cls[i] == kCand && (k & mask) == prefix) atomicAdd(&sh.hist[(k >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // lane l owns digits 255-4l .. 252-4l; scan from the largest digit down
-      uint32_t c[4];
-      uint32_t local = 0;
+struct Stats { uint32_t n_cand, kmin, kmax; bool bad; };
+
+// candidates of the workgroup, their key range and whether any entry is malformed; one barrier (AT: the words it uses)
+template <int NT, int S, int AT = 0>
+__device__ __forceinline__ Stats block_stats(RankShared& sh, const uint32_t (&key)[S], uint32_t candm, bool bad) {
+  constexpr int NW = NT / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
+  uint32_t n = 0, hi = 0, nlo = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { c[k] = sh.hist[255 - 4 * lane - k]; local += c[k]; }
-      uint32_t incl = wave_incl_scan(local);
-      unsigned long long hit = __ballot(incl >= remaining);
-      int first = __ffsll((long long)hit) - 1;        // exists: remaining <= candidates under prefix
-      if (lane == first) {
-        uint32_t run = incl - local;
-        int digit = 0;
-        uint32_t rem = remaining;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (run + c[k] >= remaining) { digit = 255 - 4 * lane - k; rem = remaining - run; break; }
-          run += c[k];
-        }
-        sh.bcast[0] = (uint32_t)digit;
-        sh.bcast[1] = rem;
-      }
-    }
-    __syncthreads();
-    prefix |= sh.bcast[0] << shift;
-    mask |= 0xFFu << shift;
-    remaining = sh.bcast[1];
-    __syncthreads();
+  for (int u = 0; u < S; ++u) {
+    const bool c = (candm >> u) & 1u;
+    n += (uint32_t)__popcll(__ballot(c));
+    hi = max(hi, c ? key[u] : 0u);
+    nlo = max(nlo, c ? ~key[u] : 0u);
   }
-  *T_out = prefix;
-  *need_eq_out = remaining;
+  hi = wave_max(hi);
+  nlo = wave_max(nlo);
+  if (__ballot(bad) != 0) n |= 0x80000000u;
+  if (lane == 0) { sh.red[AT][0][wave] = n; sh.red[AT][1][wave] = hi; sh.red[AT][2][wave] = nlo; }
+  __syncthreads();
+  Stats st = {0u, 0u, 0u, false};
+  uint32_t a = 0, flags = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const uint32_t x = sh.red[AT][0][w];
+    flags |= x;
+    a += x & 0x7FFFFFFFu;
+    st.kmax = max(st.kmax, sh.red[AT][1][w]);
+    st.kmin = max(st.kmin, sh.red[AT][2][w]);
+  }
+  st.n_cand = a;
+  st.kmin = ~st.kmin;
+  st.bad = (flags >> 31) != 0;
+  return st;
+}
+
+// Eq. 4 as a threshold: returns T and need_eq such that {key > T} plus the first need_eq slots with key == T (ascending
+// slot) are exactly the `want` best candidates.  Each step spreads the remaining key range [lo, hi] over 512 bins and
+// keeps the bin the threshold lies in, until that bin is taken whole, holds one value, or fits one wave, which then ranks its
+// keys against each other.  Keys of one magnitude need one step and the ranking: 2 barriers (a radix select over all 32 key
+// bits took 16); the bins follow the float's exponent, so outliers and infinities cost at most the 4 steps of the key
+// width.  Every wave works the scan out for itself instead of waiting for one to broadcast it.
+template <int NT, int S>
+__device__ __forceinline__ void top_threshold(RankShared& sh, const uint32_t (&key)[S], uint32_t in, const Stats& st, uint32_t want,
+                                              uint32_t* T, uint32_t* need_eq) {
+  *T = 0xFFFFFFFFu; *need_eq = 0u;
+  if (want == 0) return;
+  *T = 0u; *need_eq = 0xFFFFFFFFu;
+  if (want >= st.n_cand) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t lo = st.kmin, hi = st.kmax, r = want;             // the r best of the candidates inside [lo, hi] are wanted
+  for (int it = 0; lo != hi; ++it) {
+    const int shift = max(0, (32 - __builtin_clz(hi - lo)) - kBinBits);
+    uint32_t* const hist = sh.hist[it];
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if ((in >> u) & 1u) atomicAdd(&hist[(key[u] - lo) >> shift], 1u);
+    __syncthreads();
+    // lane l owns bins 511-8l .. 504-8l; scan from the largest down
+    const uint4 c1 = reinterpret_cast<const uint4*>(hist)[2 * (kWave - 1 - lane)], c0 = reinterpret_cast<const uint4*>(hist)[2 * (kWave - 1 - lane) + 1];
+    const uint32_t c[8] = {c0.w, c0.z, c0.y, c0.x, c1.w, c1.z, c1.y, c1.x};
+    const uint32_t local = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+    const uint32_t incl = wave_incl_scan(local);
+    const int first = __ffsll((long long)__ballot(incl >= r)) - 1;     // exists: r <= candidates in the range
+    uint32_t run = incl - local, digit = 0, above = 0, n_bin = 0;
+    bool found = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const bool here = !found && run + c[k] >= r;
+      if (here) { digit = (uint32_t)(kBins - 1 - 8 * lane - k); above = run; n_bin = c[k]; found = true; }
+      run += c[k];
+    }
+    digit = lane_of(digit, first);
+    r -= lane_of(above, first);
+    n_bin = lane_of(n_bin, first);
+    const uint32_t span = (1u << shift) - 1u;
+    lo += digit << shift;
+    hi = lo + min(hi - lo, span);
+    if (r == n_bin) {                                        // the bin is taken whole
+      if (lo == 0u) { *T = 0u; *need_eq = 0xFFFFFFFFu; }
+      else { *T = lo - 1u; *need_eq = 0u; }
+      return;
+    }
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if (key[u] < lo || key[u] > hi) in &= ~(1u << u);
+    if (n_bin <= kWave) {
+#pragma unroll
+      for (int u = 0; u < S; ++u)
+        if ((in >> u) & 1u) sh.list[atomicAdd(&sh.list_n, 1u)] = key[u];
+      __syncthreads();
+      const uint32_t k = lane < (int)n_bin ? sh.list[lane] : 0u;
+      uint32_t gt = 0, ge = 0;
+      for (int j = 0; j < (int)n_bin; ++j) {
+        const uint32_t kj = lane_of(k, j);
+        gt += kj > k;
+        ge += kj >= k;
+      }
+      const int at = __ffsll((long long)__ballot(lane < (int)n_bin && gt < r && r <= ge)) - 1;
+      *T = lane_of(k, at);
+      *need_eq = r - lane_of(gt, at);
+      return;
+    }
+  }
+  *T = lo;
+  *need_eq = r;
+}
+
+// Places of the kept slots in ascending slot order: kept are those of `sure` and the first need_eq of `eq`.  dest[u] and bit u
+// of the result for this thread's slots; *count gets the number kept.  One barrier.
+template <int NT, int S>
+__device__ __forceinline__ uint32_t place_kept(RankShared& sh, uint32_t sure, uint32_t eq, uint32_t need_eq, uint32_t (&dest)[S], uint32_t* count) {
+  constexpr int NW = NT / kWave, E = S * NW;
+  static_assert(E <= 2 * kWave, "one or two entries per lane");
+  const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
+  unsigned long long am[S], em[S];
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    am[u] = __ballot((sure >> u) & 1u);
+    em[u] = __ballot((eq >> u) & 1u);
+    if (lane == 0) sh.tot[u * NW + wave] = (uint32_t)__popcll(am[u]) | ((uint32_t)__popcll(em[u]) << 16);
+  }
+  __syncthreads();
+  const uint32_t x0 = lane < E ? sh.tot[lane] : 0u;
+  const uint32_t i0 = wave_incl_scan(x0);
+  uint32_t total = lane_of(i0, kWave - 1), x1 = 0, i1 = 0;
+  if constexpr (E > kWave) {
+    x1 = kWave + lane < E ? sh.tot[kWave + lane] : 0u;
+    i1 = wave_incl_scan(x1) + total;
+    total = lane_of(i1, kWave - 1);
+  }
+  uint32_t take = 0;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    const int at = u * NW + wave;
+    const uint32_t base = (E > kWave && at >= kWave) ? lane_of(i1 - x1, at - kWave) : lane_of(i0 - x0, min(at, kWave - 1));
+    const uint32_t e = (base >> 16) + lanes_below(em[u]);
+    dest[u] = (base & 0xFFFFu) + lanes_below(am[u]) + min(e, need_eq);
+    if (((sure >> u) & 1u) || (((eq >> u) & 1u) && e < need_eq)) take |= 1u << u;
+  }
+  *count = (total & 0xFFFFu) + min(total >> 16, need_eq);
+  return take;
 }
 
 __device__ __forceinline__ int effective_budget(const adsa_seq& q, int s) {
@@ -132,36 +231,67 @@ struct LaunchShape {
   long long slot_stride_b, head_stride_b;    // bytes
 };
 
-// Ranks of kRankSlots slots at once (4 when few workgroups run and memory latency is what counts, 1 when the launch
-// fills the chip anyway and registers are better spent on occupancy): v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32
-// adds (the order one slot at a time would use); slots with on[u] false give 0 and touch no memory.  The loads of all
-// slots, and of the next batch of rows while one batch is added, are in flight together: a workgroup ranks its
-// sequence in two or three memory round trips instead of one per slot and batch.
-constexpr int kRankRows = 8;
-template <int kRankSlots>
-__device__ __forceinline__ void rank_values(const float* score, int rows, int cap, const int* idx, const bool* on, float* v) {
-  float cur[kRankSlots][kRankRows], nxt[kRankSlots][kRankRows];
-  auto load_rows = [&](int r0, float (&t)[kRankSlots][kRankRows]) {
+// v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32 adds.  The loads of all slots and of two
+// batches of rows are in flight together: one memory round trip for up to 2 * RB + 1 rows.
+template <int S>
+__device__ __forceinline__ void rank_values(const gfloat* score, int rows, int cap, const int (&idx)[S], float (&v)[S]) {
+  constexpr int RB = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
+  float cur[S][RB], nxt[S][RB];
+  auto load_rows = [&](int r0, float (&t)[S][RB]) {
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u)
+    for (int k = 0; k < RB; ++k)
 #pragma unroll
-      for (int k = 0; k < kRankRows; ++k)
-        t[u][k] = (on[u] && r0 + k < rows) ? score[(size_t)(r0 + k) * cap + idx[u]] : 0.0f;
+      for (int u = 0; u < S; ++u) t[u][k] = score[(size_t)min(r0 + k, rows - 1) * cap + idx[u]];    // (rows past the last: not added)
   };
 #pragma unroll
-  for (int u = 0; u < kRankSlots; ++u) v[u] = on[u] ? score[idx[u]] : 0.0f;
-  if (rows > 1) load_rows(1, cur);
-  for (int r = 1; r < rows; r += kRankRows) {
-    if (r + kRankRows < rows) load_rows(r + kRankRows, nxt);
+  for (int u = 0; u < S; ++u) v[u] = score[idx[u]];
+  if (rows == 1) return;
+  load_rows(1, cur);
+  for (int r = 1; r < rows; r += RB) {
+    if (r + RB < rows) load_rows(r + RB, nxt);
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u)
+    for (int k = 0; k < RB; ++k)
 #pragma unroll
-      for (int k = 0; k < kRankRows; ++k)
-        if (r + k < rows) v[u] += cur[u][k];
+      for (int u = 0; u < S; ++u) v[u] = r + k < rows ? v[u] + cur[u][k] : v[u];
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u)
+    for (int u = 0; u < S; ++u)
 #pragma unroll
-      for (int k = 0; k < kRankRows; ++k) cur[u][k] = nxt[u][k];
+      for (int k = 0; k < RB; ++k) cur[u][k] = nxt[u][k];
+  }
+}
+
+// The fused V-cosine form's rows: rows 2h and 2h+1 hold head h's share of |v|^2 and of v.u.  Both sums over the heads,
+// ascending, with two batches of loads in flight like rank_values.
+template <int S>
+__device__ __forceinline__ void rank_pairs(const gfloat* score, int heads, int cap, const int (&idx)[S], float (&ss)[S], float (&dot)[S]) {
+  constexpr int RB = S == 1 ? 8 : S <= 3 ? 4 : S == 4 ? 2 : 1;
+  float a[2][S][RB], b[2][S][RB];
+  auto load_rows = [&](int h0, float (&x)[S][RB], float (&y)[S][RB]) {
+#pragma unroll
+    for (int k = 0; k < RB; ++k)
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const size_t r = (size_t)(2 * min(h0 + k, heads - 1)) * cap + idx[u];
+        x[u][k] = score[r];
+        y[u][k] = score[r + cap];
+      }
+  };
+#pragma unroll
+  for (int u = 0; u < S; ++u) ss[u] = dot[u] = 0.0f;
+  load_rows(0, a[0], b[0]);
+  for (int h = 0; h < heads; h += RB) {
+    if (h + RB < heads) load_rows(h + RB, a[1], b[1]);
+#pragma unroll
+    for (int k = 0; k < RB; ++k)
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        ss[u] = h + k < heads ? ss[u] + a[0][u][k] : ss[u];
+        dot[u] = h + k < heads ? dot[u] + b[0][u][k] : dot[u];
+      }
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+#pragma unroll
+      for (int k = 0; k < RB; ++k) { a[0][u][k] = a[1][u][k]; b[0][u][k] = b[1][u][k]; }
   }
 }
 
@@ -169,21 +299,17 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
   return mode == ADSA_SCORE_ATTN_MASS || mode == ADSA_SCORE_EXT_LARGEST;
 }
 
-template <int kRankSlots>
-__global__ __launch_bounds__(kSelThreads) void k_select(LaunchShape L, adsa_seq* seqs, int32_t* sel_idx,
-                                                       int32_t* sel_cnt, int plan_append) {
-  __shared__ RankShared sh;
-  extern __shared__ uint32_t s_rank_dyn[];
-  uint32_t* key = s_rank_dyn;                                  // [cap] order-preserving keys
-  uint8_t* cls = reinterpret_cast<uint8_t*>(s_rank_dyn + L.cap);   // [cap]
-  __shared__ int s_bad;
+template <int NT, int S>
+__global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append, LaunchShape L) {
+  __shared__ __align__(16) RankShared sh;
   const int b = blockIdx.x, tid = threadIdx.x;
   adsa_seq& sq = seqs[b];
+  const gint* const pos = (const gint*)sq.pos;
+  gfloat* const score = (gfloat*)sq.score;
   const int s = sq.step;
   int n = sq.n_res;
   const int status_in = sq.status;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
+  rank_clear<NT>(sh);                                        // (while the record is on its way)
   if (s < 0 || status_in != 0) { if (tid == 0) { sel_cnt[b] = 0; sq.pending_slot = -1; } return; }
   if (n < 0 || n > L.cap || s > L.grid_h * L.grid_w) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
@@ -206,79 +332,60 @@ __global__ __launch_bounds__(kSelThreads) void k_select(LaunchShape L, adsa_seq*
     }
   }
 
-  // ---- Eq. 1: partition, keys into LDS
+  // ---- Eq. 1: partition, keys into registers
   const QueryCell cell = make_query_cell(sq, s, L.grid_w, L.R, L.w, L.recent_m);
-  const bool largest = keep_largest_of(L.score_mode);
-  const bool ranked = L.evict_policy == ADSA_EVICT_ROW_END;
-  uint32_t my_cand = 0;
-  for (int i0 = tid; i0 < n; i0 += kRankSlots * kSelThreads) {
-    int idx[kRankSlots], posv[kRankSlots];
-    bool in[kRankSlots], planned[kRankSlots], rk[kRankSlots];
-    float rv[kRankSlots];
+  int idx[S], posv[S];
+  float rank[S];
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u) {
-      const int i = i0 + u * kSelThreads;
-      in[u] = i < n;
-      idx[u] = in[u] ? i : n - 1;
-      planned[u] = i == slot_new;                   // the slot the query token will occupy
-      posv[u] = sq.pos[idx[u]];
-      // (evict-one-when-full policies attend every candidate: their rank is never looked at)
-      rk[u] = in[u] && ranked && !planned[u];
-    }
-    rank_values<kRankSlots>(sq.score, L.score_rows, L.cap, idx, rk, rv);
-#pragma unroll
-    for (int u = 0; u < kRankSlots; ++u) {
-      if (!in[u]) continue;
-      const int i = idx[u];
-      const bool freed = i == hole && !planned[u];  // evicted, not yet reused: nobody attends it
-      const int c = (planned[u] || freed) ? 0 : select_class(cell, posv[u]);
-      if (c < 0) s_bad = 1;
-      cls[i] = freed ? kSkip : c == 1 ? kCand : kFixed;
-      key[i] = order_key(rv[u], largest);
-      my_cand += (c == 1);
-    }
+  for (int u = 0; u < S; ++u) {
+    idx[u] = min(u * NT + tid, n - 1);
+    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
+    rank[u] = 0.0f;
   }
-  uint32_t n_cand;
-  block_excl_scan(sh, my_cand, &n_cand);   // also orders the LDS writes above before the reads below
-  if (s_bad) {
+  // (evict-one-when-full policies attend every candidate: their rank is never looked at)
+  if (n > 0 && L.evict_policy == ADSA_EVICT_ROW_END) rank_values<S>(score, L.score_rows, L.cap, idx, rank);
+  const bool largest = keep_largest_of(L.score_mode);
+  uint32_t key[S], candm = 0, fixedm = 0;
+  bool bad = false;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    const int i = u * NT + tid;
+    const bool in = i < n, planned = i == slot_new;          // the slot the query token will occupy
+    const bool freed = i == hole && !planned;                // evicted, not yet reused: nobody attends it
+    const int c = (planned || freed) ? 0 : select_class(cell, posv[u]);
+    key[u] = order_key(rank[u], largest);
+    bad |= in && c < 0;
+    if (in && c == 1) candm |= 1u << u;
+    if (in && c != 1 && !freed) fixedm |= 1u << u;
+  }
+  const Stats st = block_stats<NT, S>(sh, key, candm, bad);
+  if (st.bad) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
     return;
   }
 
   // ---- Eq. 4: threshold of the top-B candidates
   // the streaming policy attends everything resident (context == cache, Tables 1-2)
-  const uint32_t B = L.evict_policy != ADSA_EVICT_ROW_END ? n_cand : (uint32_t)effective_budget(sq, s);
+  const uint32_t B = L.evict_policy != ADSA_EVICT_ROW_END ? st.n_cand : (uint32_t)effective_budget(sq, s);
   uint32_t T, need_eq;
-  radix_threshold(sh, key, cls, n, n_cand, B < n_cand ? B : n_cand, &T, &need_eq);
+  top_threshold<NT, S>(sh, key, candm, st, B < st.n_cand ? B : st.n_cand, &T, &need_eq);
 
-  // ---- ascending slot list: contiguous run of slots per thread, packed (kept | equal<<16) scan
-  const int per = (n + kSelThreads - 1) / kSelThreads;
-  const int lo = tid * per, hi = min(n, lo + per);
-  uint32_t a = 0, e = 0;
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t k = key[i];
-    const uint8_t c = cls[i];
-    a += (c == kFixed) || (c == kCand && k > T);
-    e += c == kCand && (k == T);
+  // ---- ascending slot list
+  uint32_t sure = fixedm, eq = 0, dest[S], cnt;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (((candm >> u) & 1u) && key[u] > T) sure |= 1u << u;
+    if (((candm >> u) & 1u) && key[u] == T) eq |= 1u << u;
   }
-  uint32_t total;
-  uint32_t ex = block_excl_scan(sh, a | (e << 16), &total);
-  uint32_t a_run = ex & 0xFFFFu, e_run = ex >> 16;
+  const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &cnt);
   int32_t* out = sel_idx + (size_t)b * L.sel_cap;
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t k = key[i];
-    const uint8_t c = cls[i];
-    bool take = (c == kFixed) || (c == kCand && k > T);
-    const bool eq = c == kCand && (k == T);
-    const uint32_t dest = a_run + min(e_run, need_eq);
-    if (eq) { take = e_run < need_eq; ++e_run; } else if (take) ++a_run;
-    if (take && dest < (uint32_t)L.sel_cap) out[dest] = i;
-  }
-  const uint32_t cnt = (total & 0xFFFFu) + min(total >> 16, need_eq);
+#pragma unroll
+  for (int u = 0; u < S; ++u)
+    if (((take >> u) & 1u) && dest[u] < (uint32_t)L.sel_cap) out[dest[u]] = u * NT + tid;
   const bool ok = cnt <= (uint32_t)L.sel_cap;
   const bool reserve = ok && slot_new >= 0;          // commit the planned append: the slot now holds the query token
   if (reserve)
-    for (int r = tid; r < L.score_rows; r += kSelThreads) sq.score[(size_t)r * L.cap + slot_new] = 0.0f;
+    for (int r = tid; r < L.score_rows; r += NT) score[(size_t)r * L.cap + slot_new] = 0.0f;
   if (tid == 0) {
     if (!ok) { sq.status = status_in | ADSA_SEQ_SEL_OVERFLOW; sel_cnt[b] = 0; sq.pending_slot = -1; }
     else {
@@ -294,16 +401,15 @@ __global__ __launch_bounds__(kSelThreads) void k_select(LaunchShape L, adsa_seq*
 }
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
-template <int kRankSlots>
-__global__ __launch_bounds__(kSelThreads) void k_compact_plan(LaunchShape L, adsa_seq* seqs,
-                                                             int32_t* keep_map, int32_t* plan,
-                                                             int advance_step, const float* vcos_s) {
-  __shared__ RankShared sh;
-  extern __shared__ uint32_t s_rank_dyn[];
-  uint32_t* key = s_rank_dyn;                                  // [cap] keys, later the keep map
-  uint8_t* cls = reinterpret_cast<uint8_t*>(s_rank_dyn + L.cap);
-  const int b = blockIdx.x, tid = threadIdx.x;
+template <int NT, int S>
+__global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* keep_map, int32_t* plan, int advance_step,
+                                                    const float* vcos_s, LaunchShape L) {
+  __shared__ __align__(16) RankShared sh;
+  constexpr int NW = NT / kWave;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
   adsa_seq& sq = seqs[b];
+  gint* const pos = (gint*)sq.pos;
+  gfloat* const score = (gfloat*)sq.score;
   const int s = sq.step, n = sq.n_res, W = L.grid_w;
   const bool active = s >= 0 && sq.status == 0;
   // per-row policy: act when the query token closed a grid row; streaming policy (Section 4.2 as
@@ -321,171 +427,125 @@ __global__ __launch_bounds__(kSelThreads) void k_compact_plan(LaunchShape L, ads
     return;
   }
   const QueryCell cell = make_query_cell(sq, s, W, L.R, L.w, L.recent_m);
-  const bool largest = keep_largest_of(L.score_mode);
-  uint32_t my_rest = 0;
-  for (int i0 = tid; i0 < n; i0 += kRankSlots * kSelThreads) {
-    int idx[kRankSlots], posv[kRankSlots];
-    bool in[kRankSlots], rk[kRankSlots];
-    float rv[kRankSlots];
+  const bool largest = keep_largest_of(L.score_mode), fused = L.score_mode == ADSA_SCORE_VCOS_FUSED;
+  int idx[S], posv[S];
+  float rank[S], dot[S];
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u) {
-      const int i = i0 + u * kSelThreads;
-      in[u] = i < n;
-      idx[u] = in[u] ? i : n - 1;
-      posv[u] = sq.pos[idx[u]];
-      rk[u] = in[u] && L.score_mode != ADSA_SCORE_VCOS_FUSED;      // (fused form: keys of the candidates follow once N is known)
-    }
-    rank_values<kRankSlots>(sq.score, L.score_rows, L.cap, idx, rk, rv);
+  for (int u = 0; u < S; ++u) {
+    idx[u] = min(u * NT + tid, n - 1);
+    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
+    rank[u] = dot[u] = 0.0f;
+  }
+  rank_clear<NT>(sh);
+  // Fused form: Eq. 3 from what the last attention launch left per (head, slot): S_i = (v^_i.u - v^_i.v^_i)/(N-1) with
+  // |v_i|^2 and v_i.u summed over the heads' rows (ascending).  If those rows do not belong to this
+  // step, the two-pass computation has just written S_i to the workspace instead.
+  bool rows_ok = false;
+  if (fused && n > 0) {
+    const gfloat* tags = sq.vcos_u ? (const gfloat*)sq.vcos_u + (size_t)L.n_heads * L.head_dim : nullptr;
+    rows_ok = tags && tags[1] == (float)(s + 1);
+    if (rows_ok) rank_pairs<S>(score, L.n_heads, L.cap, idx, rank, dot);
+    else {
 #pragma unroll
-    for (int u = 0; u < kRankSlots; ++u) {
-      if (!in[u]) continue;
-      const int i = idx[u];
-      // streaming: the partition of the incoming query (its local region must survive)
-      const int c = streaming ? (select_class(cell, posv[u]) == 1 ? 1 : 0) : evict_class(cell, posv[u]);
-      cls[i] = c == 1 ? kCand : kFixed;
-      key[i] = L.score_mode == ADSA_SCORE_VCOS_FUSED ? 0u : order_key(rv[u], largest);
-      my_rest += (c == 1);
+      for (int u = 0; u < S; ++u) rank[u] = ((const gfloat*)vcos_s)[(size_t)b * L.cap + idx[u]];
     }
+  } else if (n > 0) {
+    rank_values<S>(score, L.score_rows, L.cap, idx, rank);
   }
-  uint32_t n_rest;
-  block_excl_scan(sh, my_rest, &n_rest);
-  if (L.score_mode == ADSA_SCORE_VCOS_FUSED) {
-    // Eq. 3 from what the last attention launch left per (head, slot): S_i = (v^_i.u - v^_i.v^_i)/(N-1) with
-    // |v_i|^2 and v_i.u summed over the heads' rows (ascending).  If those rows do not belong to this
-    // step, the two-pass computation has just written S_i to the workspace instead.
-    const float* tags = sq.vcos_u ? sq.vcos_u + (size_t)L.n_heads * L.head_dim : nullptr;
-    const bool rows_ok = tags && tags[1] == (float)(s + 1);
-    const float inv_nm1 = n_rest > 1 ? 1.0f / (float)(n_rest - 1) : 0.0f;
-    for (int i = tid; i < n; i += kSelThreads) {
-      if (cls[i] != kCand) continue;
-      float S;
-      if (rows_ok) {
-        float ss = 0.0f, dot = 0.0f;
-        for (int hh = 0; hh < L.n_heads; ++hh) {
-          ss += sq.score[(size_t)(2 * hh) * L.cap + i];
-          dot += sq.score[(size_t)(2 * hh + 1) * L.cap + i];
-        }
-        const float inv = 1.0f / fmaxf(sqrtf(ss), 1e-8f);
-        S = (dot * inv - ss * inv * inv) * inv_nm1;
-      } else {
-        S = vcos_s[(size_t)b * L.cap + i];
-      }
-      key[i] = order_key(S, false);
+  uint32_t key[S], restm = 0, in = 0;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    // streaming: the partition of the incoming query (its local region must survive)
+    const int c = streaming ? (select_class(cell, posv[u]) == 1 ? 1 : 0) : evict_class(cell, posv[u]);
+    if (u * NT + tid < n) in |= 1u << u;
+    if (((in >> u) & 1u) && c == 1) restm |= 1u << u;
+    key[u] = fused ? 0u : order_key(rank[u], largest);
+  }
+  Stats st = block_stats<NT, S>(sh, key, restm, false);
+  if (fused) {                                               // the keys need N, the number of candidates
+    const float inv_nm1 = st.n_cand > 1 ? 1.0f / (float)(st.n_cand - 1) : 0.0f;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const float ss = rank[u], inv = 1.0f / fmaxf(sqrtf(ss), 1e-8f);
+      key[u] = order_key(rows_ok ? (dot[u] * inv - ss * inv * inv) * inv_nm1 : rank[u], false);
     }
-    __syncthreads();
+    st = block_stats<NT, S, 1>(sh, key, restm, false);
   }
+  int32_t* const map = keep_map + (size_t)b * L.cap;
   if (reuse) {
     // Evict the candidate ranked last -- smallest key, among equals the newest position -- and leave
     // everything where it is: the freed slot goes to the incoming token.
-    unsigned long long best = ~0ull;                  // (key, ~pos): the minimum is the victim
-    int best_i = -1;
-    for (int i = tid; i < n; i += kSelThreads) {
-      if (cls[i] != kCand) continue;
-      const unsigned long long v = ((unsigned long long)key[i] << 32) | (uint32_t)~(uint32_t)sq.pos[i];
-      if (v < best) { best = v; best_i = i; }
-    }
+    uint32_t newest = 0;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const unsigned long long o = __shfl_xor(best, d, kWave);
-      const int oi = __shfl_xor(best_i, d, kWave);
-      if (o < best) { best = o; best_i = oi; }
-    }
-    __shared__ unsigned long long s_best[kSelThreads / kWave];
-    __shared__ int s_best_i[kSelThreads / kWave];
-    if ((tid & (kWave - 1)) == 0) { s_best[tid / kWave] = best; s_best_i[tid / kWave] = best_i; }
+    for (int u = 0; u < S; ++u)
+      if (((restm >> u) & 1u) && key[u] == st.kmin) newest = max(newest, (uint32_t)posv[u] + 1u);
+    newest = wave_max(newest);
+    if (lane == 0) sh.newest[wave_id()] = newest;
     __syncthreads();
-    int victim = -1;
-    unsigned long long vb = ~0ull;
 #pragma unroll
-    for (int w = 0; w < kSelThreads / kWave; ++w)
-      if (s_best_i[w] >= 0 && s_best[w] < vb) { vb = s_best[w]; victim = s_best_i[w]; }
-    int32_t* map = keep_map + (size_t)b * L.cap;
-    if (victim >= 0)
-      for (int i = tid; i < n; i += kSelThreads) map[i] = i == victim ? -1 : i;
+    for (int w = 0; w < NW; ++w) newest = max(newest, sh.newest[w]);
+    if (st.n_cand > 0) {
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int i = u * NT + tid;
+        const bool victim = ((restm >> u) & 1u) && key[u] == st.kmin && (uint32_t)posv[u] + 1u == newest;
+        if (i < n) map[i] = victim ? -1 : i;
+        if (victim) sq.hole = i + 1;
+      }
+    }
     if (tid == 0) {
       plan[4 * b + 0] = n; plan[4 * b + 1] = n; plan[4 * b + 2] = 0; plan[4 * b + 3] = n;
-      sq.compacted = victim >= 0 ? 1 : 0;
-      if (victim >= 0) sq.hole = victim + 1;
+      sq.compacted = st.n_cand > 0 ? 1 : 0;
       if (advance_step) sq.step = s + 1;
     }
     return;
   }
   uint32_t B = (uint32_t)effective_budget(sq, s);
-  if (streaming) B = n_rest > 0 ? n_rest - 1 : 0;      // all candidates but the one ranked last
+  if (streaming) B = st.n_cand > 0 ? st.n_cand - 1 : 0;      // all candidates but the one ranked last
   uint32_t T, need_eq;
-  radix_threshold(sh, key, cls, n, n_rest, B < n_rest ? B : n_rest, &T, &need_eq);
-
-  const int per = (n + kSelThreads - 1) / kSelThreads;
-  const int lo = tid * per, hi = min(n, lo + per);
-  uint32_t a = 0, e = 0;
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t k = key[i];
-    const bool cand = cls[i] == kCand;
-    a += (!cand) || (k > T);
-    e += cand && (k == T);
+  top_threshold<NT, S>(sh, key, restm, st, B < st.n_cand ? B : st.n_cand, &T, &need_eq);
+  uint32_t sure = in & ~restm, eq = 0, dest[S], n_new;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (((restm >> u) & 1u) && key[u] > T) sure |= 1u << u;
+    if (((restm >> u) & 1u) && key[u] == T) eq |= 1u << u;
   }
-  uint32_t total;
-  uint32_t ex = block_excl_scan(sh, a | (e << 16), &total);
-  uint32_t a_run = ex & 0xFFFFu, e_run = ex >> 16;
-  int32_t* map = keep_map + (size_t)b * L.cap;
-  int my_first = n;
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t k = key[i];
-    const bool cand = cls[i] == kCand;
-    bool take = (!cand) || (k > T);
-    const bool eq = cand && (k == T);
-    const uint32_t dest = a_run + min(e_run, need_eq);
-    if (eq) { take = e_run < need_eq; ++e_run; } else if (take) ++a_run;
-    const int32_t m = take ? (int32_t)dest : -1;
-    map[i] = m;
-    key[i] = (uint32_t)m;                 // own run only: no other thread reads key[i] any more
-    if (m != i && i < my_first) my_first = i;
+  const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &n_new);
+  // first slot whose content changes: the first one that is dropped.  Everything before it stays put
+  uint32_t moves = 0;
+#pragma unroll
+  for (int u = S - 1; u >= 0; --u) {
+    const int i = u * NT + tid;
+    const bool kept = (take >> u) & 1u;
+    if ((in >> u) & 1u) map[i] = kept ? (int32_t)dest[u] : -1;
+    if (kept && dest[u] != (uint32_t)i) moves |= 1u << u;
+    const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
+    if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
-  // first slot whose content changes (evicted or moved): everything before it stays put
-  __syncthreads();
-  if (tid == 0) sh.bcast[2] = (uint32_t)n;
-  __syncthreads();
-  atomicMin(&sh.bcast[2], (uint32_t)my_first);
-  __syncthreads();
-  const int first = (int)sh.bcast[2];
-  const uint32_t n_new = (total & 0xFFFFu) + min(total >> 16, need_eq);
 
-  // in-place, order-preserving move of pos[] and every score row: ascending tiles, load -> barrier ->
-  // store.  A tile's destinations are <= its sources and below the next tile's sources; the rows are
-  // independent arrays, so kRowBatch of them travel together (their loads overlap: the move costs one
-  // memory round trip per tile and batch instead of one per tile and row).
-  constexpr int kRowBatch = 8, kTileSlots = 4;       // a tile: kTileSlots slots per thread
-  for (int base = (first / kSelThreads) * kSelThreads; base < n; base += kTileSlots * kSelThreads) {
-    int m[kTileSlots], src[kTileSlots], pv[kTileSlots];
-    bool mv[kTileSlots];
+  // In-place, order-preserving move of pos[] and every score row: all sources of a batch of rows are in registers before
+  // the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
+  constexpr int kRowBatch = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
+  for (int r0 = 0; r0 < L.score_rows; r0 += kRowBatch) {
+    float sv[S][kRowBatch];
 #pragma unroll
-    for (int u = 0; u < kTileSlots; ++u) {
-      const int i = base + u * kSelThreads + tid;
-      m[u] = i < n ? (int)key[i] : -1;
-      mv[u] = m[u] >= 0 && m[u] != i;
-      src[u] = mv[u] ? i : 0;
-      pv[u] = mv[u] ? sq.pos[i] : 0;
-    }
-    for (int r0 = 0; r0 < L.score_rows; r0 += kRowBatch) {
-      float sv[kTileSlots][kRowBatch];
+    for (int u = 0; u < S; ++u)
+      if ((moves >> u) & 1u) {
 #pragma unroll
-      for (int u = 0; u < kTileSlots; ++u)
-#pragma unroll
-        for (int k = 0; k < kRowBatch; ++k)
-          sv[u][k] = (mv[u] && r0 + k < L.score_rows) ? sq.score[(size_t)(r0 + k) * L.cap + src[u]] : 0.0f;
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < kTileSlots; ++u) {
-        if (!mv[u]) continue;
-        if (r0 == 0) sq.pos[m[u]] = pv[u];
-#pragma unroll
-        for (int k = 0; k < kRowBatch; ++k)
-          if (r0 + k < L.score_rows) sq.score[(size_t)(r0 + k) * L.cap + m[u]] = sv[u][k];
+        for (int k = 0; k < kRowBatch; ++k) sv[u][k] = score[(size_t)min(r0 + k, L.score_rows - 1) * L.cap + u * NT + tid];
       }
-    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if ((moves >> u) & 1u) {
+        if (r0 == 0) pos[dest[u]] = posv[u];
+#pragma unroll
+        for (int k = 0; k < kRowBatch; ++k)
+          if (r0 + k < L.score_rows) score[(size_t)(r0 + k) * L.cap + dest[u]] = sv[u][k];
+      }
   }
   if (tid == 0) {
-    plan[4 * b + 0] = n; plan[4 * b + 1] = first; plan[4 * b + 2] = 1; plan[4 * b + 3] = (int32_t)n_new;
+    plan[4 * b + 0] = n; plan[4 * b + 1] = (int)min(sh.first, (uint32_t)n); plan[4 * b + 2] = 1; plan[4 * b + 3] = (int32_t)n_new;
     sq.n_res = (int32_t)n_new;
     sq.compacted = 1;
     if (advance_step) sq.step = s + 1;
@@ -546,32 +606,44 @@ LaunchShape shape_of(const adsa_params& p) {
 
 }  // namespace
 
-// from this many sequences per launch on the ranking kernels are throughput-bound (two workgroups per CU and more)
-constexpr int kManySequences = 512;
+// Threads and slots per thread of a ranking workgroup, by the slots a sequence can have.  k_select, us at 256x3 | 512x2 |
+// 1024x1: 64 sequences x 24 rows x 696 slots 7.6 | 7.2 | 7.4; 1536 x 24 x 696 20.3 | 20.6 | 37.7; 1536 x 8 x 696
+// 12.3 | 15.1 | 35; at 256x4 | 512x2: 64 x 24 x 696 8.3 | 7.2; at 512x4 | 1024x2: 200 x 16 x 2000 11.1 | 11.4.  (One
+// workgroup of 256 threads with keys in LDS and a 4-pass radix select: 12.4, 27.3, 18.1 and 19.4 us.)  k_compact_plan in
+// the same shapes, against that form: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (was 32.7), 512 x 48 rows x 632
+// of the fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).
+#define ADSA_RANK_DISPATCH(KERNEL, ...)                                                                      \
+  do {                                                                                                       \
+    if (p.cap <= 256) ADSA_RANK_LAUNCH(KERNEL, 256, 1, __VA_ARGS__);                                         \
+    if (p.cap <= 512) ADSA_RANK_LAUNCH(KERNEL, 256, 2, __VA_ARGS__);                                         \
+    if (p.cap <= 768) ADSA_RANK_LAUNCH(KERNEL, 256, 3, __VA_ARGS__);                                         \
+    if (p.cap <= 1024) ADSA_RANK_LAUNCH(KERNEL, 512, 2, __VA_ARGS__);                                        \
+    if (p.cap <= 2048) ADSA_RANK_LAUNCH(KERNEL, 512, 4, __VA_ARGS__);                                        \
+    if (p.cap <= 4096) ADSA_RANK_LAUNCH(KERNEL, 1024, 4, __VA_ARGS__);                                       \
+    ADSA_RANK_LAUNCH(KERNEL, 1024, 8, __VA_ARGS__);                                                          \
+  } while (0)
+#define ADSA_RANK_LAUNCH(KERNEL, NT, S, ...)                                                                 \
+  do {                                                                                                       \
+    hipLaunchKernelGGL((KERNEL<NT, S>), dim3(p.n_seq), dim3(NT), 0, st, seqs, __VA_ARGS__, shape_of(p));     \
+    return hipGetLastError();                                                                                \
+  } while (0)
 
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
                          bool plan_append, hipStream_t st) {
-  if (p.n_seq >= kManySequences)
-    hipLaunchKernelGGL(k_select<1>, dim3(p.n_seq), dim3(kSelThreads), rank_lds_bytes(p.cap), st, shape_of(p), seqs,
-                       sel_idx, sel_cnt, plan_append ? 1 : 0);
-  else
-    hipLaunchKernelGGL(k_select<4>, dim3(p.n_seq), dim3(kSelThreads), rank_lds_bytes(p.cap), st, shape_of(p), seqs,
-                       sel_idx, sel_cnt, plan_append ? 1 : 0);
-  return hipGetLastError();
+  ADSA_RANK_DISPATCH(k_select, sel_idx, sel_cnt, plan_append ? 1 : 0);
+}
+
+static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* plan,
+                                      bool advance_step, const float* vcos_s, hipStream_t st) {
+  ADSA_RANK_DISPATCH(k_compact_plan, keep_map, plan, advance_step ? 1 : 0, vcos_s);
 }
 
 hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
                           const Workspace& w, bool advance_step, hipStream_t st) {
   int32_t* plan = reinterpret_cast<int32_t*>(ws + w.plan_off);
-  LaunchShape L = shape_of(p);
+  const LaunchShape L = shape_of(p);
   const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
-  if (p.n_seq >= kManySequences)
-    hipLaunchKernelGGL(k_compact_plan<1>, dim3(p.n_seq), dim3(kSelThreads), rank_lds_bytes(p.cap), st, L, seqs,
-                       keep_map, plan, advance_step ? 1 : 0, vcos_s);
-  else
-    hipLaunchKernelGGL(k_compact_plan<4>, dim3(p.n_seq), dim3(kSelThreads), rank_lds_bytes(p.cap), st, L, seqs,
-                       keep_map, plan, advance_step ? 1 : 0, vcos_s);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
   // one workgroup per 128-byte column slice of a head row (whole head row when it is narrower)
   const int head_bytes = p.head_dim * L.elem_bytes;

@@ -1,0 +1,71 @@
+"""The ranking kernels at the edges of their workgroup shapes, on scores that take every way through the threshold search: one
+value, ties that outnumber a wave, consecutive floats, all exponents with infinities, and a long tail beside a dense cluster."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_18226_amd import binding as B
+from paper_2506_18226_amd import workloads as WL
+from paper_2506_18226_amd.batch import LayerBatch
+
+from common import oracle_cfg
+from test_gpu_parity import DEV, load_state, params_for
+
+pytestmark = pytest.mark.gpu
+
+
+def score_patterns(rng, n):
+    ulps = (np.float32(1.5).view(np.uint32) + rng.permutation(n).astype(np.uint32)).view(np.float32)
+    wide = np.ldexp(rng.standard_normal(n), rng.integers(-140, 120, n)).astype(np.float32)
+    wide[rng.random(n) < 0.02] = np.inf
+    wide[rng.random(n) < 0.02] = -np.inf
+    wide[rng.random(n) < 0.05] = -0.0
+    cluster = np.where(rng.random(n) < 0.9, 1.0 + rng.integers(0, 5, n) * 2.0 ** -23, rng.random(n) * 1e6).astype(np.float32)
+    return [np.zeros(n, np.float32), rng.integers(0, 3, n).astype(np.float32), ulps, wide, cluster,
+            rng.gamma(2.0, 0.5, n).astype(np.float32)]
+
+
+@pytest.mark.parametrize("cap", [65, 255, 256, 257, 512, 513, 768, 769, 1024, 1025, 2048, 2049, 4096, 4097, 8192])
+def test_ranking_at_workgroup_edges(cap):
+    """select and the row-end eviction given the same scores: lists, keep maps, moved pos / score / K / V bit-exact."""
+    rng = np.random.default_rng(cap)
+    W, P = 16, cap % 16 + 16
+    s = cap - P                                              # every grid row so far is resident, the last one just closed
+    wl = WL.get_workload("tiny", n_heads=1, head_dim=64, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
+    k, v = (rng.standard_normal((cap, 1, 64), dtype=np.float32) for _ in range(2))
+    pos = np.arange(cap, dtype=np.int32)
+    cases = [(sc, Bud) for sc in score_patterns(rng, cap) for Bud in (1, s // 3, s - 2 * W - 1)]
+    params = params_for(wl, len(cases), cap, score_mode=B.SCORE_EXT_LARGEST)
+    batch = LayerBatch(params, DEV)
+    states = []
+    for b, (sc, Bud) in enumerate(cases):
+        cfg = oracle_cfg(wl, P=P, budget=Bud, score_mode=B.SCORE_EXT_LARGEST, cap=cap)
+        states.append((cfg, oracle.CacheState.from_arrays(cfg, k, v, pos, sc)))
+        load_state(batch, b, states[b][1], cfg, s)
+    batch.upload_seqs()
+    batch.select()
+    batch.compact()
+    torch.cuda.synchronize()
+    seqs, km, Kd, Vd = batch.read_seqs(), batch.keep_map.cpu().numpy(), batch.k_host(), batch.v_host()
+    sel, cnt, posd, scored = (x.cpu().numpy() for x in (batch.sel_idx, batch.sel_cnt, batch.pos, batch.score))
+    assert (seqs["status"] == 0).all()
+    for b, (cfg, st) in enumerate(states):
+        ref, _ = oracle.select(cfg, st.pos[:cap], st.score[:cap], None, s)
+        assert cnt[b] == ref.size and np.array_equal(sel[b, :ref.size], ref), b
+        ref_map, did = oracle.compact(cfg, st, s)
+        n = st.n_res
+        assert did and seqs["compacted"][b] == 1 and seqs["n_res"][b] == n, b
+        assert np.array_equal(km[b], ref_map), b
+        assert np.array_equal(posd[b, :n], st.pos[:n]) and np.array_equal(scored[b, 0, :n], st.score[:n]), b
+        assert np.array_equal(Kd[b, :n], st.K[:n]) and np.array_equal(Vd[b, :n], st.V[:n]), b
+
+
+def test_empty_sequences_touch_no_memory():
+    """A record that was never filled (all zero: step 0, no resident slot, null pointers) is ranked without a read."""
+    wl = WL.get_workload("tiny", n_heads=2, grid_h=4, grid_w=4, prefix_len=4)
+    batch = LayerBatch(params_for(wl, 3, 20), DEV)           # upload_seqs() not called: the device records are zero
+    batch.select()
+    batch.compact()
+    torch.cuda.synchronize()
+    assert (batch.sel_cnt.cpu().numpy() == 0).all()
