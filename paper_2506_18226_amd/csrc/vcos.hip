@@ -5,13 +5,20 @@
 // u = sum_j v^_j over the candidates,  S_i = (v^_i . u - v^_i . v^_i) / (N - 1): two streaming
 // passes over the candidates' V rows instead of O(N^2 D) work.
 //
-//  k_vcos_norm_usum : grid (slot tile, sequence).  A wave holds a slot's whole row in registers: inverse
-//                     norm by a wave reduction, then the normalised row is added to the wave's column
-//                     sums; the waves' sums are added in LDS into a per-tile partial of u
+//  k_vcos_norm_usum : grid (slot tile, sequence).  The tile's candidates are listed in LDS; a wave holds a slot's whole row
+//                     in registers: inverse norm by a wave reduction, then the normalised row is added to the wave's
+//                     column sums; the waves' sums are added in LDS into a per-tile partial of u
 //                     (deterministic order, no atomics, every row read once).
-//  k_vcos_score     : grid (slot tile, sequence).  Sums the tile partials of u into LDS, counts the
-//                     candidates, then a wave per slot takes the dot product and writes S_i into
+//  k_vcos_score     : grid (slot tile, sequence).  Every lane sums its columns of the tile partials of u into registers,
+//                     then a wave per slot takes the dot product and writes S_i into
 //                     score[slot] (non-candidate slots keep their score).
+//
+// Both are bound by the stream of V rows.  A wave keeps a ring of U rows in flight (16 bytes per lane and load, so 3 loads
+// for a row of 24 heads x 64 bf16).  256 sequences x 535 candidates of that shape, 420 MB a pass: 79 and 75 us (5.3 and
+// 5.6 TB/s); one row of 8-byte loads at a time, the next one asked for after its reduction, took 168 and 184 us.
+#include <type_traits>
+
+#include "adsa_device.h"
 #include "adsa_internal.h"
 #include "adsa_partition.h"
 
@@ -20,27 +27,31 @@ namespace {
 
 constexpr int kVcThreads = 256;
 constexpr int kVcWaves = kVcThreads / kWave;
-constexpr int kVcTile = 64;                 // slots per workgroup
-constexpr int kVcMaxDim = 8192;             // n_heads * head_dim limit of the LDS copy of u
+constexpr int kVcTile = 64;                 // slots per tile partial the workspace has room for
+constexpr int kVcMaxDim = 8192;             // n_heads * head_dim limit
 
 struct VcosArgs {
-  const adsa_seq* seqs_c;
   adsa_seq* seqs;
   float* inv_norm;      // [n_seq][cap]
   float* u_part;        // [n_seq][n_tiles][dim]
   float* s_out;         // [n_seq][cap] where S_i goes when score[] holds the fused form's rows, else NULL
-  int n_heads, head_dim, elem_bytes, cap, n_tiles;
+  int n_heads, head_dim, cap, tile, n_tiles;      // tile: slots per workgroup, 64, 128 or 256
   int grid_h, grid_w, R, w, for_compaction, recent_m, evict_policy;
   long long slot_stride_b, head_stride_b;
 };
 
+// sum over the wave: DPP inside the 16-lane rows, then lane 15 -> next row and lane 31 -> upper half; uniform result
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xF, false));
+}
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, kWave);
-  return x;
+  x = dpp_add<0x111, 0xF>(x); x = dpp_add<0x112, 0xF>(x); x = dpp_add<0x114, 0xF>(x); x = dpp_add<0x118, 0xF>(x);
+  x = dpp_add<0x142, 0xA>(x); x = dpp_add<0x143, 0xC>(x);
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWave - 1));
 }
 
-// candidate test for slot i of sequence sq (false for inactive sequences / non row-end compaction)
+// candidate test (false for inactive sequences / non row-end compaction)
 __device__ __forceinline__ bool vcos_candidate(const VcosArgs& A, const QueryCell& c, int pos) {
   if (A.for_compaction && A.evict_policy == ADSA_EVICT_ROW_END) return evict_class(c, pos) == 1;
   return select_class(c, pos) == 1;     // also the streaming eviction: the incoming query's partition
@@ -57,231 +68,349 @@ __device__ __forceinline__ bool vcos_active(const VcosArgs& A, const adsa_seq& s
   return is_row_end(sq.step, A.grid_h, A.grid_w);
 }
 
-// load 4 consecutive elements (column group g of the concatenated row) of slot `slot`
-__device__ __forceinline__ float4 load4(const VcosArgs& A, const char* vbase, int slot, int g) {
-  const int col = g * 4, head = col / A.head_dim, d = col - head * A.head_dim;
-  const char* p = vbase + (long long)slot * A.slot_stride_b + (long long)head * A.head_stride_b;
-  if (A.elem_bytes == 4) return reinterpret_cast<const float4*>(p)[d / 4];
-  const uint2 r = reinterpret_cast<const uint2*>(p)[d / 4];
-  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u),
-                     __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xFFFF0000u));
+// A concatenated V row as a wave holds it: lane l has the 16-byte pieces l, l + 64, ... (G of them at most; pieces past the
+// row's end read piece 0 and count as zero).
+template <int EB, int G>
+struct Row {
+  static constexpr int EPL = 16 / EB;        // elements per piece
+  static constexpr int U = G == 1 ? 8 : G == 2 ? 6 : G == 3 ? 4 : G == 4 ? 3 : G <= 8 ? 2 : 1;     // rows in flight per wave
+  const gchar* p[G];
+  bool on[G];
+  int col[G];                                // first column of the piece
+
+  __device__ __forceinline__ Row(const void* v, int n_heads, int head_dim, long long head_stride_b) {
+    const int lane = threadIdx.x & (kWave - 1), per_head = head_dim * EB / 16, pieces = n_heads * per_head;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int c = lane + g * kWave;
+      on[g] = c < pieces;
+      const int cc = on[g] ? c : 0, head = cc / per_head;
+      col[g] = cc * EPL;
+      p[g] = (const gchar*)v + (long long)head * head_stride_b + (cc - head * per_head) * 16;
+    }
+  }
+  __device__ __forceinline__ void load(long long off, uint4 (&x)[G]) const {
+#pragma unroll
+    for (int g = 0; g < G; ++g) x[g] = load16(p[g] + off);
+  }
+  __device__ __forceinline__ void unpack(const uint4 (&x)[G], float (&f)[G][EPL]) const {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t v = on[g] ? w[k] : 0u;
+        if constexpr (EB == 4) f[g][k] = __uint_as_float(v);
+        else { f[g][2 * k] = __uint_as_float(v << 16); f[g][2 * k + 1] = __uint_as_float(v & 0xFFFF0000u); }
+      }
+    }
+  }
+};
+
+// Calls use(k, row) for entries wave, wave + kVcWaves, ... of the m slots listed in s_row, with U rows in flight.
+template <int EB, int G, typename Use>
+__device__ __forceinline__ void for_rows(const Row<EB, G>& row, long long slot_stride_b, const int* s_row, int m, Use use) {
+  constexpr int U = Row<EB, G>::U;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  if (wave >= m) return;
+  uint4 x[U][G];
+  auto request = [&](int u, int k) {         // (entries past the last re-read it)
+    row.load((long long)__builtin_amdgcn_readfirstlane(s_row[min(k, m - 1)]) * slot_stride_b, x[u]);
+    asm volatile("" : : : "memory");         // requests leave in ring order
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) request(u, wave + u * kVcWaves);
+  for (int k = wave; k < m; k += U * kVcWaves) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ku = k + u * kVcWaves;
+      if (ku < m) {
+        float f[G][Row<EB, G>::EPL];
+        row.unpack(x[u], f);
+        use(ku, f);
+      }
+      request(u, ku + U * kVcWaves);
+    }
+  }
 }
 
-// GPL = column groups (of 4) per lane: a wave holds a whole concatenated V row in registers, so every
-// row is read from HBM once: norm by a wave reduction, then the normalised row goes into the wave's
-// running column sums.  The four waves' sums meet in LDS in wave order (deterministic).
-template <int GPL>
+// Lists the slots of [s0, s1) that `member` accepts, ascending, in s_row (one slot per thread); returns their number.
+template <typename Member>
+__device__ __forceinline__ int list_rows(int* s_row, int* s_cnt, int s0, int s1, Member member) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int i = s0 + tid;
+  const bool c = i < s1 && member(i);
+  const unsigned long long m = __ballot(c);
+  if (lane == 0) s_cnt[wave] = __popcll(m);
+  __syncthreads();
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kVcWaves; ++w) {
+    const int t = s_cnt[w];
+    if (w < wave) base += t;
+    total += t;
+  }
+  if (c) s_row[base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = i;
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(total);
+}
+
+template <int EB, int G>
 __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
-  extern __shared__ float s_acc[];                     // [kVcWaves][groups*4]
+  extern __shared__ __align__(16) float s_acc[];        // [kVcWaves][dim]
+  __shared__ int s_row[kVcThreads], s_cnt[kVcWaves];
+  __shared__ float s_inv[kVcThreads];
+  constexpr int EPL = 16 / EB;
   const int tile = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
-  const adsa_seq& sq = A.seqs_c[b];
+  const adsa_seq& sq = A.seqs[b];
   if (!vcos_active(A, sq)) return;
-  const int n = sq.n_res, s0 = tile * kVcTile;
+  const int n = sq.n_res, s0 = tile * A.tile;
   if (s0 >= n) return;
-  const int s1 = min(n, s0 + kVcTile);
+  const int s1 = min(n, s0 + A.tile), dim = A.n_heads * A.head_dim;
   const QueryCell cell = make_query_cell(sq, sq.step, A.grid_w, A.R, A.w, A.recent_m);
-  const char* vbase = reinterpret_cast<const char*>(sq.v);
-  const int groups = A.n_heads * A.head_dim / 4;
-  float4 acc[GPL];
+  const gint* const pos = (const gint*)sq.pos;
+  gfloat* const inv_norm = (gfloat*)A.inv_norm + (size_t)b * A.cap;
+  const int m = list_rows(s_row, s_cnt, s0, s1, [&](int i) {
+    const bool c = vcos_candidate(A, cell, pos[i]);
+    if (!c) inv_norm[i] = 0.0f;                          // marks "not a candidate"
+    return c;
+  });
+  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
+  float acc[G][EPL];
 #pragma unroll
-  for (int k = 0; k < GPL; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int i = s0 + wave; i < s1; i += kVcWaves) {       // ascending slots per wave: fixed summation order
-    float inv = 0.0f;                                     // 0 marks "not a candidate"
-    if (vcos_candidate(A, cell, sq.pos[i])) {             // wave-uniform
-      float4 x[GPL];
-      float ss = 0.0f;
+  for (int g = 0; g < G; ++g)
 #pragma unroll
-      for (int k = 0; k < GPL; ++k) {
-        const int g = lane + k * kWave;
-        x[k] = g < groups ? load4(A, vbase, i, g) : make_float4(0.f, 0.f, 0.f, 0.f);
-        ss = fmaf(x[k].x, x[k].x, ss); ss = fmaf(x[k].y, x[k].y, ss);
-        ss = fmaf(x[k].z, x[k].z, ss); ss = fmaf(x[k].w, x[k].w, ss);
-      }
-      ss = wave_sum(ss);
-      inv = 1.0f / fmaxf(sqrtf(ss), 1e-8f);
+    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.0f;
+  for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {     // ascending per wave: fixed order
+    float ss = 0.0f;
 #pragma unroll
-      for (int k = 0; k < GPL; ++k) {
-        acc[k].x = fmaf(x[k].x, inv, acc[k].x); acc[k].y = fmaf(x[k].y, inv, acc[k].y);
-        acc[k].z = fmaf(x[k].z, inv, acc[k].z); acc[k].w = fmaf(x[k].w, inv, acc[k].w);
-      }
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) ss = fmaf(f[g][e], f[g][e], ss);
+    ss = wave_sum(ss);
+    const float inv = 1.0f / fmaxf(sqrtf(ss), 1e-8f);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(f[g][e], inv, acc[g][e]);
+    if (lane == 0) s_inv[k] = inv;
+  });
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    if (row.on[g]) {
+#pragma unroll
+      for (int e = 0; e < EPL; e += 4)
+        *reinterpret_cast<float4*>(s_acc + (size_t)wave * dim + row.col[g] + e) = make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
     }
-    if (lane == 0) A.inv_norm[(size_t)b * A.cap + i] = inv;
-  }
-#pragma unroll
-  for (int k = 0; k < GPL; ++k) {
-    const int g = lane + k * kWave;
-    if (g < groups) reinterpret_cast<float4*>(s_acc + (size_t)wave * groups * 4)[g] = acc[k];
-  }
   __syncthreads();
-  float* up = A.u_part + ((size_t)b * A.n_tiles + tile) * (size_t)(groups * 4);
-  for (int g = tid; g < groups; g += kVcThreads) {
-    float4 t = reinterpret_cast<const float4*>(s_acc)[g];
+  if (tid < m) inv_norm[s_row[tid]] = s_inv[tid];
+  float* up = A.u_part + ((size_t)b * A.n_tiles + tile) * (size_t)dim;
+  for (int c = tid; c < dim / 4; c += kVcThreads) {
+    float4 t = reinterpret_cast<const float4*>(s_acc)[c];
 #pragma unroll
     for (int w = 1; w < kVcWaves; ++w) {
-      const float4 o = reinterpret_cast<const float4*>(s_acc + (size_t)w * groups * 4)[g];
+      const float4 o = reinterpret_cast<const float4*>(s_acc + (size_t)w * dim)[c];
       t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
     }
-    reinterpret_cast<float4*>(up)[g] = t;
+    reinterpret_cast<float4*>(up)[c] = t;
   }
 }
 
+// The sequences are walked in the opposite order of the first pass: what that read last is still in the memory-side cache.
+template <int EB, int G>
 __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
-  extern __shared__ float s_u[];                       // [dim]
-  __shared__ int s_cnt[kVcWaves];
-  const int tile = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  __shared__ int s_row[kVcThreads], s_cnt[kVcWaves], s_n[kVcWaves];
+  __shared__ float s_inv[kVcThreads], s_res[kVcThreads];       // by slot of the tile; by entry of s_row
+  constexpr int EPL = 16 / EB;
+  const int tile = gridDim.x - 1 - blockIdx.x, b = gridDim.y - 1 - blockIdx.y, tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   adsa_seq& sq = A.seqs[b];
   if (!vcos_active(A, sq)) return;
-  const int n = sq.n_res, s0 = tile * kVcTile;
+  const int n = sq.n_res, s0 = tile * A.tile;
   if (s0 >= n) return;
-  const int s1 = min(n, s0 + kVcTile);
-  const int groups = A.n_heads * A.head_dim / 4;
-  const int tiles_used = (n + kVcTile - 1) / kVcTile;
-  const float* up = A.u_part + (size_t)b * A.n_tiles * (size_t)(groups * 4);
-  for (int g = tid; g < groups; g += kVcThreads) {
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int t = 0; t < tiles_used; ++t) {             // ascending tile order: deterministic
-      const float4 x = reinterpret_cast<const float4*>(up + (size_t)t * groups * 4)[g];
-      acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
-    }
-    reinterpret_cast<float4*>(s_u)[g] = acc;
-  }
+  const int s1 = min(n, s0 + A.tile), dim = A.n_heads * A.head_dim;
+  const int tiles_used = (n + A.tile - 1) / A.tile;
+  const gfloat* const invs = (const gfloat*)A.inv_norm + (size_t)b * A.cap;
   int my = 0;
-  const float* invs = A.inv_norm + (size_t)b * A.cap;
   for (int i = tid; i < n; i += kVcThreads) my += invs[i] != 0.0f;
+  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
+  const float* up = A.u_part + (size_t)b * A.n_tiles * (size_t)dim;
+  float uu[G][EPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) uu[g][e] = 0.0f;
+  for (int t = 0; t < tiles_used; ++t) {                 // ascending tile order: deterministic
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; e += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(up + (size_t)t * dim + row.col[g] + e);
+        if (row.on[g]) { uu[g][e] += x.x; uu[g][e + 1] += x.y; uu[g][e + 2] += x.z; uu[g][e + 3] += x.w; }
+      }
+  }
   for (int d = 32; d >= 1; d >>= 1) my += __shfl_xor(my, d, kWave);
-  if (lane == 0) s_cnt[wave] = my;
-  __syncthreads();
-  int N = 0;
-  for (int w = 0; w < kVcWaves; ++w) N += s_cnt[w];
-  const char* vbase = reinterpret_cast<const char*>(sq.v);
-  for (int i = s0 + wave; i < s1; i += kVcWaves) {
+  if (lane == 0) s_n[wave] = my;
+  const int m = list_rows(s_row, s_cnt, s0, s1, [&](int i) {
     const float inv = invs[i];
-    if (inv == 0.0f) continue;                          // wave-uniform
+    s_inv[i - s0] = inv;
+    return inv != 0.0f;
+  });
+  int N = 0;
+#pragma unroll
+  for (int w = 0; w < kVcWaves; ++w) N += s_n[w];
+  gfloat* const out = A.s_out ? (gfloat*)A.s_out + (size_t)b * A.cap : (gfloat*)sq.score;
+  for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
     float dot = 0.0f, ss = 0.0f;
-    for (int g = lane; g < groups; g += kWave) {
-      const float4 x = load4(A, vbase, i, g);
-      const float4 uu = reinterpret_cast<const float4*>(s_u)[g];
-      dot = fmaf(x.x, uu.x, dot); dot = fmaf(x.y, uu.y, dot); dot = fmaf(x.z, uu.z, dot); dot = fmaf(x.w, uu.w, dot);
-      ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
-    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) { dot = fmaf(f[g][e], uu[g][e], dot); ss = fmaf(f[g][e], f[g][e], ss); }
     dot = wave_sum(dot);
     ss = wave_sum(ss);
+    const float inv = s_inv[s_row[k] - s0];
     // remove the i == j term (1 for a normal row, 0 for a zero row) and average over the others
     const float self = ss * inv * inv;
-    const float S = N > 1 ? (dot * inv - self) / (float)(N - 1) : 0.0f;
-    if (lane == 0) {
-      if (A.s_out) A.s_out[(size_t)b * A.cap + i] = S;
-      else sq.score[i] = S;
-    }
-  }
+    if (lane == 0) s_res[k] = N > 1 ? (dot * inv - self) / (float)(N - 1) : 0.0f;
+  });
+  __syncthreads();
+  if (tid < m) out[s_row[tid]] = s_res[tid];
 }
 
 // ADSA_SCORE_VCOS_FUSED: bring u to the candidate set of the NEXT step, after this step's eviction plan and
 // before its attention launch (which takes every row's dot product with u).  One workgroup per sequence.
 // If u belongs to this step: subtract the evicted row, add the rows that turn from local to candidate
 // (normally the one token that leaves the 1-D window).  Otherwise: a fresh sum over the next step's
-// candidates.  Wave w handles slots w, w+4, ... in ascending order into its own LDS copy of u; the copies
-// are added in wave order, so the result does not depend on timing.
+// candidates.  (512 sequences of 632 slots, two rows each: 10.9 us; 18.3 us with every row read twice and the sums in LDS.)
+// The slots that join or leave are listed 256 at a time; wave w takes entries w, w+4, ... in ascending order into
+// its own registers, and the waves' sums are added to u in wave order, so the result does not depend on timing.
 struct AdvArgs {
   adsa_seq* seqs;
-  int n_heads, head_dim, elem_bytes, cap, grid_h, grid_w, R, w, recent_m;
+  int n_heads, head_dim, cap, grid_h, grid_w, R, w, recent_m;
   long long slot_stride_b, head_stride_b;
 };
 
+template <int EB, int G>
 __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
-  extern __shared__ float s_u[];                        // [kVcWaves][dim]
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  extern __shared__ __align__(16) float s_acc[];        // [kVcWaves][dim]
+  __shared__ int s_row[kVcThreads], s_cnt[kVcWaves];
+  __shared__ float s_sign[kVcThreads];                  // by slot of the round
+  constexpr int EPL = 16 / EB, kAhead = 4;              // rounds whose positions are requested together
+  const int b = blockIdx.x, tid = threadIdx.x, wave = tid / kWave;
   adsa_seq& sq = A.seqs[b];
-  float* U = sq.vcos_u;
+  gfloat* const U = (gfloat*)sq.vcos_u;
   if (sq.step < 0 || sq.status != 0 || U == nullptr) return;
-  const int s = sq.step, n = sq.n_res, dim = A.n_heads * A.head_dim, groups = dim / 4;
+  const int s = sq.step, n = sq.n_res, dim = A.n_heads * A.head_dim;
   if (n < 0 || n > A.cap) return;
-  float* tags = U + dim;
+  gfloat* const tags = U + dim;
   if (s + 1 > A.grid_h * A.grid_w) {                    // no later step evicts
     if (tid == 0) tags[0] = 0.0f;
     return;
   }
-  const bool incremental = tags[0] == (float)(s + 1);   // u is the sum over THIS step's candidates
+  const gint* const pos = (const gint*)sq.pos;
   const int victim = sq.hole - 1;                       // slot freed by this step's eviction, or -1
   const QueryCell now = make_query_cell(sq, s, A.grid_w, A.R, A.w, A.recent_m);
   const QueryCell next = make_query_cell(sq, s + 1, A.grid_w, A.R, A.w, A.recent_m);
-  for (int c = tid; c < dim; c += kVcThreads) {
-    s_u[c] = incremental ? U[c] : 0.0f;
+  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
+  const bool incremental = tags[0] == (float)(s + 1);   // u is the sum over THIS step's candidates
+  float acc[G][EPL];
 #pragma unroll
-    for (int w = 1; w < kVcWaves; ++w) s_u[(size_t)w * dim + c] = 0.0f;
-  }
-  __syncthreads();
-  // what happens to each slot: +1 joins u, -1 leaves it, 0 nothing (classified by all threads at once)
-  signed char* s_sign = reinterpret_cast<signed char*>(s_u + (size_t)kVcWaves * dim);   // [cap]
-  for (int i = tid; i < n; i += kVcThreads) {
-    const int pos = sq.pos[i];
-    const bool cand_next = select_class(next, pos) == 1;
-    int sign = 0;
-    if (incremental) {
-      const bool cand_now = select_class(now, pos) == 1;
-      if (i == victim) sign = cand_now ? -1 : 0;
-      else if (cand_next && !cand_now) sign = 1;
-    } else if (cand_next && i != victim) sign = 1;
-    s_sign[i] = (signed char)sign;
-  }
-  __syncthreads();
-  VcosArgs L;                                           // for load4()
-  L.head_dim = A.head_dim; L.elem_bytes = A.elem_bytes; L.slot_stride_b = A.slot_stride_b; L.head_stride_b = A.head_stride_b;
-  const char* vbase = reinterpret_cast<const char*>(sq.v);
-  float* mine = s_u + (size_t)wave * dim;
-  for (int base = 0; base < n; base += kWave) {         // wave w owns slots w, w+4, ...: ascending, fixed order
-    const int my = base + lane;
-    const int sg = (my < n && (my % kVcWaves) == wave) ? (int)s_sign[my] : 0;
-    unsigned long long todo = __ballot(sg != 0);
-    while (todo) {
-      const int src = __ffsll((long long)todo) - 1;
-      todo &= todo - 1;
-      const int i = base + src;
-      const float sign = (float)__shfl(sg, src, kWave);
-      float ss = 0.0f;
-      for (int g = lane; g < groups; g += kWave) {
-        const float4 x = load4(L, vbase, i, g);
-        ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
-      }
-      ss = wave_sum(ss);
-      const float f = sign / fmaxf(sqrtf(ss), 1e-8f);
-      for (int g = lane; g < groups; g += kWave) {
-        const float4 x = load4(L, vbase, i, g);
-        float4 t = reinterpret_cast<float4*>(mine)[g];
-        t.x = fmaf(x.x, f, t.x); t.y = fmaf(x.y, f, t.y); t.z = fmaf(x.z, f, t.z); t.w = fmaf(x.w, f, t.w);
-        reinterpret_cast<float4*>(mine)[g] = t;
-      }
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.0f;
+  for (int base = 0; base < n; base += kAhead * kVcThreads) {
+    int posv[kAhead];
+#pragma unroll
+    for (int r = 0; r < kAhead; ++r) posv[r] = pos[min(base + r * kVcThreads + tid, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kAhead; ++r) {
+      const int s0 = base + r * kVcThreads;
+      if (s0 >= n) break;
+      // what happens to each slot: +1 joins u, -1 leaves it, 0 nothing
+      const int m = list_rows(s_row, s_cnt, s0, min(n, s0 + kVcThreads), [&](int i) {
+        const bool cand_next = select_class(next, posv[r]) == 1;
+        float sign = 0.0f;
+        if (incremental) {
+          const bool cand_now = select_class(now, posv[r]) == 1;
+          if (i == victim) sign = cand_now ? -1.0f : 0.0f;
+          else if (cand_next && !cand_now) sign = 1.0f;
+        } else if (cand_next && i != victim) sign = 1.0f;
+        s_sign[tid] = sign;
+        return sign != 0.0f;
+      });
+      for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
+        float ss = 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) ss = fmaf(f[g][e], f[g][e], ss);
+        const float c = s_sign[s_row[k] - s0] / fmaxf(sqrtf(wave_sum(ss)), 1e-8f);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(f[g][e], c, acc[g][e]);
+      });
+      __syncthreads();                                  // the list is free for the next round
     }
   }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    if (row.on[g]) {
+#pragma unroll
+      for (int e = 0; e < EPL; e += 4)
+        *reinterpret_cast<float4*>(s_acc + (size_t)wave * dim + row.col[g] + e) = make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
+    }
   __syncthreads();
   for (int c = tid; c < dim; c += kVcThreads) {
-    float t = s_u[c];
+    float t = incremental ? U[c] : 0.0f;
 #pragma unroll
-    for (int w = 1; w < kVcWaves; ++w) t += s_u[(size_t)w * dim + c];
+    for (int w = 0; w < kVcWaves; ++w) t += s_acc[(size_t)w * dim + c];
     U[c] = t;
   }
   if (tid == 0) tags[0] = (float)(s + 2);               // u now belongs to step s + 1
 }
 
+// Calls f(EB, G) as compile-time constants: G pieces of 16 bytes per lane hold a concatenated row.
+template <typename F>
+hipError_t with_row_shape(const adsa_params& p, F f) {
+  const int pieces = p.n_heads * p.head_dim * elem_bytes(p) / 16, g = (pieces + kWave - 1) / kWave;
+  auto pick = [&](auto eb) {
+    if (g <= 1) return f(eb, std::integral_constant<int, 1>());
+    if (g <= 2) return f(eb, std::integral_constant<int, 2>());
+    if (g <= 3) return f(eb, std::integral_constant<int, 3>());
+    if (g <= 4) return f(eb, std::integral_constant<int, 4>());
+    if (g <= 6) return f(eb, std::integral_constant<int, 6>());
+    if (g <= 8) return f(eb, std::integral_constant<int, 8>());
+    if (g <= 16) return f(eb, std::integral_constant<int, 16>());
+    if constexpr (decltype(eb)::value == 4) return f(eb, std::integral_constant<int, 32>());
+    else return hipErrorInvalidValue;
+  };
+  return elem_bytes(p) == 4 ? pick(std::integral_constant<int, 4>()) : pick(std::integral_constant<int, 2>());
+}
+
 }  // namespace
 
-// four copies of u and one byte per slot
+// the LDS the fused form's bookkeeping may take: four copies of u and one byte per slot
 size_t vcos_advance_lds_bytes(const adsa_params& p) {
   return sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves + (((size_t)p.cap + 15) / 16) * 16;
 }
 
 hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t st) {
-  const size_t lds = vcos_advance_lds_bytes(p);
-  if (lds > 64 * 1024) return hipErrorInvalidValue;
+  if (vcos_advance_lds_bytes(p) > 64 * 1024) return hipErrorInvalidValue;
   AdvArgs A;
-  A.seqs = seqs; A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.elem_bytes = elem_bytes(p); A.cap = p.cap;
+  A.seqs = seqs; A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
   A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius; A.recent_m = p.win_recent_m;
-  A.slot_stride_b = (long long)p.kv_slot_stride * A.elem_bytes;
-  A.head_stride_b = (long long)p.kv_head_stride * A.elem_bytes;
-  hipLaunchKernelGGL(k_vcos_advance, dim3(p.n_seq), dim3(kVcThreads), lds, st, A);
-  return hipGetLastError();
+  A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
+  A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
+  return with_row_shape(p, [&](auto eb, auto g) {
+    constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
+    if constexpr (G * 16 / EB <= 64) {                  // (longer rows: more than 64 KB of sums, refused above)
+      hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves, st, A);
+      return hipGetLastError();
+    } else return hipErrorInvalidValue;
+  });
 }
 
 hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction, char* ws,
@@ -289,40 +418,46 @@ hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction
   const int dim = p.n_heads * p.head_dim;
   if (dim > kVcMaxDim) return hipErrorInvalidValue;
   VcosArgs A;
-  A.seqs_c = seqs; A.seqs = seqs;
+  A.seqs = seqs;
   A.inv_norm = reinterpret_cast<float*>(ws + w.vcos_off);
   A.u_part = reinterpret_cast<float*>(ws + w.vcos_u_off);
   A.s_out = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<float*>(ws + w.vcos_s_off) : nullptr;
-  A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.elem_bytes = elem_bytes(p); A.cap = p.cap;
-  A.n_tiles = (p.cap + kVcTile - 1) / kVcTile;
+  A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
+  // As large a tile as still gives every CU two workgroups: the second pass reads every tile's partial of u in each workgroup
+  // (256 sequences x 692 slots: 154 us both passes with tiles of 256, 177 with 128; taking 128 or 64 sequences at a time so that
+  // the second pass finds them in the memory-side cache costs more in short launches than it saves: 192 and 256 us).
+  A.tile = 256;
+  while (A.tile > kVcTile && (long long)p.n_seq * ((p.cap + A.tile - 1) / A.tile) < 512) A.tile /= 2;
+  A.n_tiles = (p.cap + A.tile - 1) / A.tile;
   A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius;
   A.for_compaction = for_compaction ? 1 : 0; A.recent_m = p.win_recent_m; A.evict_policy = p.evict_policy;
-  A.slot_stride_b = (long long)p.kv_slot_stride * A.elem_bytes;
-  A.head_stride_b = (long long)p.kv_head_stride * A.elem_bytes;
-  dim3 grid(A.n_tiles, p.n_seq);
-  const int gpl = (dim / 4 + kWave - 1) / kWave;          // column groups per lane: 1..32
-  const size_t lds1 = sizeof(float) * (size_t)dim * kVcWaves;
-  if (gpl <= 4) hipLaunchKernelGGL(k_vcos_norm_usum<4>, grid, dim3(kVcThreads), lds1, st, A);
-  else if (gpl <= 6) hipLaunchKernelGGL(k_vcos_norm_usum<6>, grid, dim3(kVcThreads), lds1, st, A);
-  else if (gpl <= 8) hipLaunchKernelGGL(k_vcos_norm_usum<8>, grid, dim3(kVcThreads), lds1, st, A);
-  else if (gpl <= 16) hipLaunchKernelGGL(k_vcos_norm_usum<16>, grid, dim3(kVcThreads), lds1, st, A);
-  else {
+  A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
+  A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
+  const dim3 grid(A.n_tiles, p.n_seq);
+  return with_row_shape(p, [&](auto eb, auto g) {
+    constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
     // (64..128 KB of LDS, above the default per-launch limit: allowed once per device by vcos_prepare_kernels)
-    hipLaunchKernelGGL(k_vcos_norm_usum<32>, grid, dim3(kVcThreads), lds1, st, A);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_vcos_score, grid, dim3(kVcThreads), sizeof(float) * (size_t)dim, st, A);
-  return hipGetLastError();
+    hipLaunchKernelGGL((k_vcos_norm_usum<EB, G>), grid, dim3(kVcThreads), sizeof(float) * (size_t)dim * kVcWaves, st, A);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_vcos_score<EB, G>), grid, dim3(kVcThreads), 0, st, A);
+    return hipGetLastError();
+  });
 }
 
 int vcos_tiles(int cap) { return (cap + kVcTile - 1) / kVcTile; }
 
-// The widest first-pass kernel may need up to 128 KB of dynamic LDS (n_heads * head_dim = 8192 floats x 4 waves):
-// allowed here, once per device, at the library's first use of that device.
+// Rows of 4096 elements need 64 KB of dynamic LDS (4 waves' sums) beside the static words, rows of 8192 (the limit) 128 KB: more
+// than a launch may ask for by default.  Allowed here, once per device, at the library's first use of that device.
 hipError_t vcos_prepare_kernels() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vcos_norm_usum<32>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  const void* kernels[] = {reinterpret_cast<const void*>(&k_vcos_norm_usum<2, 8>), reinterpret_cast<const void*>(&k_vcos_norm_usum<2, 16>),
+                           reinterpret_cast<const void*>(&k_vcos_norm_usum<4, 16>), reinterpret_cast<const void*>(&k_vcos_norm_usum<4, 32>),
+                           reinterpret_cast<const void*>(&k_vcos_advance<2, 8>), reinterpret_cast<const void*>(&k_vcos_advance<4, 16>)};
+  for (const void* k : kernels) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace adsa
