@@ -15,6 +15,8 @@ import torch
 from . import binding as B
 from .workloads import bf16_bits
 
+_SEQ_BYTES = B.SEQ_DTYPE.itemsize
+
 
 def to_device(x: np.ndarray, dtype_code: int, device) -> torch.Tensor:
     """float32 host values (already representable in the storage type) -> device tensor."""
@@ -180,8 +182,11 @@ class ModelBatch(LayerBatch):
         B.adsa_compact(self.params, self.seqs, self.keep_map, self.workspace, flags, stream)
 
     def attend_layer(self, layer: int, q, k_new=None, v_new=None, flags: int = 0, stream=None):
-        n, p = self.n_per_layer, self.layer_params
-        b0 = layer * n
-        B.adsa_attend(p, self.seqs.data_ptr() + b0 * B.SEQ_DTYPE.itemsize, q,
-                      self.sel_idx.data_ptr() + b0 * p.sel_cap * 4, self.sel_cnt.data_ptr() + b0 * 4,
-                      self.out[b0:b0 + n], self.lse[b0:b0 + n], self.layer_workspace, flags, k_new, v_new, stream)
+        if not 0 <= layer < self.n_layers:
+            raise B.AdsaError(-1, "adsa_attend")
+        # (addresses instead of slices: a tensor slice takes as long as a third of a launch)
+        b0, out, lse = layer * self.n_per_layer, self.out, self.lse
+        B.adsa_attend(self.layer_params, self.seqs.data_ptr() + b0 * _SEQ_BYTES, q,
+                      self.sel_idx.data_ptr() + b0 * self.sel_idx.stride(0) * 4, self.sel_cnt.data_ptr() + b0 * 4,
+                      out.data_ptr() + b0 * out.stride(0) * out.element_size(), lse.data_ptr() + b0 * lse.stride(0) * 4,
+                      self.layer_workspace, flags, k_new, v_new, stream)
