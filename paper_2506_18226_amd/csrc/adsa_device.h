@@ -30,6 +30,11 @@ __device__ __forceinline__ void store16(gchar* p, const uint4& x) {
   *reinterpret_cast<ADSA_GLOBAL u32x4*>(p) = v;
 }
 
+__device__ __forceinline__ void store_stream16(gchar* p, const uint4& x) {
+  u32x4 v; v.x = x.x; v.y = x.y; v.z = x.z; v.w = x.w;
+  __builtin_nontemporal_store(v, reinterpret_cast<ADSA_GLOBAL u32x4*>(p));
+}
+
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
   uint32_t u = __float_as_uint(x);
   if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;   // NaN stays NaN
