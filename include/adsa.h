@@ -195,9 +195,9 @@ size_t adsa_workspace_bytes(const adsa_params* p);
 
 /*
  * Prepare a workspace (256-byte aligned, >= adsa_workspace_bytes(p)) for use with parameters p:
- * zeroes the arrival counters at its head with a small fill kernel on `stream`.  Call it once
+ * zeroes the words at its head with a small fill kernel on `stream`.  Call it once
  * after allocating the workspace and again before using the same memory with different
- * parameters; every later call leaves the counters zero.  A workspace may be shared by calls
+ * parameters.  A workspace may be shared by calls
  * that are ordered on one stream, not by concurrent ones.
  */
 int adsa_workspace_init(const adsa_params* p, void* workspace, size_t workspace_bytes, void* stream);

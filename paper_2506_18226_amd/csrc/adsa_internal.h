@@ -37,8 +37,8 @@ constexpr int kVcosTags = 4;      // floats after u in adsa_seq.vcos_u: [0] 1 + 
 
 // Workspace layout (byte offsets from a 256-byte aligned base).
 struct Workspace {
-  size_t counters_off;     // int32 [n_seq][head groups]  arrival counters of split grouped-query launches (zero between launches)
-  size_t persistent_bytes; // leading bytes that adsa_workspace_init zeroes and every launch leaves zero
+  size_t head_bytes;       // leading bytes that adsa_workspace_init zeroes; no kernel uses them, but they are part of the size
+                           // and of the offsets callers' workspaces were made for
   size_t logits_off;       // float [n_seq][n_heads][lg_stride]  scaled logits in log2 units
   size_t part_ml_off;      // float [n_seq][n_heads][n_chunks][2]   (m, l) per chunk
   size_t part_acc_off;     // float [n_seq][n_heads][n_chunks][head_dim]

@@ -136,7 +136,6 @@ constexpr size_t kStaticScratchBytes = ADSA_STATIC_SCRATCH_BYTES;
 constexpr int kMaxDevices = 64;
 struct StaticScratch {
   char* ptr = nullptr;          // device address of `scratch` on this GPU
-  size_t zero_bytes = 0;        // leading bytes (arrival counters) the last call's layout kept at zero; 0 = none yet
 };
 StaticScratch g_static[kMaxDevices];
 
@@ -157,7 +156,6 @@ int static_scratch(StaticScratch** out) {
     void* ptr = nullptr;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return ADSA_ERR_LAUNCH;
     s.ptr = static_cast<char*>(ptr);
-    s.zero_bytes = 0;
   }
   *out = &s;
   return ADSA_OK;
@@ -350,15 +348,9 @@ int adsa_step_static(const adsa_params* p, adsa_seq* seqs, const void* q, const 
   if (rc) return rc;
   rc = ensure_device_ready();
   if (rc) return rc;
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // The array keeps the previous call's contents.  The arrival counters at its head must start at zero: every
-  // launch leaves its own counters zero, so only a call whose counter region differs from the previous call's
-  // (it may reach into bytes that call used for something else) clears it, with a fill kernel.
-  if (sc->zero_bytes != w.persistent_bytes) {
-    if (launch_workspace_init(sc->ptr, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
-    sc->zero_bytes = w.persistent_bytes;
-  }
-  return step_launches(p, plan, w, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, flags, sc->ptr, st);
+  // (the array keeps the previous call's contents: every kernel writes what a later one of the same call reads)
+  return step_launches(p, plan, w, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, flags, sc->ptr,
+                       reinterpret_cast<hipStream_t>(stream));
 }
 
 int adsa_profile_enable(int on) {

@@ -610,10 +610,8 @@ AttendPlan make_attend_plan(const adsa_params& p) {
     a.waves = wgs >= 512 ? 4 : 8;
     // Lists are split only when they must be (the logits of a whole list, all G queries, do not fit in LDS even
     // with 4 waves) or when it was measured to pay: long lists (>= 2560 slots) of at most 32 (sequence, cache head)
-    // pairs.  The hand-off between workgroups costs a release/acquire at device scope per workgroup, which grows
-    // with the number of workgroups: 88 pairs x 16 chunks of 2800-token lists took 82 us, unsplit 42 us; one
-    // sequence (8 pairs) 25 us against 41 us.  Hence: as many chunks as fit the LDS limit, and more only while the
-    // launch stays near 128 workgroups.
+    // pairs, 8 pairs x 2700 x 128 16.7 us in 16 chunks; merged by the last of them to arrive it was 25, whole 41.
+    // Hence: as many chunks as fit the LDS limit, and more only while the launch stays near 128 workgroups.
     int nc = 1;
     const bool must = gqa_lds_bytes(p, 4, 1) > kGqaMaxLds;
     if (must || (p.sel_cap >= 2560 && wgs <= 32)) {
@@ -666,9 +664,8 @@ Workspace make_workspace(const adsa_params& p, const AttendPlan& plan) {
   const bool split = plan.reserved_chunks > 1;
   const size_t hq = (size_t)p.n_heads * (p.q_per_kv > 1 ? p.q_per_kv : 1);      // rows of out / logits / partials per sequence
   w.lg_stride = p.q_per_kv > 1 ? gqa_global_logit_stride(p) : (int)align_up((size_t)p.sel_cap, 4);
-  w.counters_off = off;
   off = align_up(off + sizeof(int32_t) * (size_t)p.n_seq * head_groups(p), 256);
-  w.persistent_bytes = off;     // must stay zero between launches
+  w.head_bytes = off;
   w.logits_off = off;
   if (split) off = align_up(off + sizeof(float) * (size_t)p.n_seq * hq * w.lg_stride, 256);
   w.part_ml_off = off;
@@ -692,9 +689,9 @@ Workspace make_workspace(const adsa_params& p, const AttendPlan& plan) {
 }
 
 hipError_t launch_workspace_init(char* ws, const Workspace& w, hipStream_t st) {
-  const size_t words = w.persistent_bytes / 4;
+  const size_t words = w.head_bytes / 4;
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st,
-                     reinterpret_cast<uint32_t*>(ws + w.counters_off), words);
+                     reinterpret_cast<uint32_t*>(ws), words);
   return hipGetLastError();
 }
 

@@ -81,6 +81,9 @@ __device__ __forceinline__ void vload(const gchar* p, uint32_t* w) {
   }
 }
 
+// lane g's value, g uniform
+__device__ __forceinline__ float lane_f(float x, int g) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), g)); }
+
 struct GqaArgs {
   adsa_seq* seqs;
   const char* q;
@@ -93,7 +96,6 @@ struct GqaArgs {
   float* logits;        // [n_seq][n_heads * G][lg_global]  scaled logits, log2 units (split launches)
   float* part_ml;       // [n_seq][n_heads * G][n_chunks][2]
   float* part_acc;      // [n_seq][n_heads * G][n_chunks][D]
-  int32_t* counters;    // [n_seq][n_heads]                 arrival counters, zero between launches
   int lg_global;        // row stride of logits
   int n_heads, G, sel_cap, lg_stride, cap, stage_b;
   int accumulate, append, advance;
@@ -107,8 +109,7 @@ struct GqaArgs {
 // without waiting for a scalar load of the argument block.  Only 14 dwords are preloaded, so the group size and
 // the two append flags ride on the head count: heads | G << 16 | append << 24 | new_f32 << 25.
 // SPLIT: the list of a (sequence, cache head) is cut into gridDim.z chunks of whole 16-token tiles, one workgroup
-// each; every workgroup leaves a partial and its logits in the workspace and the LAST one to arrive merges them, in
-// chunk order (an arrival counter; nothing waits).
+// each; every workgroup leaves a partial and its logits in the workspace and k_gqa_finish merges them in chunk order.
 template <int D, int NW, bool SPLIT>
 __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
                                                           const char* q_arg, const char* k_new_arg, const char* v_new_arg,
@@ -125,8 +126,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
                                             // 1, 2 and 3 were measured within 1 % of each other on 8 x 128 x 8-wave lists)
   constexpr int PF = 2048 / T;              // slot-list entries a thread fetches in the first round trip
   extern __shared__ __align__(16) char smem[];
-  __shared__ float s_wm[NW][16], s_wl[NW][16], s_lse2[16], s_m[16], s_l[16];
-  __shared__ int s_ticket;
+  __shared__ float s_wm[NW][16], s_wl[NW][16];
 
   const int hk = blockIdx.x, b = blockIdx.y;
   const int chunk = SPLIT ? blockIdx.z : 0, n_chunks = SPLIT ? gridDim.z : 1;
@@ -154,14 +154,20 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   uint4 qx[NC / 2];
 #pragma unroll
   for (int c2 = 0; c2 < NC / 2; ++c2) qx[c2] = load16(q_row0 + ((size_t)min(r, G - 1) * D + (D / 4) * kg) * 2 + c2 * 16);
-  int pf_slot[PF];                                   // (a chunk of a split list starts where the count says: fetched below)
+  // The slots of the wave's first R tiles (lane 16 * u + j: token j of tile u) and the whole list (one entry per thread and
+  // round) that goes to LDS for the later ones.  (A chunk of a split list starts where the count says: fetched below.)
+  static_assert(R <= 4, "16 lanes per tile");
+  const int ld_row = lane / LPR, ld_piece = lane - ld_row * LPR;
+  const int first_at = (wave + kg * NW) * 16 + r;            // list position of this lane's token
+  int slot_first = 0, slot_0 = 0, pf_slot[PF];
   if constexpr (!SPLIT) {
+    slot_0 = idx[0];
+    slot_first = idx[min(first_at, sel_cap - 1)];
 #pragma unroll
     for (int k = 0; k < PF; ++k) pf_slot[k] = idx[min(tid + k * T, sel_cap - 1)];
   }
   // the query token's row (Section 4.2 append); fp32 rows are rounded once, here: every lane keeps the pieces of
   // the rounded row it would load from the cache (K: 16 bytes at ld_piece, V: its EV columns)
-  const int ld_row = lane / LPR, ld_piece = lane - ld_row * LPR;
   const size_t new_row = ((size_t)b * n_heads + hk) * D;
   uint4 nk = make_uint4(0u, 0u, 0u, 0u);
   uint32_t nv[VW];
@@ -219,17 +225,6 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   const int t_begin = tile_begin * 16;
   const int len = min(cnt, tile_end * 16) - t_begin;           // tokens of this workgroup, numbered from 0 below
   const int n_tiles = tile_end - tile_begin;
-  // slots of the list, clamped into the cache, go to LDS (readers clamp their list position to the last token)
-  if constexpr (!SPLIT) {
-#pragma unroll
-    for (int k = 0; k < PF; ++k) {
-      const int j = tid + k * T;
-      if (j < len) s_slot[j] = min(max(pf_slot[k], 0), A.cap - 1);
-    }
-    for (int j = tid + PF * T; j < len; j += T) s_slot[j] = min(max(idx[j], 0), A.cap - 1);
-  } else {
-    for (int j = tid; j < len; j += T) s_slot[j] = min(max(idx[t_begin + j], 0), A.cap - 1);
-  }
   s16x4 qb[NC];
 #pragma unroll
   for (int c2 = 0; c2 < NC / 2; ++c2) {
@@ -238,7 +233,6 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     qb[2 * c2 + 1] = as_bf16x4(x.z, x.w);
   }
   const int new_slot = (append && pending >= 0 && pending < A.cap) ? pending : -1;
-  __syncthreads();
 
   // (the lambdas below work on copies: they capture by reference, and a reference to the kernel's argument
   //  struct was measured to cost time in the multi-head kernel)
@@ -257,28 +251,31 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   // take a uniform base and a 32-bit lane offset, two instructions of address arithmetic instead of a 64-bit product
   const uint32_t stride32 = (uint32_t)slot_stride_b;
   const uint32_t k_lane_off = (uint32_t)ld_piece * 16u, v_lane_off = (uint32_t)r * (EV * 2);
-  auto issue = [&](int u, int tile) {
-    int slot_k[LT], slot_v[4];                       // all slots of the tile first: one LDS round trip, then the loads
-#pragma unroll
-    for (int l = 0; l < LT; ++l) slot_k[l] = s_slot[min(tile * 16 + l * RPL + ld_row, len - 1)];   // (tiles past the end re-read the last row)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) slot_v[i] = s_slot[min(tile * 16 + 4 * kg + i, len - 1)];
+  auto request = [&](int u, const int (&sk)[LT], const int (&sv)[4]) {
     // The query token's own slot is read like any other (valid memory of the cache; the row is stored at the end of
     // this launch) and what arrives is replaced by the row held in registers when the tile is multiplied.
     uint32_t f = 0u;
 #pragma unroll
     for (int l = 0; l < LT; ++l) {
-      kr[u][l] = load_stream16(k_base + ((uint32_t)slot_k[l] * stride32 + k_lane_off));
-      f |= slot_k[l] == new_slot ? (1u << l) : 0u;
+      kr[u][l] = load_stream16(k_base + ((uint32_t)sk[l] * stride32 + k_lane_off));
+      f |= sk[l] == new_slot ? (1u << l) : 0u;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      vload<VW, true>(v_base + ((uint32_t)slot_v[i] * stride32 + v_lane_off), vr[u][i]);
-      f |= slot_v[i] == new_slot ? (1u << (8 + i)) : 0u;
+      vload<VW, true>(v_base + ((uint32_t)sv[i] * stride32 + v_lane_off), vr[u][i]);
+      f |= sv[i] == new_slot ? (1u << (8 + i)) : 0u;
     }
     fresh[u] = f;
     asm volatile("" : : : "memory");                 // requests leave in ring order (the wait counts rely on it)
     __builtin_amdgcn_sched_barrier(0);               // ... and before the next tile's arithmetic, which waits for ITS rows
+  };
+  auto issue = [&](int u, int tile) {
+    int sk[LT], sv[4];                               // all slots of the tile first: one LDS round trip, then the loads
+#pragma unroll
+    for (int l = 0; l < LT; ++l) sk[l] = s_slot[min(tile * 16 + l * RPL + ld_row, len - 1)];   // (tiles past the end re-read the last row)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sv[i] = s_slot[min(tile * 16 + 4 * kg + i, len - 1)];
+    request(u, sk, sv);
   };
 
   float m_run = -INFINITY, l_lane = 0.0f;            // online softmax of query g = r (l: this lane's tokens only)
@@ -362,8 +359,37 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     // the units one ring revolution later; the last trip only multiplies, and skips ring positions without a tile.
     const int n_mine = n_tiles > wave ? (n_tiles - wave + NW - 1) / NW : 0;
     const int n_trips = (n_mine + R - 1) / R;
+    if constexpr (!SPLIT) {
+      // ... from the slots the first round trip brought in registers; the list is staged in LDS while the rows are on their way
+      // (positions past the end of the list may hold anything: they read the first token's row, which is attended)
+      slot_first = min(max(first_at < len ? slot_first : slot_0, 0), A.cap - 1);
+      int sk[R][LT], sv[R][4];
 #pragma unroll
-    for (int u = 0; u < R; ++u) issue(u, wave + u * NW);
+      for (int u = 0; u < R; ++u) {
+#pragma unroll
+        for (int l = 0; l < LT; ++l) sk[u][l] = __shfl(slot_first, 16 * u + l * RPL + ld_row, kWave);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sv[u][i] = __shfl(slot_first, 16 * u + 4 * kg + i, kWave);
+      }
+#pragma unroll
+      for (int u = 0; u < R; ++u) request(u, sk[u], sv[u]);
+    }
+  // slots of the list, clamped into the cache, go to LDS (readers clamp their list position to the last token)
+  if constexpr (!SPLIT) {
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+      const int j = tid + k * T;
+      if (j < len) s_slot[j] = min(max(pf_slot[k], 0), A.cap - 1);
+    }
+    for (int j = tid + PF * T; j < len; j += T) s_slot[j] = min(max(idx[j], 0), A.cap - 1);
+  } else {
+    for (int j = tid; j < len; j += T) s_slot[j] = min(max(idx[t_begin + j], 0), A.cap - 1);
+  }
+    __syncthreads();
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) issue(u, wave + u * NW);
+    }
     int k0 = 0;                                      // unit at ring position 0
     for (int trip = 1; trip < n_trips; ++trip) {
 #pragma unroll
@@ -393,39 +419,30 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     }
   }
   __syncthreads();
-  // Softmax weights of the waves, per query: s_wm[w][g] becomes wave w's weight 2^(m_w - M).  No global
-  // store has been issued so far, so the two barriers here wait for LDS traffic only; every store of
-  // the kernel follows the last barrier and is acknowledged once, at the end.
-  if (tid < 16) {
-    float M = -INFINITY;
+  // Every wave works out for itself, lane r for query r: the waves' softmax weights 2^(m_w - M), the normaliser and its
+  // logarithm; a query's values are then fetched by lane.  (One wave doing it for all behind a second barrier was slower.)
+  float wgt[NW], M = -INFINITY, L = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_wm[w][tid]);
-    float L = 0.0f;
+  for (int w = 0; w < NW; ++w) { wgt[w] = s_wm[w][r]; M = fmaxf(M, wgt[w]); }
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float mw = s_wm[w][tid];
-      const float wgt = (mw == -INFINITY) ? 0.0f : fast_exp2(mw - M);      // a wave that saw no tile: weight 0
-      L = fmaf(s_wl[w][tid], wgt, L);
-      s_wm[w][tid] = wgt;
-    }
-    s_lse2[tid] = M + __log2f(L);
-    s_m[tid] = M; s_l[tid] = L;
-    s_wl[0][tid] = 1.0f / L;
+  for (int w = 0; w < NW; ++w) {
+    wgt[w] = (wgt[w] == -INFINITY) ? 0.0f : fast_exp2(wgt[w] - M);         // a wave that saw no tile: weight 0
+    L = fmaf(s_wl[w][r], wgt[w], L);
   }
-  __syncthreads();
+  const float lse2 = M + __log2f(L), inv_l = 1.0f / L;
   const size_t hq0 = (size_t)b * HQ + (size_t)hk * G;           // first query head of this cache head
   for (int o = tid; o < G * D; o += T) {
-    const int g = o / D, d = o - g * D;
+    const int g = __builtin_amdgcn_readfirstlane(o / D), d = o - g * D;       // (a wave's 64 columns belong to one query)
     float a = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) a = fmaf(reinterpret_cast<const float*>(s_stage + w * A.stage_b)[o], s_wm[w][g], a);
+    for (int w = 0; w < NW; ++w) a = fmaf(reinterpret_cast<const float*>(s_stage + w * A.stage_b)[o], lane_f(wgt[w], g), a);
     if constexpr (!SPLIT) {
-      out[o] = (uint16_t)f32_to_bf16_rne(a * s_wl[0][g]);
-      if (d == 0) lse[g] = s_lse2[g] * kLn2;
+      out[o] = (uint16_t)f32_to_bf16_rne(a * lane_f(inv_l, g));
+      if (d == 0) lse[g] = lane_f(lse2, g) * kLn2;
     } else {                                         // this chunk's partial, relative to its own maximum
       const size_t pidx = (hq0 + g) * n_chunks + chunk;
-      st_dev(A.part_acc + pidx * D + d, a);
-      if (d == 0) st_dev2(A.part_ml + pidx * 2, s_m[g], s_l[g]);
+      A.part_acc[pidx * D + d] = a;
+      if (d == 0) { A.part_ml[pidx * 2] = lane_f(M, g); A.part_ml[pidx * 2 + 1] = lane_f(L, g); }
     }
   }
   // Section 4.2 append: this cache head's rows of the new token, from the registers that attended them
@@ -449,86 +466,102 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     if (A.accumulate) {
       for (int t = tid; t < len; t += T) {
         float inc = 0.0f;
-        for (int g = 0; g < G; ++g) inc += fast_exp2(s_logit[(size_t)g * lgs + t] - s_lse2[g]);
+        for (int g0 = 0; g0 < G; g0 += 8) {          // eight queries' logits in flight together
+          float z[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) z[k] = s_logit[(size_t)min(g0 + k, G - 1) * lgs + t];
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (g0 + k < G) inc += fast_exp2(z[k] - lane_f(lse2, g0 + k));
+        }
         unsafeAtomicAdd((float*)(score + s_slot[t]), inc);
       }
     }
     if (hk == 0 && tid == 0 && A.advance) sqp->step = sqp->step + 1;     // no other workgroup reads step
   } else {
-    // ---------------- several chunks: publish the logits, arrive, and let the last workgroup finish the cache head.
-    // Partials and logits are written with device-scope atomic stores (written through to where all XCDs agree);
-    // every thread waits until its own stores have completed, the barrier collects the workgroup, one thread bumps
-    // the arrival counter with a device-scope release/acquire read-modify-write, and the workgroup that draws the
-    // last ticket reads everything back with device-scope atomic loads after the barrier that follows its acquire.
-    const int lgG = A.lg_global;
+    // ---------------- several chunks: this workgroup's partial and logits are in the workspace; k_gqa_finish, the next kernel
+    // on the stream, merges them (the launch boundary orders the two and makes the stores visible on every XCD)
     if (keep_logits) {
-      for (int i = tid; i < G * len; i += T) {
-        const int g = i / len, t = i - g * len;
-        st_dev(A.logits + (hq0 + g) * lgG + t_begin + t, s_logit[(size_t)g * lgs + t]);
+      for (int g = 0; g < G; ++g) {
+        float* const lg = A.logits + (hq0 + g) * A.lg_global + t_begin;
+        for (int t = tid; t < len; t += T) lg[t] = s_logit[(size_t)g * lgs + t];
       }
     }
-    const int n_nonempty = min(tiles_all, n_chunks);
-    int32_t* ctr = A.counters + (size_t)b * n_heads + hk;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (s_ticket != n_nonempty - 1) return;
-    if (tid == 0) *ctr = 0;                          // ready for the next launch
-    for (int o = tid; o < G * D; o += T) {
-      const int g = o / D, d = o - g * D;
-      const size_t pbase = (hq0 + g) * n_chunks;
-      float mc[kMaxChunks], lc[kMaxChunks], ac[kMaxChunks];
-#pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) {         // all loads in flight together
-        const bool on = c < n_chunks && ((unsigned)tiles_all * (unsigned)c) / (unsigned)n_chunks <
-                                            ((unsigned)tiles_all * (unsigned)(c + 1)) / (unsigned)n_chunks;
-        mc[c] = on ? ld_dev(A.part_ml + (pbase + c) * 2) : -INFINITY;
-        lc[c] = on ? ld_dev(A.part_ml + (pbase + c) * 2 + 1) : 0.0f;
-        ac[c] = on ? ld_dev(A.part_acc + (pbase + c) * D + d) : 0.0f;
-      }
-      float Mx = -INFINITY;
-#pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) Mx = fmaxf(Mx, mc[c]);
-      float Lx = 0.0f, a = 0.0f;
-#pragma unroll
-      for (int c = 0; c < kMaxChunks; ++c) {
-        const float wgt = (mc[c] == -INFINITY) ? 0.0f : fast_exp2(mc[c] - Mx);
-        Lx = fmaf(lc[c], wgt, Lx);
-        a = fmaf(ac[c], wgt, a);
-      }
-      out[o] = (uint16_t)f32_to_bf16_rne(__fdividef(a, Lx));
-      if (d == 0) {
-        const float lse2 = Mx + __log2f(Lx);
-        lse[g] = lse2 * kLn2;
-        s_lse2[g] = lse2;
-      }
-    }
-    if (A.accumulate) {
-      __syncthreads();
-      for (int t0 = tid; t0 < cnt; t0 += 2 * T) {     // two tokens per thread and trip: all their logits in flight together
-        float z[2][16];
-        int slot[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int t = min(t0 + u * T, cnt - 1);
-#pragma unroll
-          for (int g = 0; g < 16; ++g) z[u][g] = g < G ? ld_dev(A.logits + (hq0 + g) * lgG + t) : 0.0f;
-          slot[u] = min(max(idx[t], 0), A.cap - 1);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          if (t0 + u * T >= cnt) continue;
-          float inc = 0.0f;
-#pragma unroll
-          for (int g = 0; g < 16; ++g)
-            if (g < G) inc += fast_exp2(z[u][g] - s_lse2[g]);
-          unsafeAtomicAdd((float*)(score + slot[u]), inc);
-        }
-      }
-    }
-    if (hk == 0 && tid == 0 && A.advance) sqp->step = sqp->step + 1;
   }
+}
+
+// Second half of a split launch: grid (token slice, cache head, sequence).  Thread (g, c) weighs chunk c of query g; slice 0
+// merges the partial outputs in chunk order and writes out / lse; every slice adds the probabilities of its tokens, summed over
+// the queries in ascending order, to the cache head's score row.
+constexpr int kFinishThreads = 256, kFinishTokens = 2 * kFinishThreads;
+static_assert(kMaxChunks == 16 && kFinishThreads == 16 * 16, "one thread per (query, chunk), a query's chunks in one 16-lane row");
+template <int D>
+__global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_chunks) {
+  __shared__ float s_w[16][kMaxChunks], s_lse2[16], s_l[16];
+  const int slice = blockIdx.x, hk = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)(A.seqs + b);
+  const int cnt = min(((const gint*)A.sel_cnt)[b], A.sel_cap), G = A.G;
+  if (cnt <= 0 || slice * kFinishTokens >= cnt) return;      // (inactive sequences: zero rows, already written)
+  const size_t hq0 = ((size_t)b * A.n_heads + hk) * G;
+  const unsigned tiles = (unsigned)(cnt + 15) / 16;
+  auto on = [&](int c) {                                     // chunks without a tile hold nothing (their workspace words are stale)
+    return c < n_chunks && (tiles * (unsigned)c) / (unsigned)n_chunks < (tiles * (unsigned)(c + 1)) / (unsigned)n_chunks;
+  };
+  const gfloat* const ml = (const gfloat*)A.part_ml;
+  const gint* const idx = (const gint*)A.sel_idx + (size_t)b * A.sel_cap;
+  const int t0 = slice * kFinishTokens + tid;
+  int slot[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) slot[u] = min(max(idx[min(t0 + u * kFinishThreads, cnt - 1)], 0), A.cap - 1);
+  {
+    const int g = tid / 16, c = tid % 16;
+    const bool have = g < G && on(c);
+    const float m = have ? ml[((hq0 + g) * n_chunks + c) * 2] : -INFINITY, l = have ? ml[((hq0 + g) * n_chunks + c) * 2 + 1] : 0.0f;
+    float M = m;
+#pragma unroll
+    for (int x = 1; x < 16; x <<= 1) M = fmaxf(M, __shfl_xor(M, x, kWave));
+    const float w = m == -INFINITY ? 0.0f : fast_exp2(m - M);
+    float L = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kMaxChunks; ++k) L = fmaf(__shfl(l, (tid & 48) + k, kWave), __shfl(w, (tid & 48) + k, kWave), L);
+    s_w[g][c] = w;
+    if (c == 0) { s_lse2[g] = M + __log2f(L); s_l[g] = L; }
+  }
+  __syncthreads();
+  if (slice == 0) {
+    ADSA_GLOBAL uint16_t* const out = reinterpret_cast<ADSA_GLOBAL uint16_t*>((gchar*)A.out) + hq0 * D;
+    for (int o = tid; o < G * D; o += kFinishThreads) {
+      const int g = o / D, d = o - g * D;
+      const gfloat* const acc = (const gfloat*)A.part_acc + (hq0 + g) * n_chunks * D + d;
+      float ac[kMaxChunks], a = 0.0f;
+#pragma unroll
+      for (int c = 0; c < kMaxChunks; ++c) ac[c] = on(c) ? acc[(size_t)c * D] : 0.0f;
+#pragma unroll
+      for (int c = 0; c < kMaxChunks; ++c) a = fmaf(ac[c], s_w[g][c], a);
+      out[o] = (uint16_t)f32_to_bf16_rne(__fdividef(a, s_l[g]));
+      if (d == 0) ((gfloat*)A.lse)[hq0 + g] = s_lse2[g] * kLn2;
+    }
+  }
+  if (A.accumulate) {
+    gfloat* const score = (gfloat*)sqp->score + (size_t)hk * A.cap;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int t = t0 + u * kFinishThreads;
+      if (t >= cnt) continue;
+      const gfloat* const lg = (const gfloat*)A.logits + hq0 * A.lg_global + t;
+      float inc = 0.0f;
+      for (int g0 = 0; g0 < G; g0 += 8) {
+        float z[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) z[k] = lg[(size_t)min(g0 + k, G - 1) * A.lg_global];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (g0 + k < G) inc += fast_exp2(z[k] - s_lse2[g0 + k]);
+      }
+      unsafeAtomicAdd((float*)(score + slot[u]), inc);
+    }
+  }
+  if (slice == 0 && hk == 0 && tid == 0 && A.advance) sqp->step = sqp->step + 1;
 }
 
 template <int D, int NW, bool SPLIT>
@@ -536,12 +569,22 @@ hipError_t launch_gqa_w(const GqaArgs& A, int n_seq, int n_chunks, size_t lds, h
                         hipEvent_t ev_stop) {
   dim3 grid(A.n_heads, n_seq, n_chunks);     // (lists that need more than 64 KB of LDS: see gqa_prepare_kernels)
   const int hgf = A.n_heads | (A.G << 16) | (A.append ? 1 << 24 : 0) | (A.new_f32 ? 1 << 25 : 0);
+  // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, ev_stop, 0,
+    hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, SPLIT ? nullptr : ev_stop, 0,
                           A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
   else
     hipLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT>), grid, dim3(NW * kWave), lds, st,
                        A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
+  if constexpr (SPLIT) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 fgrid(A.accumulate ? (A.sel_cap + kFinishTokens - 1) / kFinishTokens : 1, A.n_heads, n_seq);
+    if (ev_start && ev_stop)
+      hipExtLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, nullptr, ev_stop, 0, A, n_chunks);
+    else
+      hipLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, A, n_chunks);
+  }
   return hipGetLastError();
 }
 
@@ -603,7 +646,6 @@ hipError_t launch_attend_gqa(const adsa_params& p, const AttendPlan& plan, adsa_
   A.logits = reinterpret_cast<float*>(ws + w.logits_off);
   A.part_ml = reinterpret_cast<float*>(ws + w.part_ml_off);
   A.part_acc = reinterpret_cast<float*>(ws + w.part_acc_off);
-  A.counters = reinterpret_cast<int32_t*>(ws + w.counters_off);
   A.lg_global = gqa_global_logit_stride(p);
   A.n_heads = p.n_heads; A.G = p.q_per_kv; A.sel_cap = p.sel_cap; A.lg_stride = gqa_logit_stride(p, plan.n_chunks);
   A.cap = p.cap; A.stage_b = (int)gqa_stage_bytes(p);
