@@ -19,7 +19,7 @@
 //            contraction runs over tokens).  P is split into two bf16 halves (hi + lo) so that the
 //            product carries ~16 mantissa bits of the probabilities.  When a query's running maximum
 //            m[g] grows, the accumulators are rescaled (factors fetched across lanes).
-//    Each wave keeps a small ring of tiles in flight: it waits for the OLDEST tile's K rows only (in-order wait
+//    Each wave keeps one or two tiles in flight: it waits for the OLDEST tile's K rows only (in-order wait
 //    counts; a tile is always requested as its K loads followed by its V loads, with no branch in between),
 //    multiplies it and refills its registers with the tile one ring revolution later.  Loads take a uniform base
 //    and a 32-bit lane offset; the query token's own slot is read like any other and replaced from registers.
@@ -122,8 +122,11 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   constexpr int NC = D / 16;                // 16-wide chunks of the q.k contraction
   constexpr int EV = D / 16;                // V columns a lane holds per token
   constexpr int VW = EV / 2;                // dwords of V a lane loads per token
-  constexpr int R = D == 64 ? 4 : 2;        // tiles in flight per wave (a ring: the oldest is multiplied, then refilled;
-                                            // 1, 2 and 3 were measured within 1 % of each other on 8 x 128 x 8-wave lists)
+  // Tiles in flight per wave (a ring: the oldest is multiplied, then refilled), 8 KB of loads: with no more registers than that
+  // (128) two 8-wave workgroups share a CU, and one hides the other's first trip, merge and stores.  32 x 8 x 649 x 128:
+  // 17.6 us with 1 tile, 17.9 with 2, 19.3 with 3; 48 x 8 x 300 x 128 15.7 with 1, 19.2 with 2; 32 x 8 x 649 x 64 11.4
+  // with 1 or 2, 12.9 with 4.
+  constexpr int R = D == 64 ? 2 : 1;
   constexpr int PF = 2048 / T;              // slot-list entries a thread fetches in the first round trip
   extern __shared__ __align__(16) char smem[];
   __shared__ float s_wm[NW][16], s_wl[NW][16];
