@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "adsa_internal.h"
+
 namespace adsa {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -48,6 +50,15 @@ __device__ __forceinline__ uint4 pack8_bf16(const gchar* f) {
   const float4 b = make_float4(__uint_as_float(ub.x), __uint_as_float(ub.y), __uint_as_float(ub.z), __uint_as_float(ub.w));
   return make_uint4(f32_to_bf16_rne(a.x) | (f32_to_bf16_rne(a.y) << 16), f32_to_bf16_rne(a.z) | (f32_to_bf16_rne(a.w) << 16),
                     f32_to_bf16_rne(b.x) | (f32_to_bf16_rne(b.y) << 16), f32_to_bf16_rne(b.z) | (f32_to_bf16_rne(b.w) << 16));
+}
+
+// The record at the end of an attention launch (one thread per sequence); see kAdvance.
+__device__ __forceinline__ void advance_step(ADSA_GLOBAL adsa_seq* sq, int mode) {
+  if (mode != kAdvanceNone) sq->step = sq->step + 1;
+  if (mode == kAdvanceActive) sq->compacted = 0;
+}
+__device__ __forceinline__ void advance_empty(ADSA_GLOBAL adsa_seq* sq, int mode) {      // a sequence without an attended token
+  if (mode == kAdvanceActive && sq->status == 0 && sq->step >= 0) advance_step(sq, mode);
 }
 
 // Demands a wave-uniform value that was just loaded in scalar registers AT THIS POINT of the program:

@@ -56,10 +56,19 @@ Workspace make_workspace(const adsa_params& p, const AttendPlan& plan);
 
 static inline int elem_bytes(const adsa_params& p) { return p.dtype == ADSA_F32 ? 4 : 2; }
 
+// What an attention launch does to the record when it is done with a sequence.
+enum : int {
+  kAdvanceNone = 0,
+  kAdvance = 1,            // step += 1 for every sequence it attended
+  kAdvanceActive = 2       // step += 1 and compacted = 0 for every active sequence, also one without an attended token: the
+                           // bookkeeping of a step whose eviction kernel, next on the stream, then only touches row ends
+};
+
 // Kernel launchers (each returns hipGetLastError() of its launch).
 hipError_t launch_workspace_init(char* ws, const Workspace& w, hipStream_t st);
+// tickets: NULL, or the words launch_compact_step counts in, which the launch clears
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
-                         bool plan_append, hipStream_t st);
+                         bool plan_append, int32_t* tickets, hipStream_t st);
 hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction, char* ws,
                        const Workspace& w, hipStream_t st);
 int vcos_tiles(int cap);
@@ -70,7 +79,7 @@ size_t vcos_advance_lds_bytes(const adsa_params& p);
 hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                          const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
                          void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
-                         bool advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+                         int advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
 // grouped-query path (q_per_kv >= 2): matrix-core kernel, one workgroup per (sequence, cache head, chunk of the list)
 constexpr size_t kGqaMaxLds = 128 * 1024;     // dynamic LDS one workgroup may ask for
 int gqa_logit_stride(const adsa_params& p, int n_chunks);
@@ -79,10 +88,14 @@ size_t gqa_lds_bytes(const adsa_params& p, int waves, int n_chunks);
 hipError_t launch_attend_gqa(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                              const void* k_new, const void* v_new, const int32_t* sel_idx,
                              const int32_t* sel_cnt, void* out, float* lse, char* ws, const Workspace& w,
-                             bool accumulate, bool append, bool advance, bool new_f32, hipStream_t st,
+                             bool accumulate, bool append, int advance, bool new_f32, hipStream_t st,
                              hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
                           const Workspace& w, bool advance_step, hipStream_t st);
+// The row-end eviction of a whole decode step in one launch (where one_launch_compact says so): after an attention launch with
+// kAdvanceActive, `tickets` cleared by the step's launch_select.
+bool one_launch_compact(const adsa_params& p);
+hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st);
 // once per device, before the first launch there: kernels that may ask for more than 64 KB of dynamic LDS
 hipError_t gqa_prepare_kernels();
 hipError_t vcos_prepare_kernels();

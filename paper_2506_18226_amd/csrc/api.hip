@@ -118,7 +118,7 @@ hipEvent_t prof_event() {
 hipError_t timed_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                         const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
                         void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
-                        bool advance, bool new_f32, hipStream_t st) {
+                        int advance, bool new_f32, hipStream_t st) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (g_prof.on) {
     e0 = prof_event();
@@ -176,11 +176,16 @@ int step_launches(const adsa_params* p, const AttendPlan& plan, const Workspace&
       return ADSA_ERR_LAUNCH;
   }
   if (vcos && !streaming && launch_vcos(*p, seqs, false, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
-  if (launch_select(*p, seqs, sel_idx, sel_cnt, true, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+  const bool one_launch = compact && one_launch_compact(*p);
+  int32_t* const tickets = one_launch ? reinterpret_cast<int32_t*>(ws + w.plan_off) : nullptr;
+  if (launch_select(*p, seqs, sel_idx, sel_cnt, true, tickets, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+  const int advance = one_launch ? kAdvanceActive : (!compact || streaming) ? kAdvance : kAdvanceNone;
   if (timed_attend(*p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, true,
-                   !compact || streaming, (flags & ADSA_FLAG_NEW_F32) != 0, st) != hipSuccess)
+                   advance, (flags & ADSA_FLAG_NEW_F32) != 0, st) != hipSuccess)
     return ADSA_ERR_LAUNCH;
-  if (compact && !streaming) {
+  if (one_launch) {
+    if (launch_compact_step(*p, seqs, keep_map, tickets, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+  } else if (compact && !streaming) {
     if (vcos && launch_vcos(*p, seqs, true, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
     if (launch_compact(*p, seqs, keep_map, ws, w, true, st) != hipSuccess) return ADSA_ERR_LAUNCH;
   }
@@ -264,7 +269,7 @@ int adsa_select(const adsa_params* p, adsa_seq* seqs, int32_t* sel_idx, int32_t*
     if (rc) return rc;
     if (launch_vcos(*p, seqs, false, (char*)workspace, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
   }
-  if (launch_select(*p, seqs, sel_idx, sel_cnt, (flags & ADSA_FLAG_PLAN_APPEND) != 0, st) != hipSuccess)
+  if (launch_select(*p, seqs, sel_idx, sel_cnt, (flags & ADSA_FLAG_PLAN_APPEND) != 0, nullptr, st) != hipSuccess)
     return ADSA_ERR_LAUNCH;
   return ADSA_OK;
 }
@@ -289,7 +294,7 @@ int adsa_attend(const adsa_params* p, adsa_seq* seqs, const void* q, const void*
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const bool accumulate = p->score_mode == ADSA_SCORE_ATTN_MASS && !(flags & ADSA_FLAG_NO_ACCUMULATE);
   if (timed_attend(*p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, (char*)workspace, w, accumulate,
-                   append, (flags & ADSA_FLAG_ADVANCE) != 0, (flags & ADSA_FLAG_NEW_F32) != 0, st) != hipSuccess)
+                   append, (flags & ADSA_FLAG_ADVANCE) ? kAdvance : kAdvanceNone, (flags & ADSA_FLAG_NEW_F32) != 0, st) != hipSuccess)
     return ADSA_ERR_LAUNCH;
   return ADSA_OK;
 }

@@ -76,7 +76,7 @@ struct AttendArgs {
   float* part_ml;       // [n_seq][n_heads][n_chunks][2]
   float* part_acc;      // [n_seq][n_heads][n_chunks][D]
   int n_heads, sel_cap, lg_stride, chunk_max, cap;
-  int accumulate, append, advance;     // advance: step += 1 at the end
+  int accumulate, append, advance;     // advance: see kAdvance
   int new_f32;                         // k_new / v_new are fp32 although the cache is bf16: round as they enter
   int vcos_fused;
   long long slot_stride_b, head_stride_b;
@@ -171,6 +171,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
         else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + o] = 0;
         if (o == 0) lse_g[row] = 0.0f;
       }
+      if (head == 0 && tid == 0) advance_empty(sqp, A.advance);
     }
     return;
   }
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
           tags[1] = tags[0] == want ? want : 0.0f;
         }
       }
-      if (A.advance) sqp->step = sqp->step + 1;
+      advance_step(sqp, A.advance);
     }
     return;
   } else {
@@ -533,7 +534,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
       const float want = (float)(sqp->step + 2);
       tags[1] = tags[0] == want ? want : 0.0f;
     }
-    if (A.advance) sqp->step = sqp->step + 1;
+    advance_step(sqp, A.advance);
   }
 }
 
@@ -703,7 +704,7 @@ hipError_t launch_workspace_init(char* ws, const Workspace& w, hipStream_t st) {
 hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                          const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
                          void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
-                         bool advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                         int advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (p.q_per_kv > 1)
     return launch_attend_gqa(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append,
                              advance, new_f32, st, ev_start, ev_stop);
@@ -715,7 +716,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
   A.part_acc = reinterpret_cast<float*>(ws + w.part_acc_off);
   A.n_heads = p.n_heads; A.sel_cap = p.sel_cap; A.lg_stride = w.lg_stride;
   A.chunk_max = plan.chunk_max; A.cap = p.cap;
-  A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance ? 1 : 0;
+  A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance;
   A.new_f32 = (new_f32 && append) ? 1 : 0;
   A.vcos_fused = p.score_mode == ADSA_SCORE_VCOS_FUSED ? 1 : 0;
   const int eb = elem_bytes(p);

@@ -216,6 +216,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         out[o] = 0;
         if (o % D == 0) lse[o / D] = 0.0f;
       }
+      if (hk == 0 && tid == 0) advance_empty(sqp, A.advance);
     }
     return;
   }
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         unsafeAtomicAdd((float*)(score + s_slot[t]), inc);
       }
     }
-    if (hk == 0 && tid == 0 && A.advance) sqp->step = sqp->step + 1;     // no other workgroup reads step
+    if (hk == 0 && tid == 0) advance_step(sqp, A.advance);     // no other workgroup reads step
   } else {
     // ---------------- several chunks: this workgroup's partial and logits are in the workspace; k_gqa_finish, the next kernel
     // on the stream, merges them (the launch boundary orders the two and makes the stores visible on every XCD)
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_
       unsafeAtomicAdd((float*)(score + slot[u]), inc);
     }
   }
-  if (slice == 0 && hk == 0 && tid == 0 && A.advance) sqp->step = sqp->step + 1;
+  if (slice == 0 && hk == 0 && tid == 0) advance_step(sqp, A.advance);
 }
 
 template <int D, int NW, bool SPLIT>
@@ -639,7 +640,7 @@ size_t gqa_lds_bytes(const adsa_params& p, int waves, int n_chunks) {
 hipError_t launch_attend_gqa(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                              const void* k_new, const void* v_new, const int32_t* sel_idx,
                              const int32_t* sel_cnt, void* out, float* lse, char* ws, const Workspace& w,
-                             bool accumulate, bool append, bool advance, bool new_f32, hipStream_t st,
+                             bool accumulate, bool append, int advance, bool new_f32, hipStream_t st,
                              hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (p.dtype != ADSA_BF16 || p.q_per_kv < 2 || p.q_per_kv > 16) return hipErrorInvalidValue;
   if (plan.n_chunks < 1 || plan.n_chunks > kMaxChunks) return hipErrorInvalidValue;
@@ -652,7 +653,7 @@ hipError_t launch_attend_gqa(const adsa_params& p, const AttendPlan& plan, adsa_
   A.lg_global = gqa_global_logit_stride(p);
   A.n_heads = p.n_heads; A.G = p.q_per_kv; A.sel_cap = p.sel_cap; A.lg_stride = gqa_logit_stride(p, plan.n_chunks);
   A.cap = p.cap; A.stage_b = (int)gqa_stage_bytes(p);
-  A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance ? 1 : 0;
+  A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance;
   A.new_f32 = (new_f32 && append) ? 1 : 0;
   A.slot_stride_b = (long long)p.kv_slot_stride * 2;
   A.head_stride_b = (long long)p.kv_head_stride * 2;

@@ -300,7 +300,8 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
 }
 
 template <int NT, int S>
-__global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append, LaunchShape L) {
+__global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append,
+                                             int32_t* tickets, LaunchShape L) {
   __shared__ __align__(16) RankShared sh;
   const int b = blockIdx.x, tid = threadIdx.x;
   adsa_seq& sq = seqs[b];
@@ -310,6 +311,7 @@ __global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx,
   int n = sq.n_res;
   const int status_in = sq.status;
   rank_clear<NT>(sh);                                        // (while the record is on its way)
+  if (tickets && tid == 0) tickets[4 * b] = 0;               // for this step's k_compact_step
   if (s < 0 || status_in != 0) { if (tid == 0) { sel_cnt[b] = 0; sq.pending_slot = -1; } return; }
   if (n < 0 || n > L.cap || s > L.grid_h * L.grid_w) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
@@ -397,6 +399,34 @@ __global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx,
         if (slot_new == hole) sq.hole = 0;
       }
     }
+  }
+}
+
+// In-place, order-preserving move of pos[] and every score row: all sources of a batch of rows have arrived in registers
+// before the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
+template <int NT, int S>
+__device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, int cap, uint32_t moves, const uint32_t (&dest)[S],
+                                            const int (&posv)[S]) {
+  constexpr int kRowBatch = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
+  const int tid = threadIdx.x;
+  for (int r0 = 0; r0 < rows; r0 += kRowBatch) {
+    float sv[S][kRowBatch];
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if ((moves >> u) & 1u) {
+#pragma unroll
+        for (int k = 0; k < kRowBatch; ++k) sv[u][k] = score[(size_t)min(r0 + k, rows - 1) * cap + u * NT + tid];
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if ((moves >> u) & 1u) {
+        if (r0 == 0) pos[dest[u]] = posv[u];
+#pragma unroll
+        for (int k = 0; k < kRowBatch; ++k)
+          if (r0 + k < rows) score[(size_t)(r0 + k) * cap + dest[u]] = sv[u][k];
+      }
   }
 }
 
@@ -523,28 +553,7 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
     if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
 
-  // In-place, order-preserving move of pos[] and every score row: all sources of a batch of rows have arrived in registers
-  // before the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
-  constexpr int kRowBatch = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
-  for (int r0 = 0; r0 < L.score_rows; r0 += kRowBatch) {
-    float sv[S][kRowBatch];
-#pragma unroll
-    for (int u = 0; u < S; ++u)
-      if ((moves >> u) & 1u) {
-#pragma unroll
-        for (int k = 0; k < kRowBatch; ++k) sv[u][k] = score[(size_t)min(r0 + k, L.score_rows - 1) * L.cap + u * NT + tid];
-      }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < S; ++u)
-      if ((moves >> u) & 1u) {
-        if (r0 == 0) pos[dest[u]] = posv[u];
-#pragma unroll
-        for (int k = 0; k < kRowBatch; ++k)
-          if (r0 + k < L.score_rows) score[(size_t)(r0 + k) * L.cap + dest[u]] = sv[u][k];
-      }
-  }
+  move_scores<NT, S>(score, pos, L.score_rows, L.cap, moves, dest, posv);
   if (tid == 0) {
     plan[4 * b + 0] = n; plan[4 * b + 1] = (int)min(sh.first, (uint32_t)n); plan[4 * b + 2] = 1; plan[4 * b + 3] = (int32_t)n_new;
     sq.n_res = (int32_t)n_new;
@@ -592,6 +601,106 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   }
 }
 
+// The row-end eviction of one decode step in ONE launch: grid (column slices of K, then of V; sequence).  The attention launch
+// before it has advanced the record (kAdvanceActive), so a workgroup whose sequence did not close a row leaves at once and
+// touches nothing.  Every workgroup of a sequence that did works out the ranking for itself (from L2, all at the same time)
+// and moves its slice of the rows with the map in its LDS; the one that draws the last ticket -- by then all of them have the
+// scores and positions they need in registers -- moves pos[] and the score rows and writes the keep map and the record.
+// Nothing waits for another workgroup.
+template <int NT, int S>
+__global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, int lanes_per_slice,
+                                                    int slices_per_head, LaunchShape L) {
+  __shared__ __align__(16) RankShared sh;
+  __shared__ int s_map[NT * S];
+  __shared__ int s_last;
+  constexpr int kRows = kMoveRows * kMoveThreads / NT;       // as many rows per tile as k_compact_move
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
+  adsa_seq& sq = seqs[b];
+  gint* const pos = (gint*)sq.pos;
+  gfloat* const score = (gfloat*)sq.score;
+  gchar* const kb = (gchar*)sq.k;
+  gchar* const vb = (gchar*)sq.v;
+  const int s = sq.step - 1, n = sq.n_res;                   // s: the step that has just been attended
+  if (s < 0 || sq.status != 0 || n < 0 || n > L.cap || !is_row_end(s, L.grid_h, L.grid_w)) return;
+  const QueryCell cell = make_query_cell(sq, s, L.grid_w, L.R, L.w, L.recent_m);
+  int idx[S], posv[S];
+  float rank[S];
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    idx[u] = min(u * NT + tid, n - 1);
+    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
+    rank[u] = 0.0f;
+  }
+  rank_clear<NT>(sh);
+  if (n > 0) rank_values<S>(score, L.score_rows, L.cap, idx, rank);
+  const bool largest = keep_largest_of(L.score_mode);
+  uint32_t key[S], restm = 0, in = 0;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (u * NT + tid < n) in |= 1u << u;
+    if (((in >> u) & 1u) && evict_class(cell, posv[u]) == 1) restm |= 1u << u;
+    key[u] = order_key(rank[u], largest);
+  }
+  const Stats st = block_stats<NT, S>(sh, key, restm, false);
+  const uint32_t B = (uint32_t)effective_budget(sq, s);
+  uint32_t T, need_eq;
+  top_threshold<NT, S>(sh, key, restm, st, B < st.n_cand ? B : st.n_cand, &T, &need_eq);
+  uint32_t sure = in & ~restm, eq = 0, dest[S], n_new;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (((restm >> u) & 1u) && key[u] > T) sure |= 1u << u;
+    if (((restm >> u) & 1u) && key[u] == T) eq |= 1u << u;
+  }
+  const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &n_new);
+  uint32_t moves = 0;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    const int i = u * NT + tid;
+    const bool kept = (take >> u) & 1u;
+    s_map[i] = kept ? (int)dest[u] : -1;
+    if (kept && dest[u] != (uint32_t)i) moves |= 1u << u;
+    const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
+    if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread has read what it needs of the scores and positions ...
+  __syncthreads();                                           // ... and so has the workgroup: it may draw its ticket
+  if (tid == 0) s_last = __hip_atomic_fetch_add(tickets + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+
+  const int per_cache = L.n_heads * slices_per_head;
+  const bool is_v = (int)blockIdx.x >= per_cache;
+  const int slice = (int)blockIdx.x - (is_v ? per_cache : 0), head = slice / slices_per_head, part = slice - head * slices_per_head;
+  const int rows_per_pass = NT / lanes_per_slice, row_in_pass = tid / lanes_per_slice, piece = tid % lanes_per_slice;
+  gchar* const base = (is_v ? vb : kb) + (long long)head * L.head_stride_b + ((long long)part * lanes_per_slice + piece) * 16;
+  for (int t0 = (int)min(sh.first, (uint32_t)n); t0 < n; t0 += rows_per_pass * kRows) {
+    uint4 val[kRows];
+    int dst[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const int i = t0 + u * rows_per_pass + row_in_pass;
+      const int m = i < n ? s_map[i] : -1;
+      dst[u] = m == i ? -1 : m;
+      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * L.slot_stride_b);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * L.slot_stride_b, val[u]);
+  }
+  __syncthreads();                                           // s_last is there (also when no row moves)
+  if (!s_last) return;
+
+  int32_t* const map = keep_map + (size_t)b * L.cap;
+#pragma unroll
+  for (int u = 0; u < S; ++u)
+    if ((in >> u) & 1u) map[u * NT + tid] = ((take >> u) & 1u) ? (int32_t)dest[u] : -1;
+  move_scores<NT, S>(score, pos, L.score_rows, L.cap, moves, dest, posv);
+  if (tid == 0) {
+    sq.n_res = (int32_t)n_new;
+    sq.compacted = 1;
+  }
+}
+
 LaunchShape shape_of(const adsa_params& p) {
   LaunchShape L;
   L.n_heads = p.n_heads; L.head_dim = p.head_dim; L.elem_bytes = elem_bytes(p);
@@ -627,13 +736,47 @@ LaunchShape shape_of(const adsa_params& p) {
   } while (0)
 
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
-                         bool plan_append, hipStream_t st) {
-  ADSA_RANK_DISPATCH(k_select, sel_idx, sel_cnt, plan_append ? 1 : 0);
+                         bool plan_append, int32_t* tickets, hipStream_t st) {
+  ADSA_RANK_DISPATCH(k_select, sel_idx, sel_cnt, plan_append ? 1 : 0, tickets);
 }
 
 static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* plan,
                                       bool advance_step, const float* vcos_s, hipStream_t st) {
   ADSA_RANK_DISPATCH(k_compact_plan, keep_map, plan, advance_step ? 1 : 0, vcos_s);
+}
+
+// column slices of a head row: 128 bytes, or the whole row when it is narrower
+struct Slices { int lanes, per_head; };
+static Slices row_slices(const adsa_params& p) {
+  const int head_bytes = p.head_dim * elem_bytes(p), slice_bytes = head_bytes < 128 ? head_bytes : 128;
+  return {slice_bytes / 16, head_bytes / slice_bytes};
+}
+
+// One launch instead of two saves a small step ~2.5 us of launching and, most steps closing no row, an empty kernel.  Its ranking
+// is repeated by every workgroup, so a large launch pays for it at a row end.  adsa_step, us with two launches | with one:
+// 4 sequences x 20 heads (160 workgroups) 17.9 | 16.1 inside a row, 28.3 | 28.6 at its end; 16 x 20 (640) 24.6 | 22.9, 39.8 | 40.0;
+// 64 x 24 (3072) 57 | 55, 94 | 105.  So: up to 1024 workgroups, lists up to 2048 slots (the map in LDS), rankings
+// that need no pass over V.
+bool one_launch_compact(const adsa_params& p) {
+  return p.evict_policy == ADSA_EVICT_ROW_END && !is_vcos(p) && p.cap <= 2048 &&
+         (long long)p.n_seq * p.n_heads * row_slices(p).per_head * 2 <= 1024;
+}
+
+hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st) {
+  const Slices sl = row_slices(p);
+  const dim3 grid(2 * p.n_heads * sl.per_head, p.n_seq);
+#define ADSA_STEP_LAUNCH(NT, S)                                                                              \
+  do {                                                                                                       \
+    hipLaunchKernelGGL((k_compact_step<NT, S>), grid, dim3(NT), 0, st, seqs, keep_map, tickets, sl.lanes,    \
+                       sl.per_head, shape_of(p));                                                            \
+    return hipGetLastError();                                                                                \
+  } while (0)
+  if (p.cap <= 256) ADSA_STEP_LAUNCH(256, 1);
+  if (p.cap <= 512) ADSA_STEP_LAUNCH(256, 2);
+  if (p.cap <= 768) ADSA_STEP_LAUNCH(256, 3);
+  if (p.cap <= 1024) ADSA_STEP_LAUNCH(512, 2);
+  if (p.cap <= 2048) ADSA_STEP_LAUNCH(512, 4);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
@@ -643,13 +786,10 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
   hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
-  // one workgroup per 128-byte column slice of a head row (whole head row when it is narrower)
-  const int head_bytes = p.head_dim * L.elem_bytes;
-  const int slice_bytes = head_bytes < 128 ? head_bytes : 128;
-  const int lanes = slice_bytes / 16, slices_per_head = head_bytes / slice_bytes;
-  dim3 grid(p.n_heads * slices_per_head, 2, p.n_seq);
+  const Slices sl = row_slices(p);
+  dim3 grid(p.n_heads * sl.per_head, 2, p.n_seq);
   hipLaunchKernelGGL(k_compact_move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, lanes, slices_per_head, L);
+                     (const int32_t*)plan, sl.lanes, sl.per_head, L);
   return hipGetLastError();
 }
 

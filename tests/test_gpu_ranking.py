@@ -69,3 +69,48 @@ def test_empty_sequences_touch_no_memory():
     batch.compact()
     torch.cuda.synchronize()
     assert (batch.sel_cnt.cpu().numpy() == 0).all()
+
+
+@pytest.mark.parametrize("n_seq,h,D,dtype,cap,layout", [
+    (1, 1, 64, "bf16", 70, "head_major"), (3, 4, 64, "f32", 257, "slot_major"), (2, 3, 128, "bf16", 513, "head_major"),
+    (2, 2, 128, "f32", 800, "slot_major"), (1, 5, 64, "bf16", 1025, "head_major"), (16, 32, 64, "bf16", 90, "head_major"),
+    (17, 32, 64, "bf16", 90, "head_major"), (1, 2, 64, "bf16", 2049, "head_major")])      # (the last two: two launches)
+def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, layout):
+    """adsa_step, whose eviction is one launch for small batches, against the split-phase calls on a copy of the same state: the
+    sequences close a row, stand inside one, are inactive, rejected or empty; everything either of them writes is the same."""
+    W, P, R = 10, 7, 1
+    H = (cap - P) // W + 3
+    rng = np.random.default_rng(cap)
+    wl = WL.get_workload("tiny", n_heads=h, head_dim=D, grid_h=H, grid_w=W, prefix_len=P, win_rows_back=R, win_col_radius=2, dtype=dtype)
+    batches = [LayerBatch(params_for(wl, n_seq, cap, layout=layout), DEV) for _ in range(2)]
+    rows = ((cap - P) // W - 1) * W                          # whole rows that fit
+    for b in range(n_seq):
+        s = rows if b % 4 != 1 else rows - 3                 # this step's query token closes the row, or does not
+        n = P + s - 1
+        k, v = (WL.quantise(wl, rng.standard_normal((n, h, D), dtype=np.float32)) for _ in range(2))
+        score = rng.random((h, n)).astype(np.float32)
+        for batch in batches:
+            batch.set_sequence(b, k=k, v=v, pos=np.arange(n, dtype=np.int32), score=score, step=s, grid_origin=P,
+                               budget=(5, s, s // 2, s - 3 * W)[b % 4])
+            if b == 5:
+                batch.seqs_host[b]["step"] = -1              # inactive
+            if b == 6:
+                batch.seqs_host[b]["status"] = 2             # rejected earlier
+            if b == 7:
+                batch.seqs_host[b]["n_res"], batch.seqs_host[b]["step"] = 0, 0
+    one, two = batches
+    for batch in batches:
+        batch.seqs_host["compacted"] = 1
+        batch.upload_seqs()
+    q, kn, vn = (torch.from_numpy(rng.standard_normal((n_seq, h, D), dtype=np.float32)).to(DEV).to(one.tdtype) for _ in range(3))
+    one.step(q, kn, vn)
+    two.select(B.FLAG_PLAN_APPEND)
+    two.attend(q, B.FLAG_APPEND, kn, vn)
+    two.compact(B.FLAG_ADVANCE)
+    torch.cuda.synchronize()
+    for name in ("K", "V", "pos", "score", "out", "lse", "sel_idx", "sel_cnt", "keep_map"):
+        assert torch.equal(getattr(one, name), getattr(two, name)), name
+    a, b = one.read_seqs(), two.read_seqs()
+    for f in ("n_res", "step", "status", "compacted", "pending_slot", "hole"):
+        assert np.array_equal(a[f], b[f]), f
+    assert a["compacted"][0] == 1 and a["step"][0] == rows + 1
