@@ -283,8 +283,9 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
 // before its attention launch (which takes every row's dot product with u).  One workgroup per sequence.
 // If u belongs to this step: subtract the evicted row, add the rows that turn from local to candidate
 // (normally the one token that leaves the 1-D window).  Otherwise: a fresh sum over the next step's
-// candidates.  (512 sequences of 632 slots, two rows each: 10.9 us; 18.3 us with every row read twice and the sums in LDS.)
-// The slots that join or leave are listed 256 at a time; wave w takes entries w, w+4, ... in ascending order into
+// candidates.  (512 sequences of 632 slots, two rows each: 8.6 us; 10.9 with 256 slots listed at a time and u requested last,
+// 18.3 with every row read twice and the sums in LDS.)
+// The slots that join or leave are listed 1024 at a time; wave w takes entries w, w+4, ... in ascending order into
 // its own registers, and the waves' sums are added to u in wave order, so the result does not depend on timing.
 struct AdvArgs {
   adsa_seq* seqs;
@@ -295,10 +296,10 @@ struct AdvArgs {
 template <int EB, int G>
 __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
   extern __shared__ __align__(16) float s_acc[];        // [kVcWaves][dim]
-  __shared__ int s_row[kVcThreads], s_cnt[kVcWaves];
-  __shared__ float s_sign[kVcThreads];                  // by slot of the round
-  constexpr int EPL = 16 / EB, kAhead = 4;              // rounds whose positions are requested together
-  const int b = blockIdx.x, tid = threadIdx.x, wave = tid / kWave;
+  constexpr int EPL = 16 / EB, kRounds = 4;             // slots per thread and list
+  __shared__ int s_row[kRounds * kVcThreads], s_cnt[kRounds][kVcWaves];
+  __shared__ float s_sign[kRounds * kVcThreads];        // by entry of s_row
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   adsa_seq& sq = A.seqs[b];
   gfloat* const U = (gfloat*)sq.vcos_u;
   if (sq.step < 0 || sq.status != 0 || U == nullptr) return;
@@ -320,40 +321,64 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[g][e] = 0.0f;
-  for (int base = 0; base < n; base += kAhead * kVcThreads) {
-    int posv[kAhead];
+  // (u itself is needed last, but requested now: with two rows to move this kernel is nothing but memory round trips)
+  constexpr int kOld = G * EPL / kVcWaves > 0 ? G * EPL / kVcWaves : 1;     // dim <= G * 64 * EPL
+  float old[kOld];
 #pragma unroll
-    for (int r = 0; r < kAhead; ++r) posv[r] = pos[min(base + r * kVcThreads + tid, n - 1)];
+  for (int k = 0; k < kOld; ++k) old[k] = U[min(tid + k * kVcThreads, dim - 1)];
+  for (int base = 0; base < n; base += kRounds * kVcThreads) {
+    int posv[kRounds];
+    float sign[kRounds];
+    unsigned long long member[kRounds];
 #pragma unroll
-    for (int r = 0; r < kAhead; ++r) {
-      const int s0 = base + r * kVcThreads;
-      if (s0 >= n) break;
+    for (int r = 0; r < kRounds; ++r) posv[r] = pos[min(base + r * kVcThreads + tid, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
       // what happens to each slot: +1 joins u, -1 leaves it, 0 nothing
-      const int m = list_rows(s_row, s_cnt, s0, min(n, s0 + kVcThreads), [&](int i) {
-        const bool cand_next = select_class(next, posv[r]) == 1;
-        float sign = 0.0f;
-        if (incremental) {
-          const bool cand_now = select_class(now, posv[r]) == 1;
-          if (i == victim) sign = cand_now ? -1.0f : 0.0f;
-          else if (cand_next && !cand_now) sign = 1.0f;
-        } else if (cand_next && i != victim) sign = 1.0f;
-        s_sign[tid] = sign;
-        return sign != 0.0f;
-      });
-      for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
-        float ss = 0.0f;
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) ss = fmaf(f[g][e], f[g][e], ss);
-        const float c = s_sign[s_row[k] - s0] / fmaxf(sqrtf(wave_sum(ss)), 1e-8f);
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(f[g][e], c, acc[g][e]);
-      });
-      __syncthreads();                                  // the list is free for the next round
+      const int i = base + r * kVcThreads + tid;
+      const bool cand_next = select_class(next, posv[r]) == 1;
+      sign[r] = 0.0f;
+      if (incremental) {
+        const bool cand_now = select_class(now, posv[r]) == 1;
+        if (i == victim) sign[r] = cand_now ? -1.0f : 0.0f;
+        else if (cand_next && !cand_now) sign[r] = 1.0f;
+      } else if (cand_next && i != victim) sign[r] = 1.0f;
+      if (i >= n) sign[r] = 0.0f;
+      member[r] = __ballot(sign[r] != 0.0f);
+      if (lane == 0) s_cnt[r][wave] = __popcll(member[r]);
     }
+    __syncthreads();
+    int m = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {                 // ascending slots: round, wave, lane
+      int at = m;
+#pragma unroll
+      for (int w = 0; w < kVcWaves; ++w) {
+        const int t = s_cnt[r][w];
+        if (w < wave) at += t;
+        m += t;
+      }
+      if (sign[r] != 0.0f) {
+        at += __builtin_amdgcn_mbcnt_hi((uint32_t)(member[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)member[r], 0u));
+        s_row[at] = base + r * kVcThreads + tid;
+        s_sign[at] = sign[r];
+      }
+    }
+    m = __builtin_amdgcn_readfirstlane(m);
+    __syncthreads();
+    for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
+      float ss = 0.0f;
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) ss = fmaf(f[g][e], f[g][e], ss);
+      const float c = s_sign[k] / fmaxf(sqrtf(wave_sum(ss)), 1e-8f);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(f[g][e], c, acc[g][e]);
+    });
+    __syncthreads();                                    // the list is free for the next 1024 slots
   }
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -363,8 +388,11 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
         *reinterpret_cast<float4*>(s_acc + (size_t)wave * dim + row.col[g] + e) = make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
     }
   __syncthreads();
-  for (int c = tid; c < dim; c += kVcThreads) {
-    float t = incremental ? U[c] : 0.0f;
+#pragma unroll
+  for (int k = 0; k < kOld; ++k) {
+    const int c = tid + k * kVcThreads;
+    if (c >= dim) break;
+    float t = incremental ? old[k] : 0.0f;
 #pragma unroll
     for (int w = 0; w < kVcWaves; ++w) t += s_acc[(size_t)w * dim + c];
     U[c] = t;
