@@ -108,9 +108,8 @@ struct Row {
 };
 
 // Calls use(k, row) for entries wave, wave + kVcWaves, ... of the m slots listed in s_row, with U rows in flight.
-template <int EB, int G, typename Use>
+template <int EB, int G, int U = Row<EB, G>::U, typename Use>
 __device__ __forceinline__ void for_rows(const Row<EB, G>& row, long long slot_stride_b, const int* s_row, int m, Use use) {
-  constexpr int U = Row<EB, G>::U;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   if (wave >= m) return;
   uint4 x[U][G];
@@ -283,8 +282,8 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
 // before its attention launch (which takes every row's dot product with u).  One workgroup per sequence.
 // If u belongs to this step: subtract the evicted row, add the rows that turn from local to candidate
 // (normally the one token that leaves the 1-D window).  Otherwise: a fresh sum over the next step's
-// candidates.  (512 sequences of 632 slots, two rows each: 8.6 us; 10.9 with 256 slots listed at a time and u requested last,
-// 18.3 with every row read twice and the sums in LDS.)
+// candidates.  (512 | 1536 sequences of 632 slots, two rows each: 8.1 | 14.8 us; 8.6 | 16.2 with a ring of 4 rows and the list
+// beside the sums in LDS, 10.9 with 256 slots listed at a time and u requested last, 18.3 with every row read twice.)
 // The slots that join or leave are listed 1024 at a time; wave w takes entries w, w+4, ... in ascending order into
 // its own registers, and the waves' sums are added to u in wave order, so the result does not depend on timing.
 struct AdvArgs {
@@ -293,12 +292,15 @@ struct AdvArgs {
   long long slot_stride_b, head_stride_b;
 };
 
+constexpr int kAdvRounds = 4;                           // slots per thread and list
+// (a ring of one row: two rows are all there is to read in most steps, and the registers of a deeper one would cost residency)
 template <int EB, int G>
 __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
-  extern __shared__ __align__(16) float s_acc[];        // [kVcWaves][dim]
-  constexpr int EPL = 16 / EB, kRounds = 4;             // slots per thread and list
-  __shared__ int s_row[kRounds * kVcThreads], s_cnt[kRounds][kVcWaves];
-  __shared__ float s_sign[kRounds * kVcThreads];        // by entry of s_row
+  extern __shared__ __align__(16) float s_acc[];        // the list (slots, then signs), after it [kVcWaves][dim]
+  constexpr int EPL = 16 / EB, kRounds = kAdvRounds;
+  __shared__ int s_cnt[kRounds][kVcWaves];
+  int* const s_row = reinterpret_cast<int*>(s_acc);
+  float* const s_sign = s_acc + kRounds * kVcThreads;   // by entry of s_row
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   adsa_seq& sq = A.seqs[b];
   gfloat* const U = (gfloat*)sq.vcos_u;
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
     }
     m = __builtin_amdgcn_readfirstlane(m);
     __syncthreads();
-    for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
+    for_rows<EB, G, 1>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
       float ss = 0.0f;
 #pragma unroll
       for (int g = 0; g < G; ++g)
@@ -435,7 +437,8 @@ hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t
   return with_row_shape(p, [&](auto eb, auto g) {
     constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
     if constexpr (G * 16 / EB <= 64) {                  // (longer rows: more than 64 KB of sums, refused above)
-      hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves, st, A);
+      const size_t list = 2 * sizeof(int) * kAdvRounds * kVcThreads, sums = sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves;
+      hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), list > sums ? list : sums, st, A);
       return hipGetLastError();
     } else return hipErrorInvalidValue;
   });
