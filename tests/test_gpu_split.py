@@ -68,3 +68,23 @@ def test_split_lists_and_their_merge(n_heads, D, dtype, layout, fused, lens):
         assert np.allclose(rows[b, 0::2][:, sels[b]].T, sq, rtol=1e-5)
         assert np.allclose(rows[b, 1::2][:, sels[b]].T, dot, rtol=1e-5, atol=1e-4)
         assert batch.vcos_u[b, n_heads * D + 1] == 602.0       # the rows are the next step's
+
+
+def test_timing_hook_counts_a_split_launch_once():
+    """A split launch is two kernels; the benchmark's hook reports it as one, from the start of the first to the end of the second."""
+    params = B.make_params(n_seq=1, n_heads=2, head_dim=64, grid_h=72, grid_w=72, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
+                           score_mode=B.SCORE_ATTN_MASS, cap=4200)
+    batch = LayerBatch(params, DEV)
+    batch.seqs_host["n_res"], batch.seqs_host["step"] = 4200, 600
+    batch.upload_seqs()
+    batch.sel_idx[0] = torch.arange(4200, dtype=torch.int32, device=DEV)
+    batch.sel_cnt.fill_(4200)
+    q = torch.ones((1, 2, 64), dtype=torch.bfloat16, device=DEV)
+    batch.attend(q)
+    B.adsa_profile_enable(True)
+    for _ in range(3):
+        batch.attend(q)
+    torch.cuda.synchronize()
+    n, ms = B.adsa_profile_read()
+    B.adsa_profile_enable(False)
+    assert n == 3 and 0.0 < ms < 100.0
