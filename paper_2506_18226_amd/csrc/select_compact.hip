@@ -233,9 +233,9 @@ struct LaunchShape {
 
 // v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32 adds.  The loads of all slots and of two
 // batches of rows are in flight together: one memory round trip for up to 2 * RB + 1 rows.
-template <int S>
+constexpr int rank_batch(int S) { return S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4; }
+template <int S, int RB>
 __device__ __forceinline__ void rank_values(const gfloat* score, int rows, int cap, const int (&idx)[S], float (&v)[S]) {
-  constexpr int RB = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
   float cur[S][RB], nxt[S][RB];
   auto load_rows = [&](int r0, float (&t)[S][RB]) {
 #pragma unroll
@@ -299,7 +299,7 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
   return mode == ADSA_SCORE_ATTN_MASS || mode == ADSA_SCORE_EXT_LARGEST;
 }
 
-template <int NT, int S>
+template <int NT, int S, int RB = rank_batch(S)>
 __global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append,
                                              int32_t* tickets, LaunchShape L) {
   __shared__ __align__(16) RankShared sh;
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx,
     rank[u] = 0.0f;
   }
   // (evict-one-when-full policies attend every candidate: their rank is never looked at)
-  if (n > 0 && L.evict_policy == ADSA_EVICT_ROW_END) rank_values<S>(score, L.score_rows, L.cap, idx, rank);
+  if (n > 0 && L.evict_policy == ADSA_EVICT_ROW_END) rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
   const bool largest = keep_largest_of(L.score_mode);
   uint32_t key[S], candm = 0, fixedm = 0;
   bool bad = false;
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx,
 template <int NT, int S>
 __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, int cap, uint32_t moves, const uint32_t (&dest)[S],
                                             const int (&posv)[S]) {
-  constexpr int kRowBatch = S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4;
+  constexpr int kRowBatch = S <= 3 ? 24 : S == 4 ? 8 : 4;
   const int tid = threadIdx.x;
   for (int r0 = 0; r0 < rows; r0 += kRowBatch) {
     float sv[S][kRowBatch];
@@ -431,7 +431,7 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
 }
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
-template <int NT, int S>
+template <int NT, int S, int RB = rank_batch(S)>
 __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* keep_map, int32_t* plan, int advance_step,
                                                     const float* vcos_s, LaunchShape L) {
   __shared__ __align__(16) RankShared sh;
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
       for (int u = 0; u < S; ++u) rank[u] = ((const gfloat*)vcos_s)[(size_t)b * L.cap + idx[u]];
     }
   } else if (n > 0) {
-    rank_values<S>(score, L.score_rows, L.cap, idx, rank);
+    rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
   }
   uint32_t key[S], restm = 0, in = 0;
 #pragma unroll
@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
 // and moves its slice of the rows with the map in its LDS; the one that draws the last ticket -- by then all of them have the
 // scores and positions they need in registers -- moves pos[] and the score rows and writes the keep map and the record.
 // Nothing waits for another workgroup.
-template <int NT, int S>
+template <int NT, int S, int RB = rank_batch(S)>
 __global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, int lanes_per_slice,
                                                     int slices_per_head, LaunchShape L) {
   __shared__ __align__(16) RankShared sh;
@@ -632,7 +632,7 @@ __global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* ke
     rank[u] = 0.0f;
   }
   rank_clear<NT>(sh);
-  if (n > 0) rank_values<S>(score, L.score_rows, L.cap, idx, rank);
+  if (n > 0) rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
   const bool largest = keep_largest_of(L.score_mode);
   uint32_t key[S], restm = 0, in = 0;
 #pragma unroll
@@ -713,25 +713,32 @@ LaunchShape shape_of(const adsa_params& p) {
 
 }  // namespace
 
+template <int NT, int... REST>
+static constexpr int rank_threads() { return NT; }
+
 // Threads and slots per thread of a ranking workgroup, by the slots a sequence can have.  k_select, us at 256x3 | 512x2 |
 // 1024x1: 64 sequences x 24 rows x 696 slots 7.6 | 7.2 | 7.4; 1536 x 24 x 696 20.3 | 20.6 | 37.7; 1536 x 8 x 696
 // 12.3 | 15.1 | 35; at 256x4 | 512x2: 64 x 24 x 696 8.3 | 7.2; at 512x4 | 1024x2: 200 x 16 x 2000 11.1 | 11.4.  (One
-// workgroup of 256 threads with keys in LDS and a 4-pass radix select: 12.4, 27.3, 18.1 and 19.4 us.)  k_compact_plan in
+// workgroup of 256 threads with keys in LDS and a 4-pass radix select: 12.4, 27.3, 18.1 and 19.4 us.)  With 3 slots per
+// thread, batches of 12 score rows instead of 8 put 25 rows in flight for 28 more registers: k_select 64 x 24 rows
+// 7.9 -> 7.3 us, 576 x 20 10.9 -> 10.5, but 1536 x 8 rows 12.2 -> 14.2 for the residency lost: below 1024 sequences only.  k_compact_plan in
 // the same shapes, against that form: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (was 32.7), 512 x 48 rows x 632
 // of the fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).
 #define ADSA_RANK_DISPATCH(KERNEL, ...)                                                                      \
   do {                                                                                                       \
-    if (p.cap <= 256) ADSA_RANK_LAUNCH(KERNEL, 256, 1, __VA_ARGS__);                                         \
-    if (p.cap <= 512) ADSA_RANK_LAUNCH(KERNEL, 256, 2, __VA_ARGS__);                                         \
-    if (p.cap <= 768) ADSA_RANK_LAUNCH(KERNEL, 256, 3, __VA_ARGS__);                                         \
-    if (p.cap <= 1024) ADSA_RANK_LAUNCH(KERNEL, 512, 2, __VA_ARGS__);                                        \
-    if (p.cap <= 2048) ADSA_RANK_LAUNCH(KERNEL, 512, 4, __VA_ARGS__);                                        \
-    if (p.cap <= 4096) ADSA_RANK_LAUNCH(KERNEL, 1024, 4, __VA_ARGS__);                                       \
-    ADSA_RANK_LAUNCH(KERNEL, 1024, 8, __VA_ARGS__);                                                          \
+    if (p.cap <= 256) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 1), __VA_ARGS__);                             \
+    if (p.cap <= 512) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 2), __VA_ARGS__);                             \
+    if (p.cap <= 768 && p.n_seq < 1024) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 3, 12), __VA_ARGS__);       \
+    if (p.cap <= 768) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 3), __VA_ARGS__);                             \
+    if (p.cap <= 1024) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(512, 2), __VA_ARGS__);                            \
+    if (p.cap <= 2048) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(512, 4), __VA_ARGS__);                            \
+    if (p.cap <= 4096) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(1024, 4), __VA_ARGS__);                           \
+    ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(1024, 8), __VA_ARGS__);                                              \
   } while (0)
-#define ADSA_RANK_LAUNCH(KERNEL, NT, S, ...)                                                                 \
+#define ADSA_SHAPE(...) __VA_ARGS__
+#define ADSA_RANK_LAUNCH(KERNEL, SHAPE, ...)                                                                 \
   do {                                                                                                       \
-    hipLaunchKernelGGL((KERNEL<NT, S>), dim3(p.n_seq), dim3(NT), 0, st, seqs, __VA_ARGS__, shape_of(p));     \
+    hipLaunchKernelGGL((KERNEL<SHAPE>), dim3(p.n_seq), dim3(rank_threads<SHAPE>()), 0, st, seqs, __VA_ARGS__, shape_of(p)); \
     return hipGetLastError();                                                                                \
   } while (0)
 
@@ -765,15 +772,15 @@ bool one_launch_compact(const adsa_params& p) {
 hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st) {
   const Slices sl = row_slices(p);
   const dim3 grid(2 * p.n_heads * sl.per_head, p.n_seq);
-#define ADSA_STEP_LAUNCH(NT, S)                                                                              \
+#define ADSA_STEP_LAUNCH(NT, ...)                                                                            \
   do {                                                                                                       \
-    hipLaunchKernelGGL((k_compact_step<NT, S>), grid, dim3(NT), 0, st, seqs, keep_map, tickets, sl.lanes,    \
+    hipLaunchKernelGGL((k_compact_step<NT, __VA_ARGS__>), grid, dim3(NT), 0, st, seqs, keep_map, tickets, sl.lanes,    \
                        sl.per_head, shape_of(p));                                                            \
     return hipGetLastError();                                                                                \
   } while (0)
   if (p.cap <= 256) ADSA_STEP_LAUNCH(256, 1);
   if (p.cap <= 512) ADSA_STEP_LAUNCH(256, 2);
-  if (p.cap <= 768) ADSA_STEP_LAUNCH(256, 3);
+  if (p.cap <= 768) ADSA_STEP_LAUNCH(256, 3, 12);
   if (p.cap <= 1024) ADSA_STEP_LAUNCH(512, 2);
   if (p.cap <= 2048) ADSA_STEP_LAUNCH(512, 4);
   return hipErrorInvalidValue;

@@ -114,3 +114,31 @@ def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, 
     for f in ("n_res", "step", "status", "compacted", "pending_slot", "hole"):
         assert np.array_equal(a[f], b[f]), f
     assert a["compacted"][0] == 1 and a["step"][0] == rows + 1
+
+
+@pytest.mark.parametrize("rows", [1, 9, 26])
+def test_many_sequences_rank_like_few(rows):
+    """From 1024 sequences on the ranking keeps fewer score rows in flight: same lists and keep maps as for a small batch."""
+    cap, P, W, few = 600, 8, 16, 3
+    s = cap - P                                              # 37 whole rows
+    wl = WL.get_workload("xl", n_heads=rows, head_dim=64, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
+    g = torch.Generator().manual_seed(rows)
+    score = torch.randint(0, 40, (few, rows, cap), generator=g).float() / 8
+    got = []
+    for n_seq in (few, 1030):
+        batch = LayerBatch(params_for(wl, n_seq, cap, score_mode=B.SCORE_ATTN_MASS), DEV)
+        batch.pos.copy_(torch.arange(cap, dtype=torch.int32).expand(n_seq, cap))
+        batch.score.copy_(score[torch.arange(n_seq) % few])
+        h = batch.seqs_host
+        h["n_res"], h["step"], h["grid_origin"], h["n_keep_prefix"] = cap, s, P, P
+        h["budget"] = 100 + 150 * (np.arange(n_seq) % few)
+        batch.upload_seqs()
+        batch.select()
+        batch.compact()
+        torch.cuda.synchronize()
+        n_res = batch.read_seqs()["n_res"]
+        got.append((batch.sel_idx.cpu(), batch.sel_cnt.cpu(), batch.keep_map.cpu(), torch.from_numpy(n_res.copy()), batch.score.cpu()))
+    at = torch.arange(1030) % few
+    for a, b in zip(*got):
+        assert torch.equal(a[at], b)
+    assert len(set(got[0][1].tolist())) == few
