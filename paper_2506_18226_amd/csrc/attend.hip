@@ -633,11 +633,16 @@ AttendPlan make_attend_plan(const adsa_params& p) {
     a.chunk_max = gqa_logit_stride(p, nc);
     return a;
   }
-  // One workgroup per (sequence, head): 4 waves where there are more pairs than CUs, else 8.  Measured, 4 | 8 | 16 waves,
-  // bf16: 320 pairs x 457 tokens x 64 10.6 | 11.1 | 15.4 us; 768 x 200 9.6 | 10.6 | 19.9; 256 x 650 x 128 16.2 | 15.8 | 17.0;
-  // 192 x 650 x 64 9.3 | 8.5 | 10.9; 128 x 4000 x 128 60.3 | 53.0 | 52.4; 40 x 400 x 64 6.3 | 5.9 | 7.2.
+  // One workgroup per (sequence, head): 8 waves up to one pair per CU, 4 from two on; in between 8 where the lists together
+  // are long (80 MB), for the waves that then wait side by side, and 4 where starting the workgroups is a good part of
+  // the launch.  Measured, us with 4 | 8 | 16 waves, bf16: 320 pairs x 457 tokens x 64 (37 MB) 10.6 | 11.1 | 15.4;
+  // 400 x 650 x 64 (67 MB) 14.6 | 14.9 | 20.6; 480 x 700 x 64 (86 MB) 17.8 | 16.7; 288 x 1300 x 64 (96 MB) 24.6 | 23.3;
+  // 400 x 700 x 128 (143 MB) 26.8 | 25.9; 768 x 200 x 64 9.6 | 10.6 | 19.9; 768 x 649 x 64 22.6 | 22.7 | 32.3;
+  // 256 x 650 x 128 16.2 | 15.8 | 17.0; 192 x 650 x 64 9.3 | 8.5 | 10.9; 128 x 4000 x 128 60.3 | 53.0 | 52.4;
+  // 40 x 400 x 64 6.3 | 5.9 | 7.2; fp32: 288 x 300 x 128 (88 MB) 21.0 | 20.3; 400 x 300 x 128 22.9 | 22.1.
   const long long pairs = (long long)p.n_seq * p.n_heads;
-  a.waves = pairs > 256 ? 4 : 8;
+  const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
+  a.waves = pairs >= 512 || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
   // Splitting a list costs a second launch, ~3 us.  What it can save: a workgroup alone streams ~55 GB/s (8 or 16 waves
   // alike), the chip ~5.5 TB/s, as much as ~100 workgroups.  So a list of b bytes on each of `pairs` workgroups is split
   // when b * (1 - max(pairs / 100, 1 / chunks)) is more than 230 KB, ~4 us; into 8-wave chunks of at least 64 KB that
@@ -646,7 +651,6 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   // 80 x 384 KB 12.8 | 12.8; 64 x 154 KB 7.1 | 9.8.  (One launch whose last workgroup to arrive merges, behind a
   // device-scope release / acquire, took 12 us for 8 x 512 KB, 58 for 32 x 4 MB and 17.5 for 40 lists of 102 KB, which
   // take 5.9 us whole.)
-  const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
   long long nc = (256 + pairs - 1) / pairs;
   if (nc > b_list / (64 << 10)) nc = b_list / (64 << 10);
   if (nc > kMaxChunks) nc = kMaxChunks;
