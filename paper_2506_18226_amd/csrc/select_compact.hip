@@ -1,7 +1,7 @@
 // Partition + ranking kernels of the ADSA decode path (gfx950).
 //
-//  k_select        : Eq. 1 partition of the resident slots, Eq. 4 ranking of the candidates by an
-//                    LDS-resident 4-pass MSB radix select with lowest-slot tie-break, and the
+//  k_select        : Eq. 1 partition of the resident slots, Eq. 4 ranking of the candidates as a
+//                    threshold found by narrowing histograms, lowest-slot tie-break, and the
 //                    ascending attended-slot list.  It can plan for the query token's append
 //                    (Section 4.2: new tokens go to the end of the cache) that the attention
 //                    launch performs, so the ranking never waits for the token's K/V.
@@ -10,6 +10,7 @@
 //                    Section 4.2 as written (evict the one most redundant candidate when full), closing
 //                    the hole in order or leaving it to the incoming token.
 //  k_compact_move  : in-place, order-preserving move of the surviving K and V rows.
+//  k_compact_step  : the per-row plan and move of a small decode step in one launch.
 //
 // One workgroup owns one sequence in the first two kernels.  Its slots live in registers, S per thread (slot = u * NT +
 // thread), from the one read of the score array to the last write: what crosses threads is a histogram, at most 64
@@ -721,9 +722,9 @@ static constexpr int rank_threads() { return NT; }
 // 12.3 | 15.1 | 35; at 256x4 | 512x2: 64 x 24 x 696 8.3 | 7.2; at 512x4 | 1024x2: 200 x 16 x 2000 11.1 | 11.4.  (One
 // workgroup of 256 threads with keys in LDS and a 4-pass radix select: 12.4, 27.3, 18.1 and 19.4 us.)  With 3 slots per
 // thread, batches of 12 score rows instead of 8 put 25 rows in flight for 28 more registers: k_select 64 x 24 rows
-// 7.9 -> 7.3 us, 576 x 20 10.9 -> 10.5, but 1536 x 8 rows 12.2 -> 14.2 for the residency lost: below 1024 sequences only.  k_compact_plan in
-// the same shapes, against that form: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (was 32.7), 512 x 48 rows x 632
-// of the fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).
+// 7.9 -> 7.3 us, 576 x 20 10.9 -> 10.5, but 1536 x 8 rows 12.2 -> 14.2 for the residency lost: below 1024 sequences only.
+// k_compact_plan in the same shapes: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (32.7 with keys in LDS), 512 x 48
+// rows x 632 of the fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).
 #define ADSA_RANK_DISPATCH(KERNEL, ...)                                                                      \
   do {                                                                                                       \
     if (p.cap <= 256) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 1), __VA_ARGS__);                             \
