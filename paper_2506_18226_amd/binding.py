@@ -125,12 +125,15 @@ _raw_stream = None
 def _current_stream() -> int:
     """Handle of the current device's current stream.  torch.cuda.current_stream() wraps it in a Stream object, which takes
     2.7 us, as much as a kernel launch; the handle alone 0.2 us.  The first call goes through torch's own way, which also
-    initialises the device."""
+    initialises the device; so does every call where torch does not have the two functions (they are not documented)."""
     global _raw_stream
     if _raw_stream is None:
         import torch
         handle = torch.cuda.current_stream().cuda_stream
-        _raw_stream = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        raw, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if raw is None or device is None:
+            return handle
+        _raw_stream = raw, device
         return handle
     return _raw_stream[0](_raw_stream[1]())
 

@@ -181,3 +181,21 @@ def test_static_scratch_entry_point_checks_its_arguments_on_the_host(lib):
     assert B.adsa_workspace_bytes(big) > B.STATIC_SCRATCH_BYTES
     rc = lib.adsa_step_static(C.byref(big), ok, ok, ok, ok, ok, ok, ok, ok, ok, 0, None)
     assert rc == -9 and "built-in" in B.strerror(rc)
+
+
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_current_stream_with_and_without_the_undocumented_torch_functions(monkeypatch, missing):
+    """stream=None means torch's current stream, whether torch can hand out the bare handle or not."""
+    import types
+
+    import torch
+    current = [7]
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=current[0]))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 1, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: current[0] + 1000 * (device - 1), raising=False)
+    for name in missing:
+        monkeypatch.delattr(torch._C, name)
+    for current[0] in (7, 7, 9):
+        assert B._stream(None) == current[0]
+    assert B._stream(5) == 5 and B._stream(types.SimpleNamespace(cuda_stream=6)) == 6
