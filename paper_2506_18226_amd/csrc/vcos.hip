@@ -5,13 +5,20 @@
 // u = sum_j v^_j over the candidates,  S_i = (v^_i . u - v^_i . v^_i) / (N - 1): two streaming
 // passes over the candidates' V rows instead of O(N^2 D) work.
 //
-//  k_vcos_norm_usum : grid (slot tile, sequence).  The tile's candidates are listed in LDS; a wave holds a slot's whole row
-//                     in registers: inverse norm by a wave reduction, then the normalised row is added to the wave's
-//                     column sums; the waves' sums are added in LDS into a per-tile partial of u
-//                     (deterministic order, no atomics, every row read once).
-//  k_vcos_score     : grid (slot tile, sequence).  Every lane sums its columns of the tile partials of u into registers,
+//  k_vcos_norm_usum : grid (256 slots or a part of them, sequence).  The candidates of 256 slots are listed in LDS; a wave holds
+//                     a slot's whole row in registers: inverse norm by a wave reduction, then the normalised row is
+//                     added to the wave's column sums; the waves' sums are added in LDS into a partial of u
+//                     (no atomics, every row read once).
+//  k_vcos_score     : grid (slot tile, sequence).  Every lane sums its columns of the partials of u into registers,
 //                     then a wave per slot takes the dot product and writes S_i into
 //                     score[slot] (non-candidate slots keep their score).
+//
+// The order of u's sums does not depend on the launch, so that a sequence's scores are the same bits in whatever batch it is
+// ranked.  Entry k of the list of 256 slots belongs to part k mod 4; a part is cut into 4 runs of equal length (at most 16 rows),
+// a run is summed in ascending order, the runs in order make the part, the parts in order the group's sum, and the groups are
+// added in order.  A large launch gives a workgroup a whole group (a wave per part: together they walk the list), a small one a
+// part (a wave per run).  (The last group of a capacity that is no multiple of 256 has a part per 64 slots: that is the room
+// the workspace has.)
 //
 // Both are bound by the stream of V rows.  A wave keeps a ring of U rows in flight (16 bytes per lane and load, so 3 loads
 // for a row of 24 heads x 64 bf16).  256 sequences x 535 candidates of that shape, 420 MB a pass: 79 and 75 us (5.3 and
@@ -27,15 +34,19 @@ namespace {
 
 constexpr int kVcThreads = 256;
 constexpr int kVcWaves = kVcThreads / kWave;
-constexpr int kVcTile = 64;                 // slots per tile partial the workspace has room for
+constexpr int kVcTile = 64;                 // slots per partial of u the workspace has room for
+constexpr int kVcGroup = kVcThreads;        // slots that are listed and summed together
+constexpr int kVcParts = kVcGroup / kVcTile, kVcPartRuns = 4;
+static_assert(kVcWaves == kVcParts && kVcWaves == kVcPartRuns, "a wave per part or per class");
 constexpr int kVcMaxDim = 8192;             // n_heads * head_dim limit
 
 struct VcosArgs {
   adsa_seq* seqs;
   float* inv_norm;      // [n_seq][cap]
-  float* u_part;        // [n_seq][n_tiles][dim]
+  float* u_part;        // [n_seq][n_parts][dim]: a partial of u per group, or per part of a group (split)
   float* s_out;         // [n_seq][cap] where S_i goes when score[] holds the fused form's rows, else NULL
-  int n_heads, head_dim, cap, tile, n_tiles;      // tile: slots per workgroup, 64, 128 or 256
+  int n_heads, head_dim, cap, split, n_parts;     // split: a workgroup of the first pass takes a part of a group
+  int tile;                                       // slots per workgroup of the second pass: 64, 128 or 256
   int grid_h, grid_w, R, w, for_compaction, recent_m, evict_policy;
   long long slot_stride_b, head_stride_b;
 };
@@ -107,11 +118,10 @@ struct Row {
   }
 };
 
-// Calls use(k, row) for entries wave, wave + kVcWaves, ... of the m slots listed in s_row, with U rows in flight.
+// Calls use(k, row) for entries first, first + step, ... below m of the slots listed in s_row, with U rows in flight.
 template <int EB, int G, int U = Row<EB, G>::U, typename Use>
-__device__ __forceinline__ void for_rows(const Row<EB, G>& row, long long slot_stride_b, const int* s_row, int m, Use use) {
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  if (wave >= m) return;
+__device__ __forceinline__ void for_rows(const Row<EB, G>& row, long long slot_stride_b, const int* s_row, int first, int step, int m, Use use) {
+  if (first >= m) return;
   uint4 x[U][G];
   auto request = [&](int u, int k) {         // (entries past the last re-read it)
     row.load((long long)__builtin_amdgcn_readfirstlane(s_row[min(k, m - 1)]) * slot_stride_b, x[u]);
@@ -119,17 +129,17 @@ __device__ __forceinline__ void for_rows(const Row<EB, G>& row, long long slot_s
     __builtin_amdgcn_sched_barrier(0);
   };
 #pragma unroll
-  for (int u = 0; u < U; ++u) request(u, wave + u * kVcWaves);
-  for (int k = wave; k < m; k += U * kVcWaves) {
+  for (int u = 0; u < U; ++u) request(u, first + u * step);
+  for (int k = first; k < m; k += U * step) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int ku = k + u * kVcWaves;
+      const int ku = k + u * step;
       if (ku < m) {
         float f[G][Row<EB, G>::EPL];
         row.unpack(x[u], f);
         use(ku, f);
       }
-      request(u, ku + U * kVcWaves);
+      request(u, ku + U * step);
     }
   }
 }
@@ -161,13 +171,14 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
   __shared__ int s_row[kVcThreads], s_cnt[kVcWaves];
   __shared__ float s_inv[kVcThreads];
   constexpr int EPL = 16 / EB;
-  const int tile = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
+  const int part = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const adsa_seq& sq = A.seqs[b];
   if (!vcos_active(A, sq)) return;
-  const int n = sq.n_res, s0 = tile * A.tile;
+  const int group = A.split ? part / kVcParts : part;
+  const int n = sq.n_res, s0 = group * kVcGroup;
   if (s0 >= n) return;
-  const int s1 = min(n, s0 + A.tile), dim = A.n_heads * A.head_dim;
+  const int s1 = min(n, s0 + kVcGroup), dim = A.n_heads * A.head_dim;
   const QueryCell cell = make_query_cell(sq, sq.step, A.grid_w, A.R, A.w, A.recent_m);
   const gint* const pos = (const gint*)sq.pos;
   gfloat* const inv_norm = (gfloat*)A.inv_norm + (size_t)b * A.cap;
@@ -176,13 +187,25 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
     if (!c) inv_norm[i] = 0.0f;                          // marks "not a candidate"
     return c;
   });
+  // this wave's entries: my_part + parts * t, t from the first run's begin to the last one's end (all four runs of a part, or one)
+  const int parts = min(kVcParts, (A.cap - s0 + kVcTile - 1) / kVcTile), my_part = A.split ? part % kVcParts : wave;
+  const int n_part = my_part < parts ? (m - my_part + parts - 1) / parts : 0;
+  auto run_begin = [&](int r) { return my_part + parts * (n_part * r / kVcPartRuns); };
+  int r = A.split ? wave : 0;
+  const int k0 = run_begin(r), k1 = run_begin(A.split ? r + 1 : kVcPartRuns);
   const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
   float acc[G][EPL];
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[g][e] = 0.0f;
-  for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {     // ascending per wave: fixed order
+  float* const mine = s_acc + (size_t)wave * dim;        // the sum of this wave's runs so far
+  if (k0 == k1)
+    for (int c = lane; c < dim / 4; c += kWave) reinterpret_cast<float4*>(mine)[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  int end = k0;                                          // of run r
+  while (end == k0 && k0 < k1) end = run_begin(++r);     // (short lists have empty runs)
+  bool more = false;
+  for_rows(row, A.slot_stride_b, s_row, k0, parts, min(k1, m), [&](int k, const float (&f)[G][EPL]) {
     float ss = 0.0f;
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -195,17 +218,26 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(f[g][e], inv, acc[g][e]);
     if (lane == 0) s_inv[k] = inv;
-  });
+    if (k + parts == end) {                                // (wave-uniform) the run is complete
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-    if (row.on[g]) {
+      for (int g = 0; g < G; ++g)
+        if (row.on[g]) {
 #pragma unroll
-      for (int e = 0; e < EPL; e += 4)
-        *reinterpret_cast<float4*>(s_acc + (size_t)wave * dim + row.col[g] + e) = make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
+          for (int e = 0; e < EPL; e += 4) {
+            float4* const at = reinterpret_cast<float4*>(mine + row.col[g] + e);
+            float4 t = make_float4(acc[g][e], acc[g][e + 1], acc[g][e + 2], acc[g][e + 3]);
+            if (more) { const float4 o = *at; t.x = o.x + t.x; t.y = o.y + t.y; t.z = o.z + t.z; t.w = o.w + t.w; }
+            *at = t;
+            acc[g][e] = acc[g][e + 1] = acc[g][e + 2] = acc[g][e + 3] = 0.0f;
+          }
+        }
+      more = true;
+      while (end == k + parts && end < k1) end = run_begin(++r);
     }
+  });
   __syncthreads();
-  if (tid < m) inv_norm[s_row[tid]] = s_inv[tid];
-  float* up = A.u_part + ((size_t)b * A.n_tiles + tile) * (size_t)dim;
+  if (tid < m && (!A.split || tid % parts == my_part)) inv_norm[s_row[tid]] = s_inv[tid];
+  float* up = A.u_part + ((size_t)b * A.n_parts + part) * (size_t)dim;
   for (int c = tid; c < dim / 4; c += kVcThreads) {
     float4 t = reinterpret_cast<const float4*>(s_acc)[c];
 #pragma unroll
@@ -230,23 +262,32 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
   const int n = sq.n_res, s0 = tile * A.tile;
   if (s0 >= n) return;
   const int s1 = min(n, s0 + A.tile), dim = A.n_heads * A.head_dim;
-  const int tiles_used = (n + A.tile - 1) / A.tile;
+  const int parts_used = A.split ? min((n + kVcGroup - 1) / kVcGroup * kVcParts, A.n_parts) : (n + kVcGroup - 1) / kVcGroup;
   const gfloat* const invs = (const gfloat*)A.inv_norm + (size_t)b * A.cap;
   int my = 0;
   for (int i = tid; i < n; i += kVcThreads) my += invs[i] != 0.0f;
   const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
-  const float* up = A.u_part + (size_t)b * A.n_tiles * (size_t)dim;
+  const float* up = A.u_part + (size_t)b * A.n_parts * (size_t)dim;
   float uu[G][EPL];
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < EPL; ++e) uu[g][e] = 0.0f;
-  for (int t = 0; t < tiles_used; ++t) {                 // ascending tile order: deterministic
+  for (int t = 0; t < parts_used; t += A.split ? kVcParts : 1) {      // groups in order, a group's own parts first
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int e = 0; e < EPL; e += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(up + (size_t)t * dim + row.col[g] + e);
+        const float* const at = up + (size_t)t * dim + row.col[g] + e;
+        float4 x = *reinterpret_cast<const float4*>(at);
+        if (A.split) {
+          float4 y[kVcParts];
+#pragma unroll
+          for (int j = 1; j < kVcParts; ++j) y[j] = *reinterpret_cast<const float4*>(at + (size_t)min(j, parts_used - 1 - t) * dim);
+#pragma unroll
+          for (int j = 1; j < kVcParts; ++j)
+            if (t + j < parts_used) { x.x += y[j].x; x.y += y[j].y; x.z += y[j].z; x.w += y[j].w; }
+        }
         if (row.on[g]) { uu[g][e] += x.x; uu[g][e + 1] += x.y; uu[g][e + 2] += x.z; uu[g][e + 3] += x.w; }
       }
   }
@@ -261,7 +302,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
 #pragma unroll
   for (int w = 0; w < kVcWaves; ++w) N += s_n[w];
   gfloat* const out = A.s_out ? (gfloat*)A.s_out + (size_t)b * A.cap : (gfloat*)sq.score;
-  for_rows<EB, G>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
+  for_rows(row, A.slot_stride_b, s_row, __builtin_amdgcn_readfirstlane(wave), kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
     float dot = 0.0f, ss = 0.0f;
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -368,7 +409,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
     }
     m = __builtin_amdgcn_readfirstlane(m);
     __syncthreads();
-    for_rows<EB, G, 1>(row, A.slot_stride_b, s_row, m, [&](int k, const float (&f)[G][EPL]) {
+    for_rows<EB, G, 1>(row, A.slot_stride_b, s_row, wave, kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
       float ss = 0.0f;
 #pragma unroll
       for (int g = 0; g < G; ++g)
@@ -454,24 +495,30 @@ hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction
   A.u_part = reinterpret_cast<float*>(ws + w.vcos_u_off);
   A.s_out = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<float*>(ws + w.vcos_s_off) : nullptr;
   A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
-  // As large a tile as still gives every CU two workgroups: the second pass reads every tile's partial of u in each workgroup
+  // As large a tile as still gives every CU two workgroups: the second pass reads every partial of u in each workgroup
   // (256 sequences x 692 slots: 154 us both passes with tiles of 256, 177 with 128; taking 128 or 64 sequences at a time so that
   // the second pass finds them in the memory-side cache costs more in short launches than it saves: 192 and 256 us).
-  A.tile = 256;
+  A.tile = kVcGroup;
   while (A.tile > kVcTile && (long long)p.n_seq * ((p.cap + A.tile - 1) / A.tile) < 512) A.tile /= 2;
-  A.n_tiles = (p.cap + A.tile - 1) / A.tile;
+  // First pass: a workgroup per part for launches of few groups, where a workgroup per group leaves the chip short of rows in
+  // flight; whole groups write and read a quarter of the partials, which counts more the longer a row is.  Both passes, time of
+  // groups / time of parts over 120 random shapes, rows under 2 KB | longer ones: 100-200 groups 1.32 | 0.97, 200-350 1.16 | 1.00,
+  // 350-500 1.13 | 0.92, 640-800 1.05 | 1.00, 800-1200 1.01 | 0.93; 768 groups of 24 x 64 bf16 156 us | 170.
+  const int groups = (p.cap + kVcGroup - 1) / kVcGroup;
+  A.split = (long long)p.n_seq * groups < (dim * elem_bytes(p) < 2048 ? 640 : 320) ? 1 : 0;
+  A.n_parts = A.split ? vcos_tiles(p.cap) : groups;
   A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius;
   A.for_compaction = for_compaction ? 1 : 0; A.recent_m = p.win_recent_m; A.evict_policy = p.evict_policy;
   A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
   A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
-  const dim3 grid(A.n_tiles, p.n_seq);
+  const dim3 grid1(A.n_parts, p.n_seq), grid2((p.cap + A.tile - 1) / A.tile, p.n_seq);
   return with_row_shape(p, [&](auto eb, auto g) {
     constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
     // (64..128 KB of LDS, above the default per-launch limit: allowed once per device by vcos_prepare_kernels)
-    hipLaunchKernelGGL((k_vcos_norm_usum<EB, G>), grid, dim3(kVcThreads), sizeof(float) * (size_t)dim * kVcWaves, st, A);
+    hipLaunchKernelGGL((k_vcos_norm_usum<EB, G>), grid1, dim3(kVcThreads), sizeof(float) * (size_t)dim * kVcWaves, st, A);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_vcos_score<EB, G>), grid, dim3(kVcThreads), 0, st, A);
+    hipLaunchKernelGGL((k_vcos_score<EB, G>), grid2, dim3(kVcThreads), 0, st, A);
     return hipGetLastError();
   });
 }

@@ -90,3 +90,31 @@ def test_running_sum_starts_and_moves_on(h, D, dtype, cap):
         new = torch.from_numpy(np.stack([vs[b][cap + t] for b in range(2)])).to(DEV).to(batch.tdtype)
         batch.select(B.FLAG_PLAN_APPEND)
         batch.attend(new, B.FLAG_APPEND | B.FLAG_ADVANCE, new, new)
+
+
+@pytest.mark.parametrize("h,D,dtype,cap,layout", [(3, 64, "bf16", 700, "head_major"), (24, 64, "bf16", 513, "slot_major"),
+                                                  (9, 128, "f32", 330, "head_major"), (2, 64, "f32", 257, "head_major"),
+                                                  (5, 64, "bf16", 64, "slot_major")])
+def test_scores_do_not_depend_on_the_batch(h, D, dtype, cap, layout):
+    """A sequence's Eq. 3 scores are the same bits whether it is ranked alone or in a batch, at its edges or inside: the launch
+    is cut differently for few, some and many sequences, the sums are not."""
+    rng = np.random.default_rng(cap)
+    P, W = 3, 16
+    wl = WL.get_workload("tiny", n_heads=h, head_dim=D, grid_h=50, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=1,
+                         dtype=dtype, score_mode=WL.SCORE_VCOS)
+    lens = [cap - 1, cap // 2 + 1, cap - 40]
+    vs = [rows(wl, rng, n) for n in lens]
+    groups = (cap + 255) // 256
+    got = []
+    for n_seq in (3, 500 // groups, 600 // groups, 700 // groups):         # by parts with small tiles; tiles of 128 and 256; whole groups
+        batch = LayerBatch(params_for(wl, n_seq, cap, layout=layout), DEV)
+        batch.seqs_host["step"] = -1
+        at = [0, n_seq // 2, n_seq - 1]
+        for b, n, v in zip(at, lens, vs):
+            batch.set_sequence(b, k=v, v=v, pos=np.arange(n, dtype=np.int32), score=None, step=n - P + 1, grid_origin=P, budget=7)
+        batch.upload_seqs()
+        batch.select()
+        torch.cuda.synchronize()
+        got.append(batch.score[at, 0].cpu())
+        assert all(torch.count_nonzero(x) > 1 for x in got[-1])
+    assert all(torch.equal(got[0], x) for x in got[1:])
