@@ -300,8 +300,9 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
   return mode == ADSA_SCORE_ATTN_MASS || mode == ADSA_SCORE_EXT_LARGEST;
 }
 
+// (512 x 16 needs 130 registers, two more than let a second workgroup share the CU: held to four waves per SIMD)
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append,
+__global__ __launch_bounds__(NT, S >= 16 ? 4 : 1) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append,
                                              int32_t* tickets, LaunchShape L) {
   __shared__ __align__(16) RankShared sh;
   const int b = blockIdx.x, tid = threadIdx.x;
@@ -717,40 +718,62 @@ LaunchShape shape_of(const adsa_params& p) {
 template <int NT, int... REST>
 static constexpr int rank_threads() { return NT; }
 
+#define ADSA_RANK_LAUNCH(KERNEL, SHAPE, ...)                                                                 \
+  do {                                                                                                       \
+    hipLaunchKernelGGL((KERNEL<SHAPE>), dim3(p.n_seq), dim3(rank_threads<SHAPE>()), 0, st, seqs, __VA_ARGS__, shape_of(p)); \
+    return hipGetLastError();                                                                                \
+  } while (0)
+#define ADSA_SHAPE(...) __VA_ARGS__
+
 // Threads and slots per thread of a ranking workgroup, by the slots a sequence can have.  k_select, us at 256x3 | 512x2 |
 // 1024x1: 64 sequences x 24 rows x 696 slots 7.6 | 7.2 | 7.4; 1536 x 24 x 696 20.3 | 20.6 | 37.7; 1536 x 8 x 696
 // 12.3 | 15.1 | 35; at 256x4 | 512x2: 64 x 24 x 696 8.3 | 7.2; at 512x4 | 1024x2: 200 x 16 x 2000 11.1 | 11.4.  (One
 // workgroup of 256 threads with keys in LDS and a 4-pass radix select: 12.4, 27.3, 18.1 and 19.4 us.)  With 3 slots per
 // thread, batches of 12 score rows instead of 8 put 25 rows in flight for 28 more registers: k_select 64 x 24 rows
 // 7.9 -> 7.3 us, 576 x 20 10.9 -> 10.5, but 1536 x 8 rows 12.2 -> 14.2 for the residency lost: below 1024 sequences only.
-// k_compact_plan in the same shapes: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (32.7 with keys in LDS), 512 x 48
-// rows x 632 of the fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).
-#define ADSA_RANK_DISPATCH(KERNEL, ...)                                                                      \
-  do {                                                                                                       \
-    if (p.cap <= 256) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 1), __VA_ARGS__);                             \
-    if (p.cap <= 512) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 2), __VA_ARGS__);                             \
-    if (p.cap <= 768 && p.n_seq < 1024) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 3, 12), __VA_ARGS__);       \
-    if (p.cap <= 768) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(256, 3), __VA_ARGS__);                             \
-    if (p.cap <= 1024) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(512, 2), __VA_ARGS__);                            \
-    if (p.cap <= 2048) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(512, 4), __VA_ARGS__);                            \
-    if (p.cap <= 4096) ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(1024, 4), __VA_ARGS__);                           \
-    ADSA_RANK_LAUNCH(KERNEL, ADSA_SHAPE(1024, 8), __VA_ARGS__);                                              \
-  } while (0)
-#define ADSA_SHAPE(...) __VA_ARGS__
-#define ADSA_RANK_LAUNCH(KERNEL, SHAPE, ...)                                                                 \
-  do {                                                                                                       \
-    hipLaunchKernelGGL((KERNEL<SHAPE>), dim3(p.n_seq), dim3(rank_threads<SHAPE>()), 0, st, seqs, __VA_ARGS__, shape_of(p)); \
-    return hipGetLastError();                                                                                \
-  } while (0)
-
+// Above 2048 slots residency decides as soon as there are more sequences than CUs: a workgroup of 1024 threads, or of 512 with
+// more than 128 registers, has a CU to itself.  us for 16 sequences x 24 score rows, 1024 x 1, 1024 x 24 (in brackets keys in LDS,
+// 256 threads): 3072 slots at 512x6 11.8, 23.6, 58.9, at 1024x4 13.2, 39.6, 76.9 (28.1, 26.3, 73.2); 3100 at 512x8 14.0, 26.3,
+// 62.3, at 1024x4 13.3, 40.2, 78.3 (31.3, 28.1, 74.6); 6144 at 512x12 19.6, 38.1, 131.6, at 1024x6 18.2, 50.6, 146.7, at 1024x8
+// 21.3, 58.6, 160.9 (50.5, 51.6, 155.3); 6200 at 512x16 23.9, 46.2, 139.2, at 1024x8 21.6, 58.8, 158.1 (53.3, 53.2, 152.4).
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
                          bool plan_append, int32_t* tickets, hipStream_t st) {
-  ADSA_RANK_DISPATCH(k_select, sel_idx, sel_cnt, plan_append ? 1 : 0, tickets);
+#define ADSA_SELECT(...) ADSA_RANK_LAUNCH(k_select, ADSA_SHAPE(__VA_ARGS__), sel_idx, sel_cnt, plan_append ? 1 : 0, tickets)
+  if (p.cap <= 256) ADSA_SELECT(256, 1);
+  if (p.cap <= 512) ADSA_SELECT(256, 2);
+  if (p.cap <= 768 && p.n_seq < 1024) ADSA_SELECT(256, 3, 12);
+  if (p.cap <= 768) ADSA_SELECT(256, 3);
+  if (p.cap <= 1024) ADSA_SELECT(512, 2);
+  if (p.cap <= 2048) ADSA_SELECT(512, 4);
+  if (p.cap <= 3072) ADSA_SELECT(512, 6);
+  if (p.n_seq <= 256) {
+    if (p.cap <= 4096) ADSA_SELECT(1024, 4);
+    if (p.cap <= 6144) ADSA_SELECT(1024, 6);
+    ADSA_SELECT(1024, 8);
+  }
+  if (p.cap <= 4096) ADSA_SELECT(512, 8);
+  if (p.cap <= 6144) ADSA_SELECT(512, 12, 1);
+  ADSA_SELECT(512, 16, 1);
 }
 
+// k_compact_plan: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (32.7 with keys in LDS), 512 x 48 rows x 632 of the
+// fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).  It needs more registers than
+// k_select (512x8 and 512x12 above 128), so above 3072 slots the workgroups of 1024 threads stay ahead at any number of
+// sequences.  Nothing dropped, 16 sequences x 24 rows, 1024 x 1, 1024 x 24: 3072 slots at 512x6 12.3, 17.2, 77.5, at 1024x4 12.5, 26.7,
+// 92.4; 4096 at 1024x4 12.5, 28.8, 118, at 512x8 14.8, 32.5, 120; 6144 at 1024x6 16.5, 35.7, 167, at 1024x8 20.9, 43.5, 185,
+// at 512x12 19.5, 46.1, 178.  (1024x8 keeps 28 bytes of a thread's state in scratch memory.)
 static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* plan,
                                       bool advance_step, const float* vcos_s, hipStream_t st) {
-  ADSA_RANK_DISPATCH(k_compact_plan, keep_map, plan, advance_step ? 1 : 0, vcos_s);
+#define ADSA_PLAN(...) ADSA_RANK_LAUNCH(k_compact_plan, ADSA_SHAPE(__VA_ARGS__), keep_map, plan, advance_step ? 1 : 0, vcos_s)
+  if (p.cap <= 256) ADSA_PLAN(256, 1);
+  if (p.cap <= 512) ADSA_PLAN(256, 2);
+  if (p.cap <= 768) ADSA_PLAN(256, 3, 12);
+  if (p.cap <= 1024) ADSA_PLAN(512, 2);
+  if (p.cap <= 2048) ADSA_PLAN(512, 4);
+  if (p.cap <= 3072) ADSA_PLAN(512, 6);
+  if (p.cap <= 4096) ADSA_PLAN(1024, 4);
+  if (p.cap <= 6144) ADSA_PLAN(1024, 6);
+  ADSA_PLAN(1024, 8);
 }
 
 // column slices of a head row: 128 bytes, or the whole row when it is narrower

@@ -142,3 +142,37 @@ def test_many_sequences_rank_like_few(rows):
     for a, b in zip(*got):
         assert torch.equal(a[at], b)
     assert len(set(got[0][1].tolist())) == few
+
+
+@pytest.mark.parametrize("cap", [3072, 3073, 6144, 6145])
+def test_ranking_at_the_edges_of_the_wide_shapes(cap):
+    test_ranking_at_workgroup_edges(cap)
+
+
+@pytest.mark.parametrize("cap", [2049, 3073, 4096, 4097, 6144, 6145, 8192])
+def test_more_sequences_than_compute_units_rank_like_few(cap):
+    """Above 2048 slots launches of more than 256 sequences use smaller workgroups: same lists and keep maps as for a small batch."""
+    rng = np.random.default_rng(cap)
+    W, P = 16, cap % 16 + 16
+    s = cap - P
+    wl = WL.get_workload("tiny", n_heads=1, head_dim=64, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
+    patterns = score_patterns(rng, cap)
+    few = len(patterns)
+    got = []
+    for n_seq in (few, 259):
+        batch = LayerBatch(params_for(wl, n_seq, cap, score_mode=B.SCORE_EXT_LARGEST), DEV)
+        at = torch.arange(n_seq) % few
+        batch.pos.copy_(torch.arange(cap, dtype=torch.int32).expand(n_seq, cap))
+        batch.score.copy_(torch.from_numpy(np.stack(patterns))[at][:, None])
+        h = batch.seqs_host
+        h["n_res"], h["step"], h["grid_origin"], h["n_keep_prefix"] = cap, s, P, P
+        h["budget"] = s // 3 + at.numpy()
+        batch.upload_seqs()
+        batch.select()
+        batch.compact()
+        torch.cuda.synchronize()
+        n_res = torch.from_numpy(batch.read_seqs()["n_res"].copy())
+        got.append([x.cpu() for x in (batch.sel_idx, batch.sel_cnt, batch.keep_map, n_res, batch.score, batch.pos)])
+    for a, b in zip(*got):
+        assert torch.equal(a[at].view(torch.int32), b.view(torch.int32))
+    assert (got[0][1] > s // 3).all()
