@@ -406,10 +406,13 @@ __global__ __launch_bounds__(NT, S >= 16 ? 4 : 1) void k_select(adsa_seq* seqs, 
 
 // In-place, order-preserving move of pos[] and every score row: all sources of a batch of rows have arrived in registers
 // before the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
+// Rows per batch: as many as leave the kernels around it their residency.  k_compact_plan with 2 slots per thread, us with 8 | 12 |
+// 16 | 24 rows (74 | 94 | 122 | 160 registers): 900 slots, 66 sequences x 24 rows 10.1 | 10.2 | 10.4 | 10.0, 514 x 24
+// 20.8 | 23.4 | 25.3 | 30.1, 516 x 8 12.1 | 14.4 | 15.5 | 23.2, 1538 x 24 53 | 54 | 56 | 66; with 3 slots 24 rows and 8 have the same residency (114 and 102 registers).
 template <int NT, int S>
 __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, int cap, uint32_t moves, const uint32_t (&dest)[S],
                                             const int (&posv)[S]) {
-  constexpr int kRowBatch = S <= 3 ? 24 : S == 4 ? 8 : 4;
+  constexpr int kRowBatch = S == 2 ? 8 : S <= 3 ? 24 : S == 4 ? 8 : 4;
   const int tid = threadIdx.x;
   for (int r0 = 0; r0 < rows; r0 += kRowBatch) {
     float sv[S][kRowBatch];
