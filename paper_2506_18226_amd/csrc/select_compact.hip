@@ -572,8 +572,12 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
 // are at most its sources and below the next tile's).  Bound by the copy: kMoveRows rows per thread in flight, and since nothing
 // reads a row again before the next step's attention, streaming loads and stores.  512 sequences, 1.05 GB moved:
 // 182 us; with 4 rows and ordinary accesses 212, with 8 and streaming 196, with 16 and ordinary 205, K and V together
-// in one workgroup 8 rows each 199.
+// in one workgroup 8 rows each 199.  ROWS: no more than the longest sequence needs for a single tile, since many short sequences
+// are bound by how many workgroups fit a CU (132 registers with 16 rows, 68 with 8, 36 with 4).  350 sequences x 33 heads x 64
+// bf16, us with 16 rows | the ROWS of the rule: 100 slots 86.9 | 55.1, 128 slots 93.3 | 64.5 (4 rows), 140 slots 97.8 | 77.1,
+// 256 slots 134.6 | 132.4 (8 rows).
 constexpr int kMoveRows = 16;
+template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
                                                               int lanes_per_slice, int slices_per_head, LaunchShape L) {
   const int b = blockIdx.z;
@@ -586,22 +590,22 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const int row_in_pass = threadIdx.x / lanes_per_slice, lane = threadIdx.x % lanes_per_slice;
   gchar* const base = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v) + (long long)head * L.head_stride_b + ((long long)part * lanes_per_slice + lane) * 16;
   const gint* const map = (const gint*)keep_map + (size_t)b * L.cap;
-  for (int t0 = first; t0 < n_old; t0 += rows_per_pass * kMoveRows) {
-    uint4 val[kMoveRows];
-    int dst[kMoveRows];
+  for (int t0 = first; t0 < n_old; t0 += rows_per_pass * ROWS) {
+    uint4 val[ROWS];
+    int dst[ROWS];
 #pragma unroll
-    for (int u = 0; u < kMoveRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
       const int i = t0 + u * rows_per_pass + row_in_pass;
       const int m = i < n_old ? map[i] : -1;
       dst[u] = m == i ? -1 : m;
     }
 #pragma unroll
-    for (int u = 0; u < kMoveRows; ++u)
+    for (int u = 0; u < ROWS; ++u)
       if (dst[u] >= 0) val[u] = load_stream16(base + (long long)(t0 + u * rows_per_pass + row_in_pass) * L.slot_stride_b);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this thread's rows are in registers ...
     __syncthreads();                                         // ... and so are everybody's, before any of them is overwritten
 #pragma unroll
-    for (int u = 0; u < kMoveRows; ++u)
+    for (int u = 0; u < ROWS; ++u)
       if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * L.slot_stride_b, val[u]);
   }
 }
@@ -822,7 +826,9 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
   const Slices sl = row_slices(p);
   dim3 grid(p.n_heads * sl.per_head, 2, p.n_seq);
-  hipLaunchKernelGGL(k_compact_move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
+  const int rows_per_pass = kMoveThreads / sl.lanes;
+  auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8> : k_compact_move<kMoveRows>;
+  hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
                      (const int32_t*)plan, sl.lanes, sl.per_head, L);
   return hipGetLastError();
 }

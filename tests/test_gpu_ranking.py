@@ -149,6 +149,11 @@ def test_ranking_at_the_edges_of_the_wide_shapes(cap):
     test_ranking_at_workgroup_edges(cap)
 
 
+@pytest.mark.parametrize("cap", [127, 128, 129])             # (256 and 257: above)
+def test_rows_move_at_the_edges_of_the_tile_sizes(cap):
+    test_ranking_at_workgroup_edges(cap)
+
+
 @pytest.mark.parametrize("cap", [2049, 3073, 4096, 4097, 6144, 6145, 8192])
 def test_more_sequences_than_compute_units_rank_like_few(cap):
     """Above 2048 slots launches of more than 256 sequences use smaller workgroups: same lists and keep maps as for a small batch."""
