@@ -645,20 +645,27 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   a.waves = pairs >= 512 || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
   // Splitting a list costs a second launch, ~3 us.  What it can save: a workgroup alone streams ~55 GB/s (8 or 16 waves
   // alike), the chip ~5.5 TB/s, as much as ~100 workgroups.  So a list of b bytes on each of `pairs` workgroups is split
-  // when b * (1 - max(pairs / 100, 1 / chunks)) is more than 230 KB, ~4 us; into 8-wave chunks of at least 64 KB that
+  // when b * (1 - max(pairs / 100, 1 / chunks)) is more than 230 KB, ~4 us; into 8-wave chunks of about 64 KB that
   // together occupy every CU.  Measured, us whole | split: 8 pairs x 256 KB 8.0 | 8.7; 20 x 205 KB 7.4 | 9.2;
   // 16 x 384 KB 11.9 | 9.6; 8 x 512 KB 13.4 | 9.4; 8 x 2 MB 44 | 11.6; 32 x 1 MB 24.6 | 12.6; 32 x 4 MB 84.7 | 27.1;
   // 80 x 384 KB 12.8 | 12.8; 64 x 154 KB 7.1 | 9.8.  (One launch whose last workgroup to arrive merges, behind a
   // device-scope release / acquire, took 12 us for 8 x 512 KB, 58 for 32 x 4 MB and 17.5 for 40 lists of 102 KB, which
   // take 5.9 us whole.)
-  long long nc = (256 + pairs - 1) / pairs;
-  if (nc > b_list / (64 << 10)) nc = b_list / (64 << 10);
-  if (nc > kMaxChunks) nc = kMaxChunks;
-  if (nc < 1) nc = 1;
+  // 64 KB is what the rings of 8 waves hold at once: where the CUs allow it a chunk has no more, so that none ends in a
+  // second, nearly empty revolution (2 x 300 KB fused: 11.2 with 4 chunks, 9.9 with 5; 2 x 300 KB plain 9.5 and 8.3).  Rows of the
+  // fused V-cosine form take longer, so their line is 175 KB of such chunks: 2 x 200 KB 9.4 | 9.8, 2 x 250 KB 10.5 | 9.6,
+  // 16 x 300 KB 12.4 | 10.4.
+  const bool fused = p.score_mode == ADSA_SCORE_VCOS_FUSED;
+  const long long full = b_list / (64 << 10), snug = (b_list + (64 << 10) - 1) / (64 << 10);
+  auto chunks = [](long long n) { return n > kMaxChunks ? (long long)kMaxChunks : n < 1 ? 1ll : n; };
+  long long nc = chunks(std::min(full, (256 + pairs - 1) / pairs));
+  const long long snug_nc = pairs * snug <= 256 ? chunks(snug) : nc;
+  if (fused) nc = snug_nc;
   const long long hidden = pairs * nc > 100 ? pairs * nc : 100;          // b_list * (1 - max(pairs / 100, 1 / nc)), in units of 1 / (100 nc)
-  if (pairs >= 96 || b_list * (100 * nc - hidden) <= 230000ll * 100 * nc) nc = 1;
+  if (pairs >= 96 || b_list * (100 * nc - hidden) <= (fused ? 175000ll : 230000ll) * 100 * nc) nc = 1;
+  else nc = snug_nc;
   // the logits (two rows of them for the fused V-cosine form) and the slot list of a chunk must fit in LDS
-  const int lds_rows = (p.score_mode == ADSA_SCORE_VCOS_FUSED ? 2 : 1) + 1;
+  const int lds_rows = (fused ? 2 : 1) + 1;
   while (nc < kMaxChunks && (size_t)lds_rows * ((p.sel_cap + nc - 1) / nc + 1) * sizeof(float) > 40 * 1024) ++nc;
   a.n_chunks = (int)nc;
   a.reserved_chunks = reserved_chunks(p);
