@@ -639,10 +639,12 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   // 400 x 650 x 64 (67 MB) 14.6 | 14.9 | 20.6; 480 x 700 x 64 (86 MB) 17.8 | 16.7; 288 x 1300 x 64 (96 MB) 24.6 | 23.3;
   // 400 x 700 x 128 (143 MB) 26.8 | 25.9; 768 x 200 x 64 9.6 | 10.6 | 19.9; 768 x 649 x 64 22.6 | 22.7 | 32.3;
   // 256 x 650 x 128 16.2 | 15.8 | 17.0; 192 x 650 x 64 9.3 | 8.5 | 10.9; 128 x 4000 x 128 60.3 | 53.0 | 52.4;
-  // 40 x 400 x 64 6.3 | 5.9 | 7.2; fp32: 288 x 300 x 128 (88 MB) 21.0 | 20.3; 400 x 300 x 128 22.9 | 22.1.
+  // 40 x 400 x 64 6.3 | 5.9 | 7.2; fp32: 288 x 300 x 128 (88 MB) 21.0 | 20.3; 400 x 300 x 128 22.9 | 22.1.  Lists that the
+  // rings of 4 waves hold at once (32 KB) gain nothing from more of them: 16 pairs x 64 tokens x 64 3.7 | 4.3, 256 x 128 x 64
+  // 4.3 | 4.9, 16 x 32 x 128 fp32 3.3 | 3.8, fused 64 x 64 x 128 4.8 | 6.5; 16 x 192 x 64 (48 KB) 4.4 | 4.5, fp32 16 x 48 x 128 4.2 | 3.9.
   const long long pairs = (long long)p.n_seq * p.n_heads;
   const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
-  a.waves = pairs >= 512 || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
+  a.waves = pairs >= 512 || b_list <= (32 << 10) || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
   // Splitting a list costs a second launch, ~3 us.  What it can save: a workgroup alone streams ~55 GB/s (8 or 16 waves
   // alike), the chip ~5.5 TB/s, as much as ~100 workgroups.  So a list of b bytes on each of `pairs` workgroups is split
   // when b * (1 - max(pairs / 100, 1 / chunks)) is more than 230 KB, ~4 us; into 8-wave chunks of about 64 KB that
