@@ -15,12 +15,13 @@ constexpr int kWave = 64;
 constexpr int kMoveThreads = 256;
 constexpr int kMaxChunks = 16;         // a list is split over at most this many workgroups
 
-// Attend launch plan: a workgroup handles (sequence, head, token chunk).
+// Attend launch plan: a workgroup handles (sequence, head or heads, token chunk).
 struct AttendPlan {
   int n_chunks;         // token chunks per list; every sequence splits its own count evenly
   int chunk_max;        // upper bound of tokens in one chunk, + 1
   int reserved_chunks;  // chunks per list the workspace has room for (>= n_chunks)
   int waves;            // waves per attend workgroup: 4 or 8
+  int heads;            // heads per attend workgroup: 1, or 512 bytes' worth of a token of a [slot][head][D] cache
 };
 
 // Rows of adsa_seq.score: one accumulator per head for ATTN_MASS (the rank of a slot is their sum),

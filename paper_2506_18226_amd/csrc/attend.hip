@@ -2,12 +2,12 @@
 // attention over the selected slots, plus the cache append (Section 4.2) and the per-head
 // attention-mass update, in ONE launch.
 //
-//  k_attend<EB, D, U, NW, VF, DIRECT> : grid (token chunk, head, sequence), NW waves.
-//    A 16-byte-per-lane streaming load of one wave covers RPW = 64 / (D*EB/16) consecutive tokens of ONE head.
+//  k_attend<EB, D, HT, U, NW, VF, DIRECT> : grid (token chunk, HT heads, sequence), NW waves.
+//    HT = 1: a 16-byte-per-lane streaming load of one wave covers RPW = 64 / (D*EB/16) consecutive tokens of ONE head.
 //    That holds for [slot][head][D] caches too: a row is 128 bytes or more, whole cache lines, so a workgroup that
-//    walks one head's rows at a stride fetches nothing it does not use.  (Taking all heads of a token in one
-//    1 KB burst per wave-load was slower at every size: 32 x 24 heads x 64, 649 tokens, bf16 34.7 us against 25.0;
-//    8 x 12 heads, 300 tokens 11.6 against 5.8 us.)
+//    walks one head's rows at a stride fetches nothing it does not use.  But it visits every page of the sequence for its
+//    128 or 256 bytes a token, and so do the workgroups of the other heads: large launches over such caches take
+//    512 bytes of a token (HT heads) per workgroup; the rule and its figures stand in make_attend_plan.
 //    q.k is reduced over the lanes of a row with DPP; every lane keeps an online-softmax state (m, l, acc) in
 //    registers, fp32, log2 domain.  The lane groups of a wave merge in registers (DPP and 16-/32-lane
 //    swaps), the waves through one small LDS record each.
@@ -60,6 +60,8 @@ template <> struct Elems<4> {      // fp32: 4 values per 16-byte vector
   }
 };
 
+constexpr int kBurst = 512;        // bytes of a token that a workgroup of several heads takes
+
 // chunk c of a list of cnt (<= ADSA_MAX_CAP) tokens split evenly over nc (<= kMaxChunks) chunks
 __device__ __forceinline__ int chunk_begin(int cnt, int c, int nc) { return (int)(((unsigned)cnt * (unsigned)c) / (unsigned)nc); }
 
@@ -87,28 +89,32 @@ struct AttendArgs {
 // The arguments the first round trip needs come first, as plain scalars: the build asks for leading kernel
 // arguments to be preloaded into scalar registers at wave launch, so those loads can leave at once, without
 // waiting for a scalar load of the argument block (which would also wait for the sequence record's).
-template <int EB, int D, int U, int NW, bool VF, bool DIRECT>
+// HT > 1: the workgroup takes HT heads, the lane groups of a wave-load being the HT heads of RPW / HT tokens.
+template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT>
 __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
                                                       const char* q_arg, const char* k_new_arg, const char* v_new_arg,
                                                       int heads_and_flags, int sel_cap_arg, AttendArgs A) {
   constexpr int kAttThreads = NW * kWave;           // the waves of the workgroup share one token chunk
   constexpr int EPL = Elems<EB>::N;                 // elements per lane
   constexpr int LPR = D / EPL;                      // lanes per row
-  constexpr int RPW = kWave / LPR;                  // rows per wave-load
+  constexpr int RPW = kWave / LPR / HT;             // tokens per wave-load
+  static_assert(HT == 1 || (DIRECT && !VF && RPW * HT * LPR == kWave), "several heads: whole lists only");
   constexpr int PF = 1024 / kAttThreads;            // score read-modify-writes a thread starts early
-  extern __shared__ float s_logit[];                // logits [chunk_max] ([2][chunk_max] for VF), then
+  extern __shared__ float s_logit[];                // logits [HT][chunk_max] ([2][chunk_max] for VF), then
                                                     // the chunk's slot list int [chunk_max]
   // merge: the lane groups of a wave meet in registers, the waves through these (one state per wave)
-  __shared__ float s_wm[NW], s_wl[NW];
-  __shared__ __attribute__((aligned(16))) float s_wacc[NW * D];
+  __shared__ float s_wm[NW * HT], s_wl[NW * HT];
+  __shared__ __attribute__((aligned(16))) float s_wacc[NW * HT * D];
 
-  const int chunk = DIRECT ? 0 : blockIdx.x, head = blockIdx.y, b = blockIdx.z;
+  const int chunk = DIRECT ? 0 : blockIdx.x, b = blockIdx.z;
   const int n_chunks = DIRECT ? 1 : gridDim.x;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int ts = lane / LPR, dl = lane - ts * LPR;  // token of this lane's row within a wave-load, 16-byte piece of the row
   // (only 14 dwords of arguments are preloaded: the two flags the first trip needs ride on the head count)
   const int n_heads = heads_and_flags & 0xFFFF, sel_cap = sel_cap_arg;
+  // token and head of this lane's row within a wave-load, 16-byte piece of the row (heads past the last repeat it)
+  const int dl = lane % LPR, ts = lane / LPR / HT, hs = HT == 1 ? 0 : lane / LPR % HT;
+  const int head0 = blockIdx.y * HT, head = HT == 1 ? head0 : min(head0 + hs, n_heads - 1), heads_here = HT == 1 ? 1 : min(HT, n_heads - head0);
 
   // ---- first round trip: everything that depends on the kernel arguments only -- the count, the
   // sequence record, q and (when the list is not split, so its chunk starts at 0) the first slots of
@@ -165,13 +171,13 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   const int cnt = min(cnt_raw, sel_cap);
   if (cnt <= 0) {                                   // inactive or rejected sequence: zero-filled row
     if (chunk == 0) {
-      const size_t row = (size_t)b * n_heads + head;
-      for (int o = tid; o < D; o += kAttThreads) {
+      const size_t row = (size_t)b * n_heads + head0;
+      for (int o = tid; o < heads_here * D; o += kAttThreads) {
         if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + o] = 0.0f;
         else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + o] = 0;
-        if (o == 0) lse_g[row] = 0.0f;
+        if (o % D == 0) lse_g[row + o / D] = 0.0f;
       }
-      if (head == 0 && tid == 0) advance_empty(sqp, A.advance);
+      if (head0 == 0 && tid == 0) advance_empty(sqp, A.advance);
     }
     return;
   }
@@ -179,7 +185,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   const int t_end = DIRECT ? cnt : chunk_begin(cnt, chunk + 1, n_chunks);
   if (t_begin >= t_end) return;                     // fewer tokens than chunks
   const int len = t_end - t_begin;
-  int* const s_idx = reinterpret_cast<int*>(s_logit + (VF ? 2 : 1) * A.chunk_max);   // the chunk's slot list (filled below)
+  int* const s_idx = reinterpret_cast<int*>(s_logit + (VF ? 2 : HT) * A.chunk_max);   // the chunk's slot list (filled below)
   if constexpr (!DIRECT) {
 #pragma unroll
     for (int u = 0; u < U; ++u) slot_a[u] = idx[t_begin + min((wave + u * NW) * RPW + ts, len - 1)];
@@ -241,7 +247,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
       d = row_sum<LPR>(d);
       const float z = on ? d : -INFINITY;
-      if (A.accumulate && dl == 0 && on) s_logit[tok[u]] = z;
+      if (A.accumulate && dl == 0 && on) s_logit[hs * A.chunk_max + tok[u]] = z;
       const float m_new = fmaxf(m, z);
       const float corr = (m == -INFINITY) ? 0.0f : fast_exp2(m - m_new);     // (l and acc are 0 while m is -inf)
       const float pr = on ? fast_exp2(z - m_new) : 0.0f;
@@ -301,7 +307,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     }
     __syncthreads();
     // thread i of the final score update serves tokens i, i + threads, ...; start the first PF reads now
-    if (DIRECT && A.accumulate) {
+    if (DIRECT && HT == 1 && A.accumulate) {
 #pragma unroll
       for (int k = 0; k < PF; ++k) {
         const int i = tid + k * kAttThreads;
@@ -333,14 +339,14 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   if constexpr (RPW > 1) {
     float M = m;
 #pragma unroll
-    for (int x = LPR; x < kWave; x <<= 1)
+    for (int x = LPR * HT; x < kWave; x <<= 1)
       M = x == 8 ? xor_max<8>(M) : x == 16 ? xor_max<16>(M) : xor_max<32>(M);
     const float sc = (m == -INFINITY) ? 0.0f : fast_exp2(m - M);     // a group that saw no token weighs 0
     l *= sc;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] *= sc;
 #pragma unroll
-    for (int x = LPR; x < kWave; x <<= 1) {
+    for (int x = LPR * HT; x < kWave; x <<= 1) {
       l = x == 8 ? xor_sum<8>(l) : x == 16 ? xor_sum<16>(l) : xor_sum<32>(l);
 #pragma unroll
       for (int e = 0; e < EPL; ++e) acc[e] = x == 8 ? xor_sum<8>(acc[e]) : x == 16 ? xor_sum<16>(acc[e]) : xor_sum<32>(acc[e]);
@@ -350,17 +356,56 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   // ---- step 2 (LDS): one state per wave; after ONE barrier every thread works out the
   // normaliser itself, the first D threads each finish one output element
   if (ts == 0) {
-    if (dl == 0) { s_wm[wave] = m; s_wl[wave] = l; }
-    float4* dst = reinterpret_cast<float4*>(&s_wacc[wave * D + dl * EPL]);
+    if (dl == 0) { s_wm[wave * HT + hs] = m; s_wl[wave * HT + hs] = l; }
+    float4* dst = reinterpret_cast<float4*>(&s_wacc[(wave * HT + hs) * D + dl * EPL]);
 #pragma unroll
     for (int e = 0; e < EPL; e += 4) dst[e / 4] = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
   }
   __syncthreads();
   // Section 4.2: the query token's row enters the cache (nothing in this launch reads it from there)
-  if (new_slot >= 0 && chunk == n_chunks - 1 && wave == 0 && ts == 0) {
+  if (new_slot >= 0 && chunk == n_chunks - 1 && wave == 0 && ts == 0 && hs < heads_here) {
     const long long off = (long long)new_slot * A.slot_stride_b;
     store16(kb + off, nk);
     store16(vb + off, nv);
+  }
+  if constexpr (HT > 1) {
+    // ---- several heads: a thread finishes output elements of one head after the other, then adds its tokens' probabilities to
+    // all the heads' score rows
+    __shared__ float s_lse2[HT];
+    for (int o = tid; o < heads_here * D; o += kAttThreads) {
+      const int h = o / D, d = o - h * D;
+      float w[NW], M = -INFINITY, L = 0.0f, a = 0.0f;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) { w[k] = s_wm[k * HT + h]; M = fmaxf(M, w[k]); }
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        w[k] = (w[k] == -INFINITY) ? 0.0f : fast_exp2(w[k] - M);
+        L = fmaf(s_wl[k * HT + h], w[k], L);
+        a = fmaf(s_wacc[(k * HT + h) * D + d], w[k], a);
+      }
+      const float val = __fdividef(a, L);
+      const size_t row = (size_t)b * n_heads + head0 + h;
+      if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + d] = val;
+      else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + d] = (uint16_t)f32_to_bf16_rne(val);
+      if (d == 0) { s_lse2[h] = M + __log2f(L); lse_g[row] = s_lse2[h] * kLn2; }
+    }
+    if (A.accumulate) {
+      __syncthreads();
+      float lse2[HT];
+#pragma unroll
+      for (int h = 0; h < HT; ++h) lse2[h] = s_lse2[min(h, heads_here - 1)];
+      for (int i = tid; i < len; i += kAttThreads) {
+        gfloat* const at = score + (size_t)head0 * A.cap + s_idx[i];
+        float old[HT];
+#pragma unroll
+        for (int h = 0; h < HT; ++h) old[h] = at[(size_t)min(h, heads_here - 1) * A.cap];
+#pragma unroll
+        for (int h = 0; h < HT; ++h)
+          if (h < heads_here) at[(size_t)h * A.cap] = old[h] + fast_exp2(s_logit[h * A.chunk_max + i] - lse2[h]);
+      }
+    }
+    if (head0 == 0 && tid == 0) advance_step(sqp, A.advance);
+    return;
   }
   // log2-domain normaliser of the whole workgroup, worked out by every thread from the waves' states
   float wgt[NW], M = -INFINITY, L = 0.0f;
@@ -538,20 +583,20 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
   }
 }
 
-template <int EB, int D, int NW, bool VF, bool DIRECT>
+template <int EB, int D, int HT, int NW, bool VF, bool DIRECT>
 hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
   // row pairs in flight per lane: 2, 3, 6 and 8 were measured no faster on 4- and 8-wave workgroups
   constexpr int U = 4;
-  const size_t lds = (size_t)((VF ? 2 : 1) + 1) * plan.chunk_max * sizeof(float);      // logits rows + the slot list
-  dim3 grid(plan.n_chunks, A.n_heads, n_seq);
+  const size_t lds = (size_t)((VF ? 2 : HT) + 1) * plan.chunk_max * sizeof(float);      // logits rows + the slot list
+  dim3 grid(plan.n_chunks, (A.n_heads + HT - 1) / HT, n_seq);
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
   const int hf = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0);
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend<EB, D, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
+    hipExtLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
                           DIRECT ? ev_stop : nullptr, 0, A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
   else
-    hipLaunchKernelGGL((k_attend<EB, D, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), lds, st,
+    hipLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), lds, st,
                        A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
   if constexpr (!DIRECT) {
     const hipError_t e = hipGetLastError();
@@ -568,9 +613,12 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
 template <int EB, int D, bool VF>
 hipError_t launch_attend_v(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (plan.n_chunks > 1) return launch_attend_w<EB, D, 8, VF, false>(A, plan, n_seq, st, ev_start, ev_stop);
-  if (plan.waves == 8) return launch_attend_w<EB, D, 8, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
-  return launch_attend_w<EB, D, 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
+  if constexpr (!VF && kBurst > D * EB) {
+    if (plan.heads > 1) return launch_attend_w<EB, D, kBurst / (D * EB), 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
+  }
+  if (plan.n_chunks > 1) return launch_attend_w<EB, D, 1, 8, VF, false>(A, plan, n_seq, st, ev_start, ev_stop);
+  if (plan.waves == 8) return launch_attend_w<EB, D, 1, 8, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
+  return launch_attend_w<EB, D, 1, 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
 }
 
 template <int EB, int D>
@@ -630,6 +678,7 @@ AttendPlan make_attend_plan(const adsa_params& p) {
     while (nc == 1 && a.waves > 4 && gqa_lds_bytes(p, a.waves, 1) > kGqaMaxLds) a.waves /= 2;
     if (nc > 1) a.waves = 4;
     a.n_chunks = a.reserved_chunks = nc;
+    a.heads = 1;
     a.chunk_max = gqa_logit_stride(p, nc);
     return a;
   }
@@ -670,6 +719,19 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   const int lds_rows = (fused ? 2 : 1) + 1;
   while (nc < kMaxChunks && (size_t)lds_rows * ((p.sel_cap + nc - 1) / nc + 1) * sizeof(float) > 40 * 1024) ++nc;
   a.n_chunks = (int)nc;
+  // Heads per workgroup over a [slot][head][D] cache: 512 bytes of a token from 384 such workgroups of 4 waves on, which then keep
+  // the chip busy with a quarter or half of the workgroups and visit each page a quarter or half as often.  bf16, us with one
+  // head | 512 bytes (all of a 1 KB burst in one wave-load): 41 x 48 heads x 64, 810 tokens 79.2 | 64.7 (65.1); 509 x 24 x 64, 165
+  // tokens 101 | 86 (85); 44 x 48 x 64, 39 tokens 10.4 | 8.8 (9.3); 13 x 64 x 128, 879 tokens 68 | 61 (63); fp32 209 x 36 x 64, 150
+  // tokens 98 | 92 (94); below the line 32 x 36 x 64, 706 tokens 38 | 44 (51); 26 x 20 x 64, 687 tokens 21.7 | 23.0 (49);
+  // 8 x 12 x 64, 300 tokens 5.8 against 11.6 for the burst.  Heads that do not divide by HT leave lanes idle: 259 x 9 x 64, 439
+  // tokens 44 | 50, so only short lists, whose workgroups are mostly start and end, take them: 863 x 7 x 64, 52 tokens 23 | 17, 451 x 7 x 64, 61 tokens 14.3 | 11.9.
+  // Rows of 512 bytes have nothing to gain.
+  const int ht = p.kv_slot_stride > p.kv_head_stride ? kBurst / (p.head_dim * elem_bytes(p)) : 1;
+  const long long groups = (p.n_heads + ht - 1) / ht;
+  const bool fits = p.n_heads % ht == 0 || (b_list <= (32 << 10) && 100 * groups * ht <= 115ll * p.n_heads);
+  a.heads = !fused && nc == 1 && ht > 1 && p.n_seq * groups >= 384 && fits && (size_t)(ht + 1) * (p.sel_cap + 1) * sizeof(float) <= 40 * 1024 ? ht : 1;
+  if (a.heads > 1) a.waves = 4;
   a.reserved_chunks = reserved_chunks(p);
   a.chunk_max = (p.sel_cap + a.n_chunks - 1) / a.n_chunks + 1;
   return a;
