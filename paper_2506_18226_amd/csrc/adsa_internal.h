@@ -83,6 +83,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
                          int advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
 // grouped-query path (q_per_kv >= 2): matrix-core kernel, one workgroup per (sequence, cache head, chunk of the list)
 constexpr size_t kGqaMaxLds = 128 * 1024;     // dynamic LDS one workgroup may ask for
+static inline bool gqa_two_fit(size_t lds) { return 2 * (lds + 2048) <= 160 * 1024; }      // on a CU, static words included
 int gqa_logit_stride(const adsa_params& p, int n_chunks);
 int gqa_global_logit_stride(const adsa_params& p);
 size_t gqa_lds_bytes(const adsa_params& p, int waves, int n_chunks);

@@ -657,11 +657,11 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   if (p.q_per_kv > 1) {      // grouped queries: one workgroup per (sequence, cache head, chunk of whole 16-token tiles)
     const long long wgs = (long long)p.n_seq * p.n_heads;
     // 8 waves, but 4 where there is more than one workgroup per CU and the lists are short, or the logits and the waves'
-    // tiles of two 8-wave workgroups do not fit a CU.  Measured, 4 | 8 waves: 256 pairs x 649 x 128, G = 8 20.1 | 17.6 us;
-    // 512 31.6 | 30.9; 512 x 649 x 64 19.0 | 17.8; 384 x 300 x 128 15.3 | 15.9; 640 x 200 x 64 10.9 | 12.0;
-    // 512 x 649 x 128 with G = 16 (one workgroup fits) 33.8 | 37.3.
-    const bool one_fits = 2 * (gqa_lds_bytes(p, 8, 1) + 2048) > 160 * 1024;
-    a.waves = wgs >= 384 && (p.sel_cap < 448 || one_fits) ? 4 : 8;
+    // tiles of two 8-wave workgroups do not fit a CU and those of two 4-wave ones do.  Measured, 4 | 8 waves: 256 pairs x 649 x 128,
+    // G = 8 20.1 | 17.6 us; 512 31.6 | 30.9; 512 x 649 x 64 19.0 | 17.8; 384 x 300 x 128 15.3 | 15.9; 640 x 200 x 64 10.9 | 12.0;
+    // 512 x 649 x 128 with G = 16 (two fit with 4) 33.8 | 37.3; 390 x 1230 x 128 in 2336 slots (one fits either way) 58.7 | 46.3.
+    const bool four = !gqa_two_fit(gqa_lds_bytes(p, 8, 1)) && gqa_two_fit(gqa_lds_bytes(p, 4, 1));
+    a.waves = wgs >= 384 && (p.sel_cap < 448 || four) ? 4 : 8;
     // Lists are split only when they must be (the logits of a whole list, all G queries, do not fit in LDS even
     // with 4 waves) or when it was measured to pay: long lists (>= 2560 slots) of at most 32 (sequence, cache head)
     // pairs, 8 pairs x 2700 x 128 16.7 us in 16 chunks; merged by the last of them to arrive it was 25, whole 41.

@@ -3,7 +3,7 @@
 // meets G queries, so the two products are small dense contractions and run on the matrix cores
 // (v_mfma_f32_16x16x16_bf16, fp32 accumulation); the kernel is still bound by the HBM stream.
 //
-//  k_attend_gqa<D, NW> : grid (cache head, sequence), NW waves.  The list is cut into 16-token tiles,
+//  k_attend_gqa<D, NW, SPLIT, R> : grid (cache head, sequence), NW waves.  The list is cut into 16-token tiles,
 //  dealt round-robin to the waves of the workgroup (a fixed assignment: results are reproducible bit
 //  for bit; claiming tiles from a counter was measured no faster), and each wave runs its own online
 //  softmax:
@@ -84,6 +84,15 @@ __device__ __forceinline__ void vload(const gchar* p, uint32_t* w) {
 // lane g's value, g uniform
 __device__ __forceinline__ float lane_f(float x, int g) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), g)); }
 
+// Tiles in flight per wave.  8 KB of loads: with no more registers than that (124) two 8-wave workgroups share a CU, and one
+// hides the other's first trip, merge and stores (48 x 8 lists x 300 tokens x 128: 15.7 us with 1 tile, 19.2 with 2; 32 x 8 x 649
+// x 64 11.4 with 1 or 2, 12.9 with 4).  Where there is one 8-wave workgroup per CU anyway it makes no difference: 32 x 8 x 649 x 128
+// 17.6 with 1, 17.9 with 2, 19.3 with 3.
+constexpr int ring(int D) { return D == 64 ? 2 : 1; }
+// A 4-wave workgroup that has a CU to itself (its logits fill the LDS) needs twice the depth: 79 x 2 lists x 1330 tokens x 128,
+// G = 16, 34.7 us with 1 tile, 27.7 with 2; 20 x 2 x 1313 x 128, G = 4, 28.6 and 22.9.
+constexpr int deep_ring(int D) { return 2 * ring(D); }
+
 struct GqaArgs {
   adsa_seq* seqs;
   const char* q;
@@ -110,7 +119,8 @@ struct GqaArgs {
 // the two append flags ride on the head count: heads | G << 16 | append << 24 | new_f32 << 25.
 // SPLIT: the list of a (sequence, cache head) is cut into gridDim.z chunks of whole 16-token tiles, one workgroup
 // each; every workgroup leaves a partial and its logits in the workspace and k_gqa_finish merges them in chunk order.
-template <int D, int NW, bool SPLIT>
+// R: tiles in flight per wave (a ring: the oldest is multiplied, then refilled).
+template <int D, int NW, bool SPLIT, int R>
 __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
                                                           const char* q_arg, const char* k_new_arg, const char* v_new_arg,
                                                           int heads_g_flags, int sel_cap_arg, GqaArgs A) {
@@ -122,11 +132,6 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   constexpr int NC = D / 16;                // 16-wide chunks of the q.k contraction
   constexpr int EV = D / 16;                // V columns a lane holds per token
   constexpr int VW = EV / 2;                // dwords of V a lane loads per token
-  // Tiles in flight per wave (a ring: the oldest is multiplied, then refilled), 8 KB of loads: with no more registers than that
-  // (128) two 8-wave workgroups share a CU, and one hides the other's first trip, merge and stores.  32 x 8 x 649 x 128:
-  // 17.6 us with 1 tile, 17.9 with 2, 19.3 with 3; 48 x 8 x 300 x 128 15.7 with 1, 19.2 with 2; 32 x 8 x 649 x 64 11.4
-  // with 1 or 2, 12.9 with 4.
-  constexpr int R = D == 64 ? 2 : 1;
   constexpr int PF = 2048 / T;              // slot-list entries a thread fetches in the first round trip
   extern __shared__ __align__(16) char smem[];
   __shared__ float s_wm[NW][16], s_wl[NW][16];
@@ -568,17 +573,17 @@ __global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_
   if (slice == 0 && hk == 0 && tid == 0) advance_step(sqp, A.advance);
 }
 
-template <int D, int NW, bool SPLIT>
+template <int D, int NW, bool SPLIT, int R>
 hipError_t launch_gqa_w(const GqaArgs& A, int n_seq, int n_chunks, size_t lds, hipStream_t st, hipEvent_t ev_start,
                         hipEvent_t ev_stop) {
   dim3 grid(A.n_heads, n_seq, n_chunks);     // (lists that need more than 64 KB of LDS: see gqa_prepare_kernels)
   const int hgf = A.n_heads | (A.G << 16) | (A.append ? 1 << 24 : 0) | (A.new_f32 ? 1 << 25 : 0);
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, SPLIT ? nullptr : ev_stop, 0,
+    hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, SPLIT ? nullptr : ev_stop, 0,
                           A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
   else
-    hipLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT>), grid, dim3(NW * kWave), lds, st,
+    hipLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), lds, st,
                        A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
   if constexpr (SPLIT) {
     const hipError_t e = hipGetLastError();
@@ -595,9 +600,10 @@ hipError_t launch_gqa_w(const GqaArgs& A, int n_seq, int n_chunks, size_t lds, h
 template <int D>
 hipError_t launch_gqa_d(const GqaArgs& A, const AttendPlan& plan, int n_seq, size_t lds, hipStream_t st, hipEvent_t e0,
                         hipEvent_t e1) {
-  if (plan.n_chunks > 1) return launch_gqa_w<D, 4, true>(A, n_seq, plan.n_chunks, lds, st, e0, e1);     // split lists: 4 waves
-  if (plan.waves == 8) return launch_gqa_w<D, 8, false>(A, n_seq, 1, lds, st, e0, e1);
-  return launch_gqa_w<D, 4, false>(A, n_seq, 1, lds, st, e0, e1);
+  if (plan.n_chunks > 1) return launch_gqa_w<D, 4, true, ring(D)>(A, n_seq, plan.n_chunks, lds, st, e0, e1);     // split lists: 4 waves
+  if (plan.waves == 8) return launch_gqa_w<D, 8, false, ring(D)>(A, n_seq, 1, lds, st, e0, e1);
+  if (!gqa_two_fit(lds)) return launch_gqa_w<D, 4, false, deep_ring(D)>(A, n_seq, 1, lds, st, e0, e1);
+  return launch_gqa_w<D, 4, false, ring(D)>(A, n_seq, 1, lds, st, e0, e1);
 }
 
 }  // namespace
@@ -607,9 +613,10 @@ hipError_t launch_gqa_d(const GqaArgs& A, const AttendPlan& plan, int n_seq, siz
 hipError_t gqa_prepare_kernels() {
   const int lim = (int)kGqaMaxLds;
   const void* kernels[] = {
-      reinterpret_cast<const void*>(&k_attend_gqa<64, 4, false>), reinterpret_cast<const void*>(&k_attend_gqa<64, 8, false>),
-      reinterpret_cast<const void*>(&k_attend_gqa<128, 4, false>), reinterpret_cast<const void*>(&k_attend_gqa<128, 8, false>),
-      reinterpret_cast<const void*>(&k_attend_gqa<64, 4, true>), reinterpret_cast<const void*>(&k_attend_gqa<128, 4, true>)};
+      reinterpret_cast<const void*>(&k_attend_gqa<64, 4, false, ring(64)>), reinterpret_cast<const void*>(&k_attend_gqa<64, 8, false, ring(64)>),
+      reinterpret_cast<const void*>(&k_attend_gqa<128, 4, false, ring(128)>), reinterpret_cast<const void*>(&k_attend_gqa<128, 8, false, ring(128)>),
+      reinterpret_cast<const void*>(&k_attend_gqa<64, 4, false, deep_ring(64)>), reinterpret_cast<const void*>(&k_attend_gqa<128, 4, false, deep_ring(128)>),
+      reinterpret_cast<const void*>(&k_attend_gqa<64, 4, true, ring(64)>), reinterpret_cast<const void*>(&k_attend_gqa<128, 4, true, ring(128)>)};
   for (const void* k : kernels) {
     const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
     if (e != hipSuccess) return e;

@@ -222,3 +222,50 @@ def test_gqa_split_lists_of_ragged_lengths(G, h, D, layout):
             if rep == 1:
                 ref_score = oracle.accumulate(cfg, score0[b], sels[b], probs)
                 assert np.allclose(rank_host(batch)[b], ref_score, rtol=1e-5, atol=1e-6), n
+
+
+def _attend_in_64_bits(batch, q, sel, G):
+    """out [hq][D], lse [hq], probabilities [hq][n] of sequence 0 .. n_seq-1, one after the other."""
+    D = q.shape[-1]
+    K, V = (x if batch.head_major else x.transpose(1, 2) for x in (batch.K, batch.V))      # [n_seq][h][cap][D]
+    for b, idx in enumerate(sel):
+        idx = torch.from_numpy(idx.astype(np.int64)).to(DEV)
+        k, v = (x[b, :, idx].double().repeat_interleave(G, 0) for x in (K, V))
+        z = (k * q[b, :, None].double()).sum(-1) / D ** 0.5
+        p = torch.softmax(z, -1)
+        yield (p[:, :, None] * v).sum(1), torch.logsumexp(z, -1), p, idx
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("G,h,D,n_seq,cap", [
+    (16, 1, 128, 7, 1300), (16, 2, 64, 5, 1600), (4, 3, 128, 13, 4811),     # 4 waves and one workgroup per CU: the deeper ring
+    (8, 1, 128, 390, 400), (8, 1, 128, 390, 2336), (16, 1, 128, 390, 649)])  # many pairs: short lists, one workgroup, two of 4 waves
+def test_gqa_workgroup_shapes(G, h, D, n_seq, cap, layout):
+    """Every shape the launch rule picks, lists from one token to the capacity, against 64-bit sums."""
+    params = B.make_params(n_seq=n_seq, n_heads=h, head_dim=D, grid_h=100, grid_w=100, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
+                           cap=cap, layout=layout, score_mode=B.SCORE_ATTN_MASS, q_per_kv=G)
+    batch = LayerBatch(params, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(cap)
+    batch.K.normal_(generator=gen)
+    batch.V.normal_(generator=gen)
+    batch.score.uniform_(generator=gen)
+    q = torch.randn((n_seq, h * G, D), generator=gen, device=DEV).to(torch.bfloat16)
+    rng = np.random.default_rng(cap)
+    lens = rng.integers(1, cap + 1, n_seq)
+    lens[:5] = [1, 17, 130, cap - 1, cap]
+    sel = [np.sort(rng.choice(cap, n, replace=False)).astype(np.int32) for n in lens]
+    for b, s in enumerate(sel):
+        batch.sel_idx[b, :s.size] = torch.from_numpy(s).to(DEV)
+    batch.seqs_host["n_res"], batch.seqs_host["step"] = cap, 40
+    batch.upload_seqs()
+    batch.sel_cnt.copy_(torch.from_numpy(lens.astype(np.int32)))
+    old = batch.score.double()
+    batch.attend(q)
+    torch.cuda.synchronize()
+    for b, (out, lse, p, idx) in enumerate(_attend_in_64_bits(batch, q, sel, G)):
+        if b >= 40:
+            break
+        assert ((batch.out[b].double() - out).abs() <= 2.0 ** -8 * out.abs() + 1e-4).all(), (b, lens[b])       # one bf16 rounding
+        assert (batch.lse[b].double() - lse).abs().max() <= 1e-4, (b, lens[b])
+        old[b][:, idx] += p.view(h, G, -1).sum(1)
+        assert torch.allclose(batch.score[b].double(), old[b], rtol=1e-5, atol=1e-6), (b, lens[b])
