@@ -167,9 +167,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   static_assert(R <= 4, "16 lanes per tile");
   const int ld_row = lane / LPR, ld_piece = lane - ld_row * LPR;
   const int first_at = (wave + kg * NW) * 16 + r;            // list position of this lane's token
-  int slot_first = 0, slot_0 = 0, pf_slot[PF];
+  int slot_first = 0, pf_slot[PF];
   if constexpr (!SPLIT) {
-    slot_0 = idx[0];
     slot_first = idx[min(first_at, sel_cap - 1)];
 #pragma unroll
     for (int k = 0; k < PF; ++k) pf_slot[k] = idx[min(tid + k * T, sel_cap - 1)];
@@ -369,9 +368,15 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     const int n_mine = n_tiles > wave ? (n_tiles - wave + NW - 1) / NW : 0;
     const int n_trips = (n_mine + R - 1) / R;
     if constexpr (!SPLIT) {
-      // ... from the slots the first round trip brought in registers; the list is staged in LDS while the rows are on their way
-      // (positions past the end of the list may hold anything: they read the first token's row, which is attended)
-      slot_first = min(max(first_at < len ? slot_first : slot_0, 0), A.cap - 1);
+      // ... from the slots the first round trip brought in registers; the list is staged in LDS while the rows are on their way.
+      // Positions past the end of the list re-read the last token's row, as issue() does (0 times another row need not be 0: that
+      // row may hold an infinity the list's own sums do not meet there); a tile without a token reads some row and is not multiplied.
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        const int end = __builtin_amdgcn_readlane(slot_first, 16 * u + min(max(len - 1 - (wave + u * NW) * 16, 0), 15));
+        slot_first = kg == u && first_at >= len ? end : slot_first;
+      }
+      slot_first = min(max(slot_first, 0), A.cap - 1);
       int sk[R][LT], sv[R][4];
 #pragma unroll
       for (int u = 0; u < R; ++u) {

@@ -269,3 +269,33 @@ def test_gqa_workgroup_shapes(G, h, D, n_seq, cap, layout):
         assert (batch.lse[b].double() - lse).abs().max() <= 1e-4, (b, lens[b])
         old[b][:, idx] += p.view(h, G, -1).sum(1)
         assert torch.allclose(batch.score[b].double(), old[b], rtol=1e-5, atol=1e-6), (b, lens[b])
+
+
+@pytest.mark.parametrize("n", [5, 40, 127, 200])
+@pytest.mark.parametrize("D", [64, 128])
+def test_gqa_an_infinite_value_stays_in_its_column(D, n):
+    """V of the list's first token holds an infinity: its column is infinite for every query, the others are what they were.  The
+    lanes past the end of the list, whose probability is 0, must not multiply that row."""
+    h, G, cap = 2, 4, 256
+    params = B.make_params(n_seq=1, n_heads=h, head_dim=D, grid_h=100, grid_w=100, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
+                           cap=cap, score_mode=B.SCORE_ATTN_MASS, q_per_kv=G)
+    batch = LayerBatch(params, DEV)
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    batch.K.normal_(generator=gen)
+    batch.V.normal_(generator=gen)
+    q = torch.rand((1, h * G, D), generator=gen, device=DEV).to(torch.bfloat16)
+    batch.seqs_host["n_res"], batch.seqs_host["step"] = cap, 40
+    batch.upload_seqs()
+    sel = np.arange(3, 3 + n, dtype=np.int32)
+    batch.sel_idx[0, :n] = torch.from_numpy(sel).to(DEV)
+    batch.sel_cnt.fill_(n)
+    batch.V[0, 1, 3, 7] = float("inf")
+    batch.K[0, 1, 3], batch.K[0, 1, 4] = 0, 0.1              # not the likeliest token: a probability of exactly 1 has no low half,
+                                                             # and its product, 0 * inf, is not a number
+    batch.attend(q)
+    torch.cuda.synchronize()
+    out, _, p, _ = next(_attend_in_64_bits(batch, q, [sel], G))
+    got, hit = batch.out[0].double(), torch.zeros_like(out, dtype=torch.bool)
+    hit[G:, 7] = True
+    assert (got[hit] == float("inf")).all()
+    assert ((got - out)[~hit].abs() <= 2.0 ** -8 * out[~hit].abs() + 1e-4).all()
