@@ -73,10 +73,16 @@ hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx,
 hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction, char* ws,
                        const Workspace& w, hipStream_t st);
 int vcos_tiles(int cap);
+struct VcosPlan {
+  bool split;      // a workgroup of the first pass takes a part of 256 slots instead of all of them
+  int n_parts;     // partials of u per sequence
+  int tile;        // slots per workgroup of the second pass: 64, 128 or 256
+};
+VcosPlan make_vcos_plan(const adsa_params& p);
 // ADSA_SCORE_VCOS_FUSED, after the eviction plan: u <- u - evicted row + the row that turns candidate next step
 // (or a fresh sum when u does not belong to this step)
 hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t st);
-size_t vcos_advance_lds_bytes(const adsa_params& p);
+bool vcos_fused_fits(const adsa_params& p);
 hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
                          const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
                          void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
@@ -103,3 +109,13 @@ hipError_t gqa_prepare_kernels();
 hipError_t vcos_prepare_kernels();
 
 }  // namespace adsa
+
+// What the launch rules decide for parameters p, for tests that have to know which way a call goes (host only; not in adsa.h).
+extern "C" {
+struct adsa_launch_plan {
+  int32_t chunks, waves, heads;       // attention: chunks per list, waves and heads per workgroup
+  int32_t one_launch_eviction;        // adsa_step's row-end eviction is k_compact_step
+  int32_t vcos_split, vcos_tile;      // V-cosine passes
+};
+int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out);
+}

@@ -36,11 +36,11 @@ int validate_resolved(const adsa_params* p) {
   if (p->evict_policy < ADSA_EVICT_ROW_END || p->evict_policy > ADSA_EVICT_REUSE_SLOT) return ADSA_ERR_DTYPE;
   if (p->evict_policy != ADSA_EVICT_ROW_END && p->win_recent_m == 0) return ADSA_ERR_UNSUPPORTED;
   if (p->q_per_kv < 0 || p->q_per_kv > 16) return ADSA_ERR_SHAPE;
-  if (p->score_mode == ADSA_SCORE_VCOS_FUSED) {      // u lives in LDS four times; rows are per cache head
+  if (p->score_mode == ADSA_SCORE_VCOS_FUSED) {      // (rows are per cache head)
     if (p->evict_policy != ADSA_EVICT_REUSE_SLOT || !head_major || p->kv_slot_stride >= p->kv_head_stride ||
         p->q_per_kv > 1)
       return ADSA_ERR_UNSUPPORTED;
-    if (vcos_advance_lds_bytes(*p) > 64 * 1024) return ADSA_ERR_UNSUPPORTED;
+    if (!vcos_fused_fits(*p)) return ADSA_ERR_UNSUPPORTED;
     // m = 1: the token that turns candidate next step is not resident yet when the running sum is advanced
     if (p->win_recent_m < 2) return ADSA_ERR_UNSUPPORTED;
   }
@@ -356,6 +356,16 @@ int adsa_step_static(const adsa_params* p, adsa_seq* seqs, const void* q, const 
   // (the array keeps the previous call's contents: every kernel writes what a later one of the same call reads)
   return step_launches(p, plan, w, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, flags, sc->ptr,
                        reinterpret_cast<hipStream_t>(stream));
+}
+
+int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out) {
+  adsa_params eff;
+  const int rc = resolve_params(p, &eff);
+  if (rc) return rc;
+  const AttendPlan a = make_attend_plan(eff);
+  const VcosPlan v = make_vcos_plan(eff);
+  *out = {a.n_chunks, a.waves, a.heads, one_launch_compact(eff) ? 1 : 0, v.split ? 1 : 0, v.tile};
+  return ADSA_OK;
 }
 
 int adsa_profile_enable(int on) {

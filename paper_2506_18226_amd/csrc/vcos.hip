@@ -463,13 +463,33 @@ hipError_t with_row_shape(const adsa_params& p, F f) {
 
 }  // namespace
 
-// the LDS the fused form's bookkeeping may take: four copies of u and one byte per slot
-size_t vcos_advance_lds_bytes(const adsa_params& p) {
-  return sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves + (((size_t)p.cap + 15) / 16) * 16;
+int vcos_tiles(int cap) { return (cap + kVcTile - 1) / kVcTile; }
+
+VcosPlan make_vcos_plan(const adsa_params& p) {
+  // As large a tile as still gives every CU two workgroups: the second pass reads every partial of u in each workgroup
+  // (256 sequences x 692 slots: 154 us both passes with tiles of 256, 177 with 128; taking 128 or 64 sequences at a time so that
+  // the second pass finds them in the memory-side cache costs more in short launches than it saves: 192 and 256 us).
+  VcosPlan v;
+  v.tile = kVcGroup;
+  while (v.tile > kVcTile && (long long)p.n_seq * ((p.cap + v.tile - 1) / v.tile) < 512) v.tile /= 2;
+  // First pass: a workgroup per part for launches of few groups, where a workgroup per group leaves the chip short of rows in
+  // flight; whole groups write and read a quarter of the partials, which counts more the longer a row is.  Both passes, time of
+  // groups / time of parts over 120 random shapes, rows under 2 KB | longer ones: 100-200 groups 1.32 | 0.97, 200-350 1.16 | 1.00,
+  // 350-500 1.13 | 0.92, 640-800 1.05 | 1.00, 800-1200 1.01 | 0.93; 768 groups of 24 x 64 bf16 156 us | 170.
+  const int groups = (p.cap + kVcGroup - 1) / kVcGroup;
+  v.split = (long long)p.n_seq * groups < (p.n_heads * p.head_dim * elem_bytes(p) < 2048 ? 640 : 320);
+  v.n_parts = v.split ? vcos_tiles(p.cap) : groups;
+  return v;
+}
+
+// Which parameters ADSA_SCORE_VCOS_FUSED takes: those whose four sums of u and a byte per slot fit 64 KB.  A limit of the interface
+// (adsa.h states it), not what k_vcos_advance asks for: its sums, or its list of 8 KB, are always within it.
+bool vcos_fused_fits(const adsa_params& p) {
+  return sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves + (((size_t)p.cap + 15) / 16) * 16 <= 64 * 1024;
 }
 
 hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t st) {
-  if (vcos_advance_lds_bytes(p) > 64 * 1024) return hipErrorInvalidValue;
+  if (!vcos_fused_fits(p)) return hipErrorInvalidValue;
   AdvArgs A;
   A.seqs = seqs; A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
   A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius; A.recent_m = p.win_recent_m;
@@ -477,7 +497,7 @@ hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t
   A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
   return with_row_shape(p, [&](auto eb, auto g) {
     constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
-    if constexpr (G * 16 / EB <= 64) {                  // (longer rows: more than 64 KB of sums, refused above)
+    if constexpr (G * 16 / EB <= 64) {                  // (longer rows: refused above)
       const size_t list = 2 * sizeof(int) * kAdvRounds * kVcThreads, sums = sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves;
       hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), list > sums ? list : sums, st, A);
       return hipGetLastError();
@@ -495,18 +515,8 @@ hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction
   A.u_part = reinterpret_cast<float*>(ws + w.vcos_u_off);
   A.s_out = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<float*>(ws + w.vcos_s_off) : nullptr;
   A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
-  // As large a tile as still gives every CU two workgroups: the second pass reads every partial of u in each workgroup
-  // (256 sequences x 692 slots: 154 us both passes with tiles of 256, 177 with 128; taking 128 or 64 sequences at a time so that
-  // the second pass finds them in the memory-side cache costs more in short launches than it saves: 192 and 256 us).
-  A.tile = kVcGroup;
-  while (A.tile > kVcTile && (long long)p.n_seq * ((p.cap + A.tile - 1) / A.tile) < 512) A.tile /= 2;
-  // First pass: a workgroup per part for launches of few groups, where a workgroup per group leaves the chip short of rows in
-  // flight; whole groups write and read a quarter of the partials, which counts more the longer a row is.  Both passes, time of
-  // groups / time of parts over 120 random shapes, rows under 2 KB | longer ones: 100-200 groups 1.32 | 0.97, 200-350 1.16 | 1.00,
-  // 350-500 1.13 | 0.92, 640-800 1.05 | 1.00, 800-1200 1.01 | 0.93; 768 groups of 24 x 64 bf16 156 us | 170.
-  const int groups = (p.cap + kVcGroup - 1) / kVcGroup;
-  A.split = (long long)p.n_seq * groups < (dim * elem_bytes(p) < 2048 ? 640 : 320) ? 1 : 0;
-  A.n_parts = A.split ? vcos_tiles(p.cap) : groups;
+  const VcosPlan vp = make_vcos_plan(p);
+  A.tile = vp.tile; A.split = vp.split ? 1 : 0; A.n_parts = vp.n_parts;
   A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius;
   A.for_compaction = for_compaction ? 1 : 0; A.recent_m = p.win_recent_m; A.evict_policy = p.evict_policy;
   A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
@@ -522,8 +532,6 @@ hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction
     return hipGetLastError();
   });
 }
-
-int vcos_tiles(int cap) { return (cap + kVcTile - 1) / kVcTile; }
 
 // Rows of 4096 elements need 64 KB of dynamic LDS (4 waves' sums) beside the static words, rows of 8192 (the limit) 128 KB: more
 // than a launch may ask for by default.  Allowed here, once per device, at the library's first use of that device.

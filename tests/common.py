@@ -3,9 +3,12 @@ replay oracle trajectories.  The oracle (CPU) and the HIP binding are only ever 
 here and in the tests themselves."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 
 import oracle
+from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd import workloads as WL
 
 
@@ -73,6 +76,18 @@ def oracle_step_phases(cfg, st, s, q, k_new, v_new):
         pass  # compact() recomputed the V-cosine over the rest itself
     return {"out": out, "lse": lse, "sel_idx": sel, "keep_map": keep_map if did else None,
             "compacted": did, "n_res": st.n_res, "score_ranked": ranked}
+
+
+class LaunchPlan(C.Structure):
+    """What the library's launch rules decide for a parameter set (csrc/adsa_internal.h): tests ask for it where they claim to
+    take a certain way."""
+    _fields_ = [(n, C.c_int32) for n in ("chunks", "waves", "heads", "one_launch_eviction", "vcos_split", "vcos_tile")]
+
+
+def plan_of(params) -> LaunchPlan:
+    plan = LaunchPlan()
+    assert B.load_library().adsa_plan_of(C.byref(params), C.byref(plan)) == 0
+    return plan
 
 
 def rank_host(batch) -> np.ndarray:

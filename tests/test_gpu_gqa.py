@@ -13,7 +13,7 @@ from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd import workloads as WL
 from paper_2506_18226_amd.batch import LayerBatch, to_device, to_host
 
-from common import oracle_cfg, replay, rank_host
+from common import oracle_cfg, plan_of, replay, rank_host
 from test_gpu_parity import (DEV, LAYOUTS, params_for, load_state, check_out, lse_tol, _full_layer,
                              _check_full_step)
 
@@ -237,13 +237,14 @@ def _attend_in_64_bits(batch, q, sel, G):
 
 
 @pytest.mark.parametrize("layout", LAYOUTS)
-@pytest.mark.parametrize("G,h,D,n_seq,cap", [
-    (16, 1, 128, 7, 1300), (16, 2, 64, 5, 1600), (4, 3, 128, 13, 4811),     # 4 waves and one workgroup per CU: the deeper ring
-    (8, 1, 128, 390, 400), (8, 1, 128, 390, 2336), (16, 1, 128, 390, 649)])  # many pairs: short lists, one workgroup, two of 4 waves
-def test_gqa_workgroup_shapes(G, h, D, n_seq, cap, layout):
+@pytest.mark.parametrize("G,h,D,n_seq,cap,waves", [
+    (16, 1, 128, 7, 1300, 4), (16, 2, 64, 5, 1600, 4), (4, 3, 128, 13, 4811, 4),       # one workgroup per CU: the deeper ring
+    (8, 1, 128, 390, 400, 4), (8, 1, 128, 390, 2336, 8), (16, 1, 128, 390, 649, 4)])   # many pairs: short lists, one workgroup, two of 4 waves
+def test_gqa_workgroup_shapes(G, h, D, n_seq, cap, waves, layout):
     """Every shape the launch rule picks, lists from one token to the capacity, against 64-bit sums."""
     params = B.make_params(n_seq=n_seq, n_heads=h, head_dim=D, grid_h=100, grid_w=100, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
                            cap=cap, layout=layout, score_mode=B.SCORE_ATTN_MASS, q_per_kv=G)
+    assert plan_of(params).waves == waves and plan_of(params).chunks == 1
     batch = LayerBatch(params, DEV)
     gen = torch.Generator(device=DEV).manual_seed(cap)
     batch.K.normal_(generator=gen)

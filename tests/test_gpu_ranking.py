@@ -9,7 +9,7 @@ from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd import workloads as WL
 from paper_2506_18226_amd.batch import LayerBatch
 
-from common import oracle_cfg
+from common import oracle_cfg, plan_of
 from test_gpu_parity import DEV, load_state, params_for
 
 pytestmark = pytest.mark.gpu
@@ -74,7 +74,7 @@ def test_empty_sequences_touch_no_memory():
 @pytest.mark.parametrize("n_seq,h,D,dtype,cap,layout", [
     (1, 1, 64, "bf16", 70, "head_major"), (3, 4, 64, "f32", 257, "slot_major"), (2, 3, 128, "bf16", 513, "head_major"),
     (2, 2, 128, "f32", 800, "slot_major"), (1, 5, 64, "bf16", 1025, "head_major"), (16, 32, 64, "bf16", 90, "head_major"),
-    (17, 32, 64, "bf16", 90, "head_major"), (1, 2, 64, "bf16", 2049, "head_major")])      # (the last two: two launches)
+    (17, 32, 64, "bf16", 90, "head_major"), (1, 2, 64, "bf16", 2049, "head_major")])
 def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, layout):
     """adsa_step, whose eviction is one launch for small batches, against the split-phase calls on a copy of the same state: the
     sequences close a row, stand inside one, are inactive, rejected or empty; everything either of them writes is the same."""
@@ -99,6 +99,8 @@ def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, 
             if b == 7:
                 batch.seqs_host[b]["n_res"], batch.seqs_host[b]["step"] = 0, 0
     one, two = batches
+    # above 1024 workgroups and above 2048 slots adsa_step's eviction is the same two launches as adsa_compact's
+    assert plan_of(one.params).one_launch_eviction == (n_seq <= 16 and cap <= 2048)
     for batch in batches:
         batch.seqs_host["compacted"] = 1
         batch.upload_seqs()

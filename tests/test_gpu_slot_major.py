@@ -7,20 +7,22 @@ import torch
 from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd.batch import LayerBatch
 
+from common import plan_of
 from test_gpu_parity import DEV
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_seq,h,D,dtype,cap,new_f32,accumulate", [
-    (100, 16, 64, "bf16", 130, False, True),                 # 4 heads per workgroup, lists longer than a ring revolution
-    (200, 7, 64, "bf16", 128, True, True),                    # ... the second group of 4 has 3 heads
-    (97, 16, 64, "bf16", 2000, False, False),                # ... close to the LDS limit, no score update
-    (193, 4, 128, "bf16", 97, False, True), (130, 6, 64, "f32", 75, False, True),      # 2 heads per workgroup
-    (130, 7, 64, "f32", 64, False, True), (20, 16, 64, "bf16", 130, False, True)])     # (the last: one head per workgroup)
-def test_heads_that_share_a_workgroup(n_seq, h, D, dtype, cap, new_f32, accumulate):
+@pytest.mark.parametrize("n_seq,h,D,dtype,cap,new_f32,accumulate,heads", [
+    (100, 16, 64, "bf16", 130, False, True, 4),              # lists longer than a ring revolution
+    (200, 7, 64, "bf16", 128, True, True, 4),                # the second group of 4 has 3 heads
+    (97, 16, 64, "bf16", 2000, False, False, 4),             # close to the LDS limit, no score update
+    (193, 4, 128, "bf16", 97, False, True, 2), (130, 6, 64, "f32", 75, False, True, 2), (130, 7, 64, "f32", 64, False, True, 2),
+    (95, 16, 64, "bf16", 130, False, True, 1), (200, 7, 64, "bf16", 129, False, True, 1)])
+def test_heads_that_share_a_workgroup(n_seq, h, D, dtype, cap, new_f32, accumulate, heads):
     params = B.make_params(n_seq=n_seq, n_heads=h, head_dim=D, grid_h=100, grid_w=100, win_rows_back=1, win_col_radius=2,
                            dtype=B.F32 if dtype == "f32" else B.BF16, cap=cap, layout="slot_major", score_mode=B.SCORE_ATTN_MASS)
+    assert plan_of(params).heads == heads
     batch = LayerBatch(params, DEV)
     gen = torch.Generator(device=DEV).manual_seed(cap)
     for x in (batch.K, batch.V):

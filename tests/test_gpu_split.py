@@ -10,19 +10,20 @@ from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd import workloads as WL
 from paper_2506_18226_amd.batch import LayerBatch, to_device, to_host
 
-from common import oracle_cfg, rank_host
+from common import oracle_cfg, plan_of, rank_host
 from test_gpu_parity import DEV, check_out, lse_tol
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_heads,D,dtype,layout,fused,lens", [
-    (2, 128, "f32", "head_major", False, [1, 2, 15, 16, 17, 1023, 1024, 1100]),      # 16 chunks
-    (2, 64, "bf16", "slot_major", False, [3, 16, 33, 1025, 2048, 2049, 4100, 4200]),
-    (5, 128, "bf16", "slot_major", False, [1, 6, 7, 8, 511, 1024, 1025, 1500]),      # 7 chunks
-    (2, 128, "f32", "head_major", True, [1, 15, 16, 17, 1023, 1024, 1099, 1100]),    # |v|^2 and v.u rows of every chunk
+@pytest.mark.parametrize("n_heads,D,dtype,layout,fused,lens,chunks", [
+    (2, 128, "f32", "head_major", False, [1, 2, 15, 16, 17, 1023, 1024, 1100], 16),
+    (2, 64, "bf16", "slot_major", False, [3, 16, 33, 1025, 2048, 2049, 4100, 4200], 16),
+    (5, 128, "bf16", "slot_major", False, [1, 6, 7, 8, 511, 1024, 1025, 1500], 7),
+    (2, 128, "f32", "head_major", True, [1, 15, 16, 17, 1023, 1024, 1099, 1100], 16),    # |v|^2 and v.u rows of every chunk
+    (2, 128, "bf16", "head_major", True, [1, 4, 5, 6, 255, 256, 499, 500], 4),           # the fused form's earlier line
 ])
-def test_split_lists_and_their_merge(n_heads, D, dtype, layout, fused, lens):
+def test_split_lists_and_their_merge(n_heads, D, dtype, layout, fused, lens, chunks):
     n_tok, n_seq = max(lens), len(lens)
     wl = WL.get_workload("tiny", n_heads=n_heads, head_dim=D, grid_h=72, grid_w=72, prefix_len=8, dtype=dtype)
     rng = np.random.default_rng(7)
@@ -32,6 +33,7 @@ def test_split_lists_and_their_merge(n_heads, D, dtype, layout, fused, lens):
                            dtype=B.F32 if dtype == "f32" else B.BF16, cap=n_tok, layout=layout,
                            score_mode=B.SCORE_VCOS_FUSED if fused else B.SCORE_ATTN_MASS,
                            evict_policy=B.EVICT_REUSE_SLOT if fused else 0, win_recent_m=4 if fused else 0)
+    assert plan_of(params).chunks == chunks
     batch = LayerBatch(params, DEV)
     sels, score = [], rng.random((n_seq, n_tok)).astype(np.float32)
     for b, n in enumerate(lens):
@@ -71,9 +73,10 @@ def test_split_lists_and_their_merge(n_heads, D, dtype, layout, fused, lens):
 
 
 def test_timing_hook_counts_a_split_launch_once():
-    """A split launch is two kernels; the benchmark's hook reports it as one, from the start of the first to the end of the second."""
+    """A split launch is two kernels; the benchmark's hook counts it as one, with a time."""
     params = B.make_params(n_seq=1, n_heads=2, head_dim=64, grid_h=72, grid_w=72, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
                            score_mode=B.SCORE_ATTN_MASS, cap=4200)
+    assert plan_of(params).chunks > 1
     batch = LayerBatch(params, DEV)
     batch.seqs_host["n_res"], batch.seqs_host["step"] = 4200, 600
     batch.upload_seqs()

@@ -10,7 +10,7 @@ from paper_2506_18226_amd import binding as B
 from paper_2506_18226_amd import workloads as WL
 from paper_2506_18226_amd.batch import LayerBatch
 
-from common import oracle_cfg
+from common import oracle_cfg, plan_of
 from test_gpu_parity import DEV, LAYOUTS, params_for
 
 pytestmark = pytest.mark.gpu
@@ -105,9 +105,11 @@ def test_scores_do_not_depend_on_the_batch(h, D, dtype, cap, layout):
     lens = [cap - 1, cap // 2 + 1, cap - 40]
     vs = [rows(wl, rng, n) for n in lens]
     groups = (cap + 255) // 256
-    got = []
-    for n_seq in (3, 500 // groups, 600 // groups, 700 // groups):         # by parts with small tiles; tiles of 128 and 256; whole groups
+    got, ways = [], set()
+    for n_seq in (3, 500 // groups, 600 // groups, 700 // groups):
         batch = LayerBatch(params_for(wl, n_seq, cap, layout=layout), DEV)
+        plan = plan_of(batch.params)
+        ways.add((plan.vcos_split, plan.vcos_tile))
         batch.seqs_host["step"] = -1
         at = [0, n_seq // 2, n_seq - 1]
         for b, n, v in zip(at, lens, vs):
@@ -118,3 +120,4 @@ def test_scores_do_not_depend_on_the_batch(h, D, dtype, cap, layout):
         got.append(batch.score[at, 0].cpu())
         assert all(torch.count_nonzero(x) > 1 for x in got[-1])
     assert all(torch.equal(got[0], x) for x in got[1:])
+    assert {(1, 64), (0, 256)} < ways and (cap == 64 or any(tile == 128 for _, tile in ways))      # every way was taken
