@@ -76,7 +76,7 @@ typedef enum {
                                   kept up to date by adsa_compact: minus the evicted row, plus the row that
                                   leaves the local window next).  The next eviction ranks from those numbers.
                                   Needs [head][slot][D] caches, q_per_kv <= 1, win_recent_m >= 2 and
-                                  16*n_heads*head_dim + cap bytes of LDS <= 64 KB (else ADSA_ERR_UNSUPPORTED).  Whenever the running state
+                                  16*n_heads*head_dim + cap (rounded up to 16) <= 65536 (else ADSA_ERR_UNSUPPORTED).  Whenever the running state
                                   does not belong to the step at hand (first use, a cache edited by the
                                   caller) the call falls back to the two-pass computation, so results never
                                   depend on it being warm */
@@ -195,10 +195,9 @@ size_t adsa_workspace_bytes(const adsa_params* p);
 
 /*
  * Prepare a workspace (256-byte aligned, >= adsa_workspace_bytes(p)) for use with parameters p:
- * zeroes the words at its head with a small fill kernel on `stream`.  Call it once
- * after allocating the workspace and again before using the same memory with different
- * parameters.  A workspace may be shared by calls
- * that are ordered on one stream, not by concurrent ones.
+ * checks the arguments and zeroes the words at its head with a small fill kernel on `stream`.  No result depends on
+ * those words or on any other content of the memory (every call writes what its kernels read), so the call may be
+ * left out.  A workspace may be shared by calls that are ordered on one stream, not by concurrent ones.
  */
 int adsa_workspace_init(const adsa_params* p, void* workspace, size_t workspace_bytes, void* stream);
 
