@@ -586,7 +586,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
 template <int EB, int D, int HT, int NW, bool VF, bool DIRECT>
 hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
-  // row pairs in flight per lane: 2, 3, 6 and 8 were measured no faster on 4- and 8-wave workgroups
+  // Row pairs in flight per lane.  us with 2 | 3 | 4 | 6 | 8, bf16: 768 pairs x 647 tokens x 64 22.6 | 22.2 | 22.3 | 22.8 | 23.3; 128 x
+  // 1159 x 128 19.4 | 17.5 | 17.6 | 18.0 | 19.1; 40 x 427 x 64 5.8 | 5.8 | 5.6 | 7.0 | 6.4; fp32 63 x 433 x 128 13.0 | 11.3 | 11.5 | 12.2 |
+  // 13.1; only 320 x 427 x 64, whose lists fill 3.3 revolutions of 4, is better off with 3: 9.9 | 9.6 | 10.2 | 11.4 | 11.3.
   constexpr int U = 4;
   const size_t lds = (size_t)((VF ? 2 : HT) + 1) * plan.chunk_max * sizeof(float);      // logits rows + the slot list
   dim3 grid(plan.n_chunks, (A.n_heads + HT - 1) / HT, n_seq);
