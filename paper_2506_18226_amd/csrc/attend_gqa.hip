@@ -19,7 +19,7 @@
 //            contraction runs over tokens).  P is split into two bf16 halves (hi + lo) so that the
 //            product carries ~16 mantissa bits of the probabilities.  When a query's running maximum
 //            m[g] grows, the accumulators are rescaled (factors fetched across lanes).
-//    Each wave keeps one or two tiles in flight: it waits for the OLDEST tile's K rows only (in-order wait
+//    Each wave keeps one to four tiles (R) in flight: it waits for the OLDEST tile's K rows only (in-order wait
 //    counts; a tile is always requested as its K loads followed by its V loads, with no branch in between),
 //    multiplies it and refills its registers with the tile one ring revolution later.  Loads take a uniform base
 //    and a 32-bit lane offset; the query token's own slot is read like any other and replaced from registers.

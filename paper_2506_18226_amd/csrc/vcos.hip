@@ -37,7 +37,7 @@ constexpr int kVcWaves = kVcThreads / kWave;
 constexpr int kVcTile = 64;                 // slots per partial of u the workspace has room for
 constexpr int kVcGroup = kVcThreads;        // slots that are listed and summed together
 constexpr int kVcParts = kVcGroup / kVcTile, kVcPartRuns = 4;
-static_assert(kVcWaves == kVcParts && kVcWaves == kVcPartRuns, "a wave per part or per class");
+static_assert(kVcWaves == kVcParts && kVcWaves == kVcPartRuns, "a wave per part or per run");
 constexpr int kVcMaxDim = 8192;             // n_heads * head_dim limit
 
 struct VcosArgs {
