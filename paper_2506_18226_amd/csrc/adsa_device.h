@@ -37,20 +37,20 @@ __device__ __forceinline__ void store_stream16(gchar* p, const uint4& x) {
   __builtin_nontemporal_store(v, reinterpret_cast<ADSA_GLOBAL u32x4*>(p));
 }
 
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;   // NaN stays NaN
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+// Round to the nearest bf16, ties to even (v_cvt_pk_bf16_f32; subnormals are kept, a NaN stays one)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
+  const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+  return __builtin_bit_cast(uint32_t, v);
 }
+__device__ __forceinline__ uint32_t f32_to_bf16_rne(float x) { return pack2_bf16(x, 0.0f) & 0xFFFFu; }
 
-// 8 consecutive fp32 values -> 8 bf16 (round to nearest even) in one 16-byte vector
-__device__ __forceinline__ uint4 pack8_bf16(const gchar* f) {
-  const uint4 ua = load16(f), ub = load16(f + 16);
-  const float4 a = make_float4(__uint_as_float(ua.x), __uint_as_float(ua.y), __uint_as_float(ua.z), __uint_as_float(ua.w));
-  const float4 b = make_float4(__uint_as_float(ub.x), __uint_as_float(ub.y), __uint_as_float(ub.z), __uint_as_float(ub.w));
-  return make_uint4(f32_to_bf16_rne(a.x) | (f32_to_bf16_rne(a.y) << 16), f32_to_bf16_rne(a.z) | (f32_to_bf16_rne(a.w) << 16),
-                    f32_to_bf16_rne(b.x) | (f32_to_bf16_rne(b.y) << 16), f32_to_bf16_rne(b.z) | (f32_to_bf16_rne(b.w) << 16));
+// 8 consecutive fp32 values, as two 16-byte vectors -> 8 bf16 in one
+__device__ __forceinline__ uint4 pack8_bf16(const uint4& a, const uint4& b) {
+  return make_uint4(pack2_bf16(__uint_as_float(a.x), __uint_as_float(a.y)), pack2_bf16(__uint_as_float(a.z), __uint_as_float(a.w)),
+                    pack2_bf16(__uint_as_float(b.x), __uint_as_float(b.y)), pack2_bf16(__uint_as_float(b.z), __uint_as_float(b.w)));
 }
+__device__ __forceinline__ uint4 pack8_bf16(const gchar* f) { return pack8_bf16(load16(f), load16(f + 16)); }
 
 // The record at the end of an attention launch (one thread per sequence); see kAdvance.
 __device__ __forceinline__ void advance_step(ADSA_GLOBAL adsa_seq* sq, int mode) {

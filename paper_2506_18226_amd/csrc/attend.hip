@@ -21,6 +21,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "adsa_internal.h"
 #include "adsa_device.h"
@@ -38,27 +39,63 @@ __device__ __forceinline__ float row_sum(float x) {
   x += dpp_f<0x4E>(x);            // quad_perm [2,3,0,1]
   x += dpp_f<0x141>(x);           // row_half_mirror: the other quad of the 8-lane group
   if (LPR >= 16) x += dpp_f<0x140>(x);   // row_mirror: the other half of the 16-lane row
-  if (LPR >= 32) x += __shfl_xor(x, 16, kWave);
+  if (LPR >= 32) x = xor_sum<16>(x);
   return x;
 }
 
+// 16 bytes of a row as fp32 values, and their dot product with the lane's piece of q.  bf16: two products per instruction
+// (v_dot2, fp32 sums), so q stays as it arrived and the softmax scale is applied to the sum; fp32: q is scaled beforehand.
 template <int EB> struct Elems;
 template <> struct Elems<2> {      // bf16: 8 values per 16-byte vector
   static constexpr int N = 8;
+  uint32_t q[4];
+  __device__ __forceinline__ Elems(const uint4& r, float) : q{r.x, r.y, r.z, r.w} {}
   static __device__ __forceinline__ void unpack(const uint4& r, float* f) {
     f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xFFFF0000u);
     f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xFFFF0000u);
     f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xFFFF0000u);
     f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xFFFF0000u);
   }
+  __device__ __forceinline__ float dot(const uint4& r) const {
+    const uint32_t k[4] = {r.x, r.y, r.z, r.w};
+    float d = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[i]), __builtin_bit_cast(bf16x2, k[i]), d, false);
+    return d;
+  }
+  static __device__ __forceinline__ float scaled(float d, float scale) { return d * scale; }
 };
 template <> struct Elems<4> {      // fp32: 4 values per 16-byte vector
   static constexpr int N = 4;
+  float q[4];
+  __device__ __forceinline__ Elems(const uint4& r, float scale) {
+    unpack(r, q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] *= scale;
+  }
   static __device__ __forceinline__ void unpack(const uint4& r, float* f) {
     f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y);
     f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
   }
+  __device__ __forceinline__ float dot(const uint4& r) const {
+    float k[4], d = 0.0f;
+    unpack(r, k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d = fmaf(q[i], k[i], d);
+    return d;
+  }
+  static __device__ __forceinline__ float scaled(float d, float) { return d; }
 };
+
+// max(a, b, c) of which none is a signalling NaN (fmaxf would first quiet each of them)
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+constexpr float kLowest = -3.4028234663852886e38f;     // the running maximum of a state that has seen no token: z - kLowest is never NaN
+
+__device__ __forceinline__ int slot_of(int entry) { return entry < 0 ? ~entry : entry; }
 
 constexpr int kBurst = 512;        // bytes of a token that a workgroup of several heads takes
 
@@ -82,6 +119,7 @@ struct AttendArgs {
   int new_f32;                         // k_new / v_new are fp32 although the cache is bf16: round as they enter
   int vcos_fused;
   long long slot_stride_b, head_stride_b;
+  uint32_t stride24;    // slot_stride_b where a head's rows can be reached with 32-bit offsets (see launch_attend), else 0
   float scale_log2;     // softmax scale * log2(e)
 };
 
@@ -90,7 +128,7 @@ struct AttendArgs {
 // arguments to be preloaded into scalar registers at wave launch, so those loads can leave at once, without
 // waiting for a scalar load of the argument block (which would also wait for the sequence record's).
 // HT > 1: the workgroup takes HT heads, the lane groups of a wave-load being the HT heads of RPW / HT tokens.
-template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT>
+template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE>
 __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
                                                       const char* q_arg, const char* k_new_arg, const char* v_new_arg,
                                                       int heads_and_flags, int sel_cap_arg, AttendArgs A) {
@@ -99,9 +137,11 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   constexpr int LPR = D / EPL;                      // lanes per row
   constexpr int RPW = kWave / LPR / HT;             // tokens per wave-load
   static_assert(HT == 1 || (DIRECT && !VF && RPW * HT * LPR == kWave), "several heads: whole lists only");
-  constexpr int PF = 1024 / kAttThreads;            // score read-modify-writes a thread starts early
-  extern __shared__ float s_logit[];                // logits [HT][chunk_max] ([2][chunk_max] for VF), then
-                                                    // the chunk's slot list int [chunk_max]
+  constexpr int PF = 4;                             // list entries a thread fetches, and score read-modify-writes it starts, early
+  constexpr int kRev = NW * U * RPW;                // tokens of one ring revolution of the workgroup
+  extern __shared__ float s_logit[];                // logits [HT][chunk_max] ([2][chunk_max] for VF; the last word of a row takes what
+                                                    // belongs to no token), then the chunk's slot list, see s_ent
+  __shared__ int s_new[NW];
   // merge: the lane groups of a wave meet in registers, the waves through these (one state per wave)
   __shared__ float s_wm[NW * HT], s_wl[NW * HT];
   __shared__ __attribute__((aligned(16))) float s_wacc[NW * HT * D];
@@ -127,46 +167,46 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   gfloat* const score = (gfloat*)sqp->score;
   const int pending = sqp->pending_slot;
   gfloat* const u_state = VF ? (gfloat*)sqp->vcos_u : nullptr;
+  __builtin_amdgcn_sched_barrier(0);                // (the scalar loads leave first: the rows need them and the first slots)
   const gint* idx = (const gint*)sel_idx_arg + (size_t)b * sel_cap;
   const size_t row_off = ((size_t)b * n_heads + head) * D * EB + dl * 16;
-  const gchar* const q_g = (const gchar*)q_arg;
-  const gchar* const k_new_g = (const gchar*)k_new_arg;
-  const gchar* const v_new_g = (const gchar*)v_new_arg;
   gchar* const out_g = (gchar*)A.out;
   gfloat* const lse_g = (gfloat*)A.lse;
-  const uint4 qr = load16(q_g + row_off);
   // The wave takes the RPW-token units wave, wave + NW, ... of the chunk, in that order; unit number k of the
-  // wave holds, for this lane, token (wave + k * NW) * RPW + ts.  slot_a[u]: slot of unit u; slot_nx[u]: of the unit
-  // that takes ring position u next.  pf_slot: the whole list (its first PF * threads entries), one entry per
-  // thread and round: staged in LDS below so that the loop finds its slots there instead of in global memory.
+  // wave holds, for this lane, token (wave + k * NW) * RPW + ts.  slot_a[u]: slot of unit u.  pf_slot: the whole list
+  // (its first PF * threads entries), one entry per thread and round: staged in LDS below, where the loop finds its slots.
   // (These loads need nothing but preloaded arguments: they leave before anything waits for a scalar load.)
-  int slot_a[U], slot_nx[U];
+  int slot_a[U];
   int pf_slot[PF];
+  // (through a buffer descriptor of the list: entries past its end are not read and come back as 0, without a clamp each)
+  const auto list = __builtin_amdgcn_make_buffer_rsrc((void*)(const int32_t*)idx, 0, sel_cap * 4, 0x00027000);
+  auto entry = [&](int lane_at, int uniform_at) { return (int)__builtin_amdgcn_raw_buffer_load_b32(list, lane_at * 4, uniform_at * 4, 0); };
+  const int unit0 = wave * RPW + ts;                // this lane's token of the wave's first unit
   if constexpr (DIRECT) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot_a[u] = idx[min((wave + u * NW) * RPW + ts, sel_cap - 1)];
+    for (int u = 0; u < U; ++u) slot_a[u] = entry(unit0, u * NW * RPW);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < PF; ++k) pf_slot[k] = idx[min(tid + k * kAttThreads, sel_cap - 1)];
+    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, k * kAttThreads);
   }
-  // the query token's own K/V row (Section 4.2 append), as this launch attends and stores it: every lane keeps
-  // its 16-byte piece in registers; fp32 rows of a bf16 cache are rounded once, here
-  const bool append = (heads_and_flags & 0x10000) != 0, new_f32 = (heads_and_flags & 0x20000) != 0;
-  uint4 nk = make_uint4(0u, 0u, 0u, 0u), nv = nk;
-  if (append) {
-    if (EB == 2 && new_f32) {
-      const size_t off32 = ((size_t)b * n_heads + head) * D * 4 + dl * 32;
-      nk = pack8_bf16(k_new_g + off32);
-      nv = pack8_bf16(v_new_g + off32);
-    } else {
-      nk = load16(k_new_g + row_off);
-      nv = load16(v_new_g + row_off);
-    }
+  const uint4 qr = load16((const gchar*)q_arg + row_off);
+  // the query token's own K/V row (Section 4.2 append): the first wave attends and stores it, 16 bytes of K and V per lane.
+  // fp32 rows of a bf16 cache (twice as many bytes) are rounded once, when they are used
+  const bool append = (heads_and_flags & 0x10000) != 0, new_f32 = EB == 2 && (heads_and_flags & 0x20000) != 0;
+  uint4 nk[4 / EB], nv[4 / EB];
+  if (append && wave == 0) {
+    const gchar* const k_new_g = (const gchar*)k_new_arg + (new_f32 ? 2 * row_off : row_off);
+    const gchar* const v_new_g = (const gchar*)v_new_arg + (new_f32 ? 2 * row_off : row_off);
+    nk[0] = load16(k_new_g);
+    nv[0] = load16(v_new_g);
+    if constexpr (EB == 2)
+      if (new_f32) { nk[1] = load16(k_new_g + 16); nv[1] = load16(v_new_g + 16); }
   }
   pin_uniform(cnt_raw); pin_uniform(k_base); pin_uniform(v_base); pin_uniform(score); pin_uniform(pending);
   if constexpr (VF) pin_uniform(u_state);
   // (the remaining arguments the loop needs: fetched in the same batch of scalar loads, not after it)
   pin_uniform(A.cap); pin_uniform(A.chunk_max); pin_uniform(A.slot_stride_b); pin_uniform(A.head_stride_b);
-  pin_uniform(A.scale_log2); pin_uniform(A.accumulate);
+  pin_uniform(A.scale_log2); pin_uniform(A.accumulate); pin_uniform(A.stride24);
 
   const int cnt = min(cnt_raw, sel_cap);
   if (cnt <= 0) {                                   // inactive or rejected sequence: zero-filled row
@@ -185,22 +225,24 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   const int t_end = DIRECT ? cnt : chunk_begin(cnt, chunk + 1, n_chunks);
   if (t_begin >= t_end) return;                     // fewer tokens than chunks
   const int len = t_end - t_begin;
-  int* const s_idx = reinterpret_cast<int*>(s_logit + (VF ? 2 : HT) * A.chunk_max);   // the chunk's slot list (filled below)
+  // The chunk's slot list, one entry per token (filled below): the slot, or ~slot for the query token's own; then entries of no
+  // token, ~0, up to one revolution past the last unit.  A negative entry is not attended in the loop.
+  int* const s_ent = reinterpret_cast<int*>(s_logit + (VF ? 2 : HT) * A.chunk_max);
   if constexpr (!DIRECT) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot_a[u] = idx[t_begin + min((wave + u * NW) * RPW + ts, len - 1)];
+    for (int u = 0; u < U; ++u) slot_a[u] = entry(unit0, t_begin + u * NW * RPW);
+#pragma unroll
+    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, t_begin + k * kAttThreads);
   }
   // the slot adsa_select reserved for the query token (Section 4.2 append), if this launch fills it
   const int new_slot = (append && pending < A.cap) ? pending : -1;
 
-  float pf_old[PF];
-  float qf[EPL];
-  Elems<EB>::unpack(qr, qf);
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) qf[e] *= A.scale_log2;
+  const int cap = A.cap, dump = A.chunk_max - 1;
+  const float scale_log2 = A.scale_log2;
+  const Elems<EB> qv(qr, scale_log2);
   const long long lane_off = (long long)head * A.head_stride_b + dl * 16;
-  gchar* kb = k_base + lane_off;
-  gchar* vb = v_base + lane_off;
+  gchar* const kb = k_base + lane_off;
+  gchar* const vb = v_base + lane_off;
   // VF: this lane's columns of u for its head, and the two score rows of the head
   float uf[EPL];
   gfloat* vrows = nullptr;
@@ -212,162 +254,246 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     vrows = score + (size_t)(2 * head) * A.cap;
   }
 
-  float m = -INFINITY, l = 0.0f, acc[EPL];
+  float pf_old[PF];
+  float m = kLowest, l = 0.0f, acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.0f;
 
-  // Rolling gather: U units (row pairs per lane) are in flight per wave; as soon as the oldest has arrived it is
-  // folded into the lane's online-softmax state and its registers are given to the next unit's loads, so the
-  // number of outstanding requests stays constant instead of draining once per batch.
+  // Rolling gather: U units (row pairs per lane) are in flight per wave.  Two units at a time are folded into the lane's
+  // online-softmax state, which is brought to a new maximum once for both; a register quad is given to the load one
+  // revolution ahead as soon as its contents are used (the K quads after the dot products, the V quads after the sums), so the
+  // number of outstanding requests stays nearly constant instead of draining once per batch.
+  // Small launches are bound by what this loop issues: 40 lists of 427 x 64 on 8 waves each keep a SIMD with 2 waves busy for
+  // all of the 2.7 us between the slot list and the merge when a unit takes 102 issue slots (one unit at a time: a rescale per
+  // unit, products of 64 bits for addresses, q.k on unpacked values, selects of the query token's row).  It takes 50 now, and
+  // the launch 4.9 us instead of 5.6; 320 lists x 427 x 64 9.3 | 10.2, 768 x 647 x 64, which HBM bounds, 21.5 | 22.2.
   {
+    uint4 kr[U], vr[U];
+    int ent[U], nxt[U];                             // entries of the units in flight at the ring positions; of those that take them next
     const int n_units = (len + RPW - 1) / RPW;
     const int n_mine = n_units > wave ? (n_units - wave + NW - 1) / NW : 0;       // units of this wave
-    uint4 kr[U], vr[U];
-    int tok[U];                                     // token (chunk-relative) in flight at ring position u; >= len: none
-    bool fresh[U];                                  // ring position u stands for the query token's own row
-#pragma unroll
-    for (int u = 0; u < U; ++u) { kr[u] = make_uint4(0u, 0u, 0u, 0u); vr[u] = kr[u]; tok[u] = len; fresh[u] = false; }
-    auto issue = [&](int u, int slot_raw, int token) {
-      const int slot = min(max(slot_raw, 0), A.cap - 1);      // never touch memory outside the cache
-      const long long off = (long long)slot * A.slot_stride_b;
-      const bool is_new = slot == new_slot;         // the query token itself: its row is in registers (nk, nv)
-      const bool live = token < len && !is_new;     // else (also past the end of the chunk) re-read q's row: cached
-      kr[u] = load_stream16(live ? kb + off : q_g + row_off);
-      vr[u] = load_stream16(live ? vb + off : q_g + row_off);
-      tok[u] = token;
-      fresh[u] = is_new;
-    };
-    auto fold = [&](int u) {
-      const bool on = tok[u] < len;
-      const uint4 kx = fresh[u] ? nk : kr[u], vx = fresh[u] ? nv : vr[u];
-      float kf[EPL];
-      Elems<EB>::unpack(kx, kf);
-      float d = 0.0f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-      d = row_sum<LPR>(d);
-      const float z = on ? d : -INFINITY;
-      if (A.accumulate && dl == 0 && on) s_logit[hs * A.chunk_max + tok[u]] = z;
-      const float m_new = fmaxf(m, z);
-      const float corr = (m == -INFINITY) ? 0.0f : fast_exp2(m - m_new);     // (l and acc are 0 while m is -inf)
-      const float pr = on ? fast_exp2(z - m_new) : 0.0f;
-      float vf[EPL];
-      Elems<EB>::unpack(vx, vf);
-      l = fmaf(l, corr, pr);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(acc[e], corr, pr * vf[e]);
-      m = m_new;
-      if constexpr (VF) {                           // Eq. 2-3 bookkeeping of this row: |v_h|^2 and v_h . u_h
-        float dv = 0.0f, sv = 0.0f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) { dv = fmaf(vf[e], uf[e], dv); sv = fmaf(vf[e], vf[e], sv); }
-        dv = row_sum<LPR>(dv);
-        sv = row_sum<LPR>(sv);
-        if (dl == 0 && on) { s_logit[tok[u]] = sv; s_logit[A.chunk_max + tok[u]] = dv; }
-      }
-      // the state is demanded HERE, and no memory access may cross: the unit is folded completely before the
-      // loads that reuse its ring position are issued, and no later unit's arithmetic is pulled in front of it
-      // (left to itself the compiler gathers all the logits of a trip first and so waits for the whole ring)
-      static_assert(EPL == 4 || EPL == 8, "elements per lane");
-      if constexpr (EPL == 8)
-        asm volatile("" : "+v"(m), "+v"(l), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]),
-                     "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]) : : "memory");
-      else
-        asm volatile("" : "+v"(m), "+v"(l), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : : "memory");
-    };
-    // unit k of the wave lives at ring position k % U: units 0 .. U-1 are requested here, trip t folds units
-    // tU .. tU+U-1 and requests the units one ring revolution later, the last trip only folds.  (Units past
-    // the wave's last one re-read the q row, which is cached by then.)
-    auto refill = [&](int u, int k, int slot_raw) { // ring position u <- unit k; fetch the slot of unit k + U
-      const int token = (wave + k * NW) * RPW + ts;
-      issue(u, slot_raw, token);
-      slot_nx[u] = s_idx[min(token + U * NW * RPW, len - 1)];
-      asm volatile("" : : : "memory");             // requests leave in ring order (the wait counts rely on it)
-      __builtin_amdgcn_sched_barrier(0);            // ... and before the next unit's arithmetic, which waits for ITS rows
-    };
     const int n_trips = (n_mine + U - 1) / U;
-    // The first revolution's rows are requested at once, from the slots the first round trip brought in registers ...
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      issue(u, slot_a[u], (wave + u * NW) * RPW + ts);
+    // Requests leave in the order the program has them (the wait counts rely on it), and before the arithmetic that follows.
+    auto in_order = [] {
       asm volatile("" : : : "memory");
       __builtin_amdgcn_sched_barrier(0);
-    }
-    // ... and while they are on their way the chunk's slot list goes to LDS (clamped to the cache: nothing below
-    // ever leaves it), where the later revolutions and the score update find it
-    if constexpr (DIRECT) {
+    };
+    // Entries that are not attended read slot 0 (valid memory, one row for all of them) and are masked when they are folded.
+    const gchar* const ku = k_base + (long long)head0 * A.head_stride_b;        // uniform
+    const gchar* const vu = v_base + (long long)head0 * A.head_stride_b;
+    const uint32_t lane32 = (uint32_t)(head - head0) * (uint32_t)A.head_stride_b + (uint32_t)dl * 16u, stride24 = A.stride24;
+    const long long stride_b = A.slot_stride_b;
+    auto load = [&](const gchar* uni, const gchar* own, int e) -> uint4 {
+      const int slot = max(e, 0);
+      if constexpr (!WIDE) return load_stream16(uni + (__umul24((uint32_t)slot, stride24) + lane32));
+      else return load_stream16(own + (long long)slot * stride_b);
+    };
+    // prologue: the pattern of a steady-state trip, so that the loop's wait counts match
 #pragma unroll
-      for (int k = 0; k < PF; ++k) {
-        const int j = tid + k * kAttThreads;
-        if (j < len) s_idx[j] = min(max(pf_slot[k], 0), A.cap - 1);
+    for (int u = 0; u < U; u += 2) {
+#pragma unroll
+      for (int i = u; i < u + 2; ++i) {
+        const int slot = min(max(slot_a[i], 0), cap - 1);        // never touch memory outside the cache
+        ent[i] = unit0 + i * NW * RPW < len && slot != new_slot ? slot : ~slot;
       }
-      for (int j = tid + PF * kAttThreads; j < len; j += kAttThreads) s_idx[j] = min(max(idx[j], 0), A.cap - 1);
-    } else {
-      for (int j = tid; j < len; j += kAttThreads) s_idx[j] = min(max(idx[t_begin + j], 0), A.cap - 1);
+      kr[u] = load(ku, kb, ent[u]);
+      kr[u + 1] = load(ku, kb, ent[u + 1]);
+      in_order();
+      vr[u] = load(vu, vb, ent[u]);
+      vr[u + 1] = load(vu, vb, ent[u + 1]);
+      in_order();
+    }
+    // ... and while these rows are on their way the chunk's slot list goes to LDS
+    const int n_ent = ((len + kRev - 1) / kRev + 1) * kRev;
+    int new_at = 0;                               // 1 + list position of the query token's slot, if this thread stages it
+    auto stage = [&](int j, int raw) {
+      const int slot = min(max(raw, 0), cap - 1);
+      const bool own = slot == new_slot && j < len;
+      s_ent[j] = j >= len ? ~0 : own ? ~slot : slot;
+      new_at = own ? j + 1 : new_at;
+    };
+#pragma unroll
+    for (int k = 0; k < PF; ++k)
+      if (k * kAttThreads < n_ent) {                // (uniform; n_ent is a multiple of the revolution, not of the threads)
+        const int j = tid + k * kAttThreads;
+        pf_slot[k] = min(max(pf_slot[k], 0), cap - 1);
+        if (j < n_ent) stage(j, pf_slot[k]);
+      }
+    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, entry(j, t_begin));
+    if (new_slot >= 0) {                          // (uniform)
+      const unsigned long long who = __ballot(new_at != 0);
+      const int at = who ? __builtin_amdgcn_readlane(new_at, __ffsll((long long)who) - 1) : 0;
+      if (lane == 0) s_new[wave] = at;
     }
     __syncthreads();
     // thread i of the final score update serves tokens i, i + threads, ...; start the first PF reads now
     if (DIRECT && HT == 1 && A.accumulate) {
 #pragma unroll
       for (int k = 0; k < PF; ++k) {
-        const int i = tid + k * kAttThreads;
         pf_old[k] = 0.0f;
-        if (i < len) {
-          pf_slot[k] = s_idx[i];
-          pf_old[k] = score[(size_t)head * A.cap + pf_slot[k]];
+        if (k * kAttThreads < len) pf_old[k] = *(const gfloat*)((const gchar*)(score + (size_t)head * cap) + (uint32_t)pf_slot[k] * 4u);
+      }
+    }
+    // Section 4.2: the query token's row enters the cache, and, if its slot is in the list, one lane group (per head) of the
+    // first wave starts its state with it, from the registers that hold it (no lane reads that row from memory)
+    if (new_slot >= 0 && wave == 0) {
+      if constexpr (EB == 2)
+        if (new_f32) {
+          // (converted here, not where the compiler would like to: next to the loads, whose return it would wait for)
+          asm volatile("" : "+v"(nk[1].x), "+v"(nk[1].y), "+v"(nk[1].z), "+v"(nk[1].w), "+v"(nv[1].x), "+v"(nv[1].y), "+v"(nv[1].z), "+v"(nv[1].w));
+          nk[0] = pack8_bf16(nk[0], nk[1]);
+          nv[0] = pack8_bf16(nv[0], nv[1]);
+        }
+      int at = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) at = max(at, s_new[w]);
+      const bool mine = ts == 0;
+      if (mine && hs < heads_here && chunk == n_chunks - 1) {
+        const long long off = (long long)new_slot * stride_b;
+        store16(kb + off, nk[0]);
+        store16(vb + off, nv[0]);
+      }
+      if (at > 0) {
+        float z = Elems<EB>::scaled(row_sum<LPR>(qv.dot(nk[0])), scale_log2), vf[EPL];
+        Elems<EB>::unpack(nv[0], vf);
+        m = mine ? z : m;
+        l = mine ? 1.0f : 0.0f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = mine ? vf[e] : 0.0f;
+        if constexpr (VF) {
+          float dv = 0.0f, sv = 0.0f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) { dv = fmaf(vf[e], uf[e], dv); sv = fmaf(vf[e], vf[e], sv); }
+          dv = row_sum<LPR>(dv);
+          sv = row_sum<LPR>(sv);
+          if (mine) { s_logit[at - 1] = sv; s_logit[A.chunk_max + at - 1] = dv; }
+        } else {
+          if (mine) s_logit[hs * A.chunk_max + at - 1] = z;
         }
       }
     }
+    const int* next = s_ent + (wave + U * NW) * RPW + ts;    // entries of the units one revolution ahead
+    float* zpos = s_logit + (VF ? 0 : hs * A.chunk_max) + wave * RPW + ts;
+    float* const zdump = s_logit + (VF ? 0 : hs * A.chunk_max) + dump;
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot_nx[u] = s_idx[min((wave + (u + U) * NW) * RPW + ts, len - 1)];
-    asm volatile("" : : : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    int k_next = U;
+    for (int u = 0; u < U; ++u) nxt[u] = next[u * NW * RPW];
+    in_order();
+
+    // units u and u + 1 of the ring; refill: their registers go to the units one revolution ahead
+    auto fold = [&](int u, auto refill) {
+      constexpr bool kRefill = decltype(refill)::value;
+      const int ea = ent[u], eb = ent[u + 1];
+      float da = qv.dot(kr[u]), db = qv.dot(kr[u + 1]);
+      asm volatile("" : "+v"(da), "+v"(db) : : "memory");
+      if constexpr (kRefill) {
+        kr[u] = load(ku, kb, nxt[u]);
+        kr[u + 1] = load(ku, kb, nxt[u + 1]);
+        in_order();
+      }
+      da = Elems<EB>::scaled(row_sum<LPR>(da), scale_log2);
+      db = Elems<EB>::scaled(row_sum<LPR>(db), scale_log2);
+      const bool on_a = ea >= 0, on_b = eb >= 0;
+      const float za = on_a ? da : -INFINITY, zb = on_b ? db : -INFINITY;
+      float* const at_a = on_a ? zpos + u * NW * RPW : zdump;
+      float* const at_b = on_b ? zpos + (u + 1) * NW * RPW : zdump;
+      if constexpr (!VF) { *at_a = za; *at_b = zb; }         // (the lanes of a row write the same word)
+      const float m_new = max3(m, za, zb);
+      const float corr = fast_exp2(m - m_new), pa = fast_exp2(za - m_new), pb = fast_exp2(zb - m_new);
+      m = m_new;
+      l = fmaf(l, corr, pa) + pb;
+      // (what a masked entry read may be anything: 0 times it need not be 0)
+      const uint4 xa = make_uint4(on_a ? vr[u].x : 0u, on_a ? vr[u].y : 0u, on_a ? vr[u].z : 0u, on_a ? vr[u].w : 0u);
+      const uint4 xb = make_uint4(on_b ? vr[u + 1].x : 0u, on_b ? vr[u + 1].y : 0u, on_b ? vr[u + 1].z : 0u, on_b ? vr[u + 1].w : 0u);
+      float va[EPL], vc[EPL];
+      Elems<EB>::unpack(xa, va);
+      Elems<EB>::unpack(xb, vc);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(pb, vc[e], fmaf(acc[e], corr, pa * va[e]));
+      if constexpr (VF) {                         // Eq. 2-3 bookkeeping of these rows: |v_h|^2 and v_h . u_h
+        float dva = 0.0f, sva = 0.0f, dvb = 0.0f, svb = 0.0f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+          dva = fmaf(va[e], uf[e], dva); sva = fmaf(va[e], va[e], sva);
+          dvb = fmaf(vc[e], uf[e], dvb); svb = fmaf(vc[e], vc[e], svb);
+        }
+        dva = row_sum<LPR>(dva); sva = row_sum<LPR>(sva);
+        dvb = row_sum<LPR>(dvb); svb = row_sum<LPR>(svb);
+        at_a[0] = sva; at_b[0] = svb;
+        at_a[A.chunk_max] = dva; at_b[A.chunk_max] = dvb;
+      }
+      // the state is demanded HERE, and no memory access may cross: the units are folded completely before the loads that
+      // reuse their registers are issued, and no later unit's arithmetic is pulled in front of them (left to itself the
+      // compiler gathers all the logits of a trip first and so waits for the whole ring)
+      static_assert(EPL == 4 || EPL == 8, "elements per lane");
+      if constexpr (EPL == 8)
+        asm volatile("" : "+v"(m), "+v"(l), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]),
+                     "+v"(acc[5]), "+v"(acc[6]), "+v"(acc[7]) : : "memory");
+      else
+        asm volatile("" : "+v"(m), "+v"(l), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]) : : "memory");
+      if constexpr (kRefill) {
+        vr[u] = load(vu, vb, nxt[u]);
+        vr[u + 1] = load(vu, vb, nxt[u + 1]);
+        ent[u] = nxt[u]; ent[u + 1] = nxt[u + 1];
+        nxt[u] = next[(u + U) * NW * RPW]; nxt[u + 1] = next[(u + 1 + U) * NW * RPW];
+        in_order();
+      }
+    };
     for (int trip = 1; trip < n_trips; ++trip) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        fold(u);
-        refill(u, k_next + u, slot_nx[u]);
-      }
-      k_next += U;
+      for (int u = 0; u < U; u += 2) fold(u, std::true_type());
+      next += kRev;
+      zpos += kRev;
     }
+    // the last revolution; pairs without a unit of this wave are left out (wave-uniform)
 #pragma unroll
-    for (int u = 0; u < U; ++u) fold(u);
+    for (int u = 0; u < U; u += 2)
+      if ((n_trips - 1) * U + u < n_mine) fold(u, std::false_type());
   }
-  // ---- merge, step 1 (registers): the RPW lane groups of a wave that worked on the same head bring their
-  // states to the wave's maximum and add them up across lanes; every lane ends up with the wave's state.
+  // ---- merge, step 1 (registers): the RPW lane groups of a wave that worked on the same head bring their states to the wave's
+  // maximum and add them up across lanes.  The normaliser's sum goes to every lane; of the output, a swap of 32- or 16-lane
+  // halves adds two elements at once and leaves one of them in each half, so that a lane ends up with kLeft elements from e0 on.
+  constexpr int kGroups0 = LPR * HT;                 // lanes from one group of a head to its next
+  constexpr int kLeft = EPL >> ((kGroups0 <= 32 ? 1 : 0) + (kGroups0 <= 16 ? 1 : 0));
+  int e0 = 0;
   if constexpr (RPW > 1) {
     float M = m;
 #pragma unroll
-    for (int x = LPR * HT; x < kWave; x <<= 1)
-      M = x == 8 ? xor_max<8>(M) : x == 16 ? xor_max<16>(M) : xor_max<32>(M);
-    const float sc = (m == -INFINITY) ? 0.0f : fast_exp2(m - M);     // a group that saw no token weighs 0
+    for (int x = kGroups0; x < kWave; x <<= 1) M = x == 8 ? xor_max<8>(M) : x == 16 ? xor_max<16>(M) : xor_max<32>(M);
+    const float sc = fast_exp2(m - M);              // 0 for a group that saw no token, unless no group did (then l and acc are 0)
     l *= sc;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] *= sc;
 #pragma unroll
-    for (int x = LPR * HT; x < kWave; x <<= 1) {
-      l = x == 8 ? xor_sum<8>(l) : x == 16 ? xor_sum<16>(l) : xor_sum<32>(l);
+    for (int x = kGroups0; x < kWave; x <<= 1) l = x == 8 ? xor_sum<8>(l) : x == 16 ? xor_sum<16>(l) : xor_sum<32>(l);
+    auto fold_halves = [&](auto width, int n) {     // acc[0 .. n) <- per half: acc[i] + its partner's, acc[i + n] in the upper half
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = x == 8 ? xor_sum<8>(acc[e]) : x == 16 ? xor_sum<16>(acc[e]) : xor_sum<32>(acc[e]);
+      for (int i = 0; i < EPL / 2; ++i)
+        if (i < n) {
+          const uint32_t lo = __float_as_uint(acc[i]), hi = __float_as_uint(acc[i + n]);
+          const u32x2 r = decltype(width)::value == 32 ? __builtin_amdgcn_permlane32_swap(lo, hi, false, false)
+                                                       : __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+          acc[i] = __uint_as_float(r.x) + __uint_as_float(r.y);
+        }
+      e0 += (lane & decltype(width)::value) ? n : 0;
+    };
+    fold_halves(std::integral_constant<int, 32>(), EPL / 2);
+    if constexpr (kGroups0 <= 16) fold_halves(std::integral_constant<int, 16>(), EPL / 4);
+    if constexpr (kGroups0 <= 8) {
+#pragma unroll
+      for (int i = 0; i < kLeft; ++i) acc[i] = xor_sum<8>(acc[i]);
     }
     m = M;
   }
   // ---- step 2 (LDS): one state per wave; after ONE barrier every thread works out the
   // normaliser itself, the first D threads each finish one output element
-  if (ts == 0) {
-    if (dl == 0) { s_wm[wave * HT + hs] = m; s_wl[wave * HT + hs] = l; }
-    float4* dst = reinterpret_cast<float4*>(&s_wacc[(wave * HT + hs) * D + dl * EPL]);
-#pragma unroll
-    for (int e = 0; e < EPL; e += 4) dst[e / 4] = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+  if (ts == 0 && dl == 0) { s_wm[wave * HT + hs] = m; s_wl[wave * HT + hs] = l; }
+  {
+    float* const dst = &s_wacc[(wave * HT + hs) * D + dl * EPL + e0];         // (lanes that hold the same elements write the same)
+    if constexpr (kLeft == 4) *reinterpret_cast<float4*>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    else if constexpr (kLeft == 2) *reinterpret_cast<float2*>(dst) = make_float2(acc[0], acc[1]);
+    else *dst = acc[0];
   }
   __syncthreads();
-  // Section 4.2: the query token's row enters the cache (nothing in this launch reads it from there)
-  if (new_slot >= 0 && chunk == n_chunks - 1 && wave == 0 && ts == 0 && hs < heads_here) {
-    const long long off = (long long)new_slot * A.slot_stride_b;
-    store16(kb + off, nk);
-    store16(vb + off, nv);
-  }
   if constexpr (HT > 1) {
     // ---- several heads: a thread finishes output elements of one head after the other, then adds its tokens' probabilities to
     // all the heads' score rows
@@ -379,7 +505,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       for (int k = 0; k < NW; ++k) { w[k] = s_wm[k * HT + h]; M = fmaxf(M, w[k]); }
 #pragma unroll
       for (int k = 0; k < NW; ++k) {
-        w[k] = (w[k] == -INFINITY) ? 0.0f : fast_exp2(w[k] - M);
+        w[k] = fast_exp2(w[k] - M);
         L = fmaf(s_wl[k * HT + h], w[k], L);
         a = fmaf(s_wacc[(k * HT + h) * D + d], w[k], a);
       }
@@ -395,7 +521,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
 #pragma unroll
       for (int h = 0; h < HT; ++h) lse2[h] = s_lse2[min(h, heads_here - 1)];
       for (int i = tid; i < len; i += kAttThreads) {
-        gfloat* const at = score + (size_t)head0 * A.cap + s_idx[i];
+        gfloat* const at = score + (size_t)head0 * A.cap + slot_of(s_ent[i]);
         float old[HT];
 #pragma unroll
         for (int h = 0; h < HT; ++h) old[h] = at[(size_t)min(h, heads_here - 1) * A.cap];
@@ -407,21 +533,24 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     if (head0 == 0 && tid == 0) advance_step(sqp, A.advance);
     return;
   }
-  // log2-domain normaliser of the whole workgroup, worked out by every thread from the waves' states
-  float wgt[NW], M = -INFINITY, L = 0.0f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { wgt[w] = s_wm[w]; M = fmaxf(M, wgt[w]); }
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    wgt[w] = (wgt[w] == -INFINITY) ? 0.0f : fast_exp2(wgt[w] - M);       // empty wave: weight 0
-    L = fmaf(s_wl[w], wgt[w], L);
-  }
+  // log2-domain normaliser of the whole workgroup, worked out by every wave from the waves' states: lane w (modulo NW) weighs wave w
+  static_assert(NW == 4 || NW == 8, "reductions over 4 or 8 lanes");
+  const float wm = s_wm[lane % NW];
+  float M = fmaxf(wm, dpp_f<0xB1>(wm));
+  M = fmaxf(M, dpp_f<0x4E>(M));
+  if constexpr (NW == 8) M = fmaxf(M, dpp_f<0x141>(M));
+  const float weight = fast_exp2(wm - M);           // (a wave that saw no token: 0, or l and acc are 0)
+  float L = s_wl[lane % NW] * weight;
+  L += dpp_f<0xB1>(L);
+  L += dpp_f<0x4E>(L);
+  if constexpr (NW == 8) L += dpp_f<0x141>(L);
   const size_t row = (size_t)b * n_heads + head;
   if (tid < D) {
     static_assert(D <= kAttThreads, "one output element per thread");
     float a = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) a = fmaf(s_wacc[w * D + tid], wgt[w], a);
+    for (int w = 0; w < NW; ++w)
+      a = fmaf(s_wacc[w * D + tid], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), w)), a);
     if constexpr (DIRECT) {
       const float val = __fdividef(a, L);
       if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + tid] = val;
@@ -443,7 +572,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
         for (int k = 0; k < PF; ++k) {
           const int j = tid + k * kAttThreads;
           if (j < len) {
-            const int slot = min(max(pf_slot[k], 0), A.cap - 1);
+            const int slot = pf_slot[k];
             vrows[slot] = s_logit[j];
             vrows[A.cap + slot] = s_logit[A.chunk_max + j];
           }
@@ -451,7 +580,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
         j0 = tid + PF * kAttThreads;
       }
       for (int j = j0; j < len; j += kAttThreads) {
-        const int slot = s_idx[j];
+        const int slot = slot_of(s_ent[j]);
         vrows[slot] = s_logit[j];
         vrows[A.cap + slot] = s_logit[A.chunk_max + j];
       }
@@ -465,7 +594,10 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
 #pragma unroll
       for (int k = 0; k < PF; ++k) {                // reads were started before the loop
         const int i = tid + k * kAttThreads;
-        if (i < len) srow[pf_slot[k]] = pf_old[k] + fast_exp2(s_logit[i] - lse2);
+        if (k * kAttThreads < len) {                // (uniform)
+          const float sum = pf_old[k] + fast_exp2(s_logit[min(i, len - 1)] - lse2);
+          if (i < len) *(gfloat*)((gchar*)srow + (uint32_t)pf_slot[k] * 4u) = sum;
+        }
       }
       constexpr int B = 4;                          // longer lists: batches of reads, so that their latencies overlap
       for (int i0 = tid + PF * kAttThreads; i0 < len; i0 += B * kAttThreads) {
@@ -473,7 +605,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
         int slot[B];
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-          slot[k] = s_idx[min(i0 + k * kAttThreads, len - 1)];
+          slot[k] = slot_of(s_ent[min(i0 + k * kAttThreads, len - 1)]);
           old[k] = srow[slot[k]];
         }
 #pragma unroll
@@ -583,22 +715,23 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
   }
 }
 
-template <int EB, int D, int HT, int NW, bool VF, bool DIRECT>
+template <int EB, int D, int HT, int NW, bool VF, bool DIRECT, bool WIDE = false>
 hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
   // Row pairs in flight per lane.  us with 2 | 3 | 4 | 6 | 8, bf16: 768 pairs x 647 tokens x 64 22.6 | 22.2 | 22.3 | 22.8 | 23.3; 128 x
   // 1159 x 128 19.4 | 17.5 | 17.6 | 18.0 | 19.1; 40 x 427 x 64 5.8 | 5.8 | 5.6 | 7.0 | 6.4; fp32 63 x 433 x 128 13.0 | 11.3 | 11.5 | 12.2 |
   // 13.1; only 320 x 427 x 64, whose lists fill 3.3 revolutions of 4, is better off with 3: 9.9 | 9.6 | 10.2 | 11.4 | 11.3.
   constexpr int U = 4;
-  const size_t lds = (size_t)((VF ? 2 : HT) + 1) * plan.chunk_max * sizeof(float);      // logits rows + the slot list
+  constexpr int kRev = NW * U * (kWave * 16 / (D * EB) / HT);                           // tokens of a ring revolution
+  const size_t lds = ((size_t)(VF ? 2 : HT) * plan.chunk_max + ((plan.chunk_max + kRev - 1) / kRev + 1) * kRev) * sizeof(float);      // logits rows + the slot list
   dim3 grid(plan.n_chunks, (A.n_heads + HT - 1) / HT, n_seq);
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
   const int hf = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0);
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
+    hipExtLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
                           DIRECT ? ev_stop : nullptr, 0, A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
   else
-    hipLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT>), grid, dim3(NW * kWave), lds, st,
+    hipLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), lds, st,
                        A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
   if constexpr (!DIRECT) {
     const hipError_t e = hipGetLastError();
@@ -615,6 +748,10 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
 template <int EB, int D, bool VF>
 hipError_t launch_attend_v(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (A.stride24 == 0) {
+    if (plan.n_chunks > 1) return launch_attend_w<EB, D, 1, 8, VF, false, true>(A, plan, n_seq, st, ev_start, ev_stop);
+    return launch_attend_w<EB, D, 1, 8, VF, true, true>(A, plan, n_seq, st, ev_start, ev_stop);
+  }
   if constexpr (!VF && kBurst > D * EB) {
     if (plan.heads > 1) return launch_attend_w<EB, D, kBurst / (D * EB), 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
   }
@@ -652,6 +789,13 @@ static int reserved_chunks(const adsa_params& p) {
   const int lds_rows = (p.score_mode == ADSA_SCORE_VCOS_FUSED ? 2 : heads_per_group(p)) + 1;
   while (nc < kMaxChunks && (size_t)lds_rows * ((p.sel_cap + nc - 1) / nc + 1) * sizeof(float) > 40 * 1024) ++nc;
   return (int)nc;
+}
+
+// Whether a lane reaches every row of its workgroup's heads with a 24-bit product and a 32-bit offset: rows up to 16 MB apart
+// whose cache spans less than 4 GB.  (All dense caches: at most 8192 slots of 128 KB.)
+static bool short_offsets(const adsa_params& p, int heads) {
+  const long long eb = elem_bytes(p), slot_b = p.kv_slot_stride * eb;
+  return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
 }
 
 AttendPlan make_attend_plan(const adsa_params& p) {
@@ -732,8 +876,9 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   const int ht = p.kv_slot_stride > p.kv_head_stride ? kBurst / (p.head_dim * elem_bytes(p)) : 1;
   const long long groups = (p.n_heads + ht - 1) / ht;
   const bool fits = p.n_heads % ht == 0 || (b_list <= (32 << 10) && 100 * groups * ht <= 115ll * p.n_heads);
-  a.heads = !fused && nc == 1 && ht > 1 && p.n_seq * groups >= 384 && fits && (size_t)(ht + 1) * (p.sel_cap + 1) * sizeof(float) <= 40 * 1024 ? ht : 1;
+  a.heads = !fused && nc == 1 && ht > 1 && p.n_seq * groups >= 384 && fits && short_offsets(p, ht) && (size_t)(ht + 1) * (p.sel_cap + 1) * sizeof(float) <= 40 * 1024 ? ht : 1;
   if (a.heads > 1) a.waves = 4;
+  if (!short_offsets(p, 1)) a.waves = 8;       // (one form of the kernel has 64-bit offsets, for 24 more registers)
   a.reserved_chunks = reserved_chunks(p);
   a.chunk_max = (p.sel_cap + a.n_chunks - 1) / a.n_chunks + 1;
   return a;
@@ -799,6 +944,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
   const int eb = elem_bytes(p);
   A.slot_stride_b = (long long)p.kv_slot_stride * eb;
   A.head_stride_b = (long long)p.kv_head_stride * eb;
+  A.stride24 = short_offsets(p, plan.heads) ? (uint32_t)A.slot_stride_b : 0u;
   const float scale = p.softmax_scale != 0.0f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
   A.scale_log2 = scale * kLog2e;
   const int key = eb * 1000 + p.head_dim;

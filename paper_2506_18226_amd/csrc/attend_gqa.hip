@@ -190,8 +190,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         nv[0] = x.x; nv[1] = x.y; nv[2] = x.z; nv[3] = x.w;
       } else {
         const uint4 x = load16(vn + (new_row + r * 4) * 4);
-        nv[0] = f32_to_bf16_rne(__uint_as_float(x.x)) | (f32_to_bf16_rne(__uint_as_float(x.y)) << 16);
-        nv[1] = f32_to_bf16_rne(__uint_as_float(x.z)) | (f32_to_bf16_rne(__uint_as_float(x.w)) << 16);
+        nv[0] = pack2_bf16(__uint_as_float(x.x), __uint_as_float(x.y));
+        nv[1] = pack2_bf16(__uint_as_float(x.z), __uint_as_float(x.w));
       }
     } else {
       nk = load16(kn + new_row * 2 + ld_piece * 16);

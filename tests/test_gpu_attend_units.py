@@ -1,0 +1,110 @@
+"""The attention kernel's units: list lengths around a wave-load, a pair of them, a ring revolution and the entries fetched
+early; the query token's slot at every kind of place in the list; rows that are not attended hold NaN, so that no lane without a
+token may let what it read reach a result; slots further apart than 24-bit products reach.  Against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_18226_amd import binding as B
+from paper_2506_18226_amd import workloads as WL
+from paper_2506_18226_amd.batch import to_device
+
+from common import oracle_cfg, plan_of
+from test_gpu_parity import DEV, check_out, lse_tol
+
+pytestmark = pytest.mark.gpu
+
+
+def run_case(n_heads, D, dtype, layout, cap, lens, slot_stride=None, sel_cap=None, new_f32=False):
+    """One attention launch over len(lens) sequences whose caches hold NaN wherever nothing may be read from."""
+    n_seq, sel_cap = len(lens), sel_cap or max(lens)
+    wl = WL.get_workload("tiny", n_heads=n_heads, head_dim=D, grid_h=96, grid_w=96, prefix_len=8, dtype=dtype)
+    rng = np.random.default_rng(11)
+    k, v = (WL.quantise(wl, rng.standard_normal((cap, n_heads, D), dtype=np.float32)) for _ in range(2))
+    q = WL.quantise(wl, rng.standard_normal((n_seq, n_heads, D), dtype=np.float32))
+    kn, vn = (rng.standard_normal((n_seq, n_heads, D), dtype=np.float32) for _ in range(2))
+    kq, vq = WL.quantise(wl, kn), WL.quantise(wl, vn)
+    code, tdt = (B.F32, torch.float32) if dtype == "f32" else (B.BF16, torch.bfloat16)
+    p = B.make_params(n_seq=n_seq, n_heads=n_heads, head_dim=D, grid_h=96, grid_w=96, win_rows_back=1, win_col_radius=2,
+                      dtype=code, score_mode=B.SCORE_ATTN_MASS, cap=cap, sel_cap=sel_cap, layout=layout, kv_slot_stride=slot_stride)
+    span = (cap - 1) * p.kv_slot_stride + (n_heads - 1) * p.kv_head_stride + D
+    K, V = (torch.full((n_seq, span), float("nan"), dtype=tdt, device=DEV) for _ in range(2))
+    view = lambda x, b: torch.as_strided(x[b], (cap, n_heads, D), (p.kv_slot_stride, p.kv_head_stride, 1), x[b].storage_offset())
+    score = rng.random((n_seq, n_heads, cap)).astype(np.float32)
+    score_d = torch.from_numpy(score).to(DEV)
+    pos = torch.arange(cap, dtype=torch.int32, device=DEV).repeat(n_seq, 1)
+    seqs = np.zeros(n_seq, dtype=B.SEQ_DTYPE)
+    sels, news = [], []
+    sel_idx = torch.full((n_seq, sel_cap), cap + 7, dtype=torch.int32, device=DEV)      # (past a list: nothing that may be used)
+    for b, n in enumerate(lens):
+        pool = np.arange(1, cap) if n < cap and b % 2 else np.arange(cap)               # every other list leaves slot 0 out
+        sel = np.sort(rng.choice(pool, size=n, replace=False)).astype(np.int32)
+        outside = np.setdiff1d(np.arange(cap), sel)
+        # the query token's slot: first, middle, last of the list; outside it (its row is stored all the same); none
+        new = [int(sel[0]), int(sel[n // 2]), int(sel[-1]), int(outside[-1]) if len(outside) else -1, -1][b % 5]
+        rows = torch.from_numpy(sel[sel != new].astype(np.int64)).to(DEV)
+        for x, host in ((K, k), (V, v)):
+            view(x, b)[rows] = to_device(host[sel[sel != new]], code, DEV)
+        sel_idx[b, :n] = torch.from_numpy(sel).to(DEV)
+        seqs[b]["k"], seqs[b]["v"] = K[b].data_ptr(), V[b].data_ptr()
+        seqs[b]["pos"], seqs[b]["score"] = pos[b].data_ptr(), score_d[b].data_ptr()
+        seqs[b]["n_res"], seqs[b]["step"], seqs[b]["pending_slot"] = cap, 600, new
+        sels.append(sel)
+        news.append(new)
+    seqs_d = torch.from_numpy(seqs.view(np.uint8).reshape(-1).copy()).to(DEV)
+    cnt = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    out = torch.zeros((n_seq, n_heads, D), dtype=tdt, device=DEV)
+    lse = torch.zeros((n_seq, n_heads), device=DEV)
+    ws = torch.full((B.adsa_workspace_bytes(p),), 0xFF, dtype=torch.uint8, device=DEV)  # (NaN in every float)
+    new_rows = [torch.from_numpy(x).to(DEV) if new_f32 else to_device(x, code, DEV) for x in ((kn, vn) if new_f32 else (kq, vq))]
+    B.adsa_attend(p, seqs_d, to_device(q, code, DEV), sel_idx, cnt, out, lse, ws,
+                  B.FLAG_APPEND | B.FLAG_ADVANCE | (B.FLAG_NEW_F32 if new_f32 else 0), *new_rows)
+    torch.cuda.synchronize()
+    out, lse, got = out.float().cpu().numpy(), lse.cpu().numpy(), score_d.cpu().numpy()
+    steps = seqs_d.cpu().numpy().view(B.SEQ_DTYPE)["step"]
+    cfg = oracle_cfg(wl, budget=cap, cap=cap)
+    for b, n in enumerate(lens):
+        kb, vb, new, what = k.copy(), v.copy(), news[b], f"len={n} b={b}"
+        if new >= 0:
+            kb[new], vb[new] = kq[b], vq[b]
+            for x, row in ((K, kq), (V, vq)):
+                assert np.array_equal(view(x, b)[new].float().cpu().numpy(), row[b]), what
+        ro, rl, probs = oracle.attend(cfg, kb, vb, q[b], sels[b], want_probs=True)
+        check_out(wl, out[b], ro, what)
+        assert np.abs(lse[b] - rl).max() <= lse_tol(wl), what
+        want = score[b].copy()
+        want[:, sels[b]] += np.asarray(probs, dtype=np.float32).reshape(n_heads, n)
+        assert np.allclose(got[b], want, rtol=1e-5, atol=1e-6), what
+        assert steps[b] == 601
+    return p
+
+
+@pytest.mark.parametrize("n_heads,D,dtype,layout,cap,lens,waves", [
+    # waves per workgroup, tokens of a wave-load -> tokens of a revolution: 8 x 8 x 4 = 256
+    (3, 64, "bf16", "head_major", 700, [1, 2, 7, 8, 9, 15, 16, 17, 63, 64, 65, 255, 256, 257, 511, 512, 513, 700], 8),
+    (2, 128, "bf16", "slot_major", 300, [1, 3, 4, 5, 8, 127, 128, 129, 256, 257, 300], 8),
+    (3, 64, "bf16", "slot_major", 128, [1, 7, 8, 9, 31, 32, 33, 64, 96, 127, 128], 4),
+    (2, 64, "f32", "head_major", 400, [1, 3, 4, 5, 127, 128, 129, 384, 385, 400], 8),
+    (2, 128, "f32", "head_major", 200, [1, 2, 3, 4, 63, 64, 65, 128, 199, 200], 8),
+    (2, 128, "f32", "slot_major", 32, [1, 2, 3, 16, 31, 32], 4),
+    # entries beyond those fetched early (4 per thread), with 8 waves and with 4
+    (9, 64, "bf16", "head_major", 2200, [2047, 2048, 2049, 2200, 1, 2047, 2048, 2049, 2200, 1030, 1024, 5], 8),
+    (24, 64, "bf16", "head_major", 1100, [1023, 1024, 1025, 1100, 1, 8] + [16 * i + 3 for i in range(20)], 4),
+])
+def test_lengths_around_the_units(n_heads, D, dtype, layout, cap, lens, waves):
+    p = run_case(n_heads, D, dtype, layout, cap, lens)
+    plan = plan_of(p)
+    assert (plan.waves, plan.chunks, plan.heads) == (waves, 1, 1)
+
+
+@pytest.mark.parametrize("D,lens", [(64, [1, 40, 41, 300, 399, 400]), (128, [2, 100, 255, 256, 257])])
+def test_fp32_rows_enter_through_the_wave_that_attends_them(D, lens):
+    run_case(2, D, "bf16", "head_major", 400, lens, new_f32=True)
+
+
+@pytest.mark.parametrize("dtype,D,cap,lens", [("bf16", 64, 24, [1, 9, 24]), ("f32", 128, 20, [3, 20]), ("bf16", 128, 300, [300])])
+def test_slots_further_apart_than_24_bit_products_reach(dtype, D, cap, lens):
+    """Rows of a token of a larger structure: 16 MB apart, or 15 MB apart over more than 4 GB."""
+    eb = 4 if dtype == "f32" else 2
+    run_case(2, D, dtype, "slot_major", cap, lens, slot_stride=((16 << 20) + 4096) // eb if cap < 300 else (15 << 20) // eb)
