@@ -114,7 +114,7 @@ struct AttendArgs {
   float* logits;        // [n_seq][n_heads][lg_stride]   scaled logits, log2 units (split launches)
   float* part_ml;       // [n_seq][n_heads][n_chunks][2]
   float* part_acc;      // [n_seq][n_heads][n_chunks][D]
-  int n_heads, sel_cap, lg_stride, chunk_max, cap;
+  int n_heads, sel_cap, lg_stride, cap;
   int accumulate, append, advance;     // advance: see kAdvance
   int new_f32;                         // k_new / v_new are fp32 although the cache is bf16: round as they enter
   int vcos_fused;
@@ -123,15 +123,34 @@ struct AttendArgs {
   float scale_log2;     // softmax scale * log2(e)
 };
 
+// What a workgroup needs when its rows are summed (or, WIDE, for 64-bit offsets): a block of 16 dwords behind the leading arguments.
+struct AttendTail {
+  char* out;
+  float* lse;
+  float* logits;
+  float* part_ml;
+  float* part_acc;
+  int lg_stride, advance;
+  long long slot_stride_b, head_stride_b;
+};
+constexpr int kLeadBytes = 14 * 4;                  // of the arguments before the tail
+static_assert(sizeof(AttendTail) == 64, "one dword per lane of a 16-lane row");
+
+__device__ __forceinline__ uint64_t address(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
+
 // DIRECT: the list of a (sequence, head) is not split (grid.x == 1): the workgroup finishes its heads alone.
-// The arguments the first round trip needs come first, as plain scalars: the build asks for leading kernel
-// arguments to be preloaded into scalar registers at wave launch, so those loads can leave at once, without
-// waiting for a scalar load of the argument block (which would also wait for the sequence record's).
+// The build asks for leading kernel arguments to be preloaded into scalar registers at wave launch, and 14 dwords of them are.
+// Everything up to the sums is in those 14 (addresses have 48 bits, so six of them take 9 dwords): the first round trip is then
+// the count, the record, the list, q and the query token's row, and nothing waits for the argument block, whose scalar load
+// takes longer (0.85 us) than those and could not be told from them by a wait count.  The block's rest is fetched by a vector
+// load behind the first rows' and read from its lanes at the end.
+//   heads_flags: heads | append << 16 | fp32 rows << 17 | accumulate << 18 | chunks << 24;  caps: cap | sel_cap << 16
 // HT > 1: the workgroup takes HT heads, the lane groups of a wave-load being the HT heads of RPW / HT tokens.
 template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE>
-__global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
-                                                      const char* q_arg, const char* k_new_arg, const char* v_new_arg,
-                                                      int heads_and_flags, int sel_cap_arg, AttendArgs A) {
+__global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t q_lo, uint32_t kn_lo,
+                                                      uint32_t vn_lo, uint32_t seqs_idx_hi, uint32_t cnt_q_hi, uint32_t kn_vn_hi,
+                                                      uint32_t heads_flags, uint32_t caps, uint32_t stride24, uint32_t head_stride16,
+                                                      float scale_log2, AttendTail T) {
   constexpr int kAttThreads = NW * kWave;           // the waves of the workgroup share one token chunk
   constexpr int EPL = Elems<EB>::N;                 // elements per lane
   constexpr int LPR = D / EPL;                      // lanes per row
@@ -139,19 +158,18 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   static_assert(HT == 1 || (DIRECT && !VF && RPW * HT * LPR == kWave), "several heads: whole lists only");
   constexpr int PF = 4;                             // list entries a thread fetches, and score read-modify-writes it starts, early
   constexpr int kRev = NW * U * RPW;                // tokens of one ring revolution of the workgroup
-  extern __shared__ float s_logit[];                // logits [HT][chunk_max] ([2][chunk_max] for VF; the last word of a row takes what
-                                                    // belongs to no token), then the chunk's slot list, see s_ent
+  extern __shared__ int s_ent[];                    // the chunk's slot list [n_ent], then logits [HT][n_ent] ([2][n_ent] for VF)
   __shared__ int s_new[NW];
   // merge: the lane groups of a wave meet in registers, the waves through these (one state per wave)
   __shared__ float s_wm[NW * HT], s_wl[NW * HT];
   __shared__ __attribute__((aligned(16))) float s_wacc[NW * HT * D];
 
   const int chunk = DIRECT ? 0 : blockIdx.x, b = blockIdx.z;
-  const int n_chunks = DIRECT ? 1 : gridDim.x;
+  const int n_chunks = DIRECT ? 1 : heads_flags >> 24;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  // (only 14 dwords of arguments are preloaded: the two flags the first trip needs ride on the head count)
-  const int n_heads = heads_and_flags & 0xFFFF, sel_cap = sel_cap_arg;
+  const int n_heads = heads_flags & 0xFFFF, sel_cap = caps >> 16, cap = caps & 0xFFFF;
+  const bool append = (heads_flags & 0x10000) != 0, new_f32 = EB == 2 && (heads_flags & 0x20000) != 0, accumulate = (heads_flags & 0x40000) != 0;
   // token and head of this lane's row within a wave-load, 16-byte piece of the row (heads past the last repeat it)
   const int dl = lane % LPR, ts = lane / LPR / HT, hs = HT == 1 ? 0 : lane / LPR % HT;
   const int head0 = blockIdx.y * HT, head = HT == 1 ? head0 : min(head0 + hs, n_heads - 1), heads_here = HT == 1 ? 1 : min(HT, n_heads - head0);
@@ -160,18 +178,16 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   // sequence record, q and (when the list is not split, so its chunk starts at 0) the first slots of
   // the loop and the slots whose score words this thread updates at the end.  The record and the
   // count are pinned here so that they cannot drift behind the count test below.
-  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)(seqs_arg + b);
-  const int cnt_raw = ((const gint*)sel_cnt_arg)[b];
+  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)address(seqs_lo, seqs_idx_hi & 0xFFFF) + b;
+  const int cnt_raw = ((const gint*)address(cnt_lo, cnt_q_hi & 0xFFFF))[b];
   gchar* const k_base = (gchar*)sqp->k;
   gchar* const v_base = (gchar*)sqp->v;
   gfloat* const score = (gfloat*)sqp->score;
   const int pending = sqp->pending_slot;
   gfloat* const u_state = VF ? (gfloat*)sqp->vcos_u : nullptr;
   __builtin_amdgcn_sched_barrier(0);                // (the scalar loads leave first: the rows need them and the first slots)
-  const gint* idx = (const gint*)sel_idx_arg + (size_t)b * sel_cap;
+  const gint* idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
   const size_t row_off = ((size_t)b * n_heads + head) * D * EB + dl * 16;
-  gchar* const out_g = (gchar*)A.out;
-  gfloat* const lse_g = (gfloat*)A.lse;
   // The wave takes the RPW-token units wave, wave + NW, ... of the chunk, in that order; unit number k of the
   // wave holds, for this lane, token (wave + k * NW) * RPW + ts.  slot_a[u]: slot of unit u.  pf_slot: the whole list
   // (its first PF * threads entries), one entry per thread and round: staged in LDS below, where the loop finds its slots.
@@ -189,14 +205,13 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
 #pragma unroll
     for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, k * kAttThreads);
   }
-  const uint4 qr = load16((const gchar*)q_arg + row_off);
+  const uint4 qr = load16((const gchar*)address(q_lo, cnt_q_hi >> 16) + row_off);
   // the query token's own K/V row (Section 4.2 append): the first wave attends and stores it, 16 bytes of K and V per lane.
   // fp32 rows of a bf16 cache (twice as many bytes) are rounded once, when they are used
-  const bool append = (heads_and_flags & 0x10000) != 0, new_f32 = EB == 2 && (heads_and_flags & 0x20000) != 0;
   uint4 nk[4 / EB], nv[4 / EB];
   if (append && wave == 0) {
-    const gchar* const k_new_g = (const gchar*)k_new_arg + (new_f32 ? 2 * row_off : row_off);
-    const gchar* const v_new_g = (const gchar*)v_new_arg + (new_f32 ? 2 * row_off : row_off);
+    const gchar* const k_new_g = (const gchar*)address(kn_lo, kn_vn_hi & 0xFFFF) + (new_f32 ? 2 * row_off : row_off);
+    const gchar* const v_new_g = (const gchar*)address(vn_lo, kn_vn_hi >> 16) + (new_f32 ? 2 * row_off : row_off);
     nk[0] = load16(k_new_g);
     nv[0] = load16(v_new_g);
     if constexpr (EB == 2)
@@ -204,20 +219,17 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   }
   pin_uniform(cnt_raw); pin_uniform(k_base); pin_uniform(v_base); pin_uniform(score); pin_uniform(pending);
   if constexpr (VF) pin_uniform(u_state);
-  // (the remaining arguments the loop needs: fetched in the same batch of scalar loads, not after it)
-  pin_uniform(A.cap); pin_uniform(A.chunk_max); pin_uniform(A.slot_stride_b); pin_uniform(A.head_stride_b);
-  pin_uniform(A.scale_log2); pin_uniform(A.accumulate); pin_uniform(A.stride24);
 
   const int cnt = min(cnt_raw, sel_cap);
   if (cnt <= 0) {                                   // inactive or rejected sequence: zero-filled row
     if (chunk == 0) {
       const size_t row = (size_t)b * n_heads + head0;
       for (int o = tid; o < heads_here * D; o += kAttThreads) {
-        if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + o] = 0.0f;
-        else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + o] = 0;
-        if (o % D == 0) lse_g[row + o / D] = 0.0f;
+        if (EB == 4) ((gfloat*)T.out)[row * D + o] = 0.0f;
+        else ((ADSA_GLOBAL uint16_t*)T.out)[row * D + o] = 0;
+        if (o % D == 0) ((gfloat*)T.lse)[row + o / D] = 0.0f;
       }
-      if (head0 == 0 && tid == 0) advance_empty(sqp, A.advance);
+      if (head0 == 0 && tid == 0) advance_empty(sqp, T.advance);
     }
     return;
   }
@@ -226,8 +238,10 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
   if (t_begin >= t_end) return;                     // fewer tokens than chunks
   const int len = t_end - t_begin;
   // The chunk's slot list, one entry per token (filled below): the slot, or ~slot for the query token's own; then entries of no
-  // token, ~0, up to one revolution past the last unit.  A negative entry is not attended in the loop.
-  int* const s_ent = reinterpret_cast<int*>(s_logit + (VF ? 2 : HT) * A.chunk_max);
+  // token, ~0, up to one revolution past the last unit.  A negative entry is not attended in the loop.  The last word of a row
+  // of logits takes what belongs to no token.
+  const int n_ent = ((len + kRev - 1) / kRev + 1) * kRev, dump = n_ent - 1;
+  float* const s_logit = reinterpret_cast<float*>(s_ent + n_ent);
   if constexpr (!DIRECT) {
 #pragma unroll
     for (int u = 0; u < U; ++u) slot_a[u] = entry(unit0, t_begin + u * NW * RPW);
@@ -235,12 +249,12 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, t_begin + k * kAttThreads);
   }
   // the slot adsa_select reserved for the query token (Section 4.2 append), if this launch fills it
-  const int new_slot = (append && pending < A.cap) ? pending : -1;
+  const int new_slot = (append && pending < cap) ? pending : -1;
 
-  const int cap = A.cap, dump = A.chunk_max - 1;
-  const float scale_log2 = A.scale_log2;
   const Elems<EB> qv(qr, scale_log2);
-  const long long lane_off = (long long)head * A.head_stride_b + dl * 16;
+  const long long stride_b = WIDE ? T.slot_stride_b : (long long)stride24;
+  const long long head_stride_b = WIDE ? T.head_stride_b : (long long)head_stride16 * 16;
+  const long long lane_off = (long long)head * head_stride_b + dl * 16;
   gchar* const kb = k_base + lane_off;
   gchar* const vb = v_base + lane_off;
   // VF: this lane's columns of u for its head, and the two score rows of the head
@@ -251,10 +265,11 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     vf_on = u_state != nullptr;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) uf[e] = vf_on ? u_state[(size_t)head * D + dl * EPL + e] : 0.0f;
-    vrows = score + (size_t)(2 * head) * A.cap;
+    vrows = score + (size_t)(2 * head) * cap;
   }
 
   float pf_old[PF];
+  uint32_t tail;                                    // lane i (modulo 16): dword i of T
   float m = kLowest, l = 0.0f, acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.0f;
@@ -279,10 +294,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       __builtin_amdgcn_sched_barrier(0);
     };
     // Entries that are not attended read slot 0 (valid memory, one row for all of them) and are masked when they are folded.
-    const gchar* const ku = k_base + (long long)head0 * A.head_stride_b;        // uniform
-    const gchar* const vu = v_base + (long long)head0 * A.head_stride_b;
-    const uint32_t lane32 = (uint32_t)(head - head0) * (uint32_t)A.head_stride_b + (uint32_t)dl * 16u, stride24 = A.stride24;
-    const long long stride_b = A.slot_stride_b;
+    const gchar* const ku = k_base + (long long)head0 * head_stride_b;        // uniform
+    const gchar* const vu = v_base + (long long)head0 * head_stride_b;
+    const uint32_t lane32 = (uint32_t)(head - head0) * (uint32_t)head_stride_b + (uint32_t)dl * 16u;
     auto load = [&](const gchar* uni, const gchar* own, int e) -> uint4 {
       const int slot = max(e, 0);
       if constexpr (!WIDE) return load_stream16(uni + (__umul24((uint32_t)slot, stride24) + lane32));
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       in_order();
     }
     // ... and while these rows are on their way the chunk's slot list goes to LDS
-    const int n_ent = ((len + kRev - 1) / kRev + 1) * kRev;
+    tail = ((const ADSA_GLOBAL uint32_t*)((const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes))[lane % 16];
     int new_at = 0;                               // 1 + list position of the query token's slot, if this thread stages it
     auto stage = [&](int j, int raw) {
       const int slot = min(max(raw, 0), cap - 1);
@@ -327,7 +341,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     }
     __syncthreads();
     // thread i of the final score update serves tokens i, i + threads, ...; start the first PF reads now
-    if (DIRECT && HT == 1 && A.accumulate) {
+    if (DIRECT && HT == 1 && accumulate) {
 #pragma unroll
       for (int k = 0; k < PF; ++k) {
         pf_old[k] = 0.0f;
@@ -366,15 +380,15 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
           for (int e = 0; e < EPL; ++e) { dv = fmaf(vf[e], uf[e], dv); sv = fmaf(vf[e], vf[e], sv); }
           dv = row_sum<LPR>(dv);
           sv = row_sum<LPR>(sv);
-          if (mine) { s_logit[at - 1] = sv; s_logit[A.chunk_max + at - 1] = dv; }
+          if (mine) { s_logit[at - 1] = sv; s_logit[n_ent + at - 1] = dv; }
         } else {
-          if (mine) s_logit[hs * A.chunk_max + at - 1] = z;
+          if (mine) s_logit[hs * n_ent + at - 1] = z;
         }
       }
     }
     const int* next = s_ent + (wave + U * NW) * RPW + ts;    // entries of the units one revolution ahead
-    float* zpos = s_logit + (VF ? 0 : hs * A.chunk_max) + wave * RPW + ts;
-    float* const zdump = s_logit + (VF ? 0 : hs * A.chunk_max) + dump;
+    float* zpos = s_logit + (VF ? 0 : hs * n_ent) + wave * RPW + ts;
+    float* const zdump = s_logit + (VF ? 0 : hs * n_ent) + dump;
 #pragma unroll
     for (int u = 0; u < U; ++u) nxt[u] = next[u * NW * RPW];
     in_order();
@@ -419,7 +433,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
         dva = row_sum<LPR>(dva); sva = row_sum<LPR>(sva);
         dvb = row_sum<LPR>(dvb); svb = row_sum<LPR>(svb);
         at_a[0] = sva; at_b[0] = svb;
-        at_a[A.chunk_max] = dva; at_b[A.chunk_max] = dvb;
+        at_a[n_ent] = dva; at_b[n_ent] = dvb;
       }
       // the state is demanded HERE, and no memory access may cross: the units are folded completely before the loads that
       // reuse their registers are issued, and no later unit's arithmetic is pulled in front of them (left to itself the
@@ -449,6 +463,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     for (int u = 0; u < U; u += 2)
       if ((n_trips - 1) * U + u < n_mine) fold(u, std::false_type());
   }
+  auto tail_word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)tail, i); };
+  auto tail_address = [&](size_t at) { return address(tail_word(at / 4), tail_word(at / 4 + 1)); };
   // ---- merge, step 1 (registers): the RPW lane groups of a wave that worked on the same head bring their states to the wave's
   // maximum and add them up across lanes.  The normaliser's sum goes to every lane; of the output, a swap of 32- or 16-lane
   // halves adds two elements at once and leaves one of them in each half, so that a lane ends up with kLeft elements from e0 on.
@@ -494,6 +510,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     else *dst = acc[0];
   }
   __syncthreads();
+  gchar* const out_g = (gchar*)tail_address(offsetof(AttendTail, out));
+  gfloat* const lse_g = (gfloat*)tail_address(offsetof(AttendTail, lse));
+  const int advance = tail_word(offsetof(AttendTail, advance) / 4);
   if constexpr (HT > 1) {
     // ---- several heads: a thread finishes output elements of one head after the other, then adds its tokens' probabilities to
     // all the heads' score rows
@@ -515,22 +534,22 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + d] = (uint16_t)f32_to_bf16_rne(val);
       if (d == 0) { s_lse2[h] = M + __log2f(L); lse_g[row] = s_lse2[h] * kLn2; }
     }
-    if (A.accumulate) {
+    if (accumulate) {
       __syncthreads();
       float lse2[HT];
 #pragma unroll
       for (int h = 0; h < HT; ++h) lse2[h] = s_lse2[min(h, heads_here - 1)];
       for (int i = tid; i < len; i += kAttThreads) {
-        gfloat* const at = score + (size_t)head0 * A.cap + slot_of(s_ent[i]);
+        gfloat* const at = score + (size_t)head0 * cap + slot_of(s_ent[i]);
         float old[HT];
 #pragma unroll
-        for (int h = 0; h < HT; ++h) old[h] = at[(size_t)min(h, heads_here - 1) * A.cap];
+        for (int h = 0; h < HT; ++h) old[h] = at[(size_t)min(h, heads_here - 1) * cap];
 #pragma unroll
         for (int h = 0; h < HT; ++h)
-          if (h < heads_here) at[(size_t)h * A.cap] = old[h] + fast_exp2(s_logit[h * A.chunk_max + i] - lse2[h]);
+          if (h < heads_here) at[(size_t)h * cap] = old[h] + fast_exp2(s_logit[h * n_ent + i] - lse2[h]);
       }
     }
-    if (head0 == 0 && tid == 0) advance_step(sqp, A.advance);
+    if (head0 == 0 && tid == 0) advance_step(sqp, advance);
     return;
   }
   // log2-domain normaliser of the whole workgroup, worked out by every wave from the waves' states: lane w (modulo NW) weighs wave w
@@ -558,8 +577,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       if (tid == 0) lse_g[row] = (M + __log2f(L)) * kLn2;
     } else {
       const size_t pidx = row * n_chunks + chunk;
-      A.part_acc[pidx * D + tid] = a;
-      if (tid == 0) { A.part_ml[pidx * 2] = M; A.part_ml[pidx * 2 + 1] = L; }
+      ((gfloat*)tail_address(offsetof(AttendTail, part_acc)))[pidx * D + tid] = a;
+      gfloat* const ml = (gfloat*)tail_address(offsetof(AttendTail, part_ml)) + pidx * 2;
+      if (tid == 0) { ml[0] = M; ml[1] = L; }
     }
   }
 
@@ -574,7 +594,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
           if (j < len) {
             const int slot = pf_slot[k];
             vrows[slot] = s_logit[j];
-            vrows[A.cap + slot] = s_logit[A.chunk_max + j];
+            vrows[cap + slot] = s_logit[n_ent + j];
           }
         }
         j0 = tid + PF * kAttThreads;
@@ -582,15 +602,15 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
       for (int j = j0; j < len; j += kAttThreads) {
         const int slot = slot_of(s_ent[j]);
         vrows[slot] = s_logit[j];
-        vrows[A.cap + slot] = s_logit[A.chunk_max + j];
+        vrows[cap + slot] = s_logit[n_ent + j];
       }
     }
   }
   if constexpr (DIRECT) {
     // -------- this head's attention mass: score[head][slot] += p, from the logits still in LDS
-    if (A.accumulate) {
+    if (accumulate) {
       const float lse2 = M + __log2f(L);
-      gfloat* const srow = score + (size_t)head * A.cap;
+      gfloat* const srow = score + (size_t)head * cap;
 #pragma unroll
       for (int k = 0; k < PF; ++k) {                // reads were started before the loop
         const int i = tid + k * kAttThreads;
@@ -621,19 +641,19 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(adsa_seq* seqs_arg, const
     if (head == 0 && tid == 0) {
       if constexpr (VF) {
         if (u_state) {
-          gfloat* tags = u_state + (size_t)A.n_heads * D;
+          gfloat* tags = u_state + (size_t)n_heads * D;
           const float want = (float)(sqp->step + 2);
           tags[1] = tags[0] == want ? want : 0.0f;
         }
       }
-      advance_step(sqp, A.advance);
+      advance_step(sqp, advance);
     }
     return;
   } else {
     // -------- several chunks: this workgroup's partial and logits are in the workspace; k_attend_finish, the next kernel
     // on the stream, merges them (the launch boundary orders the two and makes the stores visible on every XCD)
-    if (A.accumulate) {
-      float* const lg = A.logits + row * A.lg_stride + t_begin;
+    if (accumulate) {
+      gfloat* const lg = (gfloat*)tail_address(offsetof(AttendTail, logits)) + row * tail_word(offsetof(AttendTail, lg_stride) / 4) + t_begin;
       for (int i = tid; i < len; i += kAttThreads) lg[i] = s_logit[i];
     }
   }
@@ -723,16 +743,25 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
   // 13.1; only 320 x 427 x 64, whose lists fill 3.3 revolutions of 4, is better off with 3: 9.9 | 9.6 | 10.2 | 11.4 | 11.3.
   constexpr int U = 4;
   constexpr int kRev = NW * U * (kWave * 16 / (D * EB) / HT);                           // tokens of a ring revolution
-  const size_t lds = ((size_t)(VF ? 2 : HT) * plan.chunk_max + ((plan.chunk_max + kRev - 1) / kRev + 1) * kRev) * sizeof(float);      // logits rows + the slot list
+  const size_t entries = (size_t)((plan.chunk_max - 1 + kRev - 1) / kRev + 1) * kRev;
+  const size_t lds = ((VF ? 2 : HT) + 1) * entries * sizeof(float);                     // the slot list + logits rows
   dim3 grid(plan.n_chunks, (A.n_heads + HT - 1) / HT, n_seq);
+  auto lo = [](const void* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); };
+  auto hi = [](const void* p, const void* q) { return (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 32 & 0xFFFF) | (uint32_t)(reinterpret_cast<uintptr_t>(q) >> 32) << 16; };
+  const uint32_t flags = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0) | (A.accumulate ? 0x40000 : 0) | plan.n_chunks << 24;
+  const AttendTail T = {A.out, A.lse, A.logits, A.part_ml, A.part_acc, A.lg_stride, A.advance, A.slot_stride_b, A.head_stride_b};
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
-  const int hf = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0);
+  auto launch = [&](auto go) {
+    go(lo(A.seqs), lo(A.sel_idx), lo(A.sel_cnt), lo(A.q), lo(A.k_new), lo(A.v_new), hi(A.seqs, A.sel_idx), hi(A.sel_cnt, A.q), hi(A.k_new, A.v_new),
+       flags, (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, A.stride24, (uint32_t)(A.head_stride_b / 16), A.scale_log2, T);
+  };
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
-                          DIRECT ? ev_stop : nullptr, 0, A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
+    launch([&](auto... args) {
+      hipExtLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start,
+                            DIRECT ? ev_stop : nullptr, 0, args...);
+    });
   else
-    hipLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), lds, st,
-                       A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hf, A.sel_cap, A);
+    launch([&](auto... args) { hipLaunchKernelGGL((k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE>), grid, dim3(NW * kWave), lds, st, args...); });
   if constexpr (!DIRECT) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -792,10 +821,10 @@ static int reserved_chunks(const adsa_params& p) {
 }
 
 // Whether a lane reaches every row of its workgroup's heads with a 24-bit product and a 32-bit offset: rows up to 16 MB apart
-// whose cache spans less than 4 GB.  (All dense caches: at most 8192 slots of 128 KB.)
+// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB), heads less than 64 GB apart.
 static bool short_offsets(const adsa_params& p, int heads) {
   const long long eb = elem_bytes(p), slot_b = p.kv_slot_stride * eb;
-  return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
+  return slot_b < (1ll << 24) && p.kv_head_stride * eb < (16ll << 32) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
 }
 
 AttendPlan make_attend_plan(const adsa_params& p) {
@@ -937,7 +966,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
   A.part_ml = reinterpret_cast<float*>(ws + w.part_ml_off);
   A.part_acc = reinterpret_cast<float*>(ws + w.part_acc_off);
   A.n_heads = p.n_heads; A.sel_cap = p.sel_cap; A.lg_stride = w.lg_stride;
-  A.chunk_max = plan.chunk_max; A.cap = p.cap;
+  A.cap = p.cap;
   A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance;
   A.new_f32 = (new_f32 && append) ? 1 : 0;
   A.vcos_fused = p.score_mode == ADSA_SCORE_VCOS_FUSED ? 1 : 0;
