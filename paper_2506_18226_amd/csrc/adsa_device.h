@@ -17,6 +17,14 @@ typedef ADSA_GLOBAL char gchar;
 typedef ADSA_GLOBAL float gfloat;
 typedef ADSA_GLOBAL int32_t gint;
 
+// Addresses have 48 bits: as leading kernel arguments of the attention launches, their low halves and, two to a dword, the rest
+constexpr int kLeadBytes = 14 * 4;                 // of the arguments before the block that is not preloaded
+__device__ __forceinline__ uint64_t address(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
+static inline uint32_t lo32(const void* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); }
+static inline uint32_t hi16s(const void* p, const void* q) {
+  return (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 32 & 0xFFFF) | (uint32_t)(reinterpret_cast<uintptr_t>(q) >> 32) << 16;
+}
+
 // 16-byte streaming load: K/V rows are read once per step, so keep them out of the caches' way
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_stream16(const gchar* p) {

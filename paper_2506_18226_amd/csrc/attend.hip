@@ -131,12 +131,9 @@ struct AttendTail {
   float* part_ml;
   float* part_acc;
   int lg_stride, advance;
-  long long slot_stride_b, head_stride_b;
+  long long slot_stride_b, unused;
 };
-constexpr int kLeadBytes = 14 * 4;                  // of the arguments before the tail
 static_assert(sizeof(AttendTail) == 64, "one dword per lane of a 16-lane row");
-
-__device__ __forceinline__ uint64_t address(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
 
 // DIRECT: the list of a (sequence, head) is not split (grid.x == 1): the workgroup finishes its heads alone.
 // The build asks for leading kernel arguments to be preloaded into scalar registers at wave launch, and 14 dwords of them are.
@@ -144,7 +141,8 @@ __device__ __forceinline__ uint64_t address(uint32_t lo, uint32_t hi) { return (
 // the count, the record, the list, q and the query token's row, and nothing waits for the argument block, whose scalar load
 // takes longer (0.85 us) than those and could not be told from them by a wait count.  The block's rest is fetched by a vector
 // load behind the first rows' and read from its lanes at the end.
-//   heads_flags: heads | append << 16 | fp32 rows << 17 | accumulate << 18 | chunks << 24;  caps: cap | sel_cap << 16
+//   heads_flags: heads | append << 16 | fp32 rows << 17 | accumulate << 18 | upper 5 bits of the head stride << 19 | chunks << 24;
+//   caps: cap | sel_cap << 16
 // HT > 1: the workgroup takes HT heads, the lane groups of a wave-load being the HT heads of RPW / HT tokens.
 template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE>
 __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t q_lo, uint32_t kn_lo,
@@ -253,7 +251,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
 
   const Elems<EB> qv(qr, scale_log2);
   const long long stride_b = WIDE ? T.slot_stride_b : (long long)stride24;
-  const long long head_stride_b = WIDE ? T.head_stride_b : (long long)head_stride16 * 16;
+  const long long head_stride_b = (long long)address(head_stride16, (heads_flags >> 19) & 0x1F) * 16;
   const long long lane_off = (long long)head * head_stride_b + dl * 16;
   gchar* const kb = k_base + lane_off;
   gchar* const vb = v_base + lane_off;
@@ -746,13 +744,12 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
   const size_t entries = (size_t)((plan.chunk_max - 1 + kRev - 1) / kRev + 1) * kRev;
   const size_t lds = ((VF ? 2 : HT) + 1) * entries * sizeof(float);                     // the slot list + logits rows
   dim3 grid(plan.n_chunks, (A.n_heads + HT - 1) / HT, n_seq);
-  auto lo = [](const void* p) { return (uint32_t)reinterpret_cast<uintptr_t>(p); };
-  auto hi = [](const void* p, const void* q) { return (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 32 & 0xFFFF) | (uint32_t)(reinterpret_cast<uintptr_t>(q) >> 32) << 16; };
-  const uint32_t flags = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0) | (A.accumulate ? 0x40000 : 0) | plan.n_chunks << 24;
-  const AttendTail T = {A.out, A.lse, A.logits, A.part_ml, A.part_acc, A.lg_stride, A.advance, A.slot_stride_b, A.head_stride_b};
+  const uint32_t flags = A.n_heads | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0) | (A.accumulate ? 0x40000 : 0) | (uint32_t)(A.head_stride_b >> 36 & 0x1F) << 19 |
+                         plan.n_chunks << 24;
+  const AttendTail T = {A.out, A.lse, A.logits, A.part_ml, A.part_acc, A.lg_stride, A.advance, A.slot_stride_b, 0};
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
   auto launch = [&](auto go) {
-    go(lo(A.seqs), lo(A.sel_idx), lo(A.sel_cnt), lo(A.q), lo(A.k_new), lo(A.v_new), hi(A.seqs, A.sel_idx), hi(A.sel_cnt, A.q), hi(A.k_new, A.v_new),
+    go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.q), lo32(A.k_new), lo32(A.v_new), hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.q), hi16s(A.k_new, A.v_new),
        flags, (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, A.stride24, (uint32_t)(A.head_stride_b / 16), A.scale_log2, T);
   };
   if (ev_start && ev_stop)
@@ -821,10 +818,10 @@ static int reserved_chunks(const adsa_params& p) {
 }
 
 // Whether a lane reaches every row of its workgroup's heads with a 24-bit product and a 32-bit offset: rows up to 16 MB apart
-// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB), heads less than 64 GB apart.
+// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB).
 static bool short_offsets(const adsa_params& p, int heads) {
   const long long eb = elem_bytes(p), slot_b = p.kv_slot_stride * eb;
-  return slot_b < (1ll << 24) && p.kv_head_stride * eb < (16ll << 32) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
+  return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
 }
 
 AttendPlan make_attend_plan(const adsa_params& p) {

@@ -30,6 +30,8 @@
 //    order, to its OWN cache head's row of score[]: no workgroup talks to another.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "adsa_internal.h"
 #include "adsa_device.h"
 
@@ -106,25 +108,37 @@ struct GqaArgs {
   float* part_ml;       // [n_seq][n_heads * G][n_chunks][2]
   float* part_acc;      // [n_seq][n_heads * G][n_chunks][D]
   int lg_global;        // row stride of logits
-  int n_heads, G, sel_cap, lg_stride, cap, stage_b;
+  int n_heads, G, sel_cap, cap;
   int accumulate, append, advance;
   int new_f32;          // k_new / v_new are fp32 although the cache is bf16: round as they enter
   long long slot_stride_b, head_stride_b;
   float scale_log2;
 };
 
-// The arguments the first round trip needs come first, as plain scalars (the build asks for leading kernel
-// arguments to be preloaded into scalar registers at wave launch): the vector loads of that trip then leave
-// without waiting for a scalar load of the argument block.  Only 14 dwords are preloaded, so the group size and
-// the two append flags ride on the head count: heads | G << 16 | append << 24 | new_f32 << 25.
+// What a workgroup needs when its rows are summed: a block of 16 dwords behind the leading arguments.
+struct GqaTail {
+  char* out;
+  float* lse;
+  float* logits;
+  float* part_ml;
+  float* part_acc;
+  int lg_global, advance;
+  int unused[4];
+};
+
+// Everything up to the sums is in the 14 dwords of leading arguments that are preloaded into scalar registers at wave launch (see
+// k_attend): heads_flags: heads | G << 9 | append << 16 | fp32 rows << 17 | accumulate << 18 | upper 5 bits of the head stride << 19
+// | chunks << 24;  caps: cap | sel_cap << 16.
 // SPLIT: the list of a (sequence, cache head) is cut into gridDim.z chunks of whole 16-token tiles, one workgroup
 // each; every workgroup leaves a partial and its logits in the workspace and k_gqa_finish merges them in chunk order.
 // R: tiles in flight per wave (a ring: the oldest is multiplied, then refilled).
+// (held to the 128 registers that let two 8-wave workgroups share a CU, but for the deep rings)
 template <int D, int NW, bool SPLIT, int R>
-__global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, const int32_t* sel_idx_arg, const int32_t* sel_cnt_arg,
-                                                          const char* q_arg, const char* k_new_arg, const char* v_new_arg,
-                                                          int heads_g_flags, int sel_cap_arg, GqaArgs A) {
-  constexpr int T = NW * kWave;
+__global__ __launch_bounds__(NW * kWave, R > ring(D) ? 1 : 4) void k_attend_gqa(uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t q_lo,
+                                                          uint32_t kn_lo, uint32_t vn_lo, uint32_t seqs_idx_hi, uint32_t cnt_q_hi,
+                                                          uint32_t kn_vn_hi, uint32_t heads_flags, uint32_t caps, uint32_t stride32,
+                                                          uint32_t head_stride16, float scale_log2, GqaTail T) {
+  constexpr int kThreads = NW * kWave;
   constexpr int ROWB = D * 2 + 16;          // bytes of a staged K row (padded against bank conflicts)
   constexpr int LPR = D / 8;                // lanes per K row with 16-byte loads
   constexpr int RPL = kWave / LPR;          // rows per wave-load
@@ -132,31 +146,34 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   constexpr int NC = D / 16;                // 16-wide chunks of the q.k contraction
   constexpr int EV = D / 16;                // V columns a lane holds per token
   constexpr int VW = EV / 2;                // dwords of V a lane loads per token
-  constexpr int PF = 2048 / T;              // slot-list entries a thread fetches in the first round trip
+  constexpr int PF = 2048 / kThreads;              // slot-list entries a thread fetches in the first round trip
   extern __shared__ __align__(16) char smem[];
   __shared__ float s_wm[NW][16], s_wl[NW][16];
 
   const int hk = blockIdx.x, b = blockIdx.y;
-  const int chunk = SPLIT ? blockIdx.z : 0, n_chunks = SPLIT ? gridDim.z : 1;
+  const int chunk = SPLIT ? blockIdx.z : 0, n_chunks = SPLIT ? heads_flags >> 24 : 1;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int r = lane & 15, kg = lane >> 4;                 // matrix-operand role of this lane
-  const int n_heads = heads_g_flags & 0xFFFF, G = (heads_g_flags >> 16) & 0xFF, sel_cap = sel_cap_arg;
-  const bool append = (heads_g_flags & (1 << 24)) != 0, cvt = (heads_g_flags & (1 << 25)) != 0;
+  const int n_heads = heads_flags & 0x1FF, G = (heads_flags >> 9) & 0x1F, sel_cap = caps >> 16, cap = caps & 0xFFFF;
+  const bool append = (heads_flags & 0x10000) != 0, cvt = (heads_flags & 0x20000) != 0, keep_logits = (heads_flags & 0x40000) != 0;
   const int HQ = n_heads * G;
 
   // ---- first round trip: the count and the sequence record (scalar loads), q, the whole slot list (one entry per
   // thread and round) and the query token's own K/V row as this launch attends and stores it -- everything that
   // depends on the kernel arguments only.  The record and the count are pinned so that they cannot drift behind
   // the count test below, into a second, dependent trip.
-  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)(seqs_arg + b);
-  const int cnt_raw = ((const gint*)sel_cnt_arg)[b];
+  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)address(seqs_lo, seqs_idx_hi & 0xFFFF) + b;
+  const int cnt_raw = ((const gint*)address(cnt_lo, cnt_q_hi & 0xFFFF))[b];
   gchar* const k_rec = (gchar*)sqp->k;
   gchar* const v_rec = (gchar*)sqp->v;
   gfloat* const score_rec = (gfloat*)sqp->score;
   const int pending = sqp->pending_slot;
-  const gint* const idx = (const gint*)sel_idx_arg + (size_t)b * sel_cap;
-  const gchar* const q_g = (const gchar*)q_arg;
+  __builtin_amdgcn_sched_barrier(0);                       // (the scalar loads leave first)
+  const gint* const idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
+  const auto list = __builtin_amdgcn_make_buffer_rsrc((void*)(const int32_t*)idx, 0, sel_cap * 4, 0x00027000);      // (entries past its end come back as 0)
+  auto entry = [&](int lane_at, int uniform_at) { return (int)__builtin_amdgcn_raw_buffer_load_b32(list, lane_at * 4, uniform_at * 4, 0); };
+  const gchar* const q_g = (const gchar*)address(q_lo, cnt_q_hi >> 16);
   // q as the B operand of the first product: lane (g = r, kg) holds columns [D/4*kg, D/4*(kg+1)) of query g
   const gchar* const q_row0 = q_g + ((size_t)b * HQ + (size_t)hk * G) * D * 2;        // query 0 of this cache head
   uint4 qx[NC / 2];
@@ -169,9 +186,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   const int first_at = (wave + kg * NW) * 16 + r;            // list position of this lane's token
   int slot_first = 0, pf_slot[PF];
   if constexpr (!SPLIT) {
-    slot_first = idx[min(first_at, sel_cap - 1)];
+    slot_first = entry(first_at, 0);
 #pragma unroll
-    for (int k = 0; k < PF; ++k) pf_slot[k] = idx[min(tid + k * T, sel_cap - 1)];
+    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, k * kThreads);
   }
   // the query token's row (Section 4.2 append); fp32 rows are rounded once, here: every lane keeps the pieces of
   // the rounded row it would load from the cache (K: 16 bytes at ld_piece, V: its EV columns)
@@ -181,8 +198,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
 #pragma unroll
   for (int i = 0; i < VW; ++i) nv[i] = 0u;
   if (append) {
-    const gchar* const kn = (const gchar*)k_new_arg;
-    const gchar* const vn = (const gchar*)v_new_arg;
+    const gchar* const kn = (const gchar*)address(kn_lo, kn_vn_hi & 0xFFFF);
+    const gchar* const vn = (const gchar*)address(vn_lo, kn_vn_hi >> 16);
     if (cvt) {
       nk = pack8_bf16(kn + (new_row + ld_piece * 8) * 4);
       if constexpr (EV == 8) {
@@ -199,28 +216,20 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     }
   }
   pin_uniform(cnt_raw); pin_uniform(k_rec); pin_uniform(v_rec); pin_uniform(score_rec); pin_uniform(pending);
-  // (the remaining arguments: fetched in the same batch of scalar loads, not after it)
-  pin_uniform(A.cap); pin_uniform(A.lg_stride); pin_uniform(A.stage_b); pin_uniform(A.slot_stride_b);
-  pin_uniform(A.head_stride_b); pin_uniform(A.scale_log2); pin_uniform(A.accumulate);
-
-  const int lgs = A.lg_stride;
-  float* const s_logit = reinterpret_cast<float*>(smem);                 // [G][lgs]
-  int* const s_slot = reinterpret_cast<int*>(s_logit + (size_t)G * lgs); // [lgs]
-  char* const s_stage = reinterpret_cast<char*>(s_slot + lgs);           // [NW][stage_b]: K tile [16][ROWB], later partial out [G][D]
-  gchar* const k_base = k_rec + (long long)hk * A.head_stride_b;
-  gchar* const v_base = v_rec + (long long)hk * A.head_stride_b;
-  gfloat* const score = score_rec + (size_t)hk * A.cap;
-  ADSA_GLOBAL uint16_t* const out = reinterpret_cast<ADSA_GLOBAL uint16_t*>((gchar*)A.out) + ((size_t)b * HQ + (size_t)hk * G) * D;
-  gfloat* const lse = (gfloat*)A.lse + (size_t)b * HQ + (size_t)hk * G;
+  const long long head_stride_b = (long long)address(head_stride16, (heads_flags >> 19) & 0x1F) * 16;
+  gchar* const k_base = k_rec + hk * head_stride_b;
+  gchar* const v_base = v_rec + hk * head_stride_b;
+  gfloat* const score = score_rec + (size_t)hk * cap;
 
   const int cnt = min(cnt_raw, sel_cap);
   if (cnt <= 0) {                                    // inactive or rejected sequence: zero-filled rows
     if (chunk == 0) {
-      for (int o = tid; o < G * D; o += T) {
-        out[o] = 0;
-        if (o % D == 0) lse[o / D] = 0.0f;
+      const size_t row = (size_t)b * HQ + (size_t)hk * G;
+      for (int o = tid; o < G * D; o += kThreads) {
+        ((ADSA_GLOBAL uint16_t*)T.out)[row * D + o] = 0;
+        if (o % D == 0) ((gfloat*)T.lse)[row + o / D] = 0.0f;
       }
-      if (hk == 0 && tid == 0) advance_empty(sqp, A.advance);
+      if (hk == 0 && tid == 0) advance_empty(sqp, T.advance);
     }
     return;
   }
@@ -233,6 +242,11 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   const int t_begin = tile_begin * 16;
   const int len = min(cnt, tile_end * 16) - t_begin;           // tokens of this workgroup, numbered from 0 below
   const int n_tiles = tile_end - tile_begin;
+  // LDS: per wave a K tile [16][ROWB] that later holds its partial out [G][D], the slots, the logits [G][lgs]
+  const int stage_b = max(16 * ROWB, G * D * 4), lgs = n_tiles * 16 + 4;       // (rows 4 words apart modulo the banks)
+  char* const s_stage = smem;
+  int* const s_slot = reinterpret_cast<int*>(smem + NW * stage_b);
+  float* const s_logit = reinterpret_cast<float*>(s_slot + n_tiles * 16);
   s16x4 qb[NC];
 #pragma unroll
   for (int c2 = 0; c2 < NC / 2; ++c2) {
@@ -240,71 +254,77 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     qb[2 * c2] = as_bf16x4(x.x, x.y);
     qb[2 * c2 + 1] = as_bf16x4(x.z, x.w);
   }
-  const int new_slot = (append && pending >= 0 && pending < A.cap) ? pending : -1;
+  const int new_slot = (append && pending >= 0 && pending < cap) ? pending : -1;
 
-  // (the lambdas below work on copies: they capture by reference, and a reference to the kernel's argument
-  //  struct was measured to cost time in the multi-head kernel)
-  const long long slot_stride_b = A.slot_stride_b;
-  const float scale_log2 = A.scale_log2;
-  const bool keep_logits = A.accumulate != 0;
-  char* const stage = s_stage + wave * A.stage_b;    // LDS this wave owns
+  char* const stage = s_stage + wave * stage_b;      // LDS this wave owns
 
   // Ring of R tiles per wave.  Ring position u holds unit k of the wave, i.e. tile wave + k * NW, for k = u, u + R, ...
-  // A tile is requested as LT K loads followed by 4 V loads per lane, always in that order and with no branch in
-  // between, so that "the oldest K rows have arrived" is one in-order wait count.
+  // A tile is LT K loads and 4 V loads per lane.  Its K registers go to the next tile of the ring position as soon as they
+  // are in LDS, its V registers when they are multiplied, always in that order and with no branch in between, so that "the
+  // oldest K rows have arrived" is one in-order wait count and a wave has a tile in flight nearly all the time.  (32 x 8 lists
+  // x 647 x 128, G = 8: 17.0 us with both requested when the tile was done, 16.4 now; G = 16 on 512 pairs 36.2 and 34.2, on 158 pairs with
+  // 1335 tokens 55 and 50.)
   uint4 kr[R][LT];
   uint32_t vr[R][4][VW];
-  uint32_t fresh[R];                                 // bit l: K load l, bit 8 + i: V load i stands for the query token's own row
+  uint32_t fresh_k[R], fresh_v[R];                   // bit l: K load l, bit i: V load i stands for the query token's own row
   // byte offsets inside one head's rows fit 32 bits (cap <= 8192 slots, rows at most 64 KB apart): the loads then
   // take a uniform base and a 32-bit lane offset, two instructions of address arithmetic instead of a 64-bit product
-  const uint32_t stride32 = (uint32_t)slot_stride_b;
   const uint32_t k_lane_off = (uint32_t)ld_piece * 16u, v_lane_off = (uint32_t)r * (EV * 2);
-  auto request = [&](int u, const int (&sk)[LT], const int (&sv)[4]) {
-    // The query token's own slot is read like any other (valid memory of the cache; the row is stored at the end of
-    // this launch) and what arrives is replaced by the row held in registers when the tile is multiplied.
+  // The query token's own slot is read like any other (valid memory of the cache; the row is stored at the end of
+  // this launch) and what arrives is replaced by the row held in registers when the tile is multiplied.
+  auto in_order = [] {
+    asm volatile("" : : : "memory");                 // requests leave in ring order (the wait counts rely on it)
+    __builtin_amdgcn_sched_barrier(0);               // ... and before the arithmetic that follows, which waits for ITS rows
+  };
+  auto request_k = [&](int u, const int (&sk)[LT]) {
     uint32_t f = 0u;
 #pragma unroll
     for (int l = 0; l < LT; ++l) {
       kr[u][l] = load_stream16(k_base + ((uint32_t)sk[l] * stride32 + k_lane_off));
       f |= sk[l] == new_slot ? (1u << l) : 0u;
     }
+    fresh_k[u] = f;
+    in_order();
+  };
+  auto request_v = [&](int u, const int (&sv)[4]) {
+    uint32_t f = 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       vload<VW, true>(v_base + ((uint32_t)sv[i] * stride32 + v_lane_off), vr[u][i]);
-      f |= sv[i] == new_slot ? (1u << (8 + i)) : 0u;
+      f |= sv[i] == new_slot ? (1u << i) : 0u;
     }
-    fresh[u] = f;
-    asm volatile("" : : : "memory");                 // requests leave in ring order (the wait counts rely on it)
-    __builtin_amdgcn_sched_barrier(0);               // ... and before the next tile's arithmetic, which waits for ITS rows
+    fresh_v[u] = f;
+    in_order();
   };
-  auto issue = [&](int u, int tile) {
-    int sk[LT], sv[4];                               // all slots of the tile first: one LDS round trip, then the loads
+  auto slots_k = [&](int tile, int (&sk)[LT]) {      // (tiles past the end re-read the last row)
 #pragma unroll
-    for (int l = 0; l < LT; ++l) sk[l] = s_slot[min(tile * 16 + l * RPL + ld_row, len - 1)];   // (tiles past the end re-read the last row)
+    for (int l = 0; l < LT; ++l) sk[l] = s_slot[min(tile * 16 + l * RPL + ld_row, len - 1)];
+  };
+  auto slots_v = [&](int tile, int (&sv)[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) sv[i] = s_slot[min(tile * 16 + 4 * kg + i, len - 1)];
-    request(u, sk, sv);
   };
 
+  uint32_t tail = 0u;                                // lane i (modulo 16): dword i of T
   float m_run = -INFINITY, l_lane = 0.0f;            // online softmax of query g = r (l: this lane's tokens only)
   f32x4 acc[EV];                                     // acc[j][i] = partial out[g = 4*kg + i][d = EV*r + j]
 #pragma unroll
   for (int j = 0; j < EV; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  auto fold = [&](int u, int tile) {
-    if (__any(fresh[u] != 0u)) {                     // (rare) the tile holds the query token: its row comes from registers
+  // multiplies ring position u, which holds tile `tile`; refill: requests tile `next` for it on the way
+  auto fold = [&](int u, int tile, auto refill, int next) {
+    constexpr bool kRefill = decltype(refill)::value;
+    int sk[LT], sv[4];
+    if constexpr (kRefill) { slots_k(next, sk); slots_v(next, sv); }
+    if (__any(fresh_k[u] != 0u)) {                   // (rare) the tile holds the query token: its row comes from registers
 #pragma unroll
-      for (int l = 0; l < LT; ++l) kr[u][l] = pick16(((fresh[u] >> l) & 1u) != 0, nk, kr[u][l]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int w2 = 0; w2 < VW; ++w2) vr[u][i][w2] = (fresh[u] >> (8 + i)) & 1u ? nv[w2] : vr[u][i][w2];
-      }
+      for (int l = 0; l < LT; ++l) kr[u][l] = pick16(((fresh_k[u] >> l) & 1u) != 0, nk, kr[u][l]);
     }
     wave_lds_sync();                                 // the previous tile's operand reads are issued
 #pragma unroll
     for (int l = 0; l < LT; ++l)
       *reinterpret_cast<uint4*>(stage + (l * RPL + ld_row) * ROWB + ld_piece * 16) = kr[u][l];
+    if constexpr (kRefill) { in_order(); request_k(u, sk); }
     wave_lds_sync();
     const char* rowp = stage + r * ROWB + kg * (D / 2);     // token r of the tile, this lane's columns
     f32x4 s4 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -344,6 +364,13 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
       hi[i] = __float_as_uint(p) & 0xFFFF0000u;
       lo[i] = __float_as_uint(p - __uint_as_float(hi[i])) >> 16;     // exact difference, truncated
     }
+    if (__any(fresh_v[u] != 0u)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int w2 = 0; w2 < VW; ++w2) vr[u][i][w2] = (fresh_v[u] >> i) & 1u ? nv[w2] : vr[u][i][w2];
+      }
+    }
     const s16x4 a_hi = as_bf16x4((hi[0] >> 16) | hi[1], (hi[2] >> 16) | hi[3]);
     const s16x4 a_lo = as_bf16x4(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
 #pragma unroll
@@ -359,6 +386,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     }
     // the tile is multiplied completely before the loads that reuse its ring position are issued
     asm volatile("" : "+v"(m_run), "+v"(l_lane) : : "memory");
+    if constexpr (kRefill) request_v(u, sv);
   };
 
   {
@@ -376,7 +404,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         const int end = __builtin_amdgcn_readlane(slot_first, 16 * u + min(max(len - 1 - (wave + u * NW) * 16, 0), 15));
         slot_first = kg == u && first_at >= len ? end : slot_first;
       }
-      slot_first = min(max(slot_first, 0), A.cap - 1);
+      slot_first = min(max(slot_first, 0), cap - 1);
       int sk[R][LT], sv[R][4];
 #pragma unroll
       for (int u = 0; u < R; ++u) {
@@ -386,37 +414,44 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         for (int i = 0; i < 4; ++i) sv[u][i] = __shfl(slot_first, 16 * u + 4 * kg + i, kWave);
       }
 #pragma unroll
-      for (int u = 0; u < R; ++u) request(u, sk[u], sv[u]);
+      for (int u = 0; u < R; ++u) { request_k(u, sk[u]); request_v(u, sv[u]); }
     }
   // slots of the list, clamped into the cache, go to LDS (readers clamp their list position to the last token)
   if constexpr (!SPLIT) {
 #pragma unroll
     for (int k = 0; k < PF; ++k) {
-      const int j = tid + k * T;
-      if (j < len) s_slot[j] = min(max(pf_slot[k], 0), A.cap - 1);
+      const int j = tid + k * kThreads;
+      if (j < len) s_slot[j] = min(max(pf_slot[k], 0), cap - 1);
     }
-    for (int j = tid + PF * T; j < len; j += T) s_slot[j] = min(max(idx[j], 0), A.cap - 1);
+    for (int j = tid + PF * kThreads; j < len; j += kThreads) s_slot[j] = min(max(idx[j], 0), cap - 1);
   } else {
-    for (int j = tid; j < len; j += T) s_slot[j] = min(max(idx[t_begin + j], 0), A.cap - 1);
+    for (int j = tid; j < len; j += kThreads) s_slot[j] = min(max(idx[t_begin + j], 0), cap - 1);
   }
+    // (a vector load behind the first rows': its scalar form would be waited for with the record)
+    tail = ((const ADSA_GLOBAL uint32_t*)((const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes))[lane % 16];
     __syncthreads();
     if constexpr (SPLIT) {
 #pragma unroll
-      for (int u = 0; u < R; ++u) issue(u, wave + u * NW);
+      for (int u = 0; u < R; ++u) {
+        int sk[LT], sv[4];
+        slots_k(wave + u * NW, sk);
+        slots_v(wave + u * NW, sv);
+        request_k(u, sk);
+        request_v(u, sv);
+      }
     }
     int k0 = 0;                                      // unit at ring position 0
     for (int trip = 1; trip < n_trips; ++trip) {
 #pragma unroll
       for (int u = 0; u < R; ++u) {
-        fold(u, wave + (k0 + u) * NW);
-        issue(u, wave + (k0 + R + u) * NW);
+        fold(u, wave + (k0 + u) * NW, std::true_type(), wave + (k0 + R + u) * NW);
       }
       k0 += R;
     }
 #pragma unroll
     for (int u = 0; u < R; ++u) {
       const int tile = wave + (k0 + u) * NW;
-      if (tile < n_tiles) fold(u, tile);             // wave-uniform
+      if (tile < n_tiles) fold(u, tile, std::false_type(), 0);             // wave-uniform
     }
   }
   l_lane = xor_sum<32>(xor_sum<16>(l_lane));
@@ -445,23 +480,30 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
   }
   const float lse2 = M + __log2f(L), inv_l = 1.0f / L;
   const size_t hq0 = (size_t)b * HQ + (size_t)hk * G;           // first query head of this cache head
-  for (int o = tid; o < G * D; o += T) {
+  auto tail_word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)tail, i); };
+  auto tail_address = [&](size_t at) { return address(tail_word(at / 4), tail_word(at / 4 + 1)); };
+  ADSA_GLOBAL uint16_t* const out = (ADSA_GLOBAL uint16_t*)tail_address(offsetof(GqaTail, out)) + hq0 * D;
+  gfloat* const lse = (gfloat*)tail_address(offsetof(GqaTail, lse)) + hq0;
+  gfloat* const part_acc = (gfloat*)tail_address(offsetof(GqaTail, part_acc));
+  gfloat* const part_ml = (gfloat*)tail_address(offsetof(GqaTail, part_ml));
+  const int advance = tail_word(offsetof(GqaTail, advance) / 4);
+  for (int o = tid; o < G * D; o += kThreads) {
     const int g = __builtin_amdgcn_readfirstlane(o / D), d = o - g * D;       // (a wave's 64 columns belong to one query)
     float a = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) a = fmaf(reinterpret_cast<const float*>(s_stage + w * A.stage_b)[o], lane_f(wgt[w], g), a);
+    for (int w = 0; w < NW; ++w) a = fmaf(reinterpret_cast<const float*>(s_stage + w * stage_b)[o], lane_f(wgt[w], g), a);
     if constexpr (!SPLIT) {
       out[o] = (uint16_t)f32_to_bf16_rne(a * lane_f(inv_l, g));
       if (d == 0) lse[g] = lane_f(lse2, g) * kLn2;
     } else {                                         // this chunk's partial, relative to its own maximum
       const size_t pidx = (hq0 + g) * n_chunks + chunk;
-      A.part_acc[pidx * D + d] = a;
-      if (d == 0) { A.part_ml[pidx * 2] = lane_f(M, g); A.part_ml[pidx * 2 + 1] = lane_f(L, g); }
+      part_acc[pidx * D + d] = a;
+      if (d == 0) { part_ml[pidx * 2] = lane_f(M, g); part_ml[pidx * 2 + 1] = lane_f(L, g); }
     }
   }
   // Section 4.2 append: this cache head's rows of the new token, from the registers that attended them
   if (new_slot >= 0 && wave == 0 && chunk == n_chunks - 1) {
-    const long long off = (long long)new_slot * slot_stride_b;
+    const long long off = (long long)new_slot * stride32;
     if (ld_row == 0) store16(k_base + off + ld_piece * 16, nk);
     if (kg == 0) {
       if constexpr (VW == 4) store16(v_base + off + r * 16, make_uint4(nv[0], nv[1], nv[2], nv[3]));
@@ -477,8 +519,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
     // Each (cache head, slot) word is touched by exactly one thread of one workgroup per launch, so a
     // no-return hardware add gives the same fp32 sum as a load + store, without waiting for the load
     // (requesting the old values before the loop and storing plainly was measured: not faster).
-    if (A.accumulate) {
-      for (int t = tid; t < len; t += T) {
+    if (keep_logits) {
+      for (int t = tid; t < len; t += kThreads) {
         float inc = 0.0f;
         for (int g0 = 0; g0 < G; g0 += 8) {          // eight queries' logits in flight together
           float z[8];
@@ -491,14 +533,16 @@ __global__ __launch_bounds__(NW * kWave) void k_attend_gqa(adsa_seq* seqs_arg, c
         unsafeAtomicAdd((float*)(score + s_slot[t]), inc);
       }
     }
-    if (hk == 0 && tid == 0) advance_step(sqp, A.advance);     // no other workgroup reads step
+    if (hk == 0 && tid == 0) advance_step(sqp, advance);     // no other workgroup reads step
   } else {
     // ---------------- several chunks: this workgroup's partial and logits are in the workspace; k_gqa_finish, the next kernel
     // on the stream, merges them (the launch boundary orders the two and makes the stores visible on every XCD)
     if (keep_logits) {
+      gfloat* const logits = (gfloat*)tail_address(offsetof(GqaTail, logits));
+      const int lg_global = tail_word(offsetof(GqaTail, lg_global) / 4);
       for (int g = 0; g < G; ++g) {
-        float* const lg = A.logits + (hq0 + g) * A.lg_global + t_begin;
-        for (int t = tid; t < len; t += T) lg[t] = s_logit[(size_t)g * lgs + t];
+        gfloat* const lg = logits + (hq0 + g) * lg_global + t_begin;
+        for (int t = tid; t < len; t += kThreads) lg[t] = s_logit[(size_t)g * lgs + t];
       }
     }
   }
@@ -582,14 +626,20 @@ template <int D, int NW, bool SPLIT, int R>
 hipError_t launch_gqa_w(const GqaArgs& A, int n_seq, int n_chunks, size_t lds, hipStream_t st, hipEvent_t ev_start,
                         hipEvent_t ev_stop) {
   dim3 grid(A.n_heads, n_seq, n_chunks);     // (lists that need more than 64 KB of LDS: see gqa_prepare_kernels)
-  const int hgf = A.n_heads | (A.G << 16) | (A.append ? 1 << 24 : 0) | (A.new_f32 ? 1 << 25 : 0);
+  const uint32_t flags = A.n_heads | A.G << 9 | (A.append ? 0x10000 : 0) | (A.new_f32 ? 0x20000 : 0) | (A.accumulate ? 0x40000 : 0) | (uint32_t)(A.head_stride_b >> 36 & 0x1F) << 19 | n_chunks << 24;
+  const GqaTail T = {A.out, A.lse, A.logits, A.part_ml, A.part_acc, A.lg_global, A.advance, {}};
   // (a split launch is two kernels: the start event belongs to the first, the stop event to the second)
+  auto launch = [&](auto go) {
+    go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.q), lo32(A.k_new), lo32(A.v_new), hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.q),
+       hi16s(A.k_new, A.v_new), flags, (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, (uint32_t)A.slot_stride_b, (uint32_t)(A.head_stride_b / 16),
+       A.scale_log2, T);
+  };
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, SPLIT ? nullptr : ev_stop, 0,
-                          A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
+    launch([&](auto... args) {
+      hipExtLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), (uint32_t)lds, st, ev_start, SPLIT ? nullptr : ev_stop, 0, args...);
+    });
   else
-    hipLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), lds, st,
-                       A.seqs, A.sel_idx, A.sel_cnt, A.q, A.k_new, A.v_new, hgf, A.sel_cap, A);
+    launch([&](auto... args) { hipLaunchKernelGGL((k_attend_gqa<D, NW, SPLIT, R>), grid, dim3(NW * kWave), lds, st, args...); });
   if constexpr (SPLIT) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -663,8 +713,7 @@ hipError_t launch_attend_gqa(const adsa_params& p, const AttendPlan& plan, adsa_
   A.part_ml = reinterpret_cast<float*>(ws + w.part_ml_off);
   A.part_acc = reinterpret_cast<float*>(ws + w.part_acc_off);
   A.lg_global = gqa_global_logit_stride(p);
-  A.n_heads = p.n_heads; A.G = p.q_per_kv; A.sel_cap = p.sel_cap; A.lg_stride = gqa_logit_stride(p, plan.n_chunks);
-  A.cap = p.cap; A.stage_b = (int)gqa_stage_bytes(p);
+  A.n_heads = p.n_heads; A.G = p.q_per_kv; A.sel_cap = p.sel_cap; A.cap = p.cap;
   A.accumulate = accumulate ? 1 : 0; A.append = append ? 1 : 0; A.advance = advance;
   A.new_f32 = (new_f32 && append) ? 1 : 0;
   A.slot_stride_b = (long long)p.kv_slot_stride * 2;
