@@ -174,6 +174,10 @@ class ModelBatch(LayerBatch):
         ws = B.adsa_workspace_bytes(layer_params)
         self.layer_workspace = torch.empty(ws, dtype=torch.uint8, device=self.device)
         B.adsa_workspace_init(layer_params, self.layer_workspace)
+        # bytes from one sequence's row to the next, as the C ABI has them: seqs, sel_idx, sel_cnt, out, lse
+        hq = B.query_heads(layer_params)
+        rows = (_SEQ_BYTES, layer_params.sel_cap * 4, 4, hq * layer_params.head_dim * self.K.element_size(), hq * 4)
+        self._layer_offsets = [tuple(layer * self.n_per_layer * r for r in rows) for layer in range(n_layers)]
 
     def select_all(self, flags: int = 0, stream=None):
         B.adsa_select(self.params, self.seqs, self.sel_idx, self.sel_cnt, self.workspace, flags, stream)
@@ -184,9 +188,7 @@ class ModelBatch(LayerBatch):
     def attend_layer(self, layer: int, q, k_new=None, v_new=None, flags: int = 0, stream=None):
         if not 0 <= layer < self.n_layers:
             raise B.AdsaError(-1, "adsa_attend")
-        # (addresses instead of slices: a tensor slice takes as long as a third of a launch)
-        b0, out, lse = layer * self.n_per_layer, self.out, self.lse
-        B.adsa_attend(self.layer_params, self.seqs.data_ptr() + b0 * _SEQ_BYTES, q,
-                      self.sel_idx.data_ptr() + b0 * self.sel_idx.stride(0) * 4, self.sel_cnt.data_ptr() + b0 * 4,
-                      out.data_ptr() + b0 * out.stride(0) * out.element_size(), lse.data_ptr() + b0 * lse.stride(0) * 4,
-                      self.layer_workspace, flags, k_new, v_new, stream)
+        # (tensor and byte offset instead of slices: a tensor slice takes as long as a third of a launch)
+        seqs, idx, cnt, out, lse = self._layer_offsets[layer]
+        B.adsa_attend(self.layer_params, (self.seqs, seqs), q, (self.sel_idx, idx), (self.sel_cnt, cnt), (self.out, out),
+                      (self.lse, lse), self.layer_workspace, flags, k_new, v_new, stream)

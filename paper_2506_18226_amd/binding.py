@@ -1,12 +1,15 @@
-"""ctypes binding of the ADSA HIP library: same names as include/adsa.h, marshalling only.
+"""Python binding of the ADSA HIP library: same names as include/adsa.h, marshalling only.
 
 Every function takes torch tensors (device memory) or raw integers for pointers, packs the
-host parameter struct and calls the C entry point.  No step of the decode path runs here.
+host parameter struct and calls the C entry point.  No step of the decode path runs here.  The calls of a decode step
+go through a small CPython module (csrc/native_binding.c), the others through ctypes.
 The library must be built (paper_2506_18226_amd/build.py) -- there is no fallback.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
@@ -110,6 +113,34 @@ def load_library() -> C.CDLL:
     return _lib
 
 
+_call = None                      # the CPython module's call()
+_entry = {}                       # C entry point -> its address
+
+
+def _load_native():
+    global _call
+    lib, path = load_library(), _build.NATIVE_PATH
+    if not os.path.exists(path):
+        raise FileNotFoundError(f"{path} is missing: run `python -m paper_2506_18226_amd.build` (or __graft_entry__.build()) first; "
+                                "there is no fallback path")
+    loader = importlib.machinery.ExtensionFileLoader("_adsa_native", path)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_adsa_native", loader))
+    loader.exec_module(module)
+    for name in ("adsa_select", "adsa_attend", "adsa_compact", "adsa_step", "adsa_step_static"):
+        _entry[name] = C.cast(getattr(lib, name), C.c_void_p).value
+    module.set_params_type(AdsaParams)
+    _call = module.call
+
+
+def _enqueue(name: str, params, flags, workspace, stream, *pointers) -> None:
+    """One C call; seqs is the first of the pointers.  workspace False: the entry point has none."""
+    if _call is None:
+        _load_native()
+    rc = _call(_entry[name], params, flags, workspace, _current_stream() if stream is None else _stream(stream), *pointers)
+    if rc != 0:
+        raise AdsaError(rc, name)
+
+
 def _ptr(x) -> Optional[int]:
     """Device pointer of a torch tensor, or the integer itself, or None."""
     return x if x is None or isinstance(x, int) else x.data_ptr()
@@ -195,34 +226,26 @@ def adsa_workspace_init(params, workspace, stream=None) -> None:
 
 
 def adsa_select(params, seqs, sel_idx, sel_cnt, workspace=None, flags=0, stream=None) -> None:
-    _check(load_library().adsa_select(C.byref(params), _ptr(seqs), _ptr(sel_idx), _ptr(sel_cnt), flags,
-                                      _ptr(workspace), _nbytes(workspace), _stream(stream)), "adsa_select")
+    _enqueue("adsa_select", params, flags, workspace, stream, seqs, sel_idx, sel_cnt)
 
 
 def adsa_attend(params, seqs, q, sel_idx, sel_cnt, out, lse, workspace, flags=0, k_new=None, v_new=None,
                 stream=None) -> None:
-    _check(load_library().adsa_attend(C.byref(params), _ptr(seqs), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                      _ptr(sel_idx), _ptr(sel_cnt), _ptr(out), _ptr(lse), flags,
-                                      _ptr(workspace), _nbytes(workspace), _stream(stream)), "adsa_attend")
+    _enqueue("adsa_attend", params, flags, workspace, stream, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse)
 
 
 def adsa_compact(params, seqs, keep_map, workspace, flags=0, stream=None) -> None:
-    _check(load_library().adsa_compact(C.byref(params), _ptr(seqs), _ptr(keep_map), flags, _ptr(workspace),
-                                       _nbytes(workspace), _stream(stream)), "adsa_compact")
+    _enqueue("adsa_compact", params, flags, workspace, stream, seqs, keep_map)
 
 
 def adsa_step(params, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, workspace,
               flags=0, stream=None) -> None:
-    _check(load_library().adsa_step(C.byref(params), _ptr(seqs), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                    _ptr(lse), _ptr(sel_idx), _ptr(sel_cnt), _ptr(keep_map), flags,
-                                    _ptr(workspace), _nbytes(workspace), _stream(stream)), "adsa_step")
+    _enqueue("adsa_step", params, flags, workspace, stream, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map)
 
 
 def adsa_step_static(params, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, flags=0, stream=None) -> None:
     """adsa_step on the library's built-in scratch array: no workspace argument, no allocation."""
-    _check(load_library().adsa_step_static(C.byref(params), _ptr(seqs), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                           _ptr(lse), _ptr(sel_idx), _ptr(sel_cnt), _ptr(keep_map), flags,
-                                           _stream(stream)), "adsa_step_static")
+    _enqueue("adsa_step_static", params, flags, False, stream, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map)
 
 
 def adsa_profile_enable(on: bool) -> None:

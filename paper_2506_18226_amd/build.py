@@ -9,6 +9,7 @@ ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB_DIR = os.path.join(_HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libadsa_hip.so")
+NATIVE_PATH = os.path.join(LIB_DIR, "_adsa_native.so")       # CPython side of binding.py
 CEILING_PATH = os.path.join(LIB_DIR, "read_ceiling")
 SOURCES = ["api.hip", "select_compact.hip", "attend.hip", "attend_gqa.hip", "vcos.hip"]
 
@@ -49,7 +50,18 @@ def build_library(verbose: bool = False) -> str:
     # measurement aid: the plain-read ceiling the attention kernel's roofline fraction is read against
     _compile_one(([hipcc, *[f for f in flags if f != "-fPIC"], os.path.join(CSRC, "read_ceiling.hip"), "-o", CEILING_PATH],
                   verbose))
+    build_native(verbose)
     return LIB_PATH
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compile the CPython module the binding's calls go through (host code, gcc), for the running interpreter."""
+    import sysconfig
+
+    os.makedirs(LIB_DIR, exist_ok=True)
+    _compile_one((["gcc", "-O2", "-std=c11", "-shared", "-fPIC", "-Wall", "-Wextra", "-I", sysconfig.get_paths()["include"],
+                   "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "native_binding.c"), "-o", NATIVE_PATH], verbose))
+    return NATIVE_PATH
 
 
 if __name__ == "__main__":
