@@ -16,6 +16,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 typedef ADSA_GLOBAL char gchar;
 typedef ADSA_GLOBAL float gfloat;
 typedef ADSA_GLOBAL int32_t gint;
+typedef ADSA_GLOBAL adsa_seq gseq;
 
 // Addresses have 48 bits: as leading kernel arguments of the attention launches, their low halves and, two to a dword, the rest
 constexpr int kLeadBytes = 14 * 4;                 // of the arguments before the block that is not preloaded

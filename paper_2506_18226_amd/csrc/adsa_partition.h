@@ -6,56 +6,88 @@
 
 namespace adsa {
 
-// Geometry of one sequence's query for its current decode step s.
+// j / W and j mod W for 0 <= j < 2^24 without an integer division (some 25 instructions a slot): inv_w is 1 / W rounded to the
+// nearest float, so the product is less than 1 away from the quotient (by 2^-23 of it, at most 0.67 where 1 / W is inexact).
+struct GridWidth {
+  int W;
+  float inv_w;
+  __device__ __forceinline__ int row(int j, int* col) const {
+    int q = (int)((float)j * inv_w), c = j - q * W;
+    if (c < 0) { c += W; --q; }
+    if (c >= W) { c -= W; ++q; }
+    *col = c;
+    return q;
+  }
+};
+
+// Geometry of one sequence's query for its current decode step s, as ranges of image indices j = pos - P.
 struct QueryCell {
   int P;              // grid origin (absolute position of image token 0)
   int n_keep_prefix;  // pinned leading positions
   int jq;             // image index of the query token (s - 1)
-  int r, col;         // its grid cell
-  int W, R, w;
-  int recent_m;       // > 0: 1-D window of the m most recent image tokens instead of the 2-D one
+  int col, w;         // its column; column radius of the window
+  int local_from;     // from here on everything is local: the query's row, or the recent_m most recent tokens (1-D window)
+  int above_from;     // from here on local within w columns: the R rows above (2-D window only)
+  int keep_from, keep_to;      // what an eviction at this step's row end protects: the last R rows, or the m - 1 most recent tokens (the
+                               // next row's first query, jq + 1, reaches back furthest, to j > jq + 1 - m)
+  GridWidth grid;
 };
 
-__device__ __forceinline__ QueryCell make_query_cell(const adsa_seq& sq, int s, int W, int R, int w,
-                                                     int recent_m = 0) {
+// (Seq: adsa_seq, in whatever address space)
+template <typename Seq>
+__device__ __forceinline__ QueryCell make_query_cell(const Seq& sq, int s, const GridWidth& grid, int R, int w, int recent_m) {
   QueryCell c;
-  c.P = sq.grid_origin; c.n_keep_prefix = sq.n_keep_prefix; c.jq = s - 1;
-  c.r = s >= 1 ? c.jq / W : 0;
-  c.col = s >= 1 ? c.jq - c.r * W : 0;
-  c.W = W; c.R = R; c.w = w; c.recent_m = recent_m;
+  c.P = sq.grid_origin; c.n_keep_prefix = sq.n_keep_prefix; c.jq = s - 1; c.w = w; c.grid = grid;
+  int r = 0;
+  c.col = 0;
+  if (s >= 1) r = grid.row(c.jq, &c.col);
+  if (recent_m > 0) {
+    c.local_from = c.jq - recent_m + 1;
+    c.above_from = c.keep_to = 0x7FFFFFFF;
+    c.keep_from = c.jq + 2 - recent_m;
+  } else {
+    c.local_from = r * grid.W;
+    c.above_from = R >= r ? 0 : (r - R) * grid.W;
+    c.keep_from = R > r ? 0 : (r - R + 1) * grid.W;
+    c.keep_to = (r + 1) * grid.W - 1;
+  }
   return c;
 }
 
 // Attention-time partition: 0 = pinned prefix or local window (always attended), 1 = candidate
 // ("previous"), -1 = entry newer than the query (malformed state).
 __device__ __forceinline__ int select_class(const QueryCell& c, int pos) {
-  if (pos < c.n_keep_prefix) return 0;
-  if (pos < c.P) return 1;
   const int j = pos - c.P;
-  if (j > c.jq) return -1;
-  if (c.recent_m > 0) return j > c.jq - c.recent_m ? 0 : 1;
-  const int rj = j / c.W, cj = j - rj * c.W;
-  const int dc = cj > c.col ? cj - c.col : c.col - cj;
-  const bool local = (rj == c.r) || (rj >= c.r - c.R && rj < c.r && dc <= c.w);
-  return local ? 0 : 1;
+  int col;
+  (void)c.grid.row(j, &col);                         // (of no meaning where j is no image index, and not used there)
+  const int d = col - c.col, dc = d < 0 ? -d : d;
+  const bool local = j >= c.local_from || (j >= c.above_from && dc <= c.w);
+  const int image = j > c.jq ? -1 : local ? 0 : 1;
+  return pos < c.n_keep_prefix ? 0 : pos < c.P ? 1 : image;
 }
 
-// Eviction-time partition at the end of row r: 0 = pinned prefix or a token some window of the next
-// row needs -- the last R completed rows (2-D window) or the m - 1 most recent tokens (1-D window: the
-// next row's first query, jq + 1, reaches back furthest, to j > jq + 1 - m) --, 1 = competes for the budget.
+// Eviction-time partition at the end of a row: 0 = pinned prefix or a token some window of the next row needs, 1 = competes for
+// the budget.
 __device__ __forceinline__ int evict_class(const QueryCell& c, int pos) {
-  if (pos < c.n_keep_prefix) return 0;
-  if (pos >= c.P) {
-    const int j = pos - c.P;
-    if (c.recent_m > 0) return j > c.jq + 1 - c.recent_m ? 0 : 1;
-    const int rj = j / c.W;
-    if (rj >= c.r - c.R + 1 && rj <= c.r) return 0;
-  }
-  return 1;
+  const int j = pos - c.P;
+  return pos < c.n_keep_prefix || (pos >= c.P && j >= c.keep_from && j <= c.keep_to) ? 0 : 1;
 }
 
-__device__ __forceinline__ bool is_row_end(int s, int grid_h, int W) {
-  return s >= 1 && s <= grid_h * W && ((s - 1) % W == W - 1);
+// s: the step the cell was made for; total: image tokens of the grid
+__device__ __forceinline__ bool is_row_end(const QueryCell& c, int s, int total) {
+  return s >= 1 && s <= total && c.col == c.grid.W - 1;
+}
+
+// Budget of a step: floor((P + s) * num / den) within [0, ADSA_MAX_CAP], or the given number.  (A 64-bit division is some 150
+// instructions; a quotient below 8192 is found by a float one to within 1.)
+template <typename Seq>
+__device__ __forceinline__ int effective_budget(const Seq& q, int s) {
+  if (q.budget_den <= 0) return q.budget < 0 ? 0 : q.budget > ADSA_MAX_CAP ? ADSA_MAX_CAP : q.budget;
+  const long long x = ((long long)q.grid_origin + s) * q.budget_num, den = q.budget_den;
+  if (x <= 0) return 0;
+  if (x >= den * ADSA_MAX_CAP) return ADSA_MAX_CAP;
+  const int b = (int)((float)x / (float)den);
+  return b * den > x ? b - 1 : (b + 1) * den <= x ? b + 1 : b;
 }
 
 }  // namespace adsa

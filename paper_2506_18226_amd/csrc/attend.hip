@@ -662,18 +662,22 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
 // slice adds the probabilities of its kFinishTokens tokens to the head's score row.
 constexpr int kFinishThreads = 256, kFinishTokens = 4 * kFinishThreads;
 template <int EB, int D>
-__global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, int n_chunks) {
+__global__ __launch_bounds__(kFinishThreads) void k_attend_finish(
+    uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t out_lo, uint32_t lse_lo, uint32_t lg_lo, uint32_t ml_lo, uint32_t acc_lo,
+    uint32_t seqs_idx_hi, uint32_t cnt_out_hi, uint32_t lse_lg_hi, uint32_t ml_acc_hi, uint32_t caps, uint32_t flags) {
+  const int n_heads = flags & 0x1FF, advance = (flags >> 18) & 3, n_chunks = flags >> 24, cap = caps & 0xFFFF, sel_cap = caps >> 16;
+  const bool accumulate = (flags & 0x10000) != 0, vcos_fused = (flags & 0x20000) != 0;
   const int slice = blockIdx.x, head = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)(A.seqs + b);
-  const int cnt = min(((const gint*)A.sel_cnt)[b], A.sel_cap);
+  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)address(seqs_lo, seqs_idx_hi & 0xFFFF) + b;
+  const int cnt = min(((const gint*)address(cnt_lo, cnt_out_hi & 0xFFFF))[b], sel_cap);
   gfloat* const score = (gfloat*)sqp->score;
-  gfloat* const u_state = A.vcos_fused ? (gfloat*)sqp->vcos_u : nullptr;
+  gfloat* const u_state = vcos_fused ? (gfloat*)sqp->vcos_u : nullptr;
   if (cnt <= 0 || slice * kFinishTokens >= cnt) return;      // (inactive sequences: zero rows, already written)
-  const size_t row = (size_t)b * A.n_heads + head;
-  const gfloat* const ml = (const gfloat*)A.part_ml + row * n_chunks * 2;
-  const gfloat* const acc = (const gfloat*)A.part_acc + row * n_chunks * D;
-  const gfloat* const lg = (const gfloat*)A.logits + row * A.lg_stride;
-  const gint* const idx = (const gint*)A.sel_idx + (size_t)b * A.sel_cap;
+  const size_t row = (size_t)b * n_heads + head;
+  const gfloat* const ml = (const gfloat*)address(ml_lo, ml_acc_hi & 0xFFFF) + row * n_chunks * 2;
+  const gfloat* const acc = (const gfloat*)address(acc_lo, ml_acc_hi >> 16) + row * n_chunks * D;
+  const gfloat* const lg = (const gfloat*)address(lg_lo, lse_lg_hi >> 16) + row * ((sel_cap + 3) / 4 * 4);
+  const gint* const idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
   // chunks beyond a short list hold nothing (their workspace words are stale)
   const bool merge = slice == 0 && tid < D;
   float mc[kMaxChunks], lc[kMaxChunks], ac[kMaxChunks];
@@ -687,15 +691,15 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
   constexpr int B = kFinishTokens / kFinishThreads;
   float z[B], old[B];
   int slot[B];
-  if (A.accumulate) {
+  if (accumulate) {
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int j = min(slice * kFinishTokens + u * kFinishThreads + tid, cnt - 1);
-      slot[u] = min(max(idx[j], 0), A.cap - 1);
+      slot[u] = min(max(idx[j], 0), cap - 1);
       z[u] = lg[j];
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u) old[u] = score[(size_t)head * A.cap + slot[u]];
+    for (int u = 0; u < B; ++u) old[u] = score[(size_t)head * cap + slot[u]];
   }
   float M = -INFINITY, L = 0.0f;
 #pragma unroll
@@ -712,24 +716,24 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(AttendArgs A, 
     for (int c = 0; c < kMaxChunks; ++c) a = fmaf(ac[c], mc[c], a);
     const float val = __fdividef(a, L);
     const size_t oi = row * D + tid;
-    if (EB == 4) reinterpret_cast<gfloat*>((gchar*)A.out)[oi] = val;
-    else reinterpret_cast<ADSA_GLOBAL uint16_t*>((gchar*)A.out)[oi] = (uint16_t)f32_to_bf16_rne(val);
-    if (tid == 0) ((gfloat*)A.lse)[row] = lse2 * kLn2;
+    if (EB == 4) reinterpret_cast<gfloat*>((gchar*)address(out_lo, cnt_out_hi >> 16))[oi] = val;
+    else reinterpret_cast<ADSA_GLOBAL uint16_t*>((gchar*)address(out_lo, cnt_out_hi >> 16))[oi] = (uint16_t)f32_to_bf16_rne(val);
+    if (tid == 0) ((gfloat*)address(lse_lo, lse_lg_hi & 0xFFFF))[row] = lse2 * kLn2;
   }
-  if (A.accumulate) {
+  if (accumulate) {
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int j = slice * kFinishTokens + u * kFinishThreads + tid;
-      if (j < cnt) score[(size_t)head * A.cap + slot[u]] = old[u] + fast_exp2(z[u] - lse2);
+      if (j < cnt) score[(size_t)head * cap + slot[u]] = old[u] + fast_exp2(z[u] - lse2);
     }
   }
   if (slice == 0 && head == 0 && tid == 0) {                 // last act on the sequence: see k_attend
     if (u_state) {
-      gfloat* tags = u_state + (size_t)A.n_heads * D;
+      gfloat* tags = u_state + (size_t)n_heads * D;
       const float want = (float)(sqp->step + 2);
       tags[1] = tags[0] == want ? want : 0.0f;
     }
-    advance_step(sqp, A.advance);
+    advance_step(sqp, advance);
   }
 }
 
@@ -763,10 +767,16 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 fgrid(A.accumulate ? (A.sel_cap + kFinishTokens - 1) / kFinishTokens : 1, A.n_heads, n_seq);
+    const uint32_t fflags = A.n_heads | (A.accumulate ? 0x10000 : 0) | (A.vcos_fused ? 0x20000 : 0) | (uint32_t)A.advance << 18 | plan.n_chunks << 24;
+    auto finish = [&](auto go) {
+      go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.out), lo32(A.lse), lo32(A.logits), lo32(A.part_ml), lo32(A.part_acc),
+         hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.out), hi16s(A.lse, A.logits), hi16s(A.part_ml, A.part_acc),
+         (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, fflags);
+    };
     if (ev_start && ev_stop)
-      hipExtLaunchKernelGGL((k_attend_finish<EB, D>), fgrid, dim3(kFinishThreads), 0, st, nullptr, ev_stop, 0, A, plan.n_chunks);
+      finish([&](auto... args) { hipExtLaunchKernelGGL((k_attend_finish<EB, D>), fgrid, dim3(kFinishThreads), 0, st, nullptr, ev_stop, 0, args...); });
     else
-      hipLaunchKernelGGL((k_attend_finish<EB, D>), fgrid, dim3(kFinishThreads), 0, st, A, plan.n_chunks);
+      finish([&](auto... args) { hipLaunchKernelGGL((k_attend_finish<EB, D>), fgrid, dim3(kFinishThreads), 0, st, args...); });
   }
   return hipGetLastError();
 }

@@ -554,23 +554,28 @@ __global__ __launch_bounds__(NW * kWave, R > ring(D) ? 1 : 4) void k_attend_gqa(
 constexpr int kFinishThreads = 256, kFinishTokens = 2 * kFinishThreads;
 static_assert(kMaxChunks == 16 && kFinishThreads == 16 * 16, "one thread per (query, chunk), a query's chunks in one 16-lane row");
 template <int D>
-__global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_chunks) {
+__global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(
+    uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t out_lo, uint32_t lse_lo, uint32_t lg_lo, uint32_t ml_lo, uint32_t acc_lo,
+    uint32_t seqs_idx_hi, uint32_t cnt_out_hi, uint32_t lse_lg_hi, uint32_t ml_acc_hi, uint32_t caps, uint32_t flags) {
+  const int n_heads = flags & 0x1FF, G = (flags >> 9) & 0x1F, advance = (flags >> 18) & 3, n_chunks = flags >> 24, cap = caps & 0xFFFF, sel_cap = caps >> 16;
+  const int lg_global = (sel_cap + 15) / 16 * 16 + 16;
+  const bool accumulate = (flags & 0x10000) != 0;
   __shared__ float s_w[16][kMaxChunks], s_lse2[16], s_l[16];
   const int slice = blockIdx.x, hk = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)(A.seqs + b);
-  const int cnt = min(((const gint*)A.sel_cnt)[b], A.sel_cap), G = A.G;
+  ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)address(seqs_lo, seqs_idx_hi & 0xFFFF) + b;
+  const int cnt = min(((const gint*)address(cnt_lo, cnt_out_hi & 0xFFFF))[b], sel_cap);
   if (cnt <= 0 || slice * kFinishTokens >= cnt) return;      // (inactive sequences: zero rows, already written)
-  const size_t hq0 = ((size_t)b * A.n_heads + hk) * G;
+  const size_t hq0 = ((size_t)b * n_heads + hk) * G;
   const unsigned tiles = (unsigned)(cnt + 15) / 16;
   auto on = [&](int c) {                                     // chunks without a tile hold nothing (their workspace words are stale)
     return c < n_chunks && (tiles * (unsigned)c) / (unsigned)n_chunks < (tiles * (unsigned)(c + 1)) / (unsigned)n_chunks;
   };
-  const gfloat* const ml = (const gfloat*)A.part_ml;
-  const gint* const idx = (const gint*)A.sel_idx + (size_t)b * A.sel_cap;
+  const gfloat* const ml = (const gfloat*)address(ml_lo, ml_acc_hi & 0xFFFF);
+  const gint* const idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
   const int t0 = slice * kFinishTokens + tid;
   int slot[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) slot[u] = min(max(idx[min(t0 + u * kFinishThreads, cnt - 1)], 0), A.cap - 1);
+  for (int u = 0; u < 2; ++u) slot[u] = min(max(idx[min(t0 + u * kFinishThreads, cnt - 1)], 0), cap - 1);
   {
     const int g = tid / 16, c = tid % 16;
     const bool have = g < G && on(c);
@@ -587,31 +592,31 @@ __global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_
   }
   __syncthreads();
   if (slice == 0) {
-    ADSA_GLOBAL uint16_t* const out = reinterpret_cast<ADSA_GLOBAL uint16_t*>((gchar*)A.out) + hq0 * D;
+    ADSA_GLOBAL uint16_t* const out = (ADSA_GLOBAL uint16_t*)address(out_lo, cnt_out_hi >> 16) + hq0 * D;
     for (int o = tid; o < G * D; o += kFinishThreads) {
       const int g = o / D, d = o - g * D;
-      const gfloat* const acc = (const gfloat*)A.part_acc + (hq0 + g) * n_chunks * D + d;
+      const gfloat* const acc = (const gfloat*)address(acc_lo, ml_acc_hi >> 16) + (hq0 + g) * n_chunks * D + d;
       float ac[kMaxChunks], a = 0.0f;
 #pragma unroll
       for (int c = 0; c < kMaxChunks; ++c) ac[c] = on(c) ? acc[(size_t)c * D] : 0.0f;
 #pragma unroll
       for (int c = 0; c < kMaxChunks; ++c) a = fmaf(ac[c], s_w[g][c], a);
       out[o] = (uint16_t)f32_to_bf16_rne(__fdividef(a, s_l[g]));
-      if (d == 0) ((gfloat*)A.lse)[hq0 + g] = s_lse2[g] * kLn2;
+      if (d == 0) ((gfloat*)address(lse_lo, lse_lg_hi & 0xFFFF))[hq0 + g] = s_lse2[g] * kLn2;
     }
   }
-  if (A.accumulate) {
-    gfloat* const score = (gfloat*)sqp->score + (size_t)hk * A.cap;
+  if (accumulate) {
+    gfloat* const score = (gfloat*)sqp->score + (size_t)hk * cap;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int t = t0 + u * kFinishThreads;
       if (t >= cnt) continue;
-      const gfloat* const lg = (const gfloat*)A.logits + hq0 * A.lg_global + t;
+      const gfloat* const lg = (const gfloat*)address(lg_lo, lse_lg_hi >> 16) + hq0 * lg_global + t;
       float inc = 0.0f;
       for (int g0 = 0; g0 < G; g0 += 8) {
         float z[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) z[k] = lg[(size_t)min(g0 + k, G - 1) * A.lg_global];
+        for (int k = 0; k < 8; ++k) z[k] = lg[(size_t)min(g0 + k, G - 1) * lg_global];
 #pragma unroll
         for (int k = 0; k < 8; ++k)
           if (g0 + k < G) inc += fast_exp2(z[k] - s_lse2[g0 + k]);
@@ -619,7 +624,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_gqa_finish(GqaArgs A, int n_
       unsafeAtomicAdd((float*)(score + slot[u]), inc);
     }
   }
-  if (slice == 0 && hk == 0 && tid == 0) advance_step(sqp, A.advance);
+  if (slice == 0 && hk == 0 && tid == 0) advance_step(sqp, advance);
 }
 
 template <int D, int NW, bool SPLIT, int R>
@@ -644,10 +649,16 @@ hipError_t launch_gqa_w(const GqaArgs& A, int n_seq, int n_chunks, size_t lds, h
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 fgrid(A.accumulate ? (A.sel_cap + kFinishTokens - 1) / kFinishTokens : 1, A.n_heads, n_seq);
+    const uint32_t fflags = A.n_heads | A.G << 9 | (A.accumulate ? 0x10000 : 0) | (uint32_t)A.advance << 18 | n_chunks << 24;
+    auto finish = [&](auto go) {
+      go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.out), lo32(A.lse), lo32(A.logits), lo32(A.part_ml), lo32(A.part_acc),
+         hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.out), hi16s(A.lse, A.logits), hi16s(A.part_ml, A.part_acc),
+         (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, fflags);
+    };
     if (ev_start && ev_stop)
-      hipExtLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, nullptr, ev_stop, 0, A, n_chunks);
+      finish([&](auto... args) { hipExtLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, nullptr, ev_stop, 0, args...); });
     else
-      hipLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, A, n_chunks);
+      finish([&](auto... args) { hipLaunchKernelGGL((k_gqa_finish<D>), fgrid, dim3(kFinishThreads), 0, st, args...); });
   }
   return hipGetLastError();
 }

@@ -217,20 +217,23 @@ __device__ __forceinline__ uint32_t place_kept(RankShared& sh, uint32_t sure, ui
   return take;
 }
 
-__device__ __forceinline__ int effective_budget(const adsa_seq& q, int s) {
-  long long b = q.budget;
-  if (q.budget_den > 0) b = ((long long)(q.grid_origin + s) * q.budget_num) / q.budget_den;
-  if (b < 0) b = 0;
-  if (b > ADSA_MAX_CAP) b = ADSA_MAX_CAP;
-  return (int)b;
-}
-
-struct LaunchShape {
-  int n_heads, head_dim, elem_bytes;
-  int grid_h, grid_w, R, w;
-  int cap, sel_cap, score_mode, score_rows, recent_m, evict_policy;
-  long long slot_stride_b, head_stride_b;    // bytes
+// The small arguments of the ranking kernels as preloaded dwords (see k_attend on what a load of the argument block costs):
+// flags: score rows | score mode << 10 | eviction policy << 13 | two switches << 15, 16
+struct RankFlags {
+  int rows, mode, policy;
+  bool a, b;
+  __device__ __forceinline__ explicit RankFlags(uint32_t f) : rows(f & 0x3FF), mode((f >> 10) & 7), policy((f >> 13) & 3), a((f >> 15) & 1), b((f >> 16) & 1) {}
 };
+static inline uint32_t rank_flags(const adsa_params& p, bool a, bool b) {
+  return score_rows(p) | p.score_mode << 10 | p.evict_policy << 13 | (a ? 1u << 15 : 0u) | (b ? 1u << 16 : 0u);
+}
+static inline float inv_width(const adsa_params& p) { return 1.0f / (float)p.grid_w; }
+
+// element i of an array at a uniform address, without 64-bit arithmetic per lane
+template <typename T>
+__device__ __forceinline__ ADSA_GLOBAL T& elem(ADSA_GLOBAL T* base, uint32_t i) { return *(ADSA_GLOBAL T*)((gchar*)base + i * (uint32_t)sizeof(T)); }
+template <typename T>
+__device__ __forceinline__ T elem(const ADSA_GLOBAL T* base, uint32_t i) { return *(const ADSA_GLOBAL T*)((const gchar*)base + i * (uint32_t)sizeof(T)); }
 
 // v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32 adds.  The loads of all slots and of two
 // batches of rows are in flight together: one memory round trip for up to 2 * RB + 1 rows.
@@ -242,10 +245,10 @@ __device__ __forceinline__ void rank_values(const gfloat* score, int rows, int c
 #pragma unroll
     for (int k = 0; k < RB; ++k)
 #pragma unroll
-      for (int u = 0; u < S; ++u) t[u][k] = score[(size_t)min(r0 + k, rows - 1) * cap + idx[u]];    // (rows past the last: not added)
+      for (int u = 0; u < S; ++u) t[u][k] = elem(score + (size_t)min(r0 + k, rows - 1) * cap, idx[u]);    // (rows past the last: not added)
   };
 #pragma unroll
-  for (int u = 0; u < S; ++u) v[u] = score[idx[u]];
+  for (int u = 0; u < S; ++u) v[u] = elem(score, idx[u]);
   if (rows == 1) return;
   load_rows(1, cur);
   for (int r = 1; r < rows; r += RB) {
@@ -272,9 +275,9 @@ __device__ __forceinline__ void rank_pairs(const gfloat* score, int heads, int c
     for (int k = 0; k < RB; ++k)
 #pragma unroll
       for (int u = 0; u < S; ++u) {
-        const size_t r = (size_t)(2 * min(h0 + k, heads - 1)) * cap + idx[u];
-        x[u][k] = score[r];
-        y[u][k] = score[r + cap];
+        const gfloat* const at = score + (size_t)(2 * min(h0 + k, heads - 1)) * cap;
+        x[u][k] = elem(at, idx[u]);
+        y[u][k] = elem(at + cap, idx[u]);
       }
   };
 #pragma unroll
@@ -300,34 +303,39 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
   return mode == ADSA_SCORE_ATTN_MASS || mode == ADSA_SCORE_EXT_LARGEST;
 }
 
-// (512 x 16 needs 130 registers, two more than let a second workgroup share the CU: held to four waves per SIMD)
+// (512 x 8 and 512 x 16 need 130 registers, two more than let a second workgroup share the CU: held to four waves per SIMD)
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT, S >= 16 ? 4 : 1) void k_select(adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt, int plan_append,
-                                             int32_t* tickets, LaunchShape L) {
+__global__ __launch_bounds__(NT, S >= 8 ? 4 : 1) void k_select(
+    uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t tickets_lo, uint32_t seqs_idx_hi, uint32_t cnt_tickets_hi, uint32_t caps,
+    uint32_t flags, int total, int W, int R, int w, int recent_m, float inv_w) {
   __shared__ __align__(16) RankShared sh;
   const int b = blockIdx.x, tid = threadIdx.x;
-  adsa_seq& sq = seqs[b];
+  gseq& sq = ((gseq*)address(seqs_lo, seqs_idx_hi & 0xFFFF))[b];
+  gint* const sel_cnt = (gint*)address(cnt_lo, cnt_tickets_hi & 0xFFFF);
+  const RankFlags F(flags);                                  // a: plan the append; b: there are tickets
+  const bool plan_append = F.a;
+  const int cap = caps & 0xFFFF, sel_cap = caps >> 16;
   const gint* const pos = (const gint*)sq.pos;
   gfloat* const score = (gfloat*)sq.score;
   const int s = sq.step;
   int n = sq.n_res;
   const int status_in = sq.status;
   rank_clear<NT>(sh);                                        // (while the record is on its way)
-  if (tickets && tid == 0) tickets[4 * b] = 0;               // for this step's k_compact_step
+  if (F.b && tid == 0) ((gint*)address(tickets_lo, cnt_tickets_hi >> 16))[4 * b] = 0;       // for this step's k_compact_step
   if (s < 0 || status_in != 0) { if (tid == 0) { sel_cnt[b] = 0; sq.pending_slot = -1; } return; }
-  if (n < 0 || n > L.cap || s > L.grid_h * L.grid_w) {
+  if (n < 0 || n > cap || s > total) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
     return;
   }
   // Section 4.2: the query token goes to the end of the cache (or, with ADSA_EVICT_REUSE_SLOT, into
   // the slot the last eviction freed).  When the append itself happens later in this step (inside
   // the attention launch), plan for it: that slot, always local, score 0.
-  const int hole = L.evict_policy == ADSA_EVICT_REUSE_SLOT ? sq.hole - 1 : -1;     // freed slot or -1
+  const int hole = F.policy == ADSA_EVICT_REUSE_SLOT ? sq.hole - 1 : -1;     // freed slot or -1
   int slot_new = -1;
   if (plan_append && s >= 1) {
     if (hole >= 0 && hole < n) slot_new = hole;
     else {
-      if (n + 1 > L.cap) {
+      if (n + 1 > cap) {
         if (tid == 0) { sq.status = status_in | ADSA_SEQ_CACHE_FULL; sel_cnt[b] = 0; sq.pending_slot = -1; }
         return;
       }
@@ -337,40 +345,55 @@ __global__ __launch_bounds__(NT, S >= 16 ? 4 : 1) void k_select(adsa_seq* seqs, 
   }
 
   // ---- Eq. 1: partition, keys into registers
-  const QueryCell cell = make_query_cell(sq, s, L.grid_w, L.R, L.w, L.recent_m);
+  const QueryCell cell = make_query_cell(sq, s, GridWidth{W, inv_w}, R, w, recent_m);
+  // The streaming policies attend everything resident (context == cache, Tables 1-2).  Otherwise the B best candidates are attended:
+  // their ranks need not be read where B covers every position that can be one (positions are distinct), as in the first B steps of
+  // an image and for a budget of the whole context: 8 sequences x 16 rows x 8000 slots 8.5 us without the 4 MB of scores, 13.7 with.
+  const bool streaming = F.policy != ADSA_EVICT_ROW_END;
+  const uint32_t B_row = (uint32_t)effective_budget(sq, s);
+  bool ranked = !streaming && (int)B_row < min(n, cell.P + cell.jq - cell.n_keep_prefix);
   int idx[S], posv[S];
-  float rank[S];
 #pragma unroll
   for (int u = 0; u < S; ++u) {
     idx[u] = min(u * NT + tid, n - 1);
-    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
-    rank[u] = 0.0f;
+    posv[u] = n > 0 ? elem(pos, idx[u]) : 0;                 // (an empty sequence's pointers may be null)
   }
-  // (evict-one-when-full policies attend every candidate: their rank is never looked at)
-  if (n > 0 && L.evict_policy == ADSA_EVICT_ROW_END) rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
-  const bool largest = keep_largest_of(L.score_mode);
-  uint32_t key[S], candm = 0, fixedm = 0;
+  const bool largest = keep_largest_of(F.mode);
+  uint32_t key[S], candm = 0, fixedm = 0, B;
   bool bad = false;
+  Stats st;
+  auto classify = [&] {
+    float rank[S];
 #pragma unroll
-  for (int u = 0; u < S; ++u) {
-    const int i = u * NT + tid;
-    const bool in = i < n, planned = i == slot_new;          // the slot the query token will occupy
-    const bool freed = i == hole && !planned;                // evicted, not yet reused: nobody attends it
-    const int c = (planned || freed) ? 0 : select_class(cell, posv[u]);
-    key[u] = order_key(rank[u], largest);
-    bad |= in && c < 0;
-    if (in && c == 1) candm |= 1u << u;
-    if (in && c != 1 && !freed) fixedm |= 1u << u;
+    for (int u = 0; u < S; ++u) rank[u] = 0.0f;
+    if (n > 0 && ranked) rank_values<S, RB>(score, F.rows, cap, idx, rank);
+    candm = fixedm = 0;
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int i = u * NT + tid;
+      const bool in = i < n, planned = i == slot_new;        // the slot the query token will occupy
+      const bool freed = i == hole && !planned;              // evicted, not yet reused: nobody attends it
+      const int c = (planned || freed) ? 0 : select_class(cell, posv[u]);
+      key[u] = order_key(rank[u], largest);
+      bad |= in && c < 0;
+      if (in && c == 1) candm |= 1u << u;
+      if (in && c != 1 && !freed) fixedm |= 1u << u;
+    }
+    st = block_stats<NT, S>(sh, key, candm, bad);
+    B = streaming ? st.n_cand : B_row;
+  };
+  classify();
+  if (!ranked && B < st.n_cand) {                            // (uniform) positions were not distinct after all
+    ranked = true;
+    __syncthreads();
+    classify();
   }
-  const Stats st = block_stats<NT, S>(sh, key, candm, bad);
   if (st.bad) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
     return;
   }
 
   // ---- Eq. 4: threshold of the top-B candidates
-  // the streaming policy attends everything resident (context == cache, Tables 1-2)
-  const uint32_t B = L.evict_policy != ADSA_EVICT_ROW_END ? st.n_cand : (uint32_t)effective_budget(sq, s);
   uint32_t T, need_eq;
   top_threshold<NT, S>(sh, key, candm, st, B < st.n_cand ? B : st.n_cand, &T, &need_eq);
 
@@ -382,14 +405,14 @@ __global__ __launch_bounds__(NT, S >= 16 ? 4 : 1) void k_select(adsa_seq* seqs, 
     if (((candm >> u) & 1u) && key[u] == T) eq |= 1u << u;
   }
   const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &cnt);
-  int32_t* out = sel_idx + (size_t)b * L.sel_cap;
+  gint* const out = (gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
 #pragma unroll
   for (int u = 0; u < S; ++u)
-    if (((take >> u) & 1u) && dest[u] < (uint32_t)L.sel_cap) out[dest[u]] = u * NT + tid;
-  const bool ok = cnt <= (uint32_t)L.sel_cap;
+    if (((take >> u) & 1u) && dest[u] < (uint32_t)sel_cap) elem(out, dest[u]) = u * NT + tid;
+  const bool ok = cnt <= (uint32_t)sel_cap;
   const bool reserve = ok && slot_new >= 0;          // commit the planned append: the slot now holds the query token
   if (reserve)
-    for (int r = tid; r < L.score_rows; r += NT) score[(size_t)r * L.cap + slot_new] = 0.0f;
+    for (int r = tid; r < F.rows; r += NT) score[(size_t)r * cap + slot_new] = 0.0f;
   if (tid == 0) {
     if (!ok) { sq.status = status_in | ADSA_SEQ_SEL_OVERFLOW; sel_cnt[b] = 0; sq.pending_slot = -1; }
     else {
@@ -437,23 +460,28 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* keep_map, int32_t* plan, int advance_step,
-                                                    const float* vcos_s, LaunchShape L) {
+__global__ __launch_bounds__(NT) void k_compact_plan(
+    uint32_t seqs_lo, uint32_t map_lo, uint32_t plan_lo, uint32_t vs_lo, uint32_t seqs_map_hi, uint32_t plan_vs_hi, uint32_t cap_arg, uint32_t flags,
+    int total, int W, int R, int recent_m, float inv_w, int dim) {
   __shared__ __align__(16) RankShared sh;
   constexpr int NW = NT / kWave;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
-  adsa_seq& sq = seqs[b];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), cap = (int)cap_arg;
+  gseq& sq = ((gseq*)address(seqs_lo, seqs_map_hi & 0xFFFF))[b];
+  gint* const plan = (gint*)address(plan_lo, plan_vs_hi & 0xFFFF);
+  const RankFlags F(flags);                                  // a: advance the step
+  const bool advance_step = F.a;
   gint* const pos = (gint*)sq.pos;
   gfloat* const score = (gfloat*)sq.score;
-  const int s = sq.step, n = sq.n_res, W = L.grid_w;
+  const int s = sq.step, n = sq.n_res;
   const bool active = s >= 0 && sq.status == 0;
+  const QueryCell cell = make_query_cell(sq, s, GridWidth{W, inv_w}, R, 0, recent_m);      // (streaming: a 1-D window, which has no radius)
   // per-row policy: act when the query token closed a grid row; streaming policy (Section 4.2 as
   // written): act when the cache is full and a token is about to be inserted
-  const bool streaming = L.evict_policy != ADSA_EVICT_ROW_END;
-  const bool reuse = L.evict_policy == ADSA_EVICT_REUSE_SLOT;
-  const bool row_end = active && n >= 0 && n <= L.cap &&
-                       (streaming ? (s >= 1 && s <= L.grid_h * W && n == L.cap && !(reuse && sq.hole != 0))
-                                  : is_row_end(s, L.grid_h, W));
+  const bool streaming = F.policy != ADSA_EVICT_ROW_END;
+  const bool reuse = F.policy == ADSA_EVICT_REUSE_SLOT;
+  const bool row_end = active && n >= 0 && n <= cap &&
+                       (streaming ? (s >= 1 && s <= total && n == cap && !(reuse && sq.hole != 0))
+                                  : is_row_end(cell, s, total));
   if (!row_end) {
     if (tid == 0) {
       plan[4 * b + 0] = 0; plan[4 * b + 1] = 0; plan[4 * b + 2] = 0; plan[4 * b + 3] = n;
@@ -461,14 +489,13 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
     }
     return;
   }
-  const QueryCell cell = make_query_cell(sq, s, W, L.R, L.w, L.recent_m);
-  const bool largest = keep_largest_of(L.score_mode), fused = L.score_mode == ADSA_SCORE_VCOS_FUSED;
+  const bool largest = keep_largest_of(F.mode), fused = F.mode == ADSA_SCORE_VCOS_FUSED;
   int idx[S], posv[S];
   float rank[S], dot[S];
 #pragma unroll
   for (int u = 0; u < S; ++u) {
     idx[u] = min(u * NT + tid, n - 1);
-    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
+    posv[u] = n > 0 ? elem(pos, idx[u]) : 0;                       // (an empty sequence's pointers may be null)
     rank[u] = dot[u] = 0.0f;
   }
   rank_clear<NT>(sh);
@@ -477,15 +504,15 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
   // step, the two-pass computation has just written S_i to the workspace instead.
   bool rows_ok = false;
   if (fused && n > 0) {
-    const gfloat* tags = sq.vcos_u ? (const gfloat*)sq.vcos_u + (size_t)L.n_heads * L.head_dim : nullptr;
+    const gfloat* tags = sq.vcos_u ? (const gfloat*)sq.vcos_u + dim : nullptr;
     rows_ok = tags && tags[1] == (float)(s + 1);
-    if (rows_ok) rank_pairs<S>(score, L.n_heads, L.cap, idx, rank, dot);
+    if (rows_ok) rank_pairs<S>(score, F.rows / 2, cap, idx, rank, dot);
     else {
 #pragma unroll
-      for (int u = 0; u < S; ++u) rank[u] = ((const gfloat*)vcos_s)[(size_t)b * L.cap + idx[u]];
+      for (int u = 0; u < S; ++u) rank[u] = elem((const gfloat*)address(vs_lo, plan_vs_hi >> 16) + (size_t)b * cap, idx[u]);
     }
   } else if (n > 0) {
-    rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
+    rank_values<S, RB>(score, F.rows, cap, idx, rank);
   }
   uint32_t key[S], restm = 0, in = 0;
 #pragma unroll
@@ -506,7 +533,7 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
     }
     st = block_stats<NT, S, 1>(sh, key, restm, false);
   }
-  int32_t* const map = keep_map + (size_t)b * L.cap;
+  gint* const map = (gint*)address(map_lo, seqs_map_hi >> 16) + (size_t)b * cap;
   if (reuse) {
     // Evict the candidate ranked last -- smallest key, among equals the newest position -- and leave
     // everything where it is: the freed slot goes to the incoming token.
@@ -558,7 +585,7 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
     if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
 
-  move_scores<NT, S>(score, pos, L.score_rows, L.cap, moves, dest, posv);
+  move_scores<NT, S>(score, pos, F.rows, cap, moves, dest, posv);
   if (tid == 0) {
     plan[4 * b + 0] = n; plan[4 * b + 1] = (int)min(sh.first, (uint32_t)n); plan[4 * b + 2] = 1; plan[4 * b + 3] = (int32_t)n_new;
     sq.n_res = (int32_t)n_new;
@@ -579,17 +606,17 @@ __global__ __launch_bounds__(NT) void k_compact_plan(adsa_seq* seqs, int32_t* ke
 constexpr int kMoveRows = 16;
 template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
-                                                              int lanes_per_slice, int slices_per_head, LaunchShape L) {
-  const int b = blockIdx.z;
+                                                              uint32_t slices, int cap, long long slot_stride_b, long long head_stride_b) {
+  const int b = blockIdx.z, lanes_per_slice = slices & 0xFF, slices_per_head = slices >> 8;
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
   const int n_old = pl.x, first = pl.y;
   if (pl.z == 0 || first >= n_old) return;
-  const adsa_seq& sq = seqs[b];
+  const gseq& sq = ((const gseq*)seqs)[b];
   const int head = blockIdx.x / slices_per_head, part = blockIdx.x - head * slices_per_head;
   const int rows_per_pass = kMoveThreads / lanes_per_slice;
   const int row_in_pass = threadIdx.x / lanes_per_slice, lane = threadIdx.x % lanes_per_slice;
-  gchar* const base = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v) + (long long)head * L.head_stride_b + ((long long)part * lanes_per_slice + lane) * 16;
-  const gint* const map = (const gint*)keep_map + (size_t)b * L.cap;
+  gchar* const base = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v) + (long long)head * head_stride_b + ((long long)part * lanes_per_slice + lane) * 16;
+  const gint* const map = (const gint*)keep_map + (size_t)b * cap;
   for (int t0 = first; t0 < n_old; t0 += rows_per_pass * ROWS) {
     uint4 val[ROWS];
     int dst[ROWS];
@@ -601,12 +628,12 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
     }
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
-      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)(t0 + u * rows_per_pass + row_in_pass) * L.slot_stride_b);
+      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)(t0 + u * rows_per_pass + row_in_pass) * slot_stride_b);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this thread's rows are in registers ...
     __syncthreads();                                         // ... and so are everybody's, before any of them is overwritten
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
-      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * L.slot_stride_b, val[u]);
+      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * slot_stride_b, val[u]);
   }
 }
 
@@ -617,32 +644,35 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
 // scores and positions they need in registers -- moves pos[] and the score rows and writes the keep map and the record.
 // Nothing waits for another workgroup.
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, int lanes_per_slice,
-                                                    int slices_per_head, LaunchShape L) {
+__global__ __launch_bounds__(NT) void k_compact_step(
+    uint32_t seqs_lo, uint32_t map_lo, uint32_t tickets_lo, uint32_t seqs_map_hi, uint32_t tickets_hi, uint32_t slices, int cap, uint32_t flags,
+    int total, int W, int R, int recent_m, float inv_w, int n_heads, long long slot_stride_b, long long head_stride_b) {
   __shared__ __align__(16) RankShared sh;
   __shared__ int s_map[NT * S];
   __shared__ int s_last;
   constexpr int kRows = kMoveRows * kMoveThreads / NT;       // as many rows per tile as k_compact_move
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
-  adsa_seq& sq = seqs[b];
+  const int lanes_per_slice = slices & 0xFF, slices_per_head = slices >> 8;
+  const RankFlags F(flags);
+  gseq& sq = ((gseq*)address(seqs_lo, seqs_map_hi & 0xFFFF))[b];
   gint* const pos = (gint*)sq.pos;
   gfloat* const score = (gfloat*)sq.score;
   gchar* const kb = (gchar*)sq.k;
   gchar* const vb = (gchar*)sq.v;
   const int s = sq.step - 1, n = sq.n_res;                   // s: the step that has just been attended
-  if (s < 0 || sq.status != 0 || n < 0 || n > L.cap || !is_row_end(s, L.grid_h, L.grid_w)) return;
-  const QueryCell cell = make_query_cell(sq, s, L.grid_w, L.R, L.w, L.recent_m);
+  const QueryCell cell = make_query_cell(sq, s, GridWidth{W, inv_w}, R, 0, recent_m);
+  if (s < 0 || sq.status != 0 || n < 0 || n > cap || !is_row_end(cell, s, total)) return;
   int idx[S], posv[S];
   float rank[S];
 #pragma unroll
   for (int u = 0; u < S; ++u) {
     idx[u] = min(u * NT + tid, n - 1);
-    posv[u] = n > 0 ? pos[idx[u]] : 0;                       // (an empty sequence's pointers may be null)
+    posv[u] = n > 0 ? elem(pos, idx[u]) : 0;                       // (an empty sequence's pointers may be null)
     rank[u] = 0.0f;
   }
   rank_clear<NT>(sh);
-  if (n > 0) rank_values<S, RB>(score, L.score_rows, L.cap, idx, rank);
-  const bool largest = keep_largest_of(L.score_mode);
+  if (n > 0) rank_values<S, RB>(score, F.rows, cap, idx, rank);
+  const bool largest = keep_largest_of(F.mode);
   uint32_t key[S], restm = 0, in = 0;
 #pragma unroll
   for (int u = 0; u < S; ++u) {
@@ -673,13 +703,13 @@ __global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* ke
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this thread has read what it needs of the scores and positions ...
   __syncthreads();                                           // ... and so has the workgroup: it may draw its ticket
-  if (tid == 0) s_last = __hip_atomic_fetch_add(tickets + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  if (tid == 0) s_last = __hip_atomic_fetch_add((int*)address(tickets_lo, tickets_hi) + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
 
-  const int per_cache = L.n_heads * slices_per_head;
+  const int per_cache = n_heads * slices_per_head;
   const bool is_v = (int)blockIdx.x >= per_cache;
   const int slice = (int)blockIdx.x - (is_v ? per_cache : 0), head = slice / slices_per_head, part = slice - head * slices_per_head;
   const int rows_per_pass = NT / lanes_per_slice, row_in_pass = tid / lanes_per_slice, piece = tid % lanes_per_slice;
-  gchar* const base = (is_v ? vb : kb) + (long long)head * L.head_stride_b + ((long long)part * lanes_per_slice + piece) * 16;
+  gchar* const base = (is_v ? vb : kb) + (long long)head * head_stride_b + ((long long)part * lanes_per_slice + piece) * 16;
   for (int t0 = (int)min(sh.first, (uint32_t)n); t0 < n; t0 += rows_per_pass * kRows) {
     uint4 val[kRows];
     int dst[kRows];
@@ -688,36 +718,26 @@ __global__ __launch_bounds__(NT) void k_compact_step(adsa_seq* seqs, int32_t* ke
       const int i = t0 + u * rows_per_pass + row_in_pass;
       const int m = i < n ? s_map[i] : -1;
       dst[u] = m == i ? -1 : m;
-      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * L.slot_stride_b);
+      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * slot_stride_b);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kRows; ++u)
-      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * L.slot_stride_b, val[u]);
+      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * slot_stride_b, val[u]);
   }
   __syncthreads();                                           // s_last is there (also when no row moves)
   if (!s_last) return;
 
-  int32_t* const map = keep_map + (size_t)b * L.cap;
+  gint* const map = (gint*)address(map_lo, seqs_map_hi >> 16) + (size_t)b * cap;
 #pragma unroll
   for (int u = 0; u < S; ++u)
     if ((in >> u) & 1u) map[u * NT + tid] = ((take >> u) & 1u) ? (int32_t)dest[u] : -1;
-  move_scores<NT, S>(score, pos, L.score_rows, L.cap, moves, dest, posv);
+  move_scores<NT, S>(score, pos, F.rows, cap, moves, dest, posv);
   if (tid == 0) {
     sq.n_res = (int32_t)n_new;
     sq.compacted = 1;
   }
-}
-
-LaunchShape shape_of(const adsa_params& p) {
-  LaunchShape L;
-  L.n_heads = p.n_heads; L.head_dim = p.head_dim; L.elem_bytes = elem_bytes(p);
-  L.grid_h = p.grid_h; L.grid_w = p.grid_w; L.R = p.win_rows_back; L.w = p.win_col_radius;
-  L.cap = p.cap; L.sel_cap = p.sel_cap; L.score_mode = p.score_mode; L.score_rows = score_rows(p); L.recent_m = p.win_recent_m; L.evict_policy = p.evict_policy;
-  L.slot_stride_b = (long long)p.kv_slot_stride * L.elem_bytes;
-  L.head_stride_b = (long long)p.kv_head_stride * L.elem_bytes;
-  return L;
 }
 
 }  // namespace
@@ -727,7 +747,7 @@ static constexpr int rank_threads() { return NT; }
 
 #define ADSA_RANK_LAUNCH(KERNEL, SHAPE, ...)                                                                 \
   do {                                                                                                       \
-    hipLaunchKernelGGL((KERNEL<SHAPE>), dim3(p.n_seq), dim3(rank_threads<SHAPE>()), 0, st, seqs, __VA_ARGS__, shape_of(p)); \
+    hipLaunchKernelGGL((KERNEL<SHAPE>), dim3(p.n_seq), dim3(rank_threads<SHAPE>()), 0, st, __VA_ARGS__); \
     return hipGetLastError();                                                                                \
   } while (0)
 #define ADSA_SHAPE(...) __VA_ARGS__
@@ -743,9 +763,14 @@ static constexpr int rank_threads() { return NT; }
 // 256 threads): 3072 slots at 512x6 11.8, 23.6, 58.9, at 1024x4 13.2, 39.6, 76.9 (28.1, 26.3, 73.2); 3100 at 512x8 14.0, 26.3,
 // 62.3, at 1024x4 13.3, 40.2, 78.3 (31.3, 28.1, 74.6); 6144 at 512x12 19.6, 38.1, 131.6, at 1024x6 18.2, 50.6, 146.7, at 1024x8
 // 21.3, 58.6, 160.9 (50.5, 51.6, 155.3); 6200 at 512x16 23.9, 46.2, 139.2, at 1024x8 21.6, 58.8, 158.1 (53.3, 53.2, 152.4).
+// (All of these with the arguments in a block and integer divisions by the grid width; with preloaded arguments and without divisions every
+// shape gained: 64 x 24 x 696 6.1 -> 5.7, 1536 x 24 x 696 20.5 -> 19.9, 8 x 16 x 8000 18.5 -> 17.5, 400 x 8 x 5000 27.3 -> 25.8.)
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
                          bool plan_append, int32_t* tickets, hipStream_t st) {
-#define ADSA_SELECT(...) ADSA_RANK_LAUNCH(k_select, ADSA_SHAPE(__VA_ARGS__), sel_idx, sel_cnt, plan_append ? 1 : 0, tickets)
+#define ADSA_SELECT(...)                                                                                                                        \
+  ADSA_RANK_LAUNCH(k_select, ADSA_SHAPE(__VA_ARGS__), lo32(seqs), lo32(sel_idx), lo32(sel_cnt), lo32(tickets), hi16s(seqs, sel_idx),             \
+                   hi16s(sel_cnt, tickets), (uint32_t)p.cap | (uint32_t)p.sel_cap << 16, rank_flags(p, plan_append, tickets != nullptr),         \
+                   p.grid_h * p.grid_w, p.grid_w, p.win_rows_back, p.win_col_radius, p.win_recent_m, inv_width(p))
   if (p.cap <= 256) ADSA_SELECT(256, 1);
   if (p.cap <= 512) ADSA_SELECT(256, 2);
   if (p.cap <= 768 && p.n_seq < 1024) ADSA_SELECT(256, 3, 12);
@@ -771,7 +796,10 @@ hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx,
 // at 512x12 19.5, 46.1, 178.  (1024x8 keeps 28 bytes of a thread's state in scratch memory.)
 static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* plan,
                                       bool advance_step, const float* vcos_s, hipStream_t st) {
-#define ADSA_PLAN(...) ADSA_RANK_LAUNCH(k_compact_plan, ADSA_SHAPE(__VA_ARGS__), keep_map, plan, advance_step ? 1 : 0, vcos_s)
+#define ADSA_PLAN(...)                                                                                                                          \
+  ADSA_RANK_LAUNCH(k_compact_plan, ADSA_SHAPE(__VA_ARGS__), lo32(seqs), lo32(keep_map), lo32(plan), lo32(vcos_s), hi16s(seqs, keep_map),          \
+                   hi16s(plan, vcos_s), (uint32_t)p.cap, rank_flags(p, advance_step, false), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,     \
+                   p.win_recent_m, inv_width(p), p.n_heads * p.head_dim)
   if (p.cap <= 256) ADSA_PLAN(256, 1);
   if (p.cap <= 512) ADSA_PLAN(256, 2);
   if (p.cap <= 768) ADSA_PLAN(256, 3, 12);
@@ -784,7 +812,11 @@ static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int3
 }
 
 // column slices of a head row: 128 bytes, or the whole row when it is narrower
-struct Slices { int lanes, per_head; };
+struct Slices {
+  int lanes, per_head;
+  uint32_t packed() const { return (uint32_t)lanes | (uint32_t)per_head << 8; }
+};
+static long long row_bytes(const adsa_params& p, int64_t stride) { return (long long)stride * elem_bytes(p); }
 static Slices row_slices(const adsa_params& p) {
   const int head_bytes = p.head_dim * elem_bytes(p), slice_bytes = head_bytes < 128 ? head_bytes : 128;
   return {slice_bytes / 16, head_bytes / slice_bytes};
@@ -805,8 +837,9 @@ hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* ke
   const dim3 grid(2 * p.n_heads * sl.per_head, p.n_seq);
 #define ADSA_STEP_LAUNCH(NT, ...)                                                                            \
   do {                                                                                                       \
-    hipLaunchKernelGGL((k_compact_step<NT, __VA_ARGS__>), grid, dim3(NT), 0, st, seqs, keep_map, tickets, sl.lanes,    \
-                       sl.per_head, shape_of(p));                                                            \
+    hipLaunchKernelGGL((k_compact_step<NT, __VA_ARGS__>), grid, dim3(NT), 0, st, lo32(seqs), lo32(keep_map), lo32(tickets), hi16s(seqs, keep_map), \
+                       hi16s(tickets, nullptr), sl.packed(), p.cap, rank_flags(p, false, false), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,   \
+                       p.win_recent_m, inv_width(p), p.n_heads, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));                   \
     return hipGetLastError();                                                                                \
   } while (0)
   if (p.cap <= 256) ADSA_STEP_LAUNCH(256, 1);
@@ -820,7 +853,6 @@ hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* ke
 hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
                           const Workspace& w, bool advance_step, hipStream_t st) {
   int32_t* plan = reinterpret_cast<int32_t*>(ws + w.plan_off);
-  const LaunchShape L = shape_of(p);
   const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
   hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
@@ -829,7 +861,7 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   const int rows_per_pass = kMoveThreads / sl.lanes;
   auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8> : k_compact_move<kMoveRows>;
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, sl.lanes, sl.per_head, L);
+                     (const int32_t*)plan, sl.packed(), p.cap, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));
   return hipGetLastError();
 }
 

@@ -40,16 +40,29 @@ constexpr int kVcParts = kVcGroup / kVcTile, kVcPartRuns = 4;
 static_assert(kVcWaves == kVcParts && kVcWaves == kVcPartRuns, "a wave per part or per run");
 constexpr int kVcMaxDim = 8192;             // n_heads * head_dim limit
 
+// What the two passes work on, unpacked from the preloaded kernel arguments (kVcosParams; see k_attend on what a load of the
+// argument block costs: a launch that finds nothing to do is over before it would arrive).
 struct VcosArgs {
-  adsa_seq* seqs;
+  gseq* seqs;
   float* inv_norm;      // [n_seq][cap]
   float* u_part;        // [n_seq][n_parts][dim]: a partial of u per group, or per part of a group (split)
   float* s_out;         // [n_seq][cap] where S_i goes when score[] holds the fused form's rows, else NULL
   int n_heads, head_dim, cap, split, n_parts;     // split: a workgroup of the first pass takes a part of a group
   int tile;                                       // slots per workgroup of the second pass: 64, 128 or 256
-  int grid_h, grid_w, R, w, for_compaction, recent_m, evict_policy;
-  long long slot_stride_b, head_stride_b;
+  int for_compaction, evict_policy;
+  int total, R, w, recent_m;
+  GridWidth grid;
 };
+struct VcosStrides { long long slot_b, head_b; };
+// dims: cap | partials << 16;  flags: heads | D == 128 << 9 | split << 10 | tile / 64 << 11 | for an eviction << 14 | policy << 15
+#define kVcosParams                                                                                                             \
+  uint32_t seqs_lo, uint32_t inv_lo, uint32_t up_lo, uint32_t s_lo, uint32_t seqs_inv_hi, uint32_t up_s_hi, uint32_t dims,     \
+      uint32_t flags, int total, int W, int R, int w, int recent_m, float inv_w, VcosStrides strides
+#define kVcosUnpack                                                                                                             \
+  {(gseq*)address(seqs_lo, seqs_inv_hi & 0xFFFF), reinterpret_cast<float*>(address(inv_lo, seqs_inv_hi >> 16)), \
+   reinterpret_cast<float*>(address(up_lo, up_s_hi & 0xFFFF)), reinterpret_cast<float*>(address(s_lo, up_s_hi >> 16)),         \
+   (int)(flags & 0x1FF), (flags & 0x200) ? 128 : 64, (int)(dims & 0xFFFF), (int)((flags >> 10) & 1), (int)(dims >> 16),         \
+   (int)((flags >> 11) & 7) * 64, (int)((flags >> 14) & 1), (int)((flags >> 15) & 3), total, R, w, recent_m, {W, inv_w}}
 
 // sum over the wave: DPP inside the 16-lane rows, then lane 15 -> next row and lane 31 -> upper half; uniform result
 template <int CTRL, int ROWS>
@@ -62,21 +75,26 @@ __device__ __forceinline__ float wave_sum(float x) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWave - 1));
 }
 
+__device__ __forceinline__ float4 load_f4(const gfloat* p) {
+  const uint4 x = load16((const gchar*)p);
+  return make_float4(__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
+}
+
 // candidate test (false for inactive sequences / non row-end compaction)
 __device__ __forceinline__ bool vcos_candidate(const VcosArgs& A, const QueryCell& c, int pos) {
   if (A.for_compaction && A.evict_policy == ADSA_EVICT_ROW_END) return evict_class(c, pos) == 1;
   return select_class(c, pos) == 1;     // also the streaming eviction: the incoming query's partition
 }
 
-__device__ __forceinline__ bool vcos_active(const VcosArgs& A, const adsa_seq& sq) {
+__device__ __forceinline__ bool vcos_active(const VcosArgs& A, const QueryCell& cell, const gseq& sq) {
   if (sq.step < 0 || sq.status != 0 || sq.n_res < 0 || sq.n_res > A.cap) return false;
-  if (sq.step > A.grid_h * A.grid_w) return false;
+  if (sq.step > A.total) return false;
   if (!A.for_compaction) return true;
   if (A.evict_policy == ADSA_EVICT_REUSE_SLOT && sq.hole != 0) return false;     // room was made already
-  if (A.s_out && sq.vcos_u && sq.vcos_u[A.n_heads * A.head_dim + 1] == (float)(sq.step + 1))
+  if (A.s_out && sq.vcos_u && ((const gfloat*)sq.vcos_u)[A.n_heads * A.head_dim + 1] == (float)(sq.step + 1))
     return false;                                       // the attention launch left this step's numbers
   if (A.evict_policy != ADSA_EVICT_ROW_END) return sq.step >= 1 && sq.n_res == A.cap;
-  return is_row_end(sq.step, A.grid_h, A.grid_w);
+  return is_row_end(cell, sq.step, A.total);
 }
 
 // A concatenated V row as a wave holds it: lane l has the 16-byte pieces l, l + 64, ... (G of them at most; pieces past the
@@ -166,20 +184,21 @@ __device__ __forceinline__ int list_rows(int* s_row, int* s_cnt, int s0, int s1,
 }
 
 template <int EB, int G>
-__global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
+__global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(kVcosParams) {
+  const VcosArgs A = kVcosUnpack;
   extern __shared__ __align__(16) float s_acc[];        // [kVcWaves][dim]
   __shared__ int s_row[kVcThreads], s_cnt[kVcWaves];
   __shared__ float s_inv[kVcThreads];
   constexpr int EPL = 16 / EB;
   const int part = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const adsa_seq& sq = A.seqs[b];
-  if (!vcos_active(A, sq)) return;
+  const gseq& sq = A.seqs[b];
+  const QueryCell cell = make_query_cell(sq, sq.step, A.grid, A.R, A.w, A.recent_m);
+  if (!vcos_active(A, cell, sq)) return;
   const int group = A.split ? part / kVcParts : part;
   const int n = sq.n_res, s0 = group * kVcGroup;
   if (s0 >= n) return;
   const int s1 = min(n, s0 + kVcGroup), dim = A.n_heads * A.head_dim;
-  const QueryCell cell = make_query_cell(sq, sq.step, A.grid_w, A.R, A.w, A.recent_m);
   const gint* const pos = (const gint*)sq.pos;
   gfloat* const inv_norm = (gfloat*)A.inv_norm + (size_t)b * A.cap;
   const int m = list_rows(s_row, s_cnt, s0, s1, [&](int i) {
@@ -193,7 +212,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
   auto run_begin = [&](int r) { return my_part + parts * (n_part * r / kVcPartRuns); };
   int r = A.split ? wave : 0;
   const int k0 = run_begin(r), k1 = run_begin(A.split ? r + 1 : kVcPartRuns);
-  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
+  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, strides.head_b);
   float acc[G][EPL];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -205,7 +224,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
   int end = k0;                                          // of run r
   while (end == k0 && k0 < k1) end = run_begin(++r);     // (short lists have empty runs)
   bool more = false;
-  for_rows(row, A.slot_stride_b, s_row, k0, parts, min(k1, m), [&](int k, const float (&f)[G][EPL]) {
+  for_rows(row, strides.slot_b, s_row, k0, parts, min(k1, m), [&](int k, const float (&f)[G][EPL]) {
     float ss = 0.0f;
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -237,7 +256,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
   });
   __syncthreads();
   if (tid < m && (!A.split || tid % parts == my_part)) inv_norm[s_row[tid]] = s_inv[tid];
-  float* up = A.u_part + ((size_t)b * A.n_parts + part) * (size_t)dim;
+  gchar* const up = (gchar*)((gfloat*)A.u_part + ((size_t)b * A.n_parts + part) * (size_t)dim);
   for (int c = tid; c < dim / 4; c += kVcThreads) {
     float4 t = reinterpret_cast<const float4*>(s_acc)[c];
 #pragma unroll
@@ -245,20 +264,21 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_norm_usum(VcosArgs A) {
       const float4 o = reinterpret_cast<const float4*>(s_acc + (size_t)w * dim)[c];
       t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
     }
-    reinterpret_cast<float4*>(up)[c] = t;
+    store16(up + c * 16, make_uint4(__float_as_uint(t.x), __float_as_uint(t.y), __float_as_uint(t.z), __float_as_uint(t.w)));
   }
 }
 
 // The sequences are walked in the opposite order of the first pass: what that read last is still in the memory-side cache.
 template <int EB, int G>
-__global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
+__global__ __launch_bounds__(kVcThreads) void k_vcos_score(kVcosParams) {
+  const VcosArgs A = kVcosUnpack;
   __shared__ int s_row[kVcThreads], s_cnt[kVcWaves], s_n[kVcWaves];
   __shared__ float s_inv[kVcThreads], s_res[kVcThreads];       // by slot of the tile; by entry of s_row
   constexpr int EPL = 16 / EB;
   const int tile = gridDim.x - 1 - blockIdx.x, b = gridDim.y - 1 - blockIdx.y, tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
-  adsa_seq& sq = A.seqs[b];
-  if (!vcos_active(A, sq)) return;
+  gseq& sq = A.seqs[b];
+  if (!vcos_active(A, make_query_cell(sq, sq.step, A.grid, A.R, A.w, A.recent_m), sq)) return;
   const int n = sq.n_res, s0 = tile * A.tile;
   if (s0 >= n) return;
   const int s1 = min(n, s0 + A.tile), dim = A.n_heads * A.head_dim;
@@ -266,8 +286,8 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
   const gfloat* const invs = (const gfloat*)A.inv_norm + (size_t)b * A.cap;
   int my = 0;
   for (int i = tid; i < n; i += kVcThreads) my += invs[i] != 0.0f;
-  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
-  const float* up = A.u_part + (size_t)b * A.n_parts * (size_t)dim;
+  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, strides.head_b);
+  const gfloat* const up = (const gfloat*)A.u_part + (size_t)b * A.n_parts * (size_t)dim;
   float uu[G][EPL];
 #pragma unroll
   for (int g = 0; g < G; ++g)
@@ -278,12 +298,12 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int e = 0; e < EPL; e += 4) {
-        const float* const at = up + (size_t)t * dim + row.col[g] + e;
-        float4 x = *reinterpret_cast<const float4*>(at);
+        const gfloat* const at = up + (size_t)t * dim + row.col[g] + e;
+        float4 x = load_f4(at);
         if (A.split) {
           float4 y[kVcParts];
 #pragma unroll
-          for (int j = 1; j < kVcParts; ++j) y[j] = *reinterpret_cast<const float4*>(at + (size_t)min(j, parts_used - 1 - t) * dim);
+          for (int j = 1; j < kVcParts; ++j) y[j] = load_f4(at + (size_t)min(j, parts_used - 1 - t) * dim);
 #pragma unroll
           for (int j = 1; j < kVcParts; ++j)
             if (t + j < parts_used) { x.x += y[j].x; x.y += y[j].y; x.z += y[j].z; x.w += y[j].w; }
@@ -302,7 +322,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
 #pragma unroll
   for (int w = 0; w < kVcWaves; ++w) N += s_n[w];
   gfloat* const out = A.s_out ? (gfloat*)A.s_out + (size_t)b * A.cap : (gfloat*)sq.score;
-  for_rows(row, A.slot_stride_b, s_row, __builtin_amdgcn_readfirstlane(wave), kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
+  for_rows(row, strides.slot_b, s_row, __builtin_amdgcn_readfirstlane(wave), kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
     float dot = 0.0f, ss = 0.0f;
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -327,37 +347,32 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_score(VcosArgs A) {
 // beside the sums in LDS, 10.9 with 256 slots listed at a time and u requested last, 18.3 with every row read twice.)
 // The slots that join or leave are listed 1024 at a time; wave w takes entries w, w+4, ... in ascending order into
 // its own registers, and the waves' sums are added to u in wave order, so the result does not depend on timing.
-struct AdvArgs {
-  adsa_seq* seqs;
-  int n_heads, head_dim, cap, grid_h, grid_w, R, w, recent_m;
-  long long slot_stride_b, head_stride_b;
-};
-
 constexpr int kAdvRounds = 4;                           // slots per thread and list
 // (a ring of one row: two rows are all there is to read in most steps, and the registers of a deeper one would cost residency)
 template <int EB, int G>
-__global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
+__global__ __launch_bounds__(kVcThreads) void k_vcos_advance(adsa_seq* seqs, uint32_t heads_d, int cap, int total, int W, int R, int w,
+                                                             int recent_m, float inv_w, long long slot_stride_b, long long head_stride_b) {
   extern __shared__ __align__(16) float s_acc[];        // the list (slots, then signs), after it [kVcWaves][dim]
   constexpr int EPL = 16 / EB, kRounds = kAdvRounds;
   __shared__ int s_cnt[kRounds][kVcWaves];
   int* const s_row = reinterpret_cast<int*>(s_acc);
   float* const s_sign = s_acc + kRounds * kVcThreads;   // by entry of s_row
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  adsa_seq& sq = A.seqs[b];
+  gseq& sq = ((gseq*)seqs)[b];
   gfloat* const U = (gfloat*)sq.vcos_u;
   if (sq.step < 0 || sq.status != 0 || U == nullptr) return;
-  const int s = sq.step, n = sq.n_res, dim = A.n_heads * A.head_dim;
-  if (n < 0 || n > A.cap) return;
+  const int s = sq.step, n = sq.n_res, n_heads = heads_d & 0xFFFF, head_dim = heads_d >> 16, dim = n_heads * head_dim;
+  if (n < 0 || n > cap) return;
   gfloat* const tags = U + dim;
-  if (s + 1 > A.grid_h * A.grid_w) {                    // no later step evicts
+  if (s + 1 > total) {                    // no later step evicts
     if (tid == 0) tags[0] = 0.0f;
     return;
   }
   const gint* const pos = (const gint*)sq.pos;
   const int victim = sq.hole - 1;                       // slot freed by this step's eviction, or -1
-  const QueryCell now = make_query_cell(sq, s, A.grid_w, A.R, A.w, A.recent_m);
-  const QueryCell next = make_query_cell(sq, s + 1, A.grid_w, A.R, A.w, A.recent_m);
-  const Row<EB, G> row(sq.v, A.n_heads, A.head_dim, A.head_stride_b);
+  const QueryCell now = make_query_cell(sq, s, GridWidth{W, inv_w}, R, w, recent_m);
+  const QueryCell next = make_query_cell(sq, s + 1, GridWidth{W, inv_w}, R, w, recent_m);
+  const Row<EB, G> row(sq.v, n_heads, head_dim, head_stride_b);
   const bool incremental = tags[0] == (float)(s + 1);   // u is the sum over THIS step's candidates
   float acc[G][EPL];
 #pragma unroll
@@ -409,7 +424,7 @@ __global__ __launch_bounds__(kVcThreads) void k_vcos_advance(AdvArgs A) {
     }
     m = __builtin_amdgcn_readfirstlane(m);
     __syncthreads();
-    for_rows<EB, G, 1>(row, A.slot_stride_b, s_row, wave, kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
+    for_rows<EB, G, 1>(row, slot_stride_b, s_row, wave, kVcWaves, m, [&](int k, const float (&f)[G][EPL]) {
       float ss = 0.0f;
 #pragma unroll
       for (int g = 0; g < G; ++g)
@@ -490,16 +505,13 @@ bool vcos_fused_fits(const adsa_params& p) {
 
 hipError_t launch_vcos_advance(const adsa_params& p, adsa_seq* seqs, hipStream_t st) {
   if (!vcos_fused_fits(p)) return hipErrorInvalidValue;
-  AdvArgs A;
-  A.seqs = seqs; A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
-  A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius; A.recent_m = p.win_recent_m;
-  A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
-  A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
   return with_row_shape(p, [&](auto eb, auto g) {
     constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
     if constexpr (G * 16 / EB <= 64) {                  // (longer rows: refused above)
       const size_t list = 2 * sizeof(int) * kAdvRounds * kVcThreads, sums = sizeof(float) * (size_t)p.n_heads * p.head_dim * kVcWaves;
-      hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), list > sums ? list : sums, st, A);
+      hipLaunchKernelGGL((k_vcos_advance<EB, G>), dim3(p.n_seq), dim3(kVcThreads), list > sums ? list : sums, st, seqs, (uint32_t)p.n_heads | (uint32_t)p.head_dim << 16,
+                         p.cap, p.grid_h * p.grid_w, p.grid_w, p.win_rows_back, p.win_col_radius, p.win_recent_m, 1.0f / (float)p.grid_w,
+                         (long long)p.kv_slot_stride * elem_bytes(p), (long long)p.kv_head_stride * elem_bytes(p));
       return hipGetLastError();
     } else return hipErrorInvalidValue;
   });
@@ -509,27 +521,25 @@ hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction
                        const Workspace& w, hipStream_t st) {
   const int dim = p.n_heads * p.head_dim;
   if (dim > kVcMaxDim) return hipErrorInvalidValue;
-  VcosArgs A;
-  A.seqs = seqs;
-  A.inv_norm = reinterpret_cast<float*>(ws + w.vcos_off);
-  A.u_part = reinterpret_cast<float*>(ws + w.vcos_u_off);
-  A.s_out = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<float*>(ws + w.vcos_s_off) : nullptr;
-  A.n_heads = p.n_heads; A.head_dim = p.head_dim; A.cap = p.cap;
+  const float* const inv_norm = reinterpret_cast<float*>(ws + w.vcos_off);
+  const float* const u_part = reinterpret_cast<float*>(ws + w.vcos_u_off);
+  const float* const s_out = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<float*>(ws + w.vcos_s_off) : nullptr;
   const VcosPlan vp = make_vcos_plan(p);
-  A.tile = vp.tile; A.split = vp.split ? 1 : 0; A.n_parts = vp.n_parts;
-  A.grid_h = p.grid_h; A.grid_w = p.grid_w; A.R = p.win_rows_back; A.w = p.win_col_radius;
-  A.for_compaction = for_compaction ? 1 : 0; A.recent_m = p.win_recent_m; A.evict_policy = p.evict_policy;
-  A.slot_stride_b = (long long)p.kv_slot_stride * elem_bytes(p);
-  A.head_stride_b = (long long)p.kv_head_stride * elem_bytes(p);
-  const dim3 grid1(A.n_parts, p.n_seq), grid2((p.cap + A.tile - 1) / A.tile, p.n_seq);
+  const uint32_t flags = p.n_heads | (p.head_dim == 128 ? 1u << 9 : 0u) | (vp.split ? 1u << 10 : 0u) | (uint32_t)(vp.tile / 64) << 11 |
+                         (for_compaction ? 1u << 14 : 0u) | (uint32_t)p.evict_policy << 15;
+  const VcosStrides strides = {(long long)p.kv_slot_stride * elem_bytes(p), (long long)p.kv_head_stride * elem_bytes(p)};
+  const dim3 grid1(vp.n_parts, p.n_seq), grid2((p.cap + vp.tile - 1) / vp.tile, p.n_seq);
+  auto launch = [&](auto kernel, const dim3& grid, size_t lds) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kVcThreads), lds, st, lo32(seqs), lo32(inv_norm), lo32(u_part), lo32(s_out), hi16s(seqs, inv_norm),
+                       hi16s(u_part, s_out), (uint32_t)p.cap | (uint32_t)vp.n_parts << 16, flags, p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,
+                       p.win_col_radius, p.win_recent_m, 1.0f / (float)p.grid_w, strides);
+    return hipGetLastError();
+  };
   return with_row_shape(p, [&](auto eb, auto g) {
     constexpr int EB = decltype(eb)::value, G = decltype(g)::value;
     // (64..128 KB of LDS, above the default per-launch limit: allowed once per device by vcos_prepare_kernels)
-    hipLaunchKernelGGL((k_vcos_norm_usum<EB, G>), grid1, dim3(kVcThreads), sizeof(float) * (size_t)dim * kVcWaves, st, A);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_vcos_score<EB, G>), grid2, dim3(kVcThreads), 0, st, A);
-    return hipGetLastError();
+    const hipError_t e = launch(k_vcos_norm_usum<EB, G>, grid1, sizeof(float) * (size_t)dim * kVcWaves);
+    return e == hipSuccess ? launch(k_vcos_score<EB, G>, grid2, 0) : e;
   });
 }
 
