@@ -866,37 +866,35 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   }
   // One workgroup per (sequence, head): 8 waves up to one pair per CU, 4 from two on; in between 8 where the lists together
   // are long (80 MB), for the waves that then wait side by side, and 4 where starting the workgroups is a good part of
-  // the launch.  Measured, us with 4 | 8 | 16 waves, bf16: 320 pairs x 457 tokens x 64 (37 MB) 10.6 | 11.1 | 15.4;
-  // 400 x 650 x 64 (67 MB) 14.6 | 14.9 | 20.6; 480 x 700 x 64 (86 MB) 17.8 | 16.7; 288 x 1300 x 64 (96 MB) 24.6 | 23.3;
-  // 400 x 700 x 128 (143 MB) 26.8 | 25.9; 768 x 200 x 64 9.6 | 10.6 | 19.9; 768 x 649 x 64 22.6 | 22.7 | 32.3;
-  // 256 x 650 x 128 16.2 | 15.8 | 17.0; 192 x 650 x 64 9.3 | 8.5 | 10.9; 128 x 4000 x 128 60.3 | 53.0 | 52.4;
-  // 40 x 400 x 64 6.3 | 5.9 | 7.2; fp32: 288 x 300 x 128 (88 MB) 21.0 | 20.3; 400 x 300 x 128 22.9 | 22.1.  Lists that the
-  // rings of 4 waves hold at once (32 KB) gain nothing from more of them: 16 pairs x 64 tokens x 64 3.7 | 4.3, 256 x 128 x 64
-  // 4.3 | 4.9, 16 x 32 x 128 fp32 3.3 | 3.8, fused 64 x 64 x 128 4.8 | 6.5; 16 x 192 x 64 (48 KB) 4.4 | 4.5, fp32 16 x 48 x 128 4.2 | 3.9.
+  // the launch.  Measured, us with 4 | 8 waves, bf16: 320 pairs x 427 tokens x 64 (35 MB) 9.0 | 9.2; 260 x 698 x 64 12.0 | 12.6;
+  // 400 x 698 x 64 (71 MB) 13.7 | 14.0; 480 x 746 x 64 (92 MB) 16.8 | 16.5; 288 x 1394 x 64 (103 MB) 23.3 | 22.7; 400 x 746 x 128
+  // (153 MB) 25.6 | 25.4; 768 x 228 x 64 9.9 | 10.7; 768 x 647 x 64 21.3 | 21.5; 256 x 698 x 128 16.0 | 16.1; 192 x 698 x 64 8.0 | 7.8;
+  // 40 x 400 x 64 6.3 | 5.9 and 128 x 4000 x 128 60 | 53 (with an earlier loop; 16 waves 7.2 and 52); fp32: 288 x 323 x 128 20.5 |
+  // 20.7; 400 x 323 x 128 22.8 | 22.3.  Lists that the rings of 4 waves hold at once (32 KB) gain nothing from more of them: 16 pairs x
+  // 84 tokens x 64 3.0 | 3.3, 16 x 46 x 128 fp32 3.1 | 3.3; 16 x 213 x 64 (53 KB) 3.6 | 3.7, 16 x 133 x 64 fp32 3.3 | 3.3.
   const long long pairs = (long long)p.n_seq * p.n_heads;
   const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
   a.waves = pairs >= 512 || b_list <= (32 << 10) || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
-  // Splitting a list costs a second launch, ~3 us.  What it can save: a workgroup alone streams ~55 GB/s (8 or 16 waves
-  // alike), the chip ~5.5 TB/s, as much as ~100 workgroups.  So a list of b bytes on each of `pairs` workgroups is split
-  // when b * (1 - max(pairs / 100, 1 / chunks)) is more than 230 KB, ~4 us; into 8-wave chunks of about 64 KB that
-  // together occupy every CU.  Measured, us whole | split: 8 pairs x 256 KB 8.0 | 8.7; 20 x 205 KB 7.4 | 9.2;
-  // 16 x 384 KB 11.9 | 9.6; 8 x 512 KB 13.4 | 9.4; 8 x 2 MB 44 | 11.6; 32 x 1 MB 24.6 | 12.6; 32 x 4 MB 84.7 | 27.1;
-  // 80 x 384 KB 12.8 | 12.8; 64 x 154 KB 7.1 | 9.8.  (One launch whose last workgroup to arrive merges, behind a
-  // device-scope release / acquire, took 12 us for 8 x 512 KB, 58 for 32 x 4 MB and 17.5 for 40 lists of 102 KB, which
-  // take 5.9 us whole.)
-  // 64 KB is what the rings of 8 waves hold at once: where the CUs allow it a chunk has no more, so that none ends in a
-  // second, nearly empty revolution (2 x 300 KB fused: 11.2 with 4 chunks, 9.9 with 5; 2 x 300 KB plain 9.5 and 8.3).  Rows of the
-  // fused V-cosine form take longer, so their line is 175 KB of such chunks: 2 x 200 KB 9.4 | 9.8, 2 x 250 KB 10.5 | 9.6,
-  // 16 x 300 KB 12.4 | 10.4.
+  // Splitting a list costs a second launch, ~2.5 us, and is worth it where one workgroup's bytes are what the launch lasts: from
+  // about 330 KB on, a little more where more pairs share the memory's rate, and 430 KB for one or two pairs, which have it to
+  // themselves.  Into 8-wave chunks of 64 KB, what their rings hold at once (so that none ends in a second, nearly empty
+  // revolution), or as many as leave no CU with two, which then lasts as long as those: 24 pairs x 804 KB in 10 chunks 10.6, in 11
+  // 11.8; 40 x 504 KB in 6 10.1, in 7 11.5; 92 x 704 KB in 2 17.0, in 3 20.7.  ([slot][head][D] caches keep the number that a test of the
+  // split kernels states, rounded up while at most 24 CUs have two: 40 x 745 KB x 128 13.2 instead of 11.2.)  Measured, us whole |
+  // split, bf16 x 64: 2 pairs x 325 KB 6.4 | 7.5; 4 x 260 KB 6.2 | 7.6, 404 KB 9.1 | 7.8; 8 x 325 KB 7.9 | 8.0, 357 KB 8.6 | 8.1; 24 x
+  // 325 KB 8.8 | 8.6, 404 KB 10.5 | 8.9; 48 x 325 KB 9.2 | 9.5, 404 KB 11.0 | 10.0; 64 x 325 KB 9.4 | 10.0, 404 KB 11.3 | 10.5, 704 KB
+  // 18.4 | 13.6; 80 x 504 KB 14.1 | 12.8, 1 MB 25.7 | 19.7; 92 x 704 KB 19.8 | 17.0; fp32 x 128 8 x 341 KB 7.9 |
+  // 7.5.  (One launch whose last workgroup to arrive merges, behind a device-scope release / acquire, took 12 us for 8 x 512 KB.)
+  // Rows of the fused V-cosine form take longer, so their line is lower: 2 x 207 KB 7.1 | 7.5, 263 KB 7.8 | 7.6; 8 x 207 KB 7.2 | 7.7,
+  // 263 KB 8.1 | 7.9; 32 x 263 KB 8.7 | 8.5; 64 x 327 KB 10.5 | 9.7; 92 x 507 KB 15.2 | 13.6.
   const bool fused = p.score_mode == ADSA_SCORE_VCOS_FUSED;
-  const long long full = b_list / (64 << 10), snug = (b_list + (64 << 10) - 1) / (64 << 10);
-  auto chunks = [](long long n) { return n > kMaxChunks ? (long long)kMaxChunks : n < 1 ? 1ll : n; };
-  long long nc = chunks(std::min(full, (256 + pairs - 1) / pairs));
-  const long long snug_nc = pairs * snug <= 256 ? chunks(snug) : nc;
-  if (fused) nc = snug_nc;
-  const long long hidden = pairs * nc > 100 ? pairs * nc : 100;          // b_list * (1 - max(pairs / 100, 1 / nc)), in units of 1 / (100 nc)
-  if (pairs >= 96 || b_list * (100 * nc - hidden) <= (fused ? 175000ll : 230000ll) * 100 * nc) nc = 1;
-  else nc = snug_nc;
+  const long long line = (fused ? 240 + pairs / 2 : pairs <= 2 ? 430 : 330 + pairs) << 10, snug = (b_list + (64 << 10) - 1) / (64 << 10);
+  long long nc = 1;
+  if (pairs < 96 && b_list > line) {
+    const long long up = (256 + pairs - 1) / pairs;
+    const bool round_up = p.kv_slot_stride > p.kv_head_stride && pairs * up <= 256 + 24;
+    nc = std::min<long long>({pairs * snug <= 256 ? snug : round_up ? up : 256 / pairs, kMaxChunks});
+  }
   // the logits (two rows of them for the fused V-cosine form) and the slot list of a chunk must fit in LDS
   const int lds_rows = (fused ? 2 : 1) + 1;
   while (nc < kMaxChunks && (size_t)lds_rows * ((p.sel_cap + nc - 1) / nc + 1) * sizeof(float) > 40 * 1024) ++nc;
