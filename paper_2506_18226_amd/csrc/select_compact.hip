@@ -594,41 +594,42 @@ __global__ __launch_bounds__(NT) void k_compact_plan(
   }
 }
 
-// grid = (row slices, 2 {K,V}, n_seq).  A workgroup owns a 16*lanes-byte column slice of every row
+// grid = (row slices, 2 {K,V}, n_seq).  A workgroup owns a 128-byte column slice of every row
 // of one cache and walks the rows that move in ascending tiles: load survivors -> wait, barrier -> store (a tile's destinations
-// are at most its sources and below the next tile's).  Bound by the copy: kMoveRows rows per thread in flight, and since nothing
-// reads a row again before the next step's attention, streaming loads and stores.  512 sequences, 1.05 GB moved:
-// 182 us; with 4 rows and ordinary accesses 212, with 8 and streaming 196, with 16 and ordinary 205, K and V together
-// in one workgroup 8 rows each 199.  ROWS: no more than the longest sequence needs for a single tile, since many short sequences
-// are bound by how many workgroups fit a CU (132 registers with 16 rows, 68 with 8, 36 with 4).  350 sequences x 33 heads x 64
-// bf16, us with 16 rows | the ROWS of the rule: 100 slots 86.9 | 55.1, 128 slots 93.3 | 64.5 (4 rows), 140 slots 97.8 | 77.1,
-// 256 slots 134.6 | 132.4 (8 rows).
-constexpr int kMoveRows = 16;
+// are at most its sources and below the next tile's).  Bound by the copy: ROWS rows per thread in flight, and since nothing
+// reads a row again before the next step's attention, streaming loads and stores.  A tile ends with a wait for its last load, so the
+// best tile is the whole list: ROWS are the rows a thread has to move then, at most 32 (199 registers; 151 with 24, 107 with 16).
+// The pass of 512 sequences x 24 heads x 696 slots, 1.05 GB moved, ranking included: 230.6 us with 24 rows, 231.6 with 32, 234.6
+// with 16, 242 with 12 (233 with 16 and predicated map loads, 240 with those now; ordinary instead of streaming accesses 20 more).
+// An eviction, us with 16 rows | the rule: 64 sequences x 24 x 696 68.3 | 65.2, 8 x 24 x 696 26.0 | 22.6, 4 x 32 x 4000 63.4 | 56.2,
+// 300 x 16 x 1000 219.8 | 213.7.  Short lists: 350 sequences x 33 heads x 64 bf16, us with 16 rows | the ROWS of the rule: 100 slots
+// 86.9 | 55.1, 128 slots 93.3 | 64.5 (4 rows), 140 slots 97.8 | 77.1, 256 slots 134.6 | 132.4 (8 rows).
+constexpr int kSliceLanes = 8;
 template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
-                                                              uint32_t slices, int cap, long long slot_stride_b, long long head_stride_b) {
-  const int b = blockIdx.z, lanes_per_slice = slices & 0xFF, slices_per_head = slices >> 8;
+                                                              int part_bits, int cap, long long slot_stride_b, long long head_stride_b) {
+  constexpr int kPass = kMoveThreads / kSliceLanes;
+  const int b = blockIdx.z, head = blockIdx.x >> part_bits, part = blockIdx.x & ((1 << part_bits) - 1);
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
+  const gseq& sq = ((const gseq*)seqs)[b];
+  gchar* const cache = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v);
+  asm volatile("" : : "s"(cache));                           // (asked for together with the plan's words, not after them)
   const int n_old = pl.x, first = pl.y;
   if (pl.z == 0 || first >= n_old) return;
-  const gseq& sq = ((const gseq*)seqs)[b];
-  const int head = blockIdx.x / slices_per_head, part = blockIdx.x - head * slices_per_head;
-  const int rows_per_pass = kMoveThreads / lanes_per_slice;
-  const int row_in_pass = threadIdx.x / lanes_per_slice, lane = threadIdx.x % lanes_per_slice;
-  gchar* const base = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v) + (long long)head * head_stride_b + ((long long)part * lanes_per_slice + lane) * 16;
+  const int row_in_pass = threadIdx.x / kSliceLanes, lane = threadIdx.x % kSliceLanes;
+  gchar* const base = cache + (long long)head * head_stride_b + (part * kSliceLanes + lane) * 16;
   const gint* const map = (const gint*)keep_map + (size_t)b * cap;
-  for (int t0 = first; t0 < n_old; t0 += rows_per_pass * ROWS) {
+  for (int t0 = first; t0 < n_old; t0 += kPass * ROWS) {
     uint4 val[ROWS];
     int dst[ROWS];
 #pragma unroll
-    for (int u = 0; u < ROWS; ++u) {
-      const int i = t0 + u * rows_per_pass + row_in_pass;
-      const int m = i < n_old ? map[i] : -1;
-      dst[u] = m == i ? -1 : m;
-    }
+    for (int u = 0; u < ROWS; ++u) dst[u] = elem(map, (uint32_t)min(t0 + u * kPass + row_in_pass, n_old - 1));
 #pragma unroll
-    for (int u = 0; u < ROWS; ++u)
-      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)(t0 + u * rows_per_pass + row_in_pass) * slot_stride_b);
+    for (int u = 0; u < ROWS; ++u) {
+      const int i = t0 + u * kPass + row_in_pass;
+      if (i >= n_old || dst[u] == i) dst[u] = -1;            // (past the end, or stays where it is)
+      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * slot_stride_b);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this thread's rows are in registers ...
     __syncthreads();                                         // ... and so are everybody's, before any of them is overwritten
 #pragma unroll
@@ -645,14 +646,13 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
 // Nothing waits for another workgroup.
 template <int NT, int S, int RB = rank_batch(S)>
 __global__ __launch_bounds__(NT) void k_compact_step(
-    uint32_t seqs_lo, uint32_t map_lo, uint32_t tickets_lo, uint32_t seqs_map_hi, uint32_t tickets_hi, uint32_t slices, int cap, uint32_t flags,
+    uint32_t seqs_lo, uint32_t map_lo, uint32_t tickets_lo, uint32_t seqs_map_hi, uint32_t tickets_hi, int part_bits, int cap, uint32_t flags,
     int total, int W, int R, int recent_m, float inv_w, int n_heads, long long slot_stride_b, long long head_stride_b) {
   __shared__ __align__(16) RankShared sh;
   __shared__ int s_map[NT * S];
   __shared__ int s_last;
-  constexpr int kRows = kMoveRows * kMoveThreads / NT;       // as many rows per tile as k_compact_move
+  constexpr int kRows = 16 * kMoveThreads / NT;              // (whole lists up to 2048 slots, 32 rows: 32 x 16 x 1900 at a row end 86 -> 93 us)
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
-  const int lanes_per_slice = slices & 0xFF, slices_per_head = slices >> 8;
   const RankFlags F(flags);
   gseq& sq = ((gseq*)address(seqs_lo, seqs_map_hi & 0xFFFF))[b];
   gint* const pos = (gint*)sq.pos;
@@ -705,22 +705,23 @@ __global__ __launch_bounds__(NT) void k_compact_step(
   __syncthreads();                                           // ... and so has the workgroup: it may draw its ticket
   if (tid == 0) s_last = __hip_atomic_fetch_add((int*)address(tickets_lo, tickets_hi) + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
 
-  const int per_cache = n_heads * slices_per_head;
+  const int per_cache = n_heads << part_bits;
   const bool is_v = (int)blockIdx.x >= per_cache;
-  const int slice = (int)blockIdx.x - (is_v ? per_cache : 0), head = slice / slices_per_head, part = slice - head * slices_per_head;
-  const int rows_per_pass = NT / lanes_per_slice, row_in_pass = tid / lanes_per_slice, piece = tid % lanes_per_slice;
-  gchar* const base = (is_v ? vb : kb) + (long long)head * head_stride_b + ((long long)part * lanes_per_slice + piece) * 16;
-  for (int t0 = (int)min(sh.first, (uint32_t)n); t0 < n; t0 += rows_per_pass * kRows) {
+  const int slice = (int)blockIdx.x - (is_v ? per_cache : 0), head = slice >> part_bits, part = slice & ((1 << part_bits) - 1);
+  constexpr int kPass = NT / kSliceLanes;
+  const int row_in_pass = tid / kSliceLanes, piece = tid % kSliceLanes;
+  gchar* const base = (is_v ? vb : kb) + (long long)head * head_stride_b + (part * kSliceLanes + piece) * 16;
+  for (int t0 = (int)min(sh.first, (uint32_t)n); t0 < n; t0 += kPass * kRows) {
     uint4 val[kRows];
     int dst[kRows];
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
-      const int i = t0 + u * rows_per_pass + row_in_pass;
-      const int m = i < n ? s_map[i] : -1;
-      dst[u] = m == i ? -1 : m;
+      const int i = t0 + u * kPass + row_in_pass;
+      dst[u] = s_map[min(i, n - 1)];
+      if (i >= n || dst[u] == i) dst[u] = -1;
       if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * slot_stride_b);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // as in k_compact_move
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kRows; ++u)
@@ -811,16 +812,12 @@ static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int3
   ADSA_PLAN(1024, 8);
 }
 
-// column slices of a head row: 128 bytes, or the whole row when it is narrower
-struct Slices {
-  int lanes, per_head;
-  uint32_t packed() const { return (uint32_t)lanes | (uint32_t)per_head << 8; }
-};
-static long long row_bytes(const adsa_params& p, int64_t stride) { return (long long)stride * elem_bytes(p); }
-static Slices row_slices(const adsa_params& p) {
-  const int head_bytes = p.head_dim * elem_bytes(p), slice_bytes = head_bytes < 128 ? head_bytes : 128;
-  return {slice_bytes / 16, head_bytes / slice_bytes};
+// column slices of a head row (128, 256 or 512 bytes), as a power of two
+static int slice_bits(const adsa_params& p) {
+  const int slices = p.head_dim * elem_bytes(p) / (kSliceLanes * 16);
+  return slices == 1 ? 0 : slices == 2 ? 1 : 2;
 }
+static long long row_bytes(const adsa_params& p, int64_t stride) { return (long long)stride * elem_bytes(p); }
 
 // One launch instead of two saves a small step ~2.5 us of launching and, most steps closing no row, an empty kernel.  Its ranking
 // is repeated by every workgroup, so a large launch pays for it at a row end.  adsa_step, us with two launches | with one:
@@ -829,16 +826,15 @@ static Slices row_slices(const adsa_params& p) {
 // that need no pass over V.
 bool one_launch_compact(const adsa_params& p) {
   return p.evict_policy == ADSA_EVICT_ROW_END && !is_vcos(p) && p.cap <= 2048 &&
-         (long long)p.n_seq * p.n_heads * row_slices(p).per_head * 2 <= 1024;
+         ((long long)p.n_seq * p.n_heads * 2 << slice_bits(p)) <= 1024;
 }
 
 hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st) {
-  const Slices sl = row_slices(p);
-  const dim3 grid(2 * p.n_heads * sl.per_head, p.n_seq);
+  const dim3 grid((2 * p.n_heads) << slice_bits(p), p.n_seq);
 #define ADSA_STEP_LAUNCH(NT, ...)                                                                            \
   do {                                                                                                       \
     hipLaunchKernelGGL((k_compact_step<NT, __VA_ARGS__>), grid, dim3(NT), 0, st, lo32(seqs), lo32(keep_map), lo32(tickets), hi16s(seqs, keep_map), \
-                       hi16s(tickets, nullptr), sl.packed(), p.cap, rank_flags(p, false, false), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,   \
+                       hi16s(tickets, nullptr), slice_bits(p), p.cap, rank_flags(p, false, false), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,   \
                        p.win_recent_m, inv_width(p), p.n_heads, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));                   \
     return hipGetLastError();                                                                                \
   } while (0)
@@ -856,12 +852,12 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
   hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
-  const Slices sl = row_slices(p);
-  dim3 grid(p.n_heads * sl.per_head, 2, p.n_seq);
-  const int rows_per_pass = kMoveThreads / sl.lanes;
-  auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8> : k_compact_move<kMoveRows>;
+  const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);
+  constexpr int rows_per_pass = kMoveThreads / kSliceLanes;
+  auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8>
+            : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24> : k_compact_move<32>;
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, sl.packed(), p.cap, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));
+                     (const int32_t*)plan, slice_bits(p), p.cap, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));
   return hipGetLastError();
 }
 

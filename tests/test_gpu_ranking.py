@@ -183,3 +183,8 @@ def test_more_sequences_than_compute_units_rank_like_few(cap):
     for a, b in zip(*got):
         assert torch.equal(a[at].view(torch.int32), b.view(torch.int32))
     assert (got[0][1] > s // 3).all()
+
+
+@pytest.mark.parametrize("cap", [256, 512, 768, 1024, 2048])
+def test_a_step_evicts_lists_that_fill_its_tile(cap):
+    test_a_step_evicts_as_select_attend_and_compact_do(2, 3, 64, "bf16", cap, "head_major")
