@@ -2,7 +2,7 @@
 // attention over the selected slots, plus the cache append (Section 4.2) and the per-head
 // attention-mass update, in ONE launch.
 //
-//  k_attend<EB, D, HT, U, NW, VF, DIRECT> : grid (token chunk, HT heads, sequence), NW waves.
+//  k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE> : grid (token chunk, HT heads, sequence), NW waves.
 //    HT = 1: a 16-byte-per-lane streaming load of one wave covers RPW = 64 / (D*EB/16) consecutive tokens of ONE head.
 //    That holds for [slot][head][D] caches too: a row is 128 bytes or more, whole cache lines, so a workgroup that
 //    walks one head's rows at a stride fetches nothing it does not use.  But it visits every page of the sequence for its
