@@ -46,6 +46,16 @@ __device__ __forceinline__ void store_stream16(gchar* p, const uint4& x) {
   __builtin_nontemporal_store(v, reinterpret_cast<ADSA_GLOBAL u32x4*>(p));
 }
 
+// One sequence's row of sel_idx.  Entry i of it, or 0 without an access where i >= sel_cap: kernels ask for entries of their first
+// round trip before the count has arrived.  The whole index goes into the vector offset (and the instruction's own): those two are
+// what a buffer load compares with the descriptor's size, a scalar offset is added behind the check.
+struct SlotList {
+  __amdgpu_buffer_rsrc_t row;
+  __device__ __forceinline__ SlotList(const gint* first, int sel_cap)
+      : row(__builtin_amdgcn_make_buffer_rsrc((void*)(const int32_t*)first, 0, sel_cap * 4, 0x00027000)) {}
+  __device__ __forceinline__ int operator[](int i) const { return (int)__builtin_amdgcn_raw_buffer_load_b32(row, i * 4, 0, 0); }
+};
+
 // Round to the nearest bf16, ties to even (v_cvt_pk_bf16_f32; subnormals are kept, a NaN stays one)
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {

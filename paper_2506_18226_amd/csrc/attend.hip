@@ -192,16 +192,14 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   // (These loads need nothing but preloaded arguments: they leave before anything waits for a scalar load.)
   int slot_a[U];
   int pf_slot[PF];
-  // (through a buffer descriptor of the list: entries past its end are not read and come back as 0, without a clamp each)
-  const auto list = __builtin_amdgcn_make_buffer_rsrc((void*)(const int32_t*)idx, 0, sel_cap * 4, 0x00027000);
-  auto entry = [&](int lane_at, int uniform_at) { return (int)__builtin_amdgcn_raw_buffer_load_b32(list, lane_at * 4, uniform_at * 4, 0); };
+  const SlotList list(idx, sel_cap);
   const int unit0 = wave * RPW + ts;                // this lane's token of the wave's first unit
   if constexpr (DIRECT) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot_a[u] = entry(unit0, u * NW * RPW);
+    for (int u = 0; u < U; ++u) slot_a[u] = list[unit0 + u * NW * RPW];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, k * kAttThreads);
+    for (int k = 0; k < PF; ++k) pf_slot[k] = list[tid + k * kAttThreads];
   }
   const uint4 qr = load16((const gchar*)address(q_lo, cnt_q_hi >> 16) + row_off);
   // the query token's own K/V row (Section 4.2 append): the first wave attends and stores it, 16 bytes of K and V per lane.
@@ -242,9 +240,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   float* const s_logit = reinterpret_cast<float*>(s_ent + n_ent);
   if constexpr (!DIRECT) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot_a[u] = entry(unit0, t_begin + u * NW * RPW);
+    for (int u = 0; u < U; ++u) slot_a[u] = list[t_begin + unit0 + u * NW * RPW];
 #pragma unroll
-    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, t_begin + k * kAttThreads);
+    for (int k = 0; k < PF; ++k) pf_slot[k] = list[t_begin + tid + k * kAttThreads];
   }
   // the slot adsa_select reserved for the query token (Section 4.2 append), if this launch fills it
   const int new_slot = (append && pending < cap) ? pending : -1;
@@ -331,7 +329,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
         pf_slot[k] = min(max(pf_slot[k], 0), cap - 1);
         if (j < n_ent) stage(j, pf_slot[k]);
       }
-    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, entry(j, t_begin));
+    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, list[t_begin + j]);
     if (new_slot >= 0) {                          // (uniform)
       const unsigned long long who = __ballot(new_at != 0);
       const int at = who ? __builtin_amdgcn_readlane(new_at, __ffsll((long long)who) - 1) : 0;

@@ -171,8 +171,7 @@ __global__ __launch_bounds__(NW * kWave, R > ring(D) ? 1 : 4) void k_attend_gqa(
   const int pending = sqp->pending_slot;
   __builtin_amdgcn_sched_barrier(0);                       // (the scalar loads leave first)
   const gint* const idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
-  const auto list = __builtin_amdgcn_make_buffer_rsrc((void*)(const int32_t*)idx, 0, sel_cap * 4, 0x00027000);      // (entries past its end come back as 0)
-  auto entry = [&](int lane_at, int uniform_at) { return (int)__builtin_amdgcn_raw_buffer_load_b32(list, lane_at * 4, uniform_at * 4, 0); };
+  const SlotList list(idx, sel_cap);
   const gchar* const q_g = (const gchar*)address(q_lo, cnt_q_hi >> 16);
   // q as the B operand of the first product: lane (g = r, kg) holds columns [D/4*kg, D/4*(kg+1)) of query g
   const gchar* const q_row0 = q_g + ((size_t)b * HQ + (size_t)hk * G) * D * 2;        // query 0 of this cache head
@@ -186,9 +185,9 @@ __global__ __launch_bounds__(NW * kWave, R > ring(D) ? 1 : 4) void k_attend_gqa(
   const int first_at = (wave + kg * NW) * 16 + r;            // list position of this lane's token
   int slot_first = 0, pf_slot[PF];
   if constexpr (!SPLIT) {
-    slot_first = entry(first_at, 0);
+    slot_first = list[first_at];
 #pragma unroll
-    for (int k = 0; k < PF; ++k) pf_slot[k] = entry(tid, k * kThreads);
+    for (int k = 0; k < PF; ++k) pf_slot[k] = list[tid + k * kThreads];
   }
   // the query token's row (Section 4.2 append); fp32 rows are rounded once, here: every lane keeps the pieces of
   // the rounded row it would load from the cache (K: 16 bytes at ld_piece, V: its EV columns)
