@@ -113,12 +113,12 @@ def load_library() -> C.CDLL:
     return _lib
 
 
-_call = None                      # the CPython module's call()
+_call = _call_static = None       # the CPython module's functions
 _entry = {}                       # C entry point -> its address
 
 
 def _load_native():
-    global _call
+    global _call, _call_static
     lib, path = load_library(), _build.NATIVE_PATH
     if not os.path.exists(path):
         raise FileNotFoundError(f"{path} is missing: run `python -m paper_2506_18226_amd.build` (or __graft_entry__.build()) first; "
@@ -129,14 +129,15 @@ def _load_native():
     for name in ("adsa_select", "adsa_attend", "adsa_compact", "adsa_step", "adsa_step_static"):
         _entry[name] = C.cast(getattr(lib, name), C.c_void_p).value
     module.set_params_type(AdsaParams)
+    _call_static = module.call_static
     _call = module.call
 
 
 def _enqueue(name: str, params, flags, workspace, stream, *pointers) -> None:
-    """One C call; seqs is the first of the pointers.  workspace False: the entry point has none."""
+    """One C call; seqs is the first of the pointers."""
     if _call is None:
         _load_native()
-    rc = _call(_entry[name], params, flags, workspace, _current_stream() if stream is None else _stream(stream), *pointers)
+    rc = _call(_entry[name], params, flags, _current_stream() if stream is None else _stream(stream), workspace, *pointers)
     if rc != 0:
         raise AdsaError(rc, name)
 
@@ -245,7 +246,12 @@ def adsa_step(params, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_ma
 
 def adsa_step_static(params, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map, flags=0, stream=None) -> None:
     """adsa_step on the library's built-in scratch array: no workspace argument, no allocation."""
-    _enqueue("adsa_step_static", params, flags, False, stream, seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map)
+    if _call_static is None:
+        _load_native()
+    rc = _call_static(_entry["adsa_step_static"], params, flags, _current_stream() if stream is None else _stream(stream),
+                      seqs, q, k_new, v_new, out, lse, sel_idx, sel_cnt, keep_map)
+    if rc != 0:
+        raise AdsaError(rc, "adsa_step_static")
 
 
 def adsa_profile_enable(on: bool) -> None:

@@ -54,24 +54,23 @@ typedef int (*fn_step_static)(const void*, void*, const void*, const void*, cons
 
 enum { SELECT = 3, ATTEND = 8, COMPACT = 2, STEP = 9 };         /* pointer arguments of the entry points, seqs first */
 
-/* (address of the C function, params, flags, workspace, stream, pointers...) -> its return code.  The number of pointers says
- * which entry point it is; workspace is not an argument of adsa_step_static (pass False). */
-static PyObject* call_entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
-  (void)self;
+/* a: address of the C function, params, flags, stream, workspace (has_ws), pointers...  The number of pointers says which entry
+ * point it is; adsa_step_static, which has as many as adsa_step, is the one without a workspace. */
+static PyObject* call_c(PyObject* const* a, Py_ssize_t n, int has_ws) {
   void *fn, *p[STEP], *ws = NULL, *stream;
   size_t ws_bytes = 0;
-  const Py_ssize_t np = n - 5;
-  if (np != SELECT && np != ATTEND && np != COMPACT && np != STEP) {
+  const Py_ssize_t first = has_ws ? 5 : 4, np = n - first;
+  if (np != STEP && (!has_ws || (np != SELECT && np != ATTEND && np != COMPACT))) {
     PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
     return NULL;
   }
   if (as_pointer(a[0], &fn) < 0) return NULL;
   const unsigned long flags = PyLong_AsUnsignedLongMask(a[2]);
   if (PyErr_Occurred()) return NULL;
-  if (a[3] != Py_False && (as_pointer(a[3], &ws) < 0 || as_bytes(a[3], &ws_bytes) < 0)) return NULL;
-  if (as_pointer(a[4], &stream) < 0) return NULL;
+  if (as_pointer(a[3], &stream) < 0) return NULL;
+  if (has_ws && (as_pointer(a[4], &ws) < 0 || as_bytes(a[4], &ws_bytes) < 0)) return NULL;
   for (Py_ssize_t i = 0; i < np; ++i)
-    if (as_pointer(a[5 + i], &p[i]) < 0) return NULL;
+    if (as_pointer(a[first + i], &p[i]) < 0) return NULL;
   Py_buffer params;
   const int typed = params_type ? PyObject_IsInstance(a[1], params_type) : 0;
   if (typed < 0) return NULL;
@@ -92,14 +91,24 @@ static PyObject* call_entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   if (np == ATTEND) rc = ((fn_attend)fn)(pp, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], f, ws, ws_bytes, stream);
   else if (np == SELECT) rc = ((fn_select)fn)(pp, p[0], p[1], p[2], f, ws, ws_bytes, stream);
   else if (np == COMPACT) rc = ((fn_compact)fn)(pp, p[0], p[1], f, ws, ws_bytes, stream);
-  else if (a[3] == Py_False) rc = ((fn_step_static)fn)(pp, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], f, stream);
-  else rc = ((fn_step)fn)(pp, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], f, ws, ws_bytes, stream);
+  else if (has_ws) rc = ((fn_step)fn)(pp, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], f, ws, ws_bytes, stream);
+  else rc = ((fn_step_static)fn)(pp, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], f, stream);
   Py_END_ALLOW_THREADS
   PyBuffer_Release(&params);
   return PyLong_FromLong(rc);
 }
 
-/* the ctypes mirror of adsa_params that call() takes */
+static PyObject* call_entry(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  (void)self;
+  return call_c(a, n, 1);
+}
+
+static PyObject* call_static(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  (void)self;
+  return call_c(a, n, 0);
+}
+
+/* the ctypes mirror of adsa_params that the calls take */
 static PyObject* set_params_type(PyObject* self, PyObject* type) {
   (void)self;
   Py_INCREF(type);
@@ -107,8 +116,9 @@ static PyObject* set_params_type(PyObject* self, PyObject* type) {
   Py_RETURN_NONE;
 }
 
-static PyMethodDef methods[] = {{"set_params_type", set_params_type, METH_O, "The type of call()'s params."},
-                                {"call", (PyCFunction)(void (*)(void))call_entry, METH_FASTCALL, "One C call."}, {NULL, NULL, 0, NULL}};
+static PyMethodDef methods[] = {{"set_params_type", set_params_type, METH_O, "The type of the calls' params."},
+                                {"call", (PyCFunction)(void (*)(void))call_entry, METH_FASTCALL, "One C call."},
+                                {"call_static", (PyCFunction)(void (*)(void))call_static, METH_FASTCALL, "One call of adsa_step_static."}, {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_adsa_native", NULL, -1, methods, NULL, NULL, NULL, NULL};
 
 PyMODINIT_FUNC PyInit__adsa_native(void) {

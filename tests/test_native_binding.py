@@ -46,6 +46,15 @@ def test_what_is_no_pointer_is_refused(bad):
             call()
 
 
+@pytest.mark.parametrize("bad", [False, True, 0, 1 << 40, "x"])
+def test_a_workspace_is_a_tensor_or_none(bad):
+    s, p = dict(stream=0), params(n_seq=0)
+    for call in (lambda: B.adsa_select(p, 0, 0, 0, bad, **s), lambda: B.adsa_attend(p, 0, 0, 0, 0, 0, 0, bad, **s),
+                 lambda: B.adsa_compact(p, 0, 0, bad, **s), lambda: B.adsa_step(p, 0, 0, 0, 0, 0, 0, 0, 0, 0, bad, **s)):
+        with pytest.raises(AttributeError):
+            call()
+
+
 @pytest.mark.parametrize("bad", [None, 0, b"\0" * 200, C.c_int(3), C.create_string_buffer(200)])
 def test_parameters_of_another_type_are_refused(bad):
     with pytest.raises(TypeError):
