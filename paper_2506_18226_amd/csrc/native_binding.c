@@ -13,7 +13,7 @@
 
 static PyObject *s_data_ptr, *s_numel, *s_element_size, *params_type;
 
-/* device address of x: NULL, the integer itself, x.data_ptr(), or for (x, bytes) that many further on; -1 with an exception set */
+/* device address of x: NULL, the integer itself, x.data_ptr(), or for (x, bytes) that many further on (NULL stays NULL); -1 with an exception set */
 static int as_pointer(PyObject* x, void** out) {
   if (x == Py_None) { *out = NULL; return 0; }
   if (PyTuple_CheckExact(x) && PyTuple_GET_SIZE(x) == 2) {
@@ -22,7 +22,7 @@ static int as_pointer(PyObject* x, void** out) {
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "(pointer, bytes) expected");
       return -1;
     }
-    *out = (char*)*out + off;
+    if (*out) *out = (char*)*out + off;
     return 0;
   }
   if (PyLong_Check(x)) {

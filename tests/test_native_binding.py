@@ -39,6 +39,20 @@ def test_null_pointers_and_a_missing_workspace_are_seen_as_such():
     assert e.value.code in (-4, -6)
 
 
+@pytest.mark.parametrize("null", [(None, 96), (0, 4096)])
+def test_an_offset_makes_no_pointer_of_null(null):
+    """Otherwise valid calls, one pointer after the other missing."""
+    x, q = 1 << 40, dict(stream=0)
+    calls = [(3, lambda a: B.adsa_select(params(), *a, torch.zeros(8), **q)), (2, lambda a: B.adsa_compact(params(), *a, torch.zeros(8), **q)),
+             (6, lambda a: B.adsa_attend(params(), *a, torch.zeros(8), **q)), (8, lambda a: B.adsa_attend(params(), *a[:6], torch.zeros(8), 8, *a[6:], **q)),
+             (9, lambda a: B.adsa_step(params(), *a, torch.zeros(8), **q)), (9, lambda a: B.adsa_step_static(params(), *a, **q))]
+    for n, call in calls:
+        for i in range(n):
+            with pytest.raises(B.AdsaError) as e:
+                call([null if k == i else x for k in range(n)])
+            assert e.value.code == -1
+
+
 @pytest.mark.parametrize("bad", [1.5, "x", (0, 1.5), ((0, 0), 0), (0, 1, 2), object()])
 def test_what_is_no_pointer_is_refused(bad):
     for call in entry_points(params(n_seq=0), bad, None):
