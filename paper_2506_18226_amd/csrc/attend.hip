@@ -877,8 +877,7 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   // about 330 KB on, a little more where more pairs share the memory's rate, and 430 KB for one or two pairs, which have it to
   // themselves.  Into 8-wave chunks of 64 KB, what their rings hold at once (so that none ends in a second, nearly empty
   // revolution), or as many as leave no CU with two, which then lasts as long as those: 24 pairs x 804 KB in 10 chunks 10.6, in 11
-  // 11.8; 40 x 504 KB in 6 10.1, in 7 11.5; 92 x 704 KB in 2 17.0, in 3 20.7.  ([slot][head][D] caches keep the number that a test of the
-  // split kernels states, rounded up while at most 24 CUs have two: 40 x 745 KB x 128 13.2 instead of 11.2.)  Measured, us whole |
+  // 11.8; 40 x 504 KB in 6 10.1, in 7 11.5; 92 x 704 KB in 2 17.0, in 3 20.7; [slot][head][D] 40 x 745 KB x 128 in 6 11.2, in 7 13.2.  Measured, us whole |
   // split, bf16 x 64: 2 pairs x 325 KB 6.4 | 7.5; 4 x 260 KB 6.2 | 7.6, 404 KB 9.1 | 7.8; 8 x 325 KB 7.9 | 8.0, 357 KB 8.6 | 8.1; 24 x
   // 325 KB 8.8 | 8.6, 404 KB 10.5 | 8.9; 48 x 325 KB 9.2 | 9.5, 404 KB 11.0 | 10.0; 64 x 325 KB 9.4 | 10.0, 404 KB 11.3 | 10.5, 704 KB
   // 18.4 | 13.6; 80 x 504 KB 14.1 | 12.8, 1 MB 25.7 | 19.7; 92 x 704 KB 19.8 | 17.0; fp32 x 128 8 x 341 KB 7.9 |
@@ -888,11 +887,7 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   const bool fused = p.score_mode == ADSA_SCORE_VCOS_FUSED;
   const long long line = (fused ? 240 + pairs / 2 : pairs <= 2 ? 430 : 330 + pairs) << 10, snug = (b_list + (64 << 10) - 1) / (64 << 10);
   long long nc = 1;
-  if (pairs < 96 && b_list > line) {
-    const long long up = (256 + pairs - 1) / pairs;
-    const bool round_up = p.kv_slot_stride > p.kv_head_stride && pairs * up <= 256 + 24;
-    nc = std::min<long long>({pairs * snug <= 256 ? snug : round_up ? up : 256 / pairs, kMaxChunks});
-  }
+  if (pairs < 96 && b_list > line) nc = std::min<long long>({snug, 256 / pairs, kMaxChunks});
   // the logits (two rows of them for the fused V-cosine form) and the slot list of a chunk must fit in LDS
   const int lds_rows = (fused ? 2 : 1) + 1;
   while (nc < kMaxChunks && (size_t)lds_rows * ((p.sel_cap + nc - 1) / nc + 1) * sizeof(float) > 40 * 1024) ++nc;

@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_heads,D,dtype,layout,fused,lens,chunks", [
     (2, 128, "f32", "head_major", False, [1, 2, 15, 16, 17, 1023, 1024, 1100], 16),
     (2, 64, "bf16", "slot_major", False, [3, 16, 33, 1025, 2048, 2049, 4100, 4200], 16),
-    (5, 128, "bf16", "slot_major", False, [1, 6, 7, 8, 511, 1024, 1025, 1500], 7),
+    (5, 128, "bf16", "slot_major", False, [1, 5, 6, 7, 511, 1024, 1025, 1500], 6),
+    (6, 128, "bf16", "slot_major", False, [1, 6, 7, 8, 1025, 1500], 7),
     (2, 128, "f32", "head_major", True, [1, 15, 16, 17, 1023, 1024, 1099, 1100], 16),    # |v|^2 and v.u rows of every chunk
     (2, 128, "bf16", "head_major", True, [1, 4, 5, 6, 255, 256, 499, 500], 4),           # the fused form's earlier line
 ])
