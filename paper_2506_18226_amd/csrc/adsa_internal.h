@@ -22,6 +22,7 @@ struct AttendPlan {
   int reserved_chunks;  // chunks per list the workspace has room for (>= n_chunks)
   int waves;            // waves per attend workgroup: 4 or 8
   int heads;            // heads per attend workgroup: 1, or 512 bytes' worth of a token of a [slot][head][D] cache
+  bool wide;            // rows further apart than 32-bit offsets from 24-bit products reach
 };
 
 // Rows of adsa_seq.score: one accumulator per head for ATTN_MASS (the rank of a slot is their sum),
@@ -116,6 +117,7 @@ struct adsa_launch_plan {
   int32_t chunks, waves, heads;       // attention: chunks per list, waves and heads per workgroup
   int32_t one_launch_eviction;        // adsa_step's row-end eviction is k_compact_step
   int32_t vcos_split, vcos_tile;      // V-cosine passes
+  int32_t wide;                       // attention: the form with 64-bit offsets
 };
 int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out);
 }

@@ -364,7 +364,7 @@ int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out) {
   if (rc) return rc;
   const AttendPlan a = make_attend_plan(eff);
   const VcosPlan v = make_vcos_plan(eff);
-  *out = {a.n_chunks, a.waves, a.heads, one_launch_compact(eff) ? 1 : 0, v.split ? 1 : 0, v.tile};
+  *out = {a.n_chunks, a.waves, a.heads, one_launch_compact(eff) ? 1 : 0, v.split ? 1 : 0, v.tile, a.wide ? 1 : 0};
   return ADSA_OK;
 }
 

@@ -119,7 +119,7 @@ struct AttendArgs {
   int new_f32;                         // k_new / v_new are fp32 although the cache is bf16: round as they enter
   int vcos_fused;
   long long slot_stride_b, head_stride_b;
-  uint32_t stride24;    // slot_stride_b where a head's rows can be reached with 32-bit offsets (see launch_attend), else 0
+  uint32_t stride24;    // slot_stride_b where a workgroup's rows can be reached with 32-bit offsets (see short_offsets), else 0
   float scale_log2;     // softmax scale * log2(e)
 };
 
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_attend_finish(
   }
 }
 
-template <int EB, int D, int HT, int NW, bool VF, bool DIRECT, bool WIDE = false>
+template <int EB, int D, int HT, int NW, bool VF, bool DIRECT, bool WIDE>
 hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
   // Row pairs in flight per lane.  us with 2 | 3 | 4 | 6 | 8, bf16: 768 pairs x 647 tokens x 64 22.6 | 22.2 | 22.3 | 22.8 | 23.3; 128 x
@@ -779,26 +779,22 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
   return hipGetLastError();
 }
 
-template <int EB, int D, bool VF>
+template <int EB, int D, bool VF, bool WIDE>
 hipError_t launch_attend_v(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (A.stride24 == 0) {
-    if (plan.n_chunks > 1) return launch_attend_w<EB, D, 1, 8, VF, false, true>(A, plan, n_seq, st, ev_start, ev_stop);
-    return launch_attend_w<EB, D, 1, 8, VF, true, true>(A, plan, n_seq, st, ev_start, ev_stop);
-  }
   if constexpr (!VF && kBurst > D * EB) {
-    if (plan.heads > 1) return launch_attend_w<EB, D, kBurst / (D * EB), 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
+    if (plan.heads > 1) return launch_attend_w<EB, D, kBurst / (D * EB), 4, VF, true, WIDE>(A, plan, n_seq, st, ev_start, ev_stop);
   }
-  if (plan.n_chunks > 1) return launch_attend_w<EB, D, 1, 8, VF, false>(A, plan, n_seq, st, ev_start, ev_stop);
-  if (plan.waves == 8) return launch_attend_w<EB, D, 1, 8, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
-  return launch_attend_w<EB, D, 1, 4, VF, true>(A, plan, n_seq, st, ev_start, ev_stop);
+  if (plan.n_chunks > 1) return launch_attend_w<EB, D, 1, 8, VF, false, WIDE>(A, plan, n_seq, st, ev_start, ev_stop);
+  if (plan.waves == 8) return launch_attend_w<EB, D, 1, 8, VF, true, WIDE>(A, plan, n_seq, st, ev_start, ev_stop);
+  return launch_attend_w<EB, D, 1, 4, VF, true, WIDE>(A, plan, n_seq, st, ev_start, ev_stop);
 }
 
 template <int EB, int D>
 hipError_t launch_attend_t(const AttendArgs& A, const AttendPlan& plan, int n_seq, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (A.vcos_fused) return launch_attend_v<EB, D, true>(A, plan, n_seq, st, ev_start, ev_stop);
-  return launch_attend_v<EB, D, false>(A, plan, n_seq, st, ev_start, ev_stop);
+  if (A.vcos_fused) return plan.wide ? launch_attend_v<EB, D, true, true>(A, plan, n_seq, st, ev_start, ev_stop) : launch_attend_v<EB, D, true, false>(A, plan, n_seq, st, ev_start, ev_stop);
+  return plan.wide ? launch_attend_v<EB, D, false, true>(A, plan, n_seq, st, ev_start, ev_stop) : launch_attend_v<EB, D, false, false>(A, plan, n_seq, st, ev_start, ev_stop);
 }
 
 __global__ void k_zero_words(uint32_t* p, size_t n) {
@@ -826,7 +822,9 @@ static int reserved_chunks(const adsa_params& p) {
 }
 
 // Whether a lane reaches every row of its workgroup's heads with a 24-bit product and a 32-bit offset: rows up to 16 MB apart
-// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB).
+// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB).  Others -- a slot that holds every sequence
+// and layer of a model, say -- take the form with 64-bit offsets, 4 to 8 registers more, by the same launch rule: one form of it with 8
+// waves and one head for all of them took 64 sequences x 24 x 64, rows 18 MB apart, 700 tokens from 56 us to 68, 60 tokens from 9.6 to 14.2.
 static bool short_offsets(const adsa_params& p, int heads) {
   const long long eb = elem_bytes(p), slot_b = p.kv_slot_stride * eb;
   return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
@@ -859,6 +857,7 @@ AttendPlan make_attend_plan(const adsa_params& p) {
     if (nc > 1) a.waves = 4;
     a.n_chunks = a.reserved_chunks = nc;
     a.heads = 1;
+    a.wide = false;
     a.chunk_max = gqa_logit_stride(p, nc);
     return a;
   }
@@ -903,9 +902,9 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   const int ht = p.kv_slot_stride > p.kv_head_stride ? kBurst / (p.head_dim * elem_bytes(p)) : 1;
   const long long groups = (p.n_heads + ht - 1) / ht;
   const bool fits = p.n_heads % ht == 0 || (b_list <= (32 << 10) && 100 * groups * ht <= 115ll * p.n_heads);
-  a.heads = !fused && nc == 1 && ht > 1 && p.n_seq * groups >= 384 && fits && short_offsets(p, ht) && (size_t)(ht + 1) * (p.sel_cap + 1) * sizeof(float) <= 40 * 1024 ? ht : 1;
+  a.heads = !fused && nc == 1 && ht > 1 && p.n_seq * groups >= 384 && fits && (size_t)(ht + 1) * (p.sel_cap + 1) * sizeof(float) <= 40 * 1024 ? ht : 1;
   if (a.heads > 1) a.waves = 4;
-  if (!short_offsets(p, 1)) a.waves = 8;       // (one form of the kernel has 64-bit offsets, for 24 more registers)
+  a.wide = !short_offsets(p, a.heads);
   a.reserved_chunks = reserved_chunks(p);
   a.chunk_max = (p.sel_cap + a.n_chunks - 1) / a.n_chunks + 1;
   return a;
@@ -971,7 +970,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
   const int eb = elem_bytes(p);
   A.slot_stride_b = (long long)p.kv_slot_stride * eb;
   A.head_stride_b = (long long)p.kv_head_stride * eb;
-  A.stride24 = short_offsets(p, plan.heads) ? (uint32_t)A.slot_stride_b : 0u;
+  A.stride24 = plan.wide ? 0u : (uint32_t)A.slot_stride_b;
   const float scale = p.softmax_scale != 0.0f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
   A.scale_log2 = scale * kLog2e;
   const int key = eb * 1000 + p.head_dim;

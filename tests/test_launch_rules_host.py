@@ -1,4 +1,4 @@
-"""What the attention launch rule promises of split lists, over random parameters (host code only)."""
+"""What the attention launch rule promises, over random parameters (host code only)."""
 import random
 
 from paper_2506_18226_amd import binding as B
@@ -20,3 +20,20 @@ def test_chunks_leave_no_compute_unit_with_two_and_do_not_depend_on_the_nesting(
             split += 1
             assert n_seq * n_heads < 96 and n_seq * n_heads * plans[0].chunks <= 256, what
     assert split > 2000
+
+
+def test_caches_of_wide_strides_are_launched_like_dense_ones():
+    rng, several, short = random.Random(4), 0, 0
+    for _ in range(20000):
+        kw = dict(n_seq=rng.randint(1, 200), n_heads=rng.choice((1, 2, 8, 24, 32, 40)), head_dim=rng.choice((64, 128)), grid_h=64, grid_w=64,
+                  win_rows_back=1, win_col_radius=2, dtype=rng.choice((B.F32, B.BF16)), score_mode=B.SCORE_ATTN_MASS, cap=rng.randint(100, 4000),
+                  layout="slot_major")
+        kw["sel_cap"] = rng.randint(1, kw["cap"])
+        if kw["n_heads"] == 1:
+            kw["kv_head_stride"] = 16 << 20                     # (rows of one head: both nestings; this way head_major for both)
+        dense, wide = plan_of(B.make_params(**kw)), plan_of(B.make_params(**kw, kv_slot_stride=1 << 24))
+        assert (dense.chunks, dense.waves, dense.heads) == (wide.chunks, wide.waves, wide.heads), kw
+        assert (dense.wide, wide.wide) == (0, 1), kw
+        several += wide.heads > 1
+        short += wide.waves == 4
+    assert several > 1000 and short > 1000
