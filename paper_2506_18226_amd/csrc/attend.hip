@@ -283,7 +283,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     int ent[U], nxt[U];                             // entries of the units in flight at the ring positions; of those that take them next
     const int n_units = (len + RPW - 1) / RPW;
     const int n_mine = n_units > wave ? (n_units - wave + NW - 1) / NW : 0;       // units of this wave
-    const int n_trips = (n_mine + U - 1) / U;
+    const int n_trips = max((n_mine + U - 1) / U, 1);
     // Requests leave in the order the program has them (the wait counts rely on it), and before the arithmetic that follows.
     auto in_order = [] {
       asm volatile("" : : : "memory");
