@@ -872,19 +872,21 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   const long long pairs = (long long)p.n_seq * p.n_heads;
   const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
   a.waves = pairs >= 512 || b_list <= (32 << 10) || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
-  // Splitting a list costs a second launch, ~2.5 us, and is worth it where one workgroup's bytes are what the launch lasts: from
-  // about 330 KB on, a little more where more pairs share the memory's rate, and 430 KB for one or two pairs, which have it to
-  // themselves.  Into 8-wave chunks of 64 KB, what their rings hold at once (so that none ends in a second, nearly empty
-  // revolution), or as many as leave no CU with two, which then lasts as long as those: 24 pairs x 804 KB in 10 chunks 10.6, in 11
-  // 11.8; 40 x 504 KB in 6 10.1, in 7 11.5; 92 x 704 KB in 2 17.0, in 3 20.7; [slot][head][D] 40 x 745 KB x 128 in 6 11.2, in 7 13.2.  Measured, us whole |
-  // split, bf16 x 64: 2 pairs x 325 KB 6.4 | 7.5; 4 x 260 KB 6.2 | 7.6, 404 KB 9.1 | 7.8; 8 x 325 KB 7.9 | 8.0, 357 KB 8.6 | 8.1; 24 x
-  // 325 KB 8.8 | 8.6, 404 KB 10.5 | 8.9; 48 x 325 KB 9.2 | 9.5, 404 KB 11.0 | 10.0; 64 x 325 KB 9.4 | 10.0, 404 KB 11.3 | 10.5, 704 KB
-  // 18.4 | 13.6; 80 x 504 KB 14.1 | 12.8, 1 MB 25.7 | 19.7; 92 x 704 KB 19.8 | 17.0; fp32 x 128 8 x 341 KB 7.9 |
-  // 7.5.  (One launch whose last workgroup to arrive merges, behind a device-scope release / acquire, took 12 us for 8 x 512 KB.)
-  // Rows of the fused V-cosine form take longer, so their line is lower: 2 x 207 KB 7.1 | 7.5, 263 KB 7.8 | 7.6; 8 x 207 KB 7.2 | 7.7,
-  // 263 KB 8.1 | 7.9; 32 x 263 KB 8.7 | 8.5; 64 x 327 KB 10.5 | 9.7; 92 x 507 KB 15.2 | 13.6.
+  // Splitting a list costs a second launch, ~2.5 us, and is worth it where one workgroup's bytes are what the launch lasts: from about
+  // 330 KB on, a little more where more pairs share the memory's rate.  Into 8-wave chunks of 64 KB, what their rings hold at once (so
+  // that none ends in a second, nearly empty revolution), or as many as leave no CU with two, which then lasts as long as those: 24
+  // pairs x 804 KB in 10 chunks 10.6, in 11 11.8; 40 x 504 KB in 6 10.1, in 7 11.5; 92 x 704 KB in 2 17.0, in 3 20.7; [slot][head][D]
+  // 40 x 745 KB x 128 in 6 11.2, in 7 13.2.  Measured, us whole | split, bf16 x 64: 1 pair x 300 KB 6.0 | 7.1, 350 KB 6.6 | 7.3
+  // (slot-major 7.6 | 7.3), 400 KB 8.4 | 7.3; 2 pairs x 300 KB 7.7 | 7.5, 350 KB 8.6 | 7.7; 4 x 260 KB 6.2 | 7.6, 404 KB 9.1 | 7.8; 8 x
+  // 325 KB 7.9 | 8.0, 357 KB 8.6 | 8.1; 24 x 325 KB 8.8 | 8.6, 404 KB 10.5 | 8.9; 48 x 325 KB 9.2 | 9.5, 404 KB 11.0 | 10.0; 64 x 325
+  // KB 9.4 | 10.0, 404 KB 11.3 | 10.5, 704 KB 18.4 | 13.6; 80 x 504 KB 14.1 | 12.8, 1 MB 25.7 | 19.7; 92 x 704 KB 19.8 | 17.0; fp32 x
+  // 128 1 x 350 KB 7.5 | 6.7, 8 x 341 KB 7.9 | 7.5.  All of these lists are full; host code knows only what they can hold.  With half
+  // of it, 48 pairs x 500 KB 7.9 | 9.2, 750 KB 10.7 | 10.0; 80 x 500 KB 8.4 | 9.8, 1 MB 14.5 | 13.6.  (One launch whose last workgroup
+  // to arrive merges, behind a device-scope release / acquire, took 12 us for 8 x 512 KB.) Rows of the fused V-cosine form take longer,
+  // so their line is lower: 2 x 207 KB 7.1 | 7.5, 263 KB 7.8 | 7.6; 8 x 207 KB 7.2 | 7.7, 263 KB 8.1 | 7.9; 32 x 263 KB 8.7 | 8.5; 64 x
+  // 327 KB 10.5 | 9.7; 92 x 507 KB 15.2 | 13.6.
   const bool fused = p.score_mode == ADSA_SCORE_VCOS_FUSED;
-  const long long line = (fused ? 240 + pairs / 2 : pairs <= 2 ? 430 : 330 + pairs) << 10, snug = (b_list + (64 << 10) - 1) / (64 << 10);
+  const long long line = (fused ? 240 + pairs / 2 : 330 + pairs) << 10, snug = (b_list + (64 << 10) - 1) / (64 << 10);
   long long nc = 1;
   if (pairs < 96 && b_list > line) nc = std::min<long long>({snug, 256 / pairs, kMaxChunks});
   // the logits (two rows of them for the fused V-cosine form) and the slot list of a chunk must fit in LDS

@@ -22,6 +22,15 @@ def test_chunks_leave_no_compute_unit_with_two_and_do_not_depend_on_the_nesting(
     assert split > 2000
 
 
+def test_one_and_two_pairs_split_where_more_do():
+    for pairs in (1, 2):
+        for D, dtype, eb in ((64, B.BF16, 2), (128, B.BF16, 2), (64, B.F32, 4), (128, B.F32, 4)):
+            for layout in ("head_major", "slot_major"):
+                plan = lambda kb: plan_of(B.make_params(n_seq=1, n_heads=pairs, head_dim=D, grid_h=64, grid_w=64, win_rows_back=1, win_col_radius=2,
+                                                        dtype=dtype, score_mode=B.SCORE_ATTN_MASS, cap=(kb << 10) // (2 * D * eb), layout=layout))
+                assert plan(325).chunks == 1 and plan(340).chunks == 6 and plan(420).chunks == 7
+
+
 def test_caches_of_wide_strides_are_launched_like_dense_ones():
     rng, several, short = random.Random(4), 0, 0
     for _ in range(20000):
