@@ -304,10 +304,10 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
 }
 
 // (512 x 8 and 512 x 16 need 130 registers, two more than let a second workgroup share the CU: held to four waves per SIMD.  One slot
-// per thread and 24 rows in flight need 104 if the addresses of all rows are kept, 66 held to six waves per SIMD: 1112 sequences x 26 rows x
-// 231 slots 8.4 us instead of 9.3, 1348 x 8 x 185 7.2 instead of 8.1; as k_compact_plan, 80 instead of 94, 1759 x 1 x 240 6.2 instead of 7.4.)
+// per thread and 24 rows in flight need 104 if the addresses of all rows are kept; held to seven waves per SIMD it is 66: 1112 sequences x 26
+// rows x 231 slots 8.4 us instead of 9.3, 1348 x 8 x 185 7.2 instead of 8.1.  k_compact_plan likewise, 72 instead of 94: 1759 x 1 x 240 6.0 instead of 7.4.)
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 6 : 1) void k_select(
+__global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : 1) void k_select(
     uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t tickets_lo, uint32_t seqs_idx_hi, uint32_t cnt_tickets_hi, uint32_t caps,
     uint32_t flags, int total, int W, int R, int w, int recent_m, float inv_w) {
   __shared__ __align__(16) RankShared sh;
@@ -462,7 +462,7 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT, S == 1 ? 6 : 1) void k_compact_plan(
+__global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
     uint32_t seqs_lo, uint32_t map_lo, uint32_t plan_lo, uint32_t vs_lo, uint32_t seqs_map_hi, uint32_t plan_vs_hi, uint32_t cap_arg, uint32_t flags,
     int total, int W, int R, int recent_m, float inv_w, int dim) {
   __shared__ __align__(16) RankShared sh;
