@@ -600,16 +600,22 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
 // of one cache and walks the rows that move in ascending tiles: load survivors -> wait, barrier -> store (a tile's destinations
 // are at most its sources and below the next tile's).  Bound by the copy: ROWS rows per thread in flight, and since nothing
 // reads a row again before the next step's attention, streaming loads and stores.  A tile ends with a wait for its last load, so the
-// best tile is the whole list: ROWS are the rows a thread has to move then, at most 32 (199 registers; 151 with 24, 107 with 16).
-// The pass of 512 sequences x 24 heads x 696 slots, 1.05 GB moved, ranking included: 230.6 us with 24 rows, 231.6 with 32, 234.6
-// with 16, 242 with 12 (233 with 16 and predicated map loads, 240 with those now; ordinary instead of streaming accesses 20 more).
-// An eviction, us with 16 rows | the rule: 64 sequences x 24 x 696 68.3 | 65.2, 8 x 24 x 696 26.0 | 22.6, 4 x 32 x 4000 63.4 | 56.2,
-// 300 x 16 x 1000 219.8 | 213.7.  Short lists: 350 sequences x 33 heads x 64 bf16, us with 16 rows | the ROWS of the rule: 100 slots
-// 86.9 | 55.1, 128 slots 93.3 | 64.5 (4 rows), 140 slots 97.8 | 77.1, 256 slots 134.6 | 132.4 (8 rows).
+// best tile is the whole list; but ROWS cost registers (30 with 4 rows, 58 with 8, 106 with 16, 151 with 24, 199 with 32) and most workgroups
+// of most steps find nothing to move and are over when they have been launched.  So: as many rows as the capacity needs up to 24, and 32
+// for launches that are resident with them at once, two workgroups per CU.  An eviction, plan included, us with 16 | 24 | 32 rows: full lists,
+// 4 sequences x 32 heads x 4000 slots - | 65.3 | 60.8, 300 x 24 x 1000 585 | 579 | 567, 64 x 16 x 4000 196 | 202 | 195, 162 x 1 x 7631 fp32 114 | 104 | 123;
+// 180 tokens in caches of 1500 slots, 300 x 20 69 | 76 | 95, 64 x 20 27.2 | 29.0 | 33.0; no row end, 300 x 16 x 1000 17.2 | 18.1 | 19.9, 150 x 24 x 2000
+// 19.8 | 20.5 | 21.8.  The pass of 512 x 24 x 696, 1.05 GB moved: 230.6 us with 24 rows, 234.6 with 16 (20 more with ordinary accesses).
+// Short lists: 350 sequences x 33 heads x 64 bf16, us with 16 rows | the ROWS of the rule: 100 slots 86.9 | 55.1, 128 slots 93.3 | 64.5 (4 rows),
+// 140 slots 97.8 | 77.1, 256 slots 134.6 | 132.4 (8 rows).
+// The strides come as a struct, which is not preloaded: each preloaded argument delays the launch of every wave, and 80 000
+// workgroups with nothing to move took 27.4 us with 12 dwords of them, 23.0 with 8.  The record is asked for with the plan's words: one
+// round trip less where rows move (64 x 24 x 696, 4 of them at a row end, 25.2 -> 24.0 us), 0.8 us more for 512 sequences of which none does.
 constexpr int kSliceLanes = 8;
+struct MoveStrides { long long slot_b, head_b; };
 template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
-                                                              int part_bits, int cap, long long slot_stride_b, long long head_stride_b) {
+                                                              int part_bits, int cap, MoveStrides stride) {
   constexpr int kPass = kMoveThreads / kSliceLanes;
   const int b = blockIdx.z, head = blockIdx.x >> part_bits, part = blockIdx.x & ((1 << part_bits) - 1);
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
@@ -619,7 +625,7 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const int n_old = pl.x, first = pl.y;
   if (pl.z == 0 || first >= n_old) return;
   const int row_in_pass = threadIdx.x / kSliceLanes, lane = threadIdx.x % kSliceLanes;
-  gchar* const base = cache + (long long)head * head_stride_b + (part * kSliceLanes + lane) * 16;
+  gchar* const base = cache + (long long)head * stride.head_b + (part * kSliceLanes + lane) * 16;
   const gint* const map = (const gint*)keep_map + (size_t)b * cap;
   for (int t0 = first; t0 < n_old; t0 += kPass * ROWS) {
     uint4 val[ROWS];
@@ -630,13 +636,13 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
     for (int u = 0; u < ROWS; ++u) {
       const int i = t0 + u * kPass + row_in_pass;
       if (i >= n_old || dst[u] == i) dst[u] = -1;            // (past the end, or stays where it is)
-      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * slot_stride_b);
+      if (dst[u] >= 0) val[u] = load_stream16(base + (long long)i * stride.slot_b);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this thread's rows are in registers ...
     __syncthreads();                                         // ... and so are everybody's, before any of them is overwritten
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
-      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * slot_stride_b, val[u]);
+      if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * stride.slot_b, val[u]);
   }
 }
 
@@ -856,10 +862,12 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
   const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);
   constexpr int rows_per_pass = kMoveThreads / kSliceLanes;
+  const bool resident = (long long)grid.x * grid.y * grid.z <= 2 * 256;
   auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8>
-            : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24> : k_compact_move<32>;
+            : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24>
+            : resident ? k_compact_move<32> : k_compact_move<24>;
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, slice_bits(p), p.cap, row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride));
+                     (const int32_t*)plan, slice_bits(p), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride)});
   return hipGetLastError();
 }
 

@@ -36,9 +36,23 @@ def registers(code_objects):
 @pytest.mark.parametrize("kernel,waves", [       # mangled name and template arguments, waves per SIMD
     (r"k_selectILi256ELi1E", 7), (r"k_selectILi256ELi3ELi8E", 5), (r"k_selectILi512ELi(8|12|16)E", 4),
     (r"k_compact_planILi256ELi1E", 7), (r"k_attend_gqaILi(64|128)ELi8E", 4),
+    (r"k_compact_moveILi(4|8)E", 8), (r"k_compact_moveILi16E", 4), (r"k_compact_moveILi24E", 3), (r"k_compact_moveILi32E", 2),
 ])
 def test_waves_per_simd(registers, kernel, waves):
     mine = {k: v for k, v in registers.items() if re.search(kernel, k)}
     assert mine
     for name, vgprs in mine.items():
         assert 512 // ((vgprs + 7) // 8 * 8) >= waves, (name, vgprs)
+
+
+def test_row_moves_preload_eight_dwords(code_objects):
+    """Most of their workgroups have nothing to move: what they cost is their launch, and each preloaded dword adds to it.  (A kernel
+    with preloaded arguments begins with loads of just these, for firmware that does not preload.)"""
+    seen = 0
+    for path in code_objects:
+        text = subprocess.run([f"{BIN}/llvm-objdump", "-d", "--no-show-raw-insn", "--mcpu=gfx950", path], check=True, capture_output=True,
+                              text=True, timeout=60).stdout
+        for kernel in re.findall(r"<\S*k_compact_moveILi\d+E\S*>:\n(.*?)s_branch", text, re.S):
+            seen += 1
+            assert sum(int(n or 1) for n in re.findall(r"s_load_dword(?:x(\d+))? ", kernel)) <= 8
+    assert seen == 5
