@@ -140,10 +140,12 @@ typedef struct adsa_params {
   int32_t dtype;               /* adsa_dtype of q, K, V, out */
   int32_t score_mode;          /* adsa_score_mode */
   int32_t cap;                 /* slots allocated per sequence (<= ADSA_MAX_CAP) */
-  int32_t sel_cap;             /* entries per row of sel_idx */
+  int32_t sel_cap;             /* entries per row of sel_idx: the longest list.  Attention launches are planned for lists
+                                  of this length (the counts are on the device), so a tight bound is the fast one */
   int64_t kv_slot_stride;      /* elements */
   int64_t kv_head_stride;      /* elements */
-  float   softmax_scale;       /* 0 => 1/sqrt(head_dim) */
+  float   softmax_scale;       /* 0 => 1/sqrt(head_dim).  With bf16 caches it is applied to the fp32 sum q.k, which has
+                                  to be finite without it */
   int32_t win_recent_m;        /* > 0: the paper's own 1-D local region (Section 4.1), the m most recent image
                                   tokens incl. the query token, instead of the 2-D window (R, w ignored) */
   int32_t evict_policy;        /* adsa_evict_policy */

@@ -86,7 +86,7 @@ __device__ __forceinline__ void vload(const gchar* p, uint32_t* w) {
 // lane g's value, g uniform
 __device__ __forceinline__ float lane_f(float x, int g) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), g)); }
 
-// Tiles in flight per wave.  8 KB of loads: with no more registers than that (124) two 8-wave workgroups share a CU, and one
+// Tiles in flight per wave.  8 KB of loads: with no more registers than that (124 and, at D = 128, the limit of 128) two 8-wave workgroups share a CU, and one
 // hides the other's first trip, merge and stores (48 x 8 lists x 300 tokens x 128: 15.7 us with 1 tile, 19.2 with 2; 32 x 8 x 649
 // x 64 11.4 with 1 or 2, 12.9 with 4).  Where there is one 8-wave workgroup per CU anyway it makes no difference: 32 x 8 x 649 x 128
 // 17.6 with 1, 17.9 with 2, 19.3 with 3.
@@ -125,6 +125,7 @@ struct GqaTail {
   int lg_global, advance;
   int unused[4];
 };
+static_assert(sizeof(GqaTail) == 64, "one dword per lane of a 16-lane row");
 
 // Everything up to the sums is in the 14 dwords of leading arguments that are preloaded into scalar registers at wave launch (see
 // k_attend): heads_flags: heads | G << 9 | append << 16 | fp32 rows << 17 | accumulate << 18 | upper 5 bits of the head stride << 19
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(NW * kWave, R > ring(D) ? 1 : 4) void k_attend_gqa(
     const int n_trips = (n_mine + R - 1) / R;
     if constexpr (!SPLIT) {
       // ... from the slots the first round trip brought in registers; the list is staged in LDS while the rows are on their way.
-      // Positions past the end of the list re-read the last token's row, as issue() does (0 times another row need not be 0: that
+      // Positions past the end of the list re-read the last token's row, as slots_k and slots_v do (0 times another row need not be 0: that
       // row may hold an infinity the list's own sums do not meet there); a tile without a token reads some row and is not multiplied.
 #pragma unroll
       for (int u = 0; u < R; ++u) {
