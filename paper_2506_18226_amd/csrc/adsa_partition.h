@@ -66,6 +66,12 @@ __device__ __forceinline__ int select_class(const QueryCell& c, int pos) {
   return pos < c.n_keep_prefix ? 0 : pos < c.P ? 1 : image;
 }
 
+// The same for a cell whose window is the 1-D one, which has no columns.
+__device__ __forceinline__ int select_class_1d(const QueryCell& c, int pos) {
+  const int j = pos - c.P;
+  return pos < c.n_keep_prefix ? 0 : pos < c.P ? 1 : j > c.jq ? -1 : j >= c.local_from ? 0 : 1;
+}
+
 // Eviction-time partition at the end of a row: 0 = pinned prefix or a token some window of the next row needs, 1 = competes for
 // the budget.
 __device__ __forceinline__ int evict_class(const QueryCell& c, int pos) {
@@ -77,6 +83,13 @@ __device__ __forceinline__ int evict_class(const QueryCell& c, int pos) {
 __device__ __forceinline__ bool is_row_end(const QueryCell& c, int s, int total) {
   return s >= 1 && s <= total && c.col == c.grid.W - 1;
 }
+
+// The fields of a record that a budget follows from.
+struct BudgetOf {
+  int grid_origin, budget, budget_num, budget_den;
+  template <typename Seq>
+  __device__ __forceinline__ explicit BudgetOf(const Seq& q) : grid_origin(q.grid_origin), budget(q.budget), budget_num(q.budget_num), budget_den(q.budget_den) {}
+};
 
 // Budget of a step: floor((P + s) * num / den) within [0, ADSA_MAX_CAP], or the given number.  (A 64-bit division is some 150
 // instructions; a quotient below 8192 is found by a float one to within 1.)

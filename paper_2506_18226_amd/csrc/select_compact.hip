@@ -305,9 +305,10 @@ __device__ __forceinline__ bool keep_largest_of(int mode) {
 
 // (512 x 8 and 512 x 16 need 130 registers, two more than let a second workgroup share the CU: held to four waves per SIMD.  One slot
 // per thread and 24 rows in flight need 104 if the addresses of all rows are kept; held to seven waves per SIMD it is 66: 1112 sequences x 26
-// rows x 231 slots 8.4 us instead of 9.3, 1348 x 8 x 185 7.2 instead of 8.1.  k_compact_plan likewise, 72 instead of 94: 1759 x 1 x 240 6.0 instead of 7.4.)
+// rows x 231 slots 8.4 us instead of 9.3, 1348 x 8 x 185 7.2 instead of 8.1.  k_compact_plan likewise, 72 instead of 94: 1759 x 1 x 240 6.0 instead of 7.4.
+// 256 x 3 for many sequences: 78 instead of 82, six waves instead of five, with which 1536 sequences are resident at once: x 8 rows 11.5 -> 10.3 us.)
 template <int NT, int S, int RB = rank_batch(S)>
-__global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : 1) void k_select(
+__global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : S == 3 && RB == 8 ? 6 : 1) void k_select(
     uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t tickets_lo, uint32_t seqs_idx_hi, uint32_t cnt_tickets_hi, uint32_t caps,
     uint32_t flags, int total, int W, int R, int w, int recent_m, float inv_w) {
   __shared__ __align__(16) RankShared sh;
@@ -322,6 +323,7 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : 1) void k_select(
   const int s = sq.step;
   int n = sq.n_res;
   const int status_in = sq.status;
+  const BudgetOf budget(sq);                                 // (loaded with the rest of the record, whether it is needed or not)
   rank_clear<NT>(sh);                                        // (while the record is on its way)
   if (F.b && tid == 0) ((gint*)address(tickets_lo, cnt_tickets_hi >> 16))[4 * b] = 0;       // for this step's k_compact_step
   if (s < 0 || status_in != 0) { if (tid == 0) { sel_cnt[b] = 0; sq.pending_slot = -1; } return; }
@@ -352,7 +354,7 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : 1) void k_select(
   // their ranks need not be read where B covers every position that can be one (positions are distinct), as in the first B steps of
   // an image and for a budget of the whole context: 8 sequences x 16 rows x 8000 slots 8.5 us without the 4 MB of scores, 13.7 with.
   const bool streaming = F.policy != ADSA_EVICT_ROW_END;
-  const uint32_t B_row = (uint32_t)effective_budget(sq, s);
+  const uint32_t B_row = streaming ? 0u : (uint32_t)effective_budget(budget, s);
   bool ranked = !streaming && (int)B_row < min(n, cell.P + cell.jq - cell.n_keep_prefix);
   int idx[S], posv[S];
 #pragma unroll
@@ -370,12 +372,20 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : 1) void k_select(
     for (int u = 0; u < S; ++u) rank[u] = 0.0f;
     if (n > 0 && ranked) rank_values<S, RB>(score, F.rows, cap, idx, rank);
     candm = fixedm = 0;
+    int cls[S];
+    if (recent_m > 0) {                                      // (uniform; issue slots count where many sequences stream: 1536 x 632 slots 6.2 -> 5.9 us)
+#pragma unroll
+      for (int u = 0; u < S; ++u) cls[u] = select_class_1d(cell, posv[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < S; ++u) cls[u] = select_class(cell, posv[u]);
+    }
 #pragma unroll
     for (int u = 0; u < S; ++u) {
       const int i = u * NT + tid;
       const bool in = i < n, planned = i == slot_new;        // the slot the query token will occupy
       const bool freed = i == hole && !planned;              // evicted, not yet reused: nobody attends it
-      const int c = (planned || freed) ? 0 : select_class(cell, posv[u]);
+      const int c = (planned || freed) ? 0 : cls[u];
       key[u] = order_key(rank[u], largest);
       bad |= in && c < 0;
       if (in && c == 1) candm |= 1u << u;

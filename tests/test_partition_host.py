@@ -69,6 +69,7 @@ int main() {
       const long pos = i < 6 ? r(0, P + H * W) : P + s - 1 + r(-2 * W, 3);
       if (pos < 0) continue;
       if (s >= 1 && select_class(c, (int)pos) != ref_select(pos, P, nkp, s - 1, W, R, w, m)) { printf("select pos=%ld s=%ld W=%ld R=%ld w=%ld m=%ld\n", pos, s, W, R, w, m); return 1; }
+      if (s >= 1 && m > 0 && select_class_1d(c, (int)pos) != select_class(c, (int)pos)) { printf("1-D class pos=%ld s=%ld m=%ld\n", pos, s, m); return 1; }
       if (s < 1 && pos >= P && select_class(c, (int)pos) != (pos < nkp ? 0 : -1)) { printf("select at s = 0\n"); return 1; }
       if (s >= 1 && evict_class(c, (int)pos) != ref_evict(pos, P, nkp, s - 1, W, R, m)) { printf("evict pos=%ld s=%ld W=%ld R=%ld m=%ld\n", pos, s, W, R, m); return 1; }
       ++checked;
