@@ -56,6 +56,22 @@ struct SlotList {
   __device__ __forceinline__ int operator[](int i) const { return (int)__builtin_amdgcn_raw_buffer_load_b32(row, i * 4, 0, 0); }
 };
 
+// Rows of a cache within 32-bit offsets of a uniform address: 16-byte streaming loads that read zeros, without an access, at any
+// offset from kRowBufferBytes on.  ~(slot + ADSA_MAX_CAP), as an unsigned number, is such an offset for every slot of a cache, and the
+// 16 bytes from there on don't reach the end of the 32 bits.
+constexpr uint32_t kRowBufferBytes = 0u - 2 * ADSA_MAX_CAP;
+static_assert((ADSA_MAX_CAP & (ADSA_MAX_CAP - 1)) == 0 && ADSA_MAX_CAP >= 16, "slot + ADSA_MAX_CAP is slot ^ ADSA_MAX_CAP");
+struct RowBuffer {
+  __amdgpu_buffer_rsrc_t rows;
+  __device__ __forceinline__ explicit RowBuffer(const gchar* first)
+      : rows(__builtin_amdgcn_make_buffer_rsrc((void*)(const char*)first, 0, (int)kRowBufferBytes, 0x00027000)) {}
+  __device__ __forceinline__ uint4 operator[](uint32_t offset) const {
+    const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)offset, 0, kNonTemporal));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  }
+  static constexpr int kNonTemporal = 2;           // the instruction's cache bits
+};
+
 // Round to the nearest bf16, ties to even (v_cvt_pk_bf16_f32; subnormals are kept, a NaN stays one)
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
@@ -104,14 +120,20 @@ __device__ __forceinline__ float xor_sum(float x) {
     return __uint_as_float(r.x) + __uint_as_float(r.y);       // one of the two is x itself, the other its partner
   }
 }
+// (of values of which none is a signalling NaN: fmaxf would first quiet each of them)
+__device__ __forceinline__ float max2(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 template <int X>
 __device__ __forceinline__ float xor_max(float x) {
-  if constexpr (X == 8) return fmaxf(x, dpp_f<0x128>(x));
+  if constexpr (X == 8) return max2(x, dpp_f<0x128>(x));
   else {
     const unsigned u = __float_as_uint(x);
     const u32x2 r = X == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false)
                             : __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    return max2(__uint_as_float(r.x), __uint_as_float(r.y));
   }
 }
 

@@ -93,9 +93,21 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
+// acc = acc * c + x where acc is kept (left to itself the compiler lets x's register become the sum and copies all of them back
+// wherever the pairs of a last revolution are left out)
+__device__ __forceinline__ void rescale_add(float& acc, float c, float x) { asm("v_fma_f32 %0, %0, %1, %2" : "+v"(acc) : "v"(c), "v"(x)); }
+// a raw list entry inside the cache: no lane touches memory outside it
+__device__ __forceinline__ int clamp_slot(int raw, int last) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(raw), "s"(last));
+  return r;
+}
 constexpr float kLowest = -3.4028234663852886e38f;     // the running maximum of a state that has seen no token: z - kLowest is never NaN
 
-__device__ __forceinline__ int slot_of(int entry) { return entry < 0 ? ~entry : entry; }
+// Entry of the staged list: the slot, or a negative number of it where it is not attended in the loop (see RowBuffer).
+constexpr int kUnattended = ~ADSA_MAX_CAP;
+__device__ __forceinline__ int list_entry(int slot, bool attended) { return slot ^ (attended ? 0 : kUnattended); }
+__device__ __forceinline__ int slot_of(int entry) { return entry < 0 ? entry ^ kUnattended : entry; }
 
 constexpr int kBurst = 512;        // bytes of a token that a workgroup of several heads takes
 
@@ -202,10 +214,11 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     for (int k = 0; k < PF; ++k) pf_slot[k] = list[tid + k * kAttThreads];
   }
   const uint4 qr = load16((const gchar*)address(q_lo, cnt_q_hi >> 16) + row_off);
-  // the query token's own K/V row (Section 4.2 append): the first wave attends and stores it, 16 bytes of K and V per lane.
+  // the query token's own K/V row (Section 4.2 append): the last wave, which has the fewest units, attends and stores it, 16 bytes of
+  // K and V per lane.
   // fp32 rows of a bf16 cache (twice as many bytes) are rounded once, when they are used
   uint4 nk[4 / EB], nv[4 / EB];
-  if (append && wave == 0) {
+  if (append && wave == NW - 1) {
     const gchar* const k_new_g = (const gchar*)address(kn_lo, kn_vn_hi & 0xFFFF) + (new_f32 ? 2 * row_off : row_off);
     const gchar* const v_new_g = (const gchar*)address(vn_lo, kn_vn_hi >> 16) + (new_f32 ? 2 * row_off : row_off);
     nk[0] = load16(k_new_g);
@@ -233,9 +246,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   const int t_end = DIRECT ? cnt : chunk_begin(cnt, chunk + 1, n_chunks);
   if (t_begin >= t_end) return;                     // fewer tokens than chunks
   const int len = t_end - t_begin;
-  // The chunk's slot list, one entry per token (filled below): the slot, or ~slot for the query token's own; then entries of no
-  // token, ~0, up to one revolution past the last unit.  A negative entry is not attended in the loop.  The last word of a row
-  // of logits takes what belongs to no token.
+  // The chunk's slot list, one entry per token (filled below), and entries of no token up to one revolution past the last unit.
+  // Those and the query token's own are not attended in the loop.  The last word of a row of logits takes what belongs to no token.
   const int n_ent = ((len + kRev - 1) / kRev + 1) * kRev, dump = n_ent - 1;
   float* const s_logit = reinterpret_cast<float*>(s_ent + n_ent);
   if constexpr (!DIRECT) {
@@ -276,8 +288,12 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   // number of outstanding requests stays nearly constant instead of draining once per batch.
   // Small launches are bound by what this loop issues: 40 lists of 427 x 64 on 8 waves each keep a SIMD with 2 waves busy for
   // all of the 2.7 us between the slot list and the merge when a unit takes 102 issue slots (one unit at a time: a rescale per
-  // unit, products of 64 bits for addresses, q.k on unpacked values, selects of the query token's row).  It takes 50 now, and
-  // the launch 4.9 us instead of 5.6; 320 lists x 427 x 64 9.3 | 10.2, 768 x 647 x 64, which HBM bounds, 21.5 | 22.2.
+  // unit, products of 64 bits for addresses, q.k on unpacked values, selects of the query token's row).  It took 54 with two units per
+  // rescale and 32-bit addresses, and the launch 4.9 us instead of 5.6; 51 since what is not attended arrives as zeros instead of being
+  // masked, with no copies of the sums behind the loop, no branches where the list is staged, and the outputs and the query token given
+  // to the last wave: 4.90 -> 4.72 us; 16 x 130 x 64 fp32 3.88 -> 3.73, 320 x 427 x 64 8.86 -> 8.75, 128 x 1159 x 128 16.4 -> 16.2, 768 x
+  // 640 x 64, which HBM bounds, 21.0 -> 20.9.  (16 waves for few pairs: 0.65 - 0.94 of the speed, their launch and first trip cost more
+  // than the shorter loop saves.)
   {
     uint4 kr[U], vr[U];
     int ent[U], nxt[U];                             // entries of the units in flight at the ring positions; of those that take them next
@@ -289,22 +305,21 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
       asm volatile("" : : : "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
-    // Entries that are not attended read slot 0 (valid memory, one row for all of them) and are masked when they are folded.
-    const gchar* const ku = k_base + (long long)head0 * head_stride_b;        // uniform
-    const gchar* const vu = v_base + (long long)head0 * head_stride_b;
+    // Entries that are not attended read zeros without an access (RowBuffer; an entry that is a slot is at most the offset of its
+    // row).  WIDE: they read slot 0 and are masked when they are folded.
+    const RowBuffer ku(k_base + (long long)head0 * head_stride_b), vu(v_base + (long long)head0 * head_stride_b);       // uniform
     const uint32_t lane32 = (uint32_t)(head - head0) * (uint32_t)head_stride_b + (uint32_t)dl * 16u;
-    auto load = [&](const gchar* uni, const gchar* own, int e) -> uint4 {
-      const int slot = max(e, 0);
-      if constexpr (!WIDE) return load_stream16(uni + (__umul24((uint32_t)slot, stride24) + lane32));
-      else return load_stream16(own + (long long)slot * stride_b);
+    auto load = [&](const RowBuffer& rows, const gchar* own, int e) -> uint4 {
+      if constexpr (!WIDE) return rows[max(__umul24((uint32_t)e, stride24) + lane32, (uint32_t)e)];
+      else return load_stream16(own + (long long)max(e, 0) * stride_b);
     };
+    auto entry = [&](int j, int slot) { return list_entry(slot, j < len && slot != new_slot); };
     // prologue: the pattern of a steady-state trip, so that the loop's wait counts match
 #pragma unroll
     for (int u = 0; u < U; u += 2) {
 #pragma unroll
       for (int i = u; i < u + 2; ++i) {
-        const int slot = min(max(slot_a[i], 0), cap - 1);        // never touch memory outside the cache
-        ent[i] = unit0 + i * NW * RPW < len && slot != new_slot ? slot : ~slot;
+        ent[i] = entry(unit0 + i * NW * RPW, clamp_slot(slot_a[i], cap - 1));
       }
       kr[u] = load(ku, kb, ent[u]);
       kr[u + 1] = load(ku, kb, ent[u + 1]);
@@ -316,20 +331,18 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     // ... and while these rows are on their way the chunk's slot list goes to LDS
     tail = ((const ADSA_GLOBAL uint32_t*)((const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes))[lane % 16];
     int new_at = 0;                               // 1 + list position of the query token's slot, if this thread stages it
-    auto stage = [&](int j, int raw) {
-      const int slot = min(max(raw, 0), cap - 1);
-      const bool own = slot == new_slot && j < len;
-      s_ent[j] = j >= len ? ~0 : own ? ~slot : slot;
-      new_at = own ? j + 1 : new_at;
+    auto stage = [&](int j, int slot) {
+      s_ent[j] = entry(j, slot);
+      new_at = slot == new_slot && j < len ? j + 1 : new_at;
     };
 #pragma unroll
     for (int k = 0; k < PF; ++k)
       if (k * kAttThreads < n_ent) {                // (uniform; n_ent is a multiple of the revolution, not of the threads)
         const int j = tid + k * kAttThreads;
-        pf_slot[k] = min(max(pf_slot[k], 0), cap - 1);
+        pf_slot[k] = clamp_slot(pf_slot[k], cap - 1);
         if (j < n_ent) stage(j, pf_slot[k]);
       }
-    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, list[t_begin + j]);
+    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, clamp_slot(list[t_begin + j], cap - 1));
     if (new_slot >= 0) {                          // (uniform)
       const unsigned long long who = __ballot(new_at != 0);
       const int at = who ? __builtin_amdgcn_readlane(new_at, __ffsll((long long)who) - 1) : 0;
@@ -345,8 +358,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
       }
     }
     // Section 4.2: the query token's row enters the cache, and, if its slot is in the list, one lane group (per head) of the
-    // first wave starts its state with it, from the registers that hold it (no lane reads that row from memory)
-    if (new_slot >= 0 && wave == 0) {
+    // last wave starts its state with it, from the registers that hold it (no lane reads that row from memory)
+    if (new_slot >= 0 && wave == NW - 1) {
       if constexpr (EB == 2)
         if (new_f32) {
           // (converted here, not where the compiler would like to: next to the loads, whose return it would wait for)
@@ -354,9 +367,9 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
           nk[0] = pack8_bf16(nk[0], nk[1]);
           nv[0] = pack8_bf16(nv[0], nv[1]);
         }
-      int at = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) at = max(at, s_new[w]);
+      const int news = s_new[lane % NW];
+      const unsigned long long who = __ballot(news != 0);
+      const int at = who ? __builtin_amdgcn_readlane(news, __ffsll((long long)who) - 1) : 0;
       const bool mine = ts == 0;
       if (mine && hs < heads_here && chunk == n_chunks - 1) {
         const long long off = (long long)new_slot * stride_b;
@@ -410,15 +423,17 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
       const float m_new = max3(m, za, zb);
       const float corr = fast_exp2(m - m_new), pa = fast_exp2(za - m_new), pb = fast_exp2(zb - m_new);
       m = m_new;
-      l = fmaf(l, corr, pa) + pb;
-      // (what a masked entry read may be anything: 0 times it need not be 0)
-      const uint4 xa = make_uint4(on_a ? vr[u].x : 0u, on_a ? vr[u].y : 0u, on_a ? vr[u].z : 0u, on_a ? vr[u].w : 0u);
-      const uint4 xb = make_uint4(on_b ? vr[u + 1].x : 0u, on_b ? vr[u + 1].y : 0u, on_b ? vr[u + 1].z : 0u, on_b ? vr[u + 1].w : 0u);
+      l = fmaf(l, corr, pa + pb);
+      uint4 xa = vr[u], xb = vr[u + 1];
+      if constexpr (WIDE) {                         // (what a masked entry read may be anything: 0 times it need not be 0)
+        xa = make_uint4(on_a ? xa.x : 0u, on_a ? xa.y : 0u, on_a ? xa.z : 0u, on_a ? xa.w : 0u);
+        xb = make_uint4(on_b ? xb.x : 0u, on_b ? xb.y : 0u, on_b ? xb.z : 0u, on_b ? xb.w : 0u);
+      }
       float va[EPL], vc[EPL];
       Elems<EB>::unpack(xa, va);
       Elems<EB>::unpack(xb, vc);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(pb, vc[e], fmaf(acc[e], corr, pa * va[e]));
+      for (int e = 0; e < EPL; ++e) rescale_add(acc[e], corr, fmaf(pb, vc[e], pa * va[e]));
       if constexpr (VF) {                         // Eq. 2-3 bookkeeping of these rows: |v_h|^2 and v_h . u_h
         float dva = 0.0f, sva = 0.0f, dvb = 0.0f, svb = 0.0f;
 #pragma unroll
@@ -551,31 +566,37 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   // log2-domain normaliser of the whole workgroup, worked out by every wave from the waves' states: lane w (modulo NW) weighs wave w
   static_assert(NW == 4 || NW == 8, "reductions over 4 or 8 lanes");
   const float wm = s_wm[lane % NW];
-  float M = fmaxf(wm, dpp_f<0xB1>(wm));
-  M = fmaxf(M, dpp_f<0x4E>(M));
-  if constexpr (NW == 8) M = fmaxf(M, dpp_f<0x141>(M));
+  float M = max2(wm, dpp_f<0xB1>(wm));
+  M = max2(M, dpp_f<0x4E>(M));
+  if constexpr (NW == 8) M = max2(M, dpp_f<0x141>(M));
   const float weight = fast_exp2(wm - M);           // (a wave that saw no token: 0, or l and acc are 0)
   float L = s_wl[lane % NW] * weight;
   L += dpp_f<0xB1>(L);
   L += dpp_f<0x4E>(L);
   if constexpr (NW == 8) L += dpp_f<0x141>(L);
   const size_t row = (size_t)b * n_heads + head;
-  if (tid < D) {
+  const int d = tid - (kAttThreads - D);            // output element: the last waves have the fewest tokens of the score update
+  if (d >= 0) {
     static_assert(D <= kAttThreads, "one output element per thread");
-    float a = 0.0f;
+    float w[NW], part[NW], a = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-      a = fmaf(s_wacc[w * D + tid], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), w)), a);
+    for (int k = 0; k < NW; ++k) {
+      w[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(weight), k));
+      part[k] = s_wacc[k * D + d];
+    }
+    __builtin_amdgcn_sched_barrier(0);              // (each product right behind its weight's readlane would wait for it)
+#pragma unroll
+    for (int k = 0; k < NW; ++k) a = fmaf(part[k], w[k], a);
     if constexpr (DIRECT) {
       const float val = __fdividef(a, L);
-      if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + tid] = val;
-      else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + tid] = (uint16_t)f32_to_bf16_rne(val);
-      if (tid == 0) lse_g[row] = (M + __log2f(L)) * kLn2;
+      if (EB == 4) reinterpret_cast<gfloat*>(out_g)[row * D + d] = val;
+      else reinterpret_cast<ADSA_GLOBAL uint16_t*>(out_g)[row * D + d] = (uint16_t)f32_to_bf16_rne(val);
+      if (d == 0) lse_g[row] = (M + __log2f(L)) * kLn2;
     } else {
       const size_t pidx = row * n_chunks + chunk;
-      ((gfloat*)tail_address(offsetof(AttendTail, part_acc)))[pidx * D + tid] = a;
+      ((gfloat*)tail_address(offsetof(AttendTail, part_acc)))[pidx * D + d] = a;
       gfloat* const ml = (gfloat*)tail_address(offsetof(AttendTail, part_ml)) + pidx * 2;
-      if (tid == 0) { ml[0] = M; ml[1] = L; }
+      if (d == 0) { ml[0] = M; ml[1] = L; }
     }
   }
 
@@ -822,12 +843,12 @@ static int reserved_chunks(const adsa_params& p) {
 }
 
 // Whether a lane reaches every row of its workgroup's heads with a 24-bit product and a 32-bit offset: rows up to 16 MB apart
-// whose cache spans less than 4 GB (all dense caches: at most 8192 slots of 128 KB).  Others -- a slot that holds every sequence
+// whose cache spans less than 4 GB less the offsets that stand for no row (all dense caches: at most 8192 slots of 128 KB).  Others -- a slot that holds every sequence
 // and layer of a model, say -- take the form with 64-bit offsets, 4 to 8 registers more, by the same launch rule: one form of it with 8
 // waves and one head for all of them took 64 sequences x 24 x 64, rows 18 MB apart, 700 tokens from 56 us to 68, 60 tokens from 9.6 to 14.2.
 static bool short_offsets(const adsa_params& p, int heads) {
   const long long eb = elem_bytes(p), slot_b = p.kv_slot_stride * eb;
-  return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb < (1ll << 32);
+  return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb <= (long long)kRowBufferBytes;
 }
 
 AttendPlan make_attend_plan(const adsa_params& p) {

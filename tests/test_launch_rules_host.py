@@ -46,3 +46,13 @@ def test_caches_of_wide_strides_are_launched_like_dense_ones():
         several += wide.heads > 1
         short += wide.waves == 4
     assert several > 1000 and short > 1000
+
+
+def test_32_bit_offsets_end_where_the_unattended_ones_begin():
+    """Offsets from 2^32 - 2 * 8192 on stand for no row: a cache whose rows end there is reached with 32 bits, one byte more and it is not."""
+    limit, n = (1 << 32) - 2 * B.MAX_CAP, 513                  # 512 strides and a row of 128 bytes
+    for stride, wide in (((limit - 128) // 512 // 16 * 16, 0), ((limit - 128) // 512 // 16 * 16 + 16, 1)):
+        p = B.make_params(n_seq=1, n_heads=1, head_dim=64, grid_h=64, grid_w=64, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
+                          score_mode=B.SCORE_ATTN_MASS, cap=n, layout="slot_major", kv_slot_stride=stride // 2, kv_head_stride=64)
+        assert (n - 1) * stride + 128 <= limit if not wide else (n - 1) * stride + 128 > limit
+        assert plan_of(p).wide == wide
