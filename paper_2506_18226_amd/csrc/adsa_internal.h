@@ -105,6 +105,13 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
 // kAdvanceActive, `tickets` cleared by the step's launch_select.
 bool one_launch_compact(const adsa_params& p);
 hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st);
+// A step of few pairs in two launches (where rank_in_attend says so): the attention launch ranks for itself and leaves in the workspace
+// what launch_step_finish does to the record, pos and score, at a row end with the eviction.
+bool rank_in_attend(const adsa_params& p, const AttendPlan& plan, const Workspace& w);
+hipError_t launch_ranked_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,
+                                int32_t* sel_idx, int32_t* sel_cnt, void* out, float* lse, char* ws, const Workspace& w, bool new_f32,
+                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws, const Workspace& w, hipStream_t st);
 // once per device, before the first launch there: kernels that may ask for more than 64 KB of dynamic LDS
 hipError_t gqa_prepare_kernels();
 hipError_t vcos_prepare_kernels();
@@ -120,4 +127,5 @@ struct adsa_launch_plan {
   int32_t wide;                       // attention: the form with 64-bit offsets
 };
 int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out);
+int adsa_step_launches(const adsa_params* p);      // kernels of an adsa_step that evicts by rows and ranks by attention mass: 2, 3 or 4; else 0
 }

@@ -115,18 +115,26 @@ hipEvent_t prof_event() {
   return g_prof.ev[g_prof.used++];
 }
 
-hipError_t timed_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
-                        const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
-                        void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
-                        int advance, bool new_f32, hipStream_t st) {
+// Calls launch(start, stop) with the hook's next pair of events, or with none.
+template <typename Launch>
+hipError_t timed(Launch launch) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (g_prof.on) {
     e0 = prof_event();
     e1 = prof_event();
     if (!e0 || !e1) e0 = e1 = nullptr;
   }
-  return launch_attend(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append,
-                       advance, new_f32 && p.dtype == ADSA_BF16, st, e0, e1);
+  return launch(e0, e1);
+}
+
+hipError_t timed_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
+                        const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
+                        void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
+                        int advance, bool new_f32, hipStream_t st) {
+  return timed([&](hipEvent_t e0, hipEvent_t e1) {
+    return launch_attend(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append,
+                         advance, new_f32 && p.dtype == ADSA_BF16, st, e0, e1);
+  });
 }
 
 // ---- built-in scratch of adsa_step_static: one array per GPU, held until the process ends.  In host code
@@ -176,6 +184,14 @@ int step_launches(const adsa_params* p, const AttendPlan& plan, const Workspace&
       return ADSA_ERR_LAUNCH;
   }
   if (vcos && !streaming && launch_vcos(*p, seqs, false, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+  if (compact && rank_in_attend(*p, plan, w)) {
+    const hipError_t e = timed([&](hipEvent_t e0, hipEvent_t e1) {
+      return launch_ranked_attend(*p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w,
+                                  (flags & ADSA_FLAG_NEW_F32) != 0 && p->dtype == ADSA_BF16, st, e0, e1);
+    });
+    if (e != hipSuccess || launch_step_finish(*p, seqs, keep_map, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+    return ADSA_OK;
+  }
   const bool one_launch = compact && one_launch_compact(*p);
   int32_t* const tickets = one_launch ? reinterpret_cast<int32_t*>(ws + w.plan_off) : nullptr;
   if (launch_select(*p, seqs, sel_idx, sel_cnt, true, tickets, st) != hipSuccess) return ADSA_ERR_LAUNCH;
@@ -366,6 +382,13 @@ int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out) {
   const VcosPlan v = make_vcos_plan(eff);
   *out = {a.n_chunks, a.waves, a.heads, one_launch_compact(eff) ? 1 : 0, v.split ? 1 : 0, v.tile, a.wide ? 1 : 0};
   return ADSA_OK;
+}
+
+int adsa_step_launches(const adsa_params* p) {
+  adsa_params eff;
+  if (resolve_params(p, &eff) != ADSA_OK || eff.evict_policy != ADSA_EVICT_ROW_END || eff.score_mode != ADSA_SCORE_ATTN_MASS) return 0;
+  const AttendPlan plan = make_attend_plan(eff);
+  return rank_in_attend(eff, plan, make_workspace(eff, plan)) ? 2 : one_launch_compact(eff) ? 3 : 4;
 }
 
 int adsa_profile_enable(int on) {

@@ -23,8 +23,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "adsa_internal.h"
-#include "adsa_device.h"
+#include "adsa_rank.h"
 
 namespace adsa {
 namespace {
@@ -147,6 +146,18 @@ struct AttendTail {
 };
 static_assert(sizeof(AttendTail) == 64, "one dword per lane of a 16-lane row");
 
+// The same for a launch that ranks for itself (RANK).
+struct RankTail {
+  char* out;
+  float* lse;
+  float* vals;          // [n_seq][n_heads][cap]   the resident slots' scores after this step's attention
+  int32_t* plan;        // [n_seq][4]   see k_step_finish
+  int total, W, R, w, recent_m;
+  float inv_w;
+  int unused[2];
+};
+static_assert(sizeof(RankTail) == 64 && offsetof(RankTail, out) == offsetof(AttendTail, out) && offsetof(RankTail, lse) == offsetof(AttendTail, lse), "one dword per lane of a 16-lane row");
+
 // DIRECT: the list of a (sequence, head) is not split (grid.x == 1): the workgroup finishes its heads alone.
 // The build asks for leading kernel arguments to be preloaded into scalar registers at wave launch, and 14 dwords of them are.
 // Everything up to the sums is in those 14 (addresses have 48 bits, so six of them take 9 dwords): the first round trip is then
@@ -156,16 +167,23 @@ static_assert(sizeof(AttendTail) == 64, "one dword per lane of a 16-lane row");
 //   heads_flags: heads | append << 16 | fp32 rows << 17 | accumulate << 18 | upper 5 bits of the head stride << 19 | chunks << 24;
 //   caps: cap | sel_cap << 16
 // HT > 1: the workgroup takes HT heads, the lane groups of a wave-load being the HT heads of RPW / HT tokens.
-template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE>
+// RANK > 0: one launch of a decode step of few (sequence, head) pairs instead of k_select and this one.  Every workgroup of a sequence
+// ranks its slots, RANK per thread, for itself, with the append planned, and attends the list it gets, which needs no trip through
+// memory.  It only reads the record, pos and score, which the sequence's other workgroups may be reading still: what changes of
+// them goes to the workspace, for k_step_finish, the next kernel on the stream (the first head's workgroup writes sel_idx, sel_cnt and
+// the plan; a rejected record is marked here, which is what the others find too).
+template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE, int RANK = 0>
 __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t q_lo, uint32_t kn_lo,
                                                       uint32_t vn_lo, uint32_t seqs_idx_hi, uint32_t cnt_q_hi, uint32_t kn_vn_hi,
                                                       uint32_t heads_flags, uint32_t caps, uint32_t stride24, uint32_t head_stride16,
-                                                      float scale_log2, AttendTail T) {
+                                                      float scale_log2, std::conditional_t<(RANK > 0), RankTail, AttendTail> T) {
   constexpr int kAttThreads = NW * kWave;           // the waves of the workgroup share one token chunk
   constexpr int EPL = Elems<EB>::N;                 // elements per lane
   constexpr int LPR = D / EPL;                      // lanes per row
   constexpr int RPW = kWave / LPR / HT;             // tokens per wave-load
   static_assert(HT == 1 || (DIRECT && !VF && RPW * HT * LPR == kWave), "several heads: whole lists only");
+  static_assert(RANK == 0 || (HT == 1 && DIRECT && !VF && !WIDE), "ranking: whole lists of one head");
+  constexpr int kSlots = RANK > 0 ? RANK : 1;       // slots per thread of the ranking
   constexpr int PF = 4;                             // list entries a thread fetches, and score read-modify-writes it starts, early
   constexpr int kRev = NW * U * RPW;                // tokens of one ring revolution of the workgroup
   extern __shared__ int s_ent[];                    // the chunk's slot list [n_ent], then logits [HT][n_ent] ([2][n_ent] for VF)
@@ -189,14 +207,23 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   // the loop and the slots whose score words this thread updates at the end.  The record and the
   // count are pinned here so that they cannot drift behind the count test below.
   ADSA_GLOBAL adsa_seq* const sqp = (ADSA_GLOBAL adsa_seq*)address(seqs_lo, seqs_idx_hi & 0xFFFF) + b;
-  const int cnt_raw = ((const gint*)address(cnt_lo, cnt_q_hi & 0xFFFF))[b];
+  int cnt = 0, pending = -1;
+  if constexpr (RANK == 0) {
+    cnt = ((const gint*)address(cnt_lo, cnt_q_hi & 0xFFFF))[b];
+    pending = sqp->pending_slot;
+  }
   gchar* const k_base = (gchar*)sqp->k;
   gchar* const v_base = (gchar*)sqp->v;
   gfloat* const score = (gfloat*)sqp->score;
-  const int pending = sqp->pending_slot;
+  // (RANK: the rest of the record, as the ranking needs it)
+  const int step = RANK > 0 ? sqp->step : 0, status_in = RANK > 0 ? sqp->status : 0;
+  const gint* const pos = RANK > 0 ? (const gint*)sqp->pos : nullptr;
+  const BudgetOf budget(*sqp);
+  const int n_keep_prefix = RANK > 0 ? sqp->n_keep_prefix : 0;
+  int n_res = RANK > 0 ? sqp->n_res : 0;
   gfloat* const u_state = VF ? (gfloat*)sqp->vcos_u : nullptr;
   __builtin_amdgcn_sched_barrier(0);                // (the scalar loads leave first: the rows need them and the first slots)
-  const gint* idx = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
+  const gint* const idx_row = (const gint*)address(idx_lo, seqs_idx_hi >> 16) + (size_t)b * sel_cap;
   const size_t row_off = ((size_t)b * n_heads + head) * D * EB + dl * 16;
   // The wave takes the RPW-token units wave, wave + NW, ... of the chunk, in that order; unit number k of the
   // wave holds, for this lane, token (wave + k * NW) * RPW + ts.  slot_a[u]: slot of unit u.  pf_slot: the whole list
@@ -204,9 +231,16 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   // (These loads need nothing but preloaded arguments: they leave before anything waits for a scalar load.)
   int slot_a[U];
   int pf_slot[PF];
-  const SlotList list(idx, sel_cap);
+  const SlotList list(idx_row, sel_cap);
   const int unit0 = wave * RPW + ts;                // this lane's token of the wave's first unit
-  if constexpr (DIRECT) {
+  uint32_t tail = 0u;                               // lane i (modulo 16): dword i of T
+  auto load_tail = [&] {
+    tail = ((const ADSA_GLOBAL uint32_t*)((const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes))[lane % 16];
+  };
+  auto tail_word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)tail, i); };
+  auto tail_address = [&](size_t at) { return address(tail_word(at / 4), tail_word(at / 4 + 1)); };
+  if constexpr (RANK > 0) load_tail();
+  else if constexpr (DIRECT) {
 #pragma unroll
     for (int u = 0; u < U; ++u) slot_a[u] = list[unit0 + u * NW * RPW];
     __builtin_amdgcn_sched_barrier(0);
@@ -226,10 +260,82 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     if constexpr (EB == 2)
       if (new_f32) { nk[1] = load16(k_new_g + 16); nv[1] = load16(v_new_g + 16); }
   }
-  pin_uniform(cnt_raw); pin_uniform(k_base); pin_uniform(v_base); pin_uniform(score); pin_uniform(pending);
+  pin_uniform(cnt); pin_uniform(k_base); pin_uniform(v_base); pin_uniform(score); pin_uniform(pending);
   if constexpr (VF) pin_uniform(u_state);
 
-  const int cnt = min(cnt_raw, sel_cap);
+  cnt = min(cnt, sel_cap);
+  // ---- RANK: k_select's part, of which this thread keeps the places of its slots and their old scores of this head
+  uint32_t dest[kSlots], take = 0;
+  float old_score[kSlots];
+  int n_ranked = 0;                                  // resident slots, the query token's included
+  if constexpr (RANK > 0) {
+    constexpr int NT = kAttThreads, S = kSlots;
+    __shared__ __align__(16) RankShared sh;
+    rank_clear<NT>(sh);
+    const bool active = step >= 0 && status_in == 0, sane = n_res >= 0 && n_res <= cap, full = step >= 1 && n_res >= cap;
+    const int slot_new = step >= 1 ? n_res : -1;     // the end of the cache: where the query token goes
+    const int n = slot_new + 1 > 0 ? slot_new + 1 : n_res;
+    n_ranked = n;
+    int idx[S], posv[S];
+    float rank[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) { idx[u] = min(u * NT + tid, n - 1); posv[u] = 0; rank[u] = old_score[u] = 0.0f; dest[u] = 0; }
+    if (active && sane && !full && n > 0) {          // (an empty sequence's pointers may be null)
+#pragma unroll
+      for (int u = 0; u < S; ++u) { posv[u] = elem(pos, idx[u]); old_score[u] = elem(score + (size_t)head * cap, idx[u]); }
+      rank_values<S, S == 1 ? 24 : 12>(score, n_heads, cap, idx, rank);
+    }
+    const int total = (int)tail_word(offsetof(RankTail, total) / 4);
+    uint32_t reject = !active ? 0u : !sane || step > total ? ADSA_SEQ_BAD_STATE : full ? ADSA_SEQ_CACHE_FULL : 0u;
+    if (active && reject == 0) {
+      const GridWidth grid = {(int)tail_word(offsetof(RankTail, W) / 4), __uint_as_float(tail_word(offsetof(RankTail, inv_w) / 4))};
+      struct { int grid_origin, n_keep_prefix; } cell_of = {budget.grid_origin, n_keep_prefix};
+      const QueryCell cell = make_query_cell(cell_of, step, grid, (int)tail_word(offsetof(RankTail, R) / 4), (int)tail_word(offsetof(RankTail, w) / 4),
+                                             (int)tail_word(offsetof(RankTail, recent_m) / 4));
+      uint32_t key[S], candm = 0, fixedm = 0;
+      bool bad = false;
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int i = u * NT + tid, c = i == slot_new ? 0 : select_class(cell, posv[u]);
+        key[u] = order_key(rank[u], true);
+        bad |= i < n && c < 0;
+        if (i < n && c == 1) candm |= 1u << u;
+        if (i < n && c != 1) fixedm |= 1u << u;
+        if (i == slot_new) old_score[u] = 0.0f;      // a new slot starts at 0
+      }
+      const Stats st = block_stats<NT, S>(sh, key, candm, bad);
+      if (st.bad) reject = ADSA_SEQ_BAD_STATE;
+      else {
+        const uint32_t B = (uint32_t)effective_budget(budget, step);
+        uint32_t thr, need_eq, sure = fixedm, eq = 0, count;
+        top_threshold<NT, S>(sh, key, candm, st, min(B, st.n_cand), &thr, &need_eq);
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          if (((candm >> u) & 1u) && key[u] > thr) sure |= 1u << u;
+          if (((candm >> u) & 1u) && key[u] == thr) eq |= 1u << u;
+        }
+        take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &count);
+        gint* const out = const_cast<gint*>(idx_row);
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+          if (((take >> u) & 1u) && dest[u] < (uint32_t)sel_cap) {
+            const int slot = u * NT + tid;
+            s_ent[dest[u]] = list_entry(slot, slot != slot_new);
+            if (head0 == 0) elem(out, dest[u]) = slot;
+          }
+        if (count > (uint32_t)sel_cap) reject = ADSA_SEQ_SEL_OVERFLOW;
+        else cnt = (int)count;
+      }
+    }
+    pending = reject == 0 && active ? slot_new : -1;
+    gint* const plan = (gint*)tail_address(offsetof(RankTail, plan)) + 4 * b;
+    if (head0 == 0 && tid == 0) {
+      *reinterpret_cast<ADSA_GLOBAL u32x4*>(plan) = u32x4{0u, (uint32_t)(active && reject == 0 ? step : -1), (uint32_t)n, (uint32_t)cnt};
+      ((gint*)address(cnt_lo, cnt_q_hi & 0xFFFF))[b] = cnt;
+      if (reject != 0) sqp->status = status_in | (int)reject;
+      if (!active || reject != 0) sqp->pending_slot = -1;
+    }
+  }
   if (cnt <= 0) {                                   // inactive or rejected sequence: zero-filled row
     if (chunk == 0) {
       const size_t row = (size_t)b * n_heads + head0;
@@ -238,7 +344,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
         else ((ADSA_GLOBAL uint16_t*)T.out)[row * D + o] = 0;
         if (o % D == 0) ((gfloat*)T.lse)[row + o / D] = 0.0f;
       }
-      if (head0 == 0 && tid == 0) advance_empty(sqp, T.advance);
+      if constexpr (RANK == 0)
+        if (head0 == 0 && tid == 0) advance_empty(sqp, T.advance);
     }
     return;
   }
@@ -260,7 +367,8 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   const int new_slot = (append && pending < cap) ? pending : -1;
 
   const Elems<EB> qv(qr, scale_log2);
-  const long long stride_b = WIDE ? T.slot_stride_b : (long long)stride24;
+  long long stride_b = (long long)stride24;
+  if constexpr (WIDE) stride_b = T.slot_stride_b;
   const long long head_stride_b = (long long)address(head_stride16, (heads_flags >> 19) & 0x1F) * 16;
   const long long lane_off = (long long)head * head_stride_b + dl * 16;
   gchar* const kb = k_base + lane_off;
@@ -277,7 +385,6 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   }
 
   float pf_old[PF];
-  uint32_t tail;                                    // lane i (modulo 16): dword i of T
   float m = kLowest, l = 0.0f, acc[EPL];
 #pragma unroll
   for (int e = 0; e < EPL; ++e) acc[e] = 0.0f;
@@ -314,12 +421,18 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
       else return load_stream16(own + (long long)max(e, 0) * stride_b);
     };
     auto entry = [&](int j, int slot) { return list_entry(slot, j < len && slot != new_slot); };
+    if constexpr (RANK > 0) {                      // the list is in LDS already, but for the entries of no token
+      for (int j = cnt + tid; j < n_ent; j += kAttThreads) s_ent[j] = list_entry(0, false);
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < U; ++u) slot_a[u] = s_ent[unit0 + u * NW * RPW];
+    }
     // prologue: the pattern of a steady-state trip, so that the loop's wait counts match
 #pragma unroll
     for (int u = 0; u < U; u += 2) {
 #pragma unroll
       for (int i = u; i < u + 2; ++i) {
-        ent[i] = entry(unit0 + i * NW * RPW, clamp_slot(slot_a[i], cap - 1));
+        ent[i] = RANK > 0 ? slot_a[i] : entry(unit0 + i * NW * RPW, clamp_slot(slot_a[i], cap - 1));
       }
       kr[u] = load(ku, kb, ent[u]);
       kr[u + 1] = load(ku, kb, ent[u + 1]);
@@ -329,28 +442,30 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
       in_order();
     }
     // ... and while these rows are on their way the chunk's slot list goes to LDS
-    tail = ((const ADSA_GLOBAL uint32_t*)((const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr() + kLeadBytes))[lane % 16];
-    int new_at = 0;                               // 1 + list position of the query token's slot, if this thread stages it
-    auto stage = [&](int j, int slot) {
-      s_ent[j] = entry(j, slot);
-      new_at = slot == new_slot && j < len ? j + 1 : new_at;
-    };
+    if constexpr (RANK == 0) {
+      load_tail();
+      int new_at = 0;                               // 1 + list position of the query token's slot, if this thread stages it
+      auto stage = [&](int j, int slot) {
+        s_ent[j] = entry(j, slot);
+        new_at = slot == new_slot && j < len ? j + 1 : new_at;
+      };
 #pragma unroll
-    for (int k = 0; k < PF; ++k)
-      if (k * kAttThreads < n_ent) {                // (uniform; n_ent is a multiple of the revolution, not of the threads)
-        const int j = tid + k * kAttThreads;
-        pf_slot[k] = clamp_slot(pf_slot[k], cap - 1);
-        if (j < n_ent) stage(j, pf_slot[k]);
+      for (int k = 0; k < PF; ++k)
+        if (k * kAttThreads < n_ent) {                // (uniform; n_ent is a multiple of the revolution, not of the threads)
+          const int j = tid + k * kAttThreads;
+          pf_slot[k] = clamp_slot(pf_slot[k], cap - 1);
+          if (j < n_ent) stage(j, pf_slot[k]);
+        }
+      for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, clamp_slot(list[t_begin + j], cap - 1));
+      if (new_slot >= 0) {                          // (uniform)
+        const unsigned long long who = __ballot(new_at != 0);
+        const int at = who ? __builtin_amdgcn_readlane(new_at, __ffsll((long long)who) - 1) : 0;
+        if (lane == 0) s_new[wave] = at;
       }
-    for (int j = tid + PF * kAttThreads; j < n_ent; j += kAttThreads) stage(j, clamp_slot(list[t_begin + j], cap - 1));
-    if (new_slot >= 0) {                          // (uniform)
-      const unsigned long long who = __ballot(new_at != 0);
-      const int at = who ? __builtin_amdgcn_readlane(new_at, __ffsll((long long)who) - 1) : 0;
-      if (lane == 0) s_new[wave] = at;
+      __syncthreads();
     }
-    __syncthreads();
     // thread i of the final score update serves tokens i, i + threads, ...; start the first PF reads now
-    if (DIRECT && HT == 1 && accumulate) {
+    if (RANK == 0 && DIRECT && HT == 1 && accumulate) {
 #pragma unroll
       for (int k = 0; k < PF; ++k) {
         pf_old[k] = 0.0f;
@@ -367,9 +482,12 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
           nk[0] = pack8_bf16(nk[0], nk[1]);
           nv[0] = pack8_bf16(nv[0], nv[1]);
         }
-      const int news = s_new[lane % NW];
-      const unsigned long long who = __ballot(news != 0);
-      const int at = who ? __builtin_amdgcn_readlane(news, __ffsll((long long)who) - 1) : 0;
+      int at = cnt;                                 // RANK: the newest slot ends the list
+      if constexpr (RANK == 0) {
+        const int news = s_new[lane % NW];
+        const unsigned long long who = __ballot(news != 0);
+        at = who ? __builtin_amdgcn_readlane(news, __ffsll((long long)who) - 1) : 0;
+      }
       const bool mine = ts == 0;
       if (mine && hs < heads_here && chunk == n_chunks - 1) {
         const long long off = (long long)new_slot * stride_b;
@@ -474,8 +592,6 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     for (int u = 0; u < U; u += 2)
       if ((n_trips - 1) * U + u < n_mine) fold(u, std::false_type());
   }
-  auto tail_word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)tail, i); };
-  auto tail_address = [&](size_t at) { return address(tail_word(at / 4), tail_word(at / 4 + 1)); };
   // ---- merge, step 1 (registers): the RPW lane groups of a wave that worked on the same head bring their states to the wave's
   // maximum and add them up across lanes.  The normaliser's sum goes to every lane; of the output, a swap of 32- or 16-lane
   // halves adds two elements at once and leaves one of them in each half, so that a lane ends up with kLeft elements from e0 on.
@@ -523,7 +639,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   __syncthreads();
   gchar* const out_g = (gchar*)tail_address(offsetof(AttendTail, out));
   gfloat* const lse_g = (gfloat*)tail_address(offsetof(AttendTail, lse));
-  const int advance = tail_word(offsetof(AttendTail, advance) / 4);
+  const int advance = RANK > 0 ? kAdvanceNone : (int)tail_word(offsetof(AttendTail, advance) / 4);
   if constexpr (HT > 1) {
     // ---- several heads: a thread finishes output elements of one head after the other, then adds its tokens' probabilities to
     // all the heads' score rows
@@ -625,7 +741,16 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   }
   if constexpr (DIRECT) {
     // -------- this head's attention mass: score[head][slot] += p, from the logits still in LDS
-    if (accumulate) {
+    if constexpr (RANK > 0) {
+      gfloat* const vals = (gfloat*)tail_address(offsetof(RankTail, vals)) + row * cap;
+      const float lse2 = M + __log2f(L);
+#pragma unroll
+      for (int u = 0; u < kSlots; ++u) {
+        const uint32_t slot = u * kAttThreads + tid;
+        const float p = ((take >> u) & 1u) ? fast_exp2(s_logit[((take >> u) & 1u) ? dest[u] : 0u] - lse2) : 0.0f;
+        if (slot < (uint32_t)n_ranked) elem(vals, slot) = ((take >> u) & 1u) ? old_score[u] + p : old_score[u];
+      }
+    } else if (accumulate) {
       const float lse2 = M + __log2f(L);
       gfloat* const srow = score + (size_t)head * cap;
 #pragma unroll
@@ -655,7 +780,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     // last act on a sequence (one thread; no other workgroup reads step): VF marks the score rows as the
     // next step's if u was (tags kept as floats behind u); then the step may advance.  (Written out here:
     // handing the kernel's argument struct to a helper by reference made every variant slower.)
-    if (head == 0 && tid == 0) {
+    if (RANK == 0 && head == 0 && tid == 0) {
       if constexpr (VF) {
         if (u_state) {
           gfloat* tags = u_state + (size_t)n_heads * D;
@@ -797,6 +922,25 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
     else
       finish([&](auto... args) { hipLaunchKernelGGL((k_attend_finish<EB, D>), fgrid, dim3(kFinishThreads), 0, st, args...); });
   }
+  return hipGetLastError();
+}
+
+// A decode step's ranking and attention in one launch (rank_in_attend), S slots per thread.
+template <int EB, int D, int S>
+hipError_t launch_ranked(const AttendArgs& A, const RankTail& T, const AttendPlan& plan, int n_seq, hipStream_t st, hipEvent_t ev_start,
+                         hipEvent_t ev_stop) {
+  constexpr int U = 4, NW = 8, kRev = NW * U * (kWave * 16 / (D * EB));
+  const size_t entries = (size_t)((plan.chunk_max - 1 + kRev - 1) / kRev + 1) * kRev, lds = 2 * entries * sizeof(float);
+  const dim3 grid(1, A.n_heads, n_seq), block(NW * kWave);
+  const uint32_t flags = A.n_heads | 0x10000 | (A.new_f32 ? 0x20000 : 0) | 0x40000 | (uint32_t)(A.head_stride_b >> 36 & 0x1F) << 19 | 1u << 24;
+  auto launch = [&](auto go) {
+    go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.q), lo32(A.k_new), lo32(A.v_new), hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.q), hi16s(A.k_new, A.v_new),
+       flags, (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, A.stride24, (uint32_t)(A.head_stride_b / 16), A.scale_log2, T);
+  };
+  if (ev_start && ev_stop)
+    launch([&](auto... args) { hipExtLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, S>), grid, block, (uint32_t)lds, st, ev_start, ev_stop, 0, args...); });
+  else
+    launch([&](auto... args) { hipLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, S>), grid, block, lds, st, args...); });
   return hipGetLastError();
 }
 
@@ -972,13 +1116,9 @@ hipError_t launch_workspace_init(char* ws, const Workspace& w, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
-                         const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
-                         void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
-                         int advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (p.q_per_kv > 1)
-    return launch_attend_gqa(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append,
-                             advance, new_f32, st, ev_start, ev_stop);
+static AttendArgs attend_args(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,
+                              const int32_t* sel_idx, const int32_t* sel_cnt, void* out, float* lse, char* ws, const Workspace& w,
+                              bool accumulate, bool append, int advance, bool new_f32) {
   AttendArgs A;
   A.seqs = seqs; A.q = (const char*)q; A.k_new = (const char*)k_new; A.v_new = (const char*)v_new;
   A.sel_idx = sel_idx; A.sel_cnt = sel_cnt; A.out = (char*)out; A.lse = lse;
@@ -996,12 +1136,55 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
   A.stride24 = plan.wide ? 0u : (uint32_t)A.slot_stride_b;
   const float scale = p.softmax_scale != 0.0f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
   A.scale_log2 = scale * kLog2e;
+  return A;
+}
+
+hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q,
+                         const void* k_new, const void* v_new, const int32_t* sel_idx, const int32_t* sel_cnt,
+                         void* out, float* lse, char* ws, const Workspace& w, bool accumulate, bool append,
+                         int advance, bool new_f32, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (p.q_per_kv > 1)
+    return launch_attend_gqa(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append,
+                             advance, new_f32, st, ev_start, ev_stop);
+  const AttendArgs A = attend_args(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, accumulate, append, advance, new_f32);
+  const int eb = elem_bytes(p);
   const int key = eb * 1000 + p.head_dim;
   if (key == 2064) return launch_attend_t<2, 64>(A, plan, p.n_seq, st, ev_start, ev_stop);
   if (key == 2128) return launch_attend_t<2, 128>(A, plan, p.n_seq, st, ev_start, ev_stop);
   if (key == 4064) return launch_attend_t<4, 64>(A, plan, p.n_seq, st, ev_start, ev_stop);
   if (key == 4128) return launch_attend_t<4, 128>(A, plan, p.n_seq, st, ev_start, ev_stop);
   return hipErrorInvalidValue;
+}
+
+// Whether adsa_step's ranking, attention and eviction are two launches (k_attend with RANK, k_step_finish) instead of three.  The
+// ranking is repeated by every head's workgroup, so it is for steps whose launches are chains of latencies anyway: those whose workspace
+// has room for the scores that the second kernel puts in place, which is what lists of fewer than 96 head groups may be split into.
+// adsa_step, us with three launches | with two (GPU time; a launch less is 2.4 us of the host's beside it), inside a row and where all
+// sequences close one: 1 sequence x 16 heads x 64 fp32, 124 tokens 10.2 | 8.7, 16.0 | 14.0; 7 x 9 x 128 [slot][head][D], 401 tokens 13.5 |
+// 12.2, 17.2 | 15.6; 3 x 24 x 64, 536 tokens 13.7 | 12.4, 28.6 | 23.3; 4 x 20 x 64 in 1000 slots 14.8 | 13.6, 32.4 | 28.8; 95 x 1 x 64
+// 12.8 | 11.3, 24.6 | 20.4; 20 x 16 x 64 [slot][head][D] (320 pairs, 40 groups) 19.3 | 18.5, 38.7 | 34.2.
+bool rank_in_attend(const adsa_params& p, const AttendPlan& plan, const Workspace& w) {
+  return one_launch_compact(p) && p.score_mode == ADSA_SCORE_ATTN_MASS && p.q_per_kv <= 1 && plan.n_chunks == 1 && plan.heads == 1 && !plan.wide &&
+         p.cap <= 1024 && sizeof(float) * p.n_seq * p.n_heads * p.cap <= w.plan_off - w.logits_off;
+}
+
+hipError_t launch_ranked_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,
+                                int32_t* sel_idx, int32_t* sel_cnt, void* out, float* lse, char* ws, const Workspace& w, bool new_f32,
+                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const AttendArgs A = attend_args(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, true, true, kAdvanceNone, new_f32);
+  const RankTail T = {A.out, A.lse, A.logits, reinterpret_cast<int32_t*>(ws + w.plan_off), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,
+                      p.win_col_radius, p.win_recent_m, 1.0f / (float)p.grid_w, {}};
+  auto go = [&](auto s) {
+    constexpr int S = decltype(s)::value;
+    switch (elem_bytes(p) * 1000 + p.head_dim) {
+      case 2064: return launch_ranked<2, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 2128: return launch_ranked<2, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4064: return launch_ranked<4, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4128: return launch_ranked<4, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      default: return hipErrorInvalidValue;
+    }
+  };
+  return p.cap <= 512 ? go(std::integral_constant<int, 1>()) : go(std::integral_constant<int, 2>());
 }
 
 }  // namespace adsa
