@@ -926,10 +926,10 @@ hipError_t launch_attend_w(const AttendArgs& A, const AttendPlan& plan, int n_se
 }
 
 // A decode step's ranking and attention in one launch (rank_in_attend), S slots per thread.
-template <int EB, int D, int S>
+template <int EB, int D, int NW, int S>
 hipError_t launch_ranked(const AttendArgs& A, const RankTail& T, const AttendPlan& plan, int n_seq, hipStream_t st, hipEvent_t ev_start,
                          hipEvent_t ev_stop) {
-  constexpr int U = 4, NW = 8, kRev = NW * U * (kWave * 16 / (D * EB));
+  constexpr int U = 4, kRev = NW * U * (kWave * 16 / (D * EB));
   const size_t entries = (size_t)((plan.chunk_max - 1 + kRev - 1) / kRev + 1) * kRev, lds = 2 * entries * sizeof(float);
   const dim3 grid(1, A.n_heads, n_seq), block(NW * kWave);
   const uint32_t flags = A.n_heads | 0x10000 | (A.new_f32 ? 0x20000 : 0) | 0x40000 | (uint32_t)(A.head_stride_b >> 36 & 0x1F) << 19 | 1u << 24;
@@ -995,6 +995,9 @@ static bool short_offsets(const adsa_params& p, int heads) {
   return slot_b < (1ll << 24) && (p.cap - 1) * slot_b + (heads - 1) * p.kv_head_stride * eb + p.head_dim * eb <= (long long)kRowBufferBytes;
 }
 
+// K and V bytes of the longest list that 4 waves read as fast as 8: see make_attend_plan.
+static long long short_list(const adsa_params& p) { return (p.score_mode == ADSA_SCORE_VCOS_FUSED ? 32ll : 72ll) << 10; }
+
 AttendPlan make_attend_plan(const adsa_params& p) {
   AttendPlan a;
   if (p.q_per_kv > 1) {      // grouped queries: one workgroup per (sequence, cache head, chunk of whole 16-token tiles)
@@ -1032,11 +1035,14 @@ AttendPlan make_attend_plan(const adsa_params& p) {
   // 400 x 698 x 64 (71 MB) 13.7 | 14.0; 480 x 746 x 64 (92 MB) 16.8 | 16.5; 288 x 1394 x 64 (103 MB) 23.3 | 22.7; 400 x 746 x 128
   // (153 MB) 25.6 | 25.4; 768 x 228 x 64 9.9 | 10.7; 768 x 647 x 64 21.3 | 21.5; 256 x 698 x 128 16.0 | 16.1; 192 x 698 x 64 8.0 | 7.8;
   // 40 x 400 x 64 6.3 | 5.9 and 128 x 4000 x 128 60 | 53 (with an earlier loop; 16 waves 7.2 and 52); fp32: 288 x 323 x 128 20.5 |
-  // 20.7; 400 x 323 x 128 22.8 | 22.3.  Lists that the rings of 4 waves hold at once (32 KB) gain nothing from more of them: 16 pairs x
-  // 84 tokens x 64 3.0 | 3.3, 16 x 46 x 128 fp32 3.1 | 3.3; 16 x 213 x 64 (53 KB) 3.6 | 3.7, 16 x 133 x 64 fp32 3.3 | 3.3.
+  // 20.7; 400 x 323 x 128 22.8 | 22.3.  Lists that the rings of 4 waves hold twice over (72 KB) are read in one more revolution than with
+  // 8, which costs less than the start and the merge of 4 more waves: 16 pairs x 130 tokens x 64 3.3 | 3.5, 200 3.7 | 3.9, 240 3.85 |
+  // 3.94, 300 (82 KB) 4.24 | 4.20; 64 x 200 x 64 3.9 | 4.0; 240 x 130 x 64 4.2 | 4.2, 240 5.0 | 5.3, 300 5.6 | 5.6; 128 x 110 x 128 4.2 |
+  // 4.3, 140 (82 KB) 4.5 | 4.5; 30 x 80 x 128 fp32 4.1 | 4.2; 96 x 200 x 64 [slot][head][D] 4.1 | 4.2.  (The line of the fused V-cosine
+  // form is the 32 KB of one revolution.)
   const long long pairs = (long long)p.n_seq * p.n_heads;
   const long long b_list = (long long)p.sel_cap * 2 * p.head_dim * elem_bytes(p);
-  a.waves = pairs >= 512 || b_list <= (32 << 10) || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
+  a.waves = pairs >= 512 || b_list <= short_list(p) || (pairs > 256 && pairs * b_list < (80ll << 20)) ? 4 : 8;
   // Splitting a list costs a second launch, ~2.5 us, and is worth it where one workgroup's bytes are what the launch lasts: from about
   // 330 KB on, a little more where more pairs share the memory's rate.  Into 8-wave chunks of 64 KB, what their rings hold at once (so
   // that none ends in a second, nearly empty revolution), or as many as leave no CU with two, which then lasts as long as those: 24
@@ -1160,7 +1166,7 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
 // ranking is repeated by every head's workgroup, so it is for steps whose launches are chains of latencies anyway: those whose workspace
 // has room for the scores that the second kernel puts in place, which is what lists of fewer than 96 head groups may be split into.
 // adsa_step, us with three launches | with two (GPU time; a launch less is 2.4 us of the host's beside it), inside a row and where all
-// sequences close one: 1 sequence x 16 heads x 64 fp32, 124 tokens 10.2 | 8.7, 16.0 | 14.0; 7 x 9 x 128 [slot][head][D], 401 tokens 13.5 |
+// sequences close one: 1 sequence x 16 heads x 64 fp32, 124 tokens 10.2 | 8.2, 16.0 | 13.5; 7 x 9 x 128 [slot][head][D], 401 tokens 13.5 |
 // 12.2, 17.2 | 15.6; 3 x 24 x 64, 536 tokens 13.7 | 12.4, 28.6 | 23.3; 4 x 20 x 64 in 1000 slots 14.8 | 13.6, 32.4 | 28.8; 95 x 1 x 64
 // 12.8 | 11.3, 24.6 | 20.4; 20 x 16 x 64 [slot][head][D] (320 pairs, 40 groups) 19.3 | 18.5, 38.7 | 34.2.
 bool rank_in_attend(const adsa_params& p, const AttendPlan& plan, const Workspace& w) {
@@ -1174,17 +1180,24 @@ hipError_t launch_ranked_attend(const adsa_params& p, const AttendPlan& plan, ad
   const AttendArgs A = attend_args(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, true, true, kAdvanceNone, new_f32);
   const RankTail T = {A.out, A.lse, A.logits, reinterpret_cast<int32_t*>(ws + w.plan_off), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,
                       p.win_col_radius, p.win_recent_m, 1.0f / (float)p.grid_w, {}};
-  auto go = [&](auto s) {
-    constexpr int S = decltype(s)::value;
+  auto go = [&](auto waves, auto slots) {
+    constexpr int NW = decltype(waves)::value, S = decltype(slots)::value;
     switch (elem_bytes(p) * 1000 + p.head_dim) {
-      case 2064: return launch_ranked<2, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
-      case 2128: return launch_ranked<2, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
-      case 4064: return launch_ranked<4, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
-      case 4128: return launch_ranked<4, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 2064: return launch_ranked<2, 64, NW, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 2128: return launch_ranked<2, 128, NW, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4064: return launch_ranked<4, 64, NW, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4128: return launch_ranked<4, 128, NW, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
       default: return hipErrorInvalidValue;
     }
   };
-  return p.cap <= 512 ? go(std::integral_constant<int, 1>()) : go(std::integral_constant<int, 2>());
+  const std::integral_constant<int, 1> one;
+  const std::integral_constant<int, 2> two;
+  const std::integral_constant<int, 4> four;
+  const std::integral_constant<int, 8> eight;
+  // 4 waves up to 256 slots, one a thread, however long a row is: adsa_step with 8 waves | 4, 16 pairs x 124 tokens x 64 fp32 8.7 | 8.2 us, 40 x
+  // 241 x 128 bf16 9.9 | 9.6, 84 x 242 x 128 fp32 12.5 | 12.2; with two slots a thread, 40 x 237 x 64 in 500 slots, 9.8 | 10.1.
+  if (p.cap <= 256) return go(four, one);
+  return p.cap <= 512 ? go(eight, one) : go(eight, two);
 }
 
 }  // namespace adsa
