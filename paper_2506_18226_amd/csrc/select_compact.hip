@@ -161,11 +161,10 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : S == 3 && RB == 8 ? 6
 // before the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
 // Rows per batch: as many as leave the kernels around it their residency.  k_compact_plan with 2 slots per thread, us with 8 | 12 |
 // 16 | 24 rows (74 | 94 | 122 | 160 registers): 900 slots, 66 sequences x 24 rows 10.1 | 10.2 | 10.4 | 10.0, 514 x 24
-// 20.8 | 23.4 | 25.3 | 30.1, 516 x 8 12.1 | 14.4 | 15.5 | 23.2, 1538 x 24 53 | 54 | 56 | 66; with 3 slots 24 rows and 8 have the same residency (114 and 102 registers).
-template <int NT, int S>
+// 20.8 | 23.4 | 25.3 | 30.1, 516 x 8 12.1 | 14.4 | 15.5 | 23.2, 1538 x 24 53 | 54 | 56 | 66.  (That was with every row in the plan; kMovedWithCache leaves it 11.)
+template <int NT, int S, int kRowBatch = S == 2 ? 8 : S <= 3 ? 24 : S == 4 ? 8 : 4>
 __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, int cap, uint32_t moves, const uint32_t (&dest)[S],
                                             const int (&posv)[S]) {
-  constexpr int kRowBatch = S == 2 ? 8 : S <= 3 ? 24 : S == 4 ? 8 : 4;
   const int tid = threadIdx.x;
   for (int r0 = 0; r0 < rows; r0 += kRowBatch) {
     float sv[S][kRowBatch];
@@ -187,6 +186,13 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
       }
   }
 }
+
+// From 12 score rows on, in caches of more than 128 slots, k_compact_move's workgroups move them, one a head's, and k_compact_plan, one workgroup
+// a sequence, is over a round trip or more sooner.  An eviction (us, plan | move): 5 sequences x 46 heads x 1100 slots 31.2 | 24.6, 2 x 59 x 5500
+// 38.7 | 34.7, 3 x 30 x 340 18.6 | 16.6, 52 x 28 x 600 57.1 | 53.3, 20 shapes by 1.05; a step of 64 x 24 x 600 with 2 sequences at a row end
+// 54.0 | 52.6.  Fewer rows and shorter lists cost the plan less than those workgroups: one row, 4 x 9 x 6600 37.2 | 39.1, 443 x 1 x 377 fp32
+// 23.9 | 24.7; 6 rows, 81 x 6 x 253 17.8 | 18.5; 8, a step of 200 x 8 x 250 34.2 | 34.5; 60 slots, 83 x 43 fp32 37.0 | 39.2, 406 x 12 30.2 | 31.4.
+constexpr int kMovedWithCache = 12, kPlanRowsCap = 128;
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
 template <int NT, int S, int RB = rank_batch(S)>
@@ -303,7 +309,8 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
     if (((restm >> u) & 1u) && key[u] == T) eq |= 1u << u;
   }
   const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &n_new);
-  // first slot whose content changes: the first one that is dropped.  Everything before it stays put
+  // first slot whose content changes: the first one that is dropped.  Everything before it stays put.  (Positions have been in registers
+  // since before the ranking's barriers.)
   uint32_t moves = 0;
 #pragma unroll
   for (int u = S - 1; u >= 0; --u) {
@@ -314,8 +321,13 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
     const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
     if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
-
-  move_scores<NT, S>(score, pos, F.rows, cap, moves, dest, posv);
+  if (F.rows < kMovedWithCache || cap <= kPlanRowsCap) move_scores<NT, S, S <= 3 ? kMovedWithCache - 1 : 4>(score, pos, F.rows, cap, moves, dest, posv);
+  else {
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+      if ((moves >> u) & 1u) pos[dest[u]] = posv[u];
+    __syncthreads();                                         // (sh.first is complete)
+  }
   if (tid == 0) {
     plan[4 * b + 0] = n; plan[4 * b + 1] = (int)min(sh.first, (uint32_t)n); plan[4 * b + 2] = 1; plan[4 * b + 3] = (int32_t)n_new;
     sq.n_res = (int32_t)n_new;
@@ -340,7 +352,7 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
 // workgroups with nothing to move took 27.4 us with 12 dwords of them, 23.0 with 8.  The record is asked for with the plan's words: one
 // round trip less where rows move (64 x 24 x 696, 4 of them at a row end, 25.2 -> 24.0 us), 0.8 us more for 512 sequences of which none does.
 constexpr int kSliceLanes = 8;
-struct MoveStrides { long long slot_b, head_b; };
+struct MoveStrides { long long slot_b, head_b; int score_rows; };
 template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
                                                               int part_bits, int cap, MoveStrides stride) {
@@ -355,11 +367,25 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const int row_in_pass = threadIdx.x / kSliceLanes, lane = threadIdx.x % kSliceLanes;
   gchar* const base = cache + (long long)head * stride.head_b + (part * kSliceLanes + lane) * 16;
   const gint* const map = (const gint*)keep_map + (size_t)b * cap;
-  for (int t0 = first; t0 < n_old; t0 += kPass * ROWS) {
+  // one workgroup per head also moves the head's score row (score_rows: their number where the plan leaves them, see kMovedWithCache, or 0)
+  constexpr int kTile = kPass * ROWS, SLOTS = (kTile + kMoveThreads - 1) / kMoveThreads;
+  const bool scores = blockIdx.y == 0 && part == 0 && head < stride.score_rows;
+  gfloat* const score = (gfloat*)sq.score + (size_t)head * cap;
+  for (int t0 = first; t0 < n_old; t0 += kTile) {
     uint4 val[ROWS];
-    int dst[ROWS];
+    int dst[ROWS], sdst[SLOTS];
+    float sval[SLOTS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) dst[u] = elem(map, (uint32_t)min(t0 + u * kPass + row_in_pass, n_old - 1));
+    if (scores) {
+#pragma unroll
+      for (int u = 0; u < SLOTS; ++u) {
+        const int k = u * kMoveThreads + (int)threadIdx.x, i = min(t0 + k, n_old - 1);
+        sdst[u] = elem(map, (uint32_t)i);
+        sval[u] = elem(score, (uint32_t)i);
+        if (t0 + k >= n_old || k >= kTile || sdst[u] == i) sdst[u] = -1;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
       const int i = t0 + u * kPass + row_in_pass;
@@ -371,6 +397,11 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
 #pragma unroll
     for (int u = 0; u < ROWS; ++u)
       if (dst[u] >= 0) store_stream16(base + (long long)dst[u] * stride.slot_b, val[u]);
+    if (scores) {
+#pragma unroll
+      for (int u = 0; u < SLOTS; ++u)
+        if (sdst[u] >= 0) elem(score, (uint32_t)sdst[u]) = sval[u];
+    }
   }
 }
 
@@ -468,7 +499,7 @@ __global__ __launch_bounds__(NT) void k_compact_step(
   __syncthreads();                                           // ... and so has the workgroup: it may draw its ticket
   if (tid == 0) s_last = __hip_atomic_fetch_add((int*)address(tickets_lo, tickets_hi) + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
 
-  move_slice<NT, kRows>(kb, vb, n_heads, part_bits, (int)min(sh.first, (uint32_t)n), n, s_map, MoveStrides{slot_stride_b, head_stride_b});
+  move_slice<NT, kRows>(kb, vb, n_heads, part_bits, (int)min(sh.first, (uint32_t)n), n, s_map, MoveStrides{slot_stride_b, head_stride_b, 0});
   __syncthreads();                                           // s_last is there (also when no row moves)
   if (!s_last) return;
 
@@ -704,7 +735,7 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
   auto launch = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, lo32(seqs), lo32(keep_map), lo32(plan), lo32(vals), hi16s(seqs, keep_map), hi16s(plan, vals),
                        (uint32_t)p.cap | (uint32_t)p.n_heads << 16 | (uint32_t)slice_bits(p) << 25, p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,
-                       p.win_recent_m, inv_width(p), MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride)});
+                       p.win_recent_m, inv_width(p), MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), 0});
     return hipGetLastError();
   };
   if (p.cap <= 256) return launch(k_step_finish<256, 1>, 256);
@@ -713,6 +744,8 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
   if (p.cap <= 1024) return launch(k_step_finish<512, 2>, 512);
   return hipErrorInvalidValue;
 }
+
+static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap; }
 
 hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
                           const Workspace& w, bool advance_step, hipStream_t st) {
@@ -727,7 +760,7 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
             : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24>
             : resident ? k_compact_move<32> : k_compact_move<24>;
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, slice_bits(p), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride)});
+                     (const int32_t*)plan, slice_bits(p), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), moved_with_cache(p) ? score_rows(p) : 0});
   return hipGetLastError();
 }
 

@@ -188,3 +188,37 @@ def test_more_sequences_than_compute_units_rank_like_few(cap):
 @pytest.mark.parametrize("cap", [256, 512, 768, 1024, 2048])
 def test_a_step_evicts_lists_that_fill_its_tile(cap):
     test_a_step_evicts_as_select_attend_and_compact_do(2, 3, 64, "bf16", cap, "head_major")
+
+
+@pytest.mark.parametrize("heads", [11, 12, 13])
+@pytest.mark.parametrize("cap,D,layout", [(128, 64, "head_major"), (129, 128, "slot_major"), (513, 64, "slot_major"), (770, 128, "head_major"),
+                                          (1100, 64, "head_major"), (4200, 64, "head_major")])
+def test_score_rows_move_with_the_cache_rows(heads, cap, D, layout):
+    """From 12 heads and 129 slots on each head's workgroup of the cache move takes its score row along: every row where the keep map puts it, what
+    is beyond the list and sequences with nothing to move untouched."""
+    P, W, n_seq = 8 + (cap - 8) % 16, 16, 5
+    s = cap - P
+    wl = WL.get_workload("xl", n_heads=heads, head_dim=D, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
+    g = torch.Generator().manual_seed(cap + heads)
+    batch = LayerBatch(params_for(wl, n_seq, cap, score_mode=B.SCORE_ATTN_MASS, layout=layout), DEV)
+    before = {"score": torch.randint(0, 40, batch.score.shape, generator=g).float() / 8, "pos": torch.arange(cap, dtype=torch.int32).expand(n_seq, cap),
+              "K": torch.randn(batch.K.shape, generator=g).to(batch.K.dtype), "V": torch.randn(batch.V.shape, generator=g).to(batch.V.dtype)}
+    for name, x in before.items():
+        getattr(batch, name).copy_(x)
+    h = batch.seqs_host
+    h["n_res"], h["step"], h["grid_origin"], h["n_keep_prefix"] = cap, s, P, P
+    h["budget"] = [s // 5, s // 2, 0, s, s - 2 * W - 1]
+    h["step"][3] = s - 1                                     # no row end
+    batch.upload_seqs()
+    batch.compact()
+    torch.cuda.synchronize()
+    seqs, km = batch.read_seqs(), batch.keep_map.cpu()
+    slot_axis = 1 if layout == "head_major" else 0           # (of one sequence's [heads][cap][D] or [cap][heads][D])
+    for b in range(n_seq):
+        n = int(seqs["n_res"][b])
+        kept = torch.arange(cap) if b == 3 else (km[b] >= 0).nonzero()[:, 0]
+        assert kept.numel() == n and (n < cap) == (b != 3), b
+        for name, axis in (("pos", 0), ("score", 1), ("K", slot_axis), ("V", slot_axis)):
+            want, now = before[name][b].clone(), getattr(batch, name)[b].cpu()
+            want.narrow(axis, 0, n).copy_(before[name][b].index_select(axis, kept))
+            assert torch.equal(now.narrow(axis, 0, n), want.narrow(axis, 0, n)), (b, name)
