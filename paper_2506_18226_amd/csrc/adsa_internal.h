@@ -41,10 +41,11 @@ constexpr int kVcosTags = 4;      // floats after u in adsa_seq.vcos_u: [0] 1 + 
 struct Workspace {
   size_t head_bytes;       // leading bytes that adsa_workspace_init zeroes; no kernel uses them, but they are part of the size
                            // and of the offsets callers' workspaces were made for
-  size_t logits_off;       // float [n_seq][n_heads][lg_stride]  scaled logits in log2 units
+  size_t logits_off;       // float [n_seq][n_heads][lg_stride]  scaled logits in log2 units of split lists; or, over this and the two
+                           //                      regions below, the new scores [n_seq][n_heads][cap] of a step in two launches
   size_t part_ml_off;      // float [n_seq][n_heads][n_chunks][2]   (m, l) per chunk
   size_t part_acc_off;     // float [n_seq][n_heads][n_chunks][head_dim]
-  size_t plan_off;         // int32 [n_seq][4]   compaction: old n_res, first moved slot, did, new n_res
+  size_t plan_off;         // int32 [n_seq][4]   compaction: old n_res, first moved slot, did, new n_res (k_compact_step, k_step_finish: tickets)
   size_t vcos_off;         // float [n_seq][cap]   inverse V norms of the candidates (0 = not a candidate)
   size_t vcos_u_off;       // float [n_seq][ceil(cap/64)][n_heads*head_dim]   per-tile partial sums of v^
   size_t vcos_s_off;       // float [n_seq][cap]   Eq. 3's S_i of the two-pass computation when score[] holds

@@ -6,11 +6,13 @@
 //                    (Section 4.2: new tokens go to the end of the cache) that the attention
 //                    launch performs, so the ranking never waits for the token's K/V.
 //  k_compact_plan  : Section 4.2 in per-row form: keep flags (prefix, last R rows, top-B of the
-//                    rest), ballot/prefix-sum keep map, in-place move of pos[] and score[]; or
+//                    rest), ballot/prefix-sum keep map, in-place move of pos[] and, where they are few, the score rows; or
 //                    Section 4.2 as written (evict the one most redundant candidate when full), closing
 //                    the hole in order or leaving it to the incoming token.
-//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows.
+//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows, and of the score rows where they are many.
 //  k_compact_step  : the per-row plan and move of a small decode step in one launch.
+//  k_step_finish   : the same after an attention launch that ranked for itself, with the scores, the record and the query token's
+//                    position, which that launch left alone.
 //
 // One workgroup owns one sequence in the first two kernels.  Its slots live in registers, S per thread (slot = u * NT +
 // thread), from the one read of the score array to the last write: what crosses threads is a histogram, at most 64
