@@ -105,6 +105,13 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
 // The row-end eviction of a whole decode step in one launch (where one_launch_compact says so): after an attention launch with
 // kAdvanceActive, `tickets` cleared by the step's launch_select.
 bool one_launch_compact(const adsa_params& p);
+// A larger step's attention with the eviction plans of its row ends, and the move after it, which advances the records.  The plan words
+// must be zero before (launch_select's tickets).
+bool plan_in_attend(const adsa_params& p, const AttendPlan& plan);
+hipError_t launch_planned_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,
+                                 int32_t* sel_idx, int32_t* sel_cnt, void* out, float* lse, int32_t* keep_map, char* ws, const Workspace& w, bool new_f32,
+                                 hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_step_move(const adsa_params& p, adsa_seq* seqs, const int32_t* keep_map, char* ws, const Workspace& w, hipStream_t st);
 hipError_t launch_compact_step(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, int32_t* tickets, hipStream_t st);
 // A step of few pairs in two launches (where rank_in_attend says so): the attention launch ranks for itself and leaves in the workspace
 // what launch_step_finish does to the record, pos and score, at a row end with the eviction.

@@ -223,18 +223,24 @@ __device__ __forceinline__ T elem(const ADSA_GLOBAL T* base, uint32_t i) { retur
 
 // v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32 adds.  The loads of all slots and of two
 // batches of rows are in flight together: one memory round trip for up to 2 * RB + 1 rows.
+// SHARED: by loads that see what other workgroups of the same launch have stored with scope agent, whichever XCD they ran on.
+template <bool SHARED>
+__device__ __forceinline__ float score_at(const gfloat* row, uint32_t i) {
+  if constexpr (SHARED) return __hip_atomic_load((const gfloat*)((const gchar*)row + i * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return elem(row, i);
+}
 constexpr int rank_batch(int S) { return S == 1 ? 24 : S == 2 ? 12 : S <= 4 ? 8 : 4; }
-template <int S, int RB>
+template <int S, int RB, bool SHARED = false>
 __device__ __forceinline__ void rank_values(const gfloat* score, int rows, int cap, const int (&idx)[S], float (&v)[S]) {
   float cur[S][RB], nxt[S][RB];
   auto load_rows = [&](int r0, float (&t)[S][RB]) {
 #pragma unroll
     for (int k = 0; k < RB; ++k)
 #pragma unroll
-      for (int u = 0; u < S; ++u) t[u][k] = elem(score + (size_t)min(r0 + k, rows - 1) * cap, idx[u]);    // (rows past the last: not added)
+      for (int u = 0; u < S; ++u) t[u][k] = score_at<SHARED>(score + (size_t)min(r0 + k, rows - 1) * cap, idx[u]);    // (rows past the last: not added)
   };
 #pragma unroll
-  for (int u = 0; u < S; ++u) v[u] = elem(score, idx[u]);
+  for (int u = 0; u < S; ++u) v[u] = score_at<SHARED>(score, idx[u]);
   if (rows == 1) return;
   load_rows(1, cur);
   for (int r = 1; r < rows; r += RB) {

@@ -192,6 +192,15 @@ int step_launches(const adsa_params* p, const AttendPlan& plan, const Workspace&
     if (e != hipSuccess || launch_step_finish(*p, seqs, keep_map, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
     return ADSA_OK;
   }
+  if (compact && plan_in_attend(*p, plan)) {
+    if (launch_select(*p, seqs, sel_idx, sel_cnt, true, reinterpret_cast<int32_t*>(ws + w.plan_off), st) != hipSuccess) return ADSA_ERR_LAUNCH;
+    const hipError_t e = timed([&](hipEvent_t e0, hipEvent_t e1) {
+      return launch_planned_attend(*p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, keep_map, ws, w,
+                                   (flags & ADSA_FLAG_NEW_F32) != 0 && p->dtype == ADSA_BF16, st, e0, e1);
+    });
+    if (e != hipSuccess || launch_step_move(*p, seqs, keep_map, ws, w, st) != hipSuccess) return ADSA_ERR_LAUNCH;
+    return ADSA_OK;
+  }
   const bool one_launch = compact && one_launch_compact(*p);
   int32_t* const tickets = one_launch ? reinterpret_cast<int32_t*>(ws + w.plan_off) : nullptr;
   if (launch_select(*p, seqs, sel_idx, sel_cnt, true, tickets, st) != hipSuccess) return ADSA_ERR_LAUNCH;
@@ -388,7 +397,7 @@ int adsa_step_launches(const adsa_params* p) {
   adsa_params eff;
   if (resolve_params(p, &eff) != ADSA_OK || eff.evict_policy != ADSA_EVICT_ROW_END || eff.score_mode != ADSA_SCORE_ATTN_MASS) return 0;
   const AttendPlan plan = make_attend_plan(eff);
-  return rank_in_attend(eff, plan, make_workspace(eff, plan)) ? 2 : one_launch_compact(eff) ? 3 : 4;
+  return rank_in_attend(eff, plan, make_workspace(eff, plan)) ? 2 : one_launch_compact(eff) || plan_in_attend(eff, plan) ? 3 : 4;
 }
 
 int adsa_profile_enable(int on) {

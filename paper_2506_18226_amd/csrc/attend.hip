@@ -158,6 +158,72 @@ struct RankTail {
 };
 static_assert(sizeof(RankTail) == 64 && offsetof(RankTail, out) == offsetof(AttendTail, out) && offsetof(RankTail, lse) == offsetof(AttendTail, lse), "one dword per lane of a 16-lane row");
 
+// The same for a launch that plans the evictions of row ends (PLAN).
+struct PlanTail {
+  char* out;
+  float* lse;
+  int32_t* plan;        // [n_seq][4]   { ticket, then old n_res; first slot that moves; did compact; new n_res }, zeroed by k_select
+  int32_t* keep_map;    // [n_seq][cap]
+  int W, R, total, advance;
+  float inv_w;
+  int recent_m, unused[2];
+};
+static_assert(sizeof(PlanTail) == 64 && offsetof(PlanTail, out) == offsetof(AttendTail, out) && offsetof(PlanTail, lse) == offsetof(AttendTail, lse) &&
+              offsetof(PlanTail, advance) == offsetof(AttendTail, advance), "one dword per lane of a 16-lane row");
+
+// Section 4.2's per-row plan of one sequence whose scores this launch's workgroups have just stored (k_compact_plan on which scores
+// are kept and where): keep map, positions, plan words and record.  The cache and score rows are moved by the next kernel on the stream.
+// (8 rows at once: 12 with 3 slots a thread cost 9 to 19 registers, a step of 300 x 24 x 600 191.8 -> 194.4 us, 32 x 24 39.2 -> 38.5.)
+template <int NT, int S>
+__device__ __forceinline__ void plan_row_end(RankShared& sh, ADSA_GLOBAL adsa_seq& sq, int s, int rows, int cap, const GridWidth& grid, int R, int recent_m,
+                                             gint* plan, gint* map) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), n = sq.n_res;
+  gint* const pos = (gint*)sq.pos;
+  const QueryCell cell = make_query_cell(sq, s, grid, R, 0, recent_m);
+  int idx[S], posv[S];
+  float rank[S];
+  rank_clear<NT>(sh);
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    idx[u] = min(u * NT + tid, n - 1);
+    posv[u] = elem(pos, idx[u]);
+  }
+  rank_values<S, S == 1 ? 24 : 8, true>((const gfloat*)sq.score, rows, cap, idx, rank);
+  uint32_t key[S], restm = 0, in = 0;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (u * NT + tid < n) in |= 1u << u;
+    if (((in >> u) & 1u) && evict_class(cell, posv[u]) == 1) restm |= 1u << u;
+    key[u] = order_key(rank[u], true);
+  }
+  const Stats st = block_stats<NT, S>(sh, key, restm, false);
+  const uint32_t B = (uint32_t)effective_budget(sq, s);
+  uint32_t T, need_eq;
+  top_threshold<NT, S>(sh, key, restm, st, B < st.n_cand ? B : st.n_cand, &T, &need_eq);
+  uint32_t sure = in & ~restm, eq = 0, dest[S], n_new;
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    if (((restm >> u) & 1u) && key[u] > T) sure |= 1u << u;
+    if (((restm >> u) & 1u) && key[u] == T) eq |= 1u << u;
+  }
+  const uint32_t take = place_kept<NT, S>(sh, sure, eq, need_eq, dest, &n_new);
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    const int i = u * NT + tid;
+    const bool kept = (take >> u) & 1u;
+    if ((in >> u) & 1u) map[i] = kept ? (int32_t)dest[u] : -1;
+    if (kept && dest[u] != (uint32_t)i) pos[dest[u]] = posv[u];
+    const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
+    if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
+  }
+  __syncthreads();                                  // (sh.first is complete)
+  if (tid == 0) {
+    plan[0] = n; plan[1] = (int)min(sh.first, (uint32_t)n); plan[2] = 1; plan[3] = (int32_t)n_new;
+    sq.n_res = (int32_t)n_new;
+    sq.compacted = 1;
+  }
+}
+
 // DIRECT: the list of a (sequence, head) is not split (grid.x == 1): the workgroup finishes its heads alone.
 // The build asks for leading kernel arguments to be preloaded into scalar registers at wave launch, and 14 dwords of them are.
 // Everything up to the sums is in those 14 (addresses have 48 bits, so six of them take 9 dwords): the first round trip is then
@@ -172,17 +238,23 @@ static_assert(sizeof(RankTail) == 64 && offsetof(RankTail, out) == offsetof(Atte
 // memory.  It only reads the record, pos and score, which the sequence's other workgroups may be reading still: what changes of
 // them goes to the workspace, for k_step_finish, the next kernel on the stream (the first head's workgroup writes sel_idx, sel_cnt and
 // the plan; a rejected record is marked here, which is what the others find too).
-template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE, int RANK = 0>
+// PLAN > 0: k_compact_plan's work at a row end, by the sequence's last workgroup to end, PLAN slots per thread, while other sequences are
+// still attended.  A sequence that closed a row stores its scores with scope agent and draws tickets; the others pay for nothing, and
+// nobody waits.  A score's store and load with scope agent meet behind the L2s; the store has been acknowledged (vmcnt) before the ticket is
+// drawn, and the loads leave after the last ticket has come back, so no cache is written back or invalidated for it.
+// The record's step stays, since workgroups that start later tell a row end from it: the next kernel advances it.
+template <int EB, int D, int HT, int U, int NW, bool VF, bool DIRECT, bool WIDE, int RANK = 0, int PLAN = 0>
 __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_t idx_lo, uint32_t cnt_lo, uint32_t q_lo, uint32_t kn_lo,
                                                       uint32_t vn_lo, uint32_t seqs_idx_hi, uint32_t cnt_q_hi, uint32_t kn_vn_hi,
                                                       uint32_t heads_flags, uint32_t caps, uint32_t stride24, uint32_t head_stride16,
-                                                      float scale_log2, std::conditional_t<(RANK > 0), RankTail, AttendTail> T) {
+                                                      float scale_log2, std::conditional_t<(RANK > 0), RankTail, std::conditional_t<(PLAN > 0), PlanTail, AttendTail>> T) {
   constexpr int kAttThreads = NW * kWave;           // the waves of the workgroup share one token chunk
   constexpr int EPL = Elems<EB>::N;                 // elements per lane
   constexpr int LPR = D / EPL;                      // lanes per row
   constexpr int RPW = kWave / LPR / HT;             // tokens per wave-load
   static_assert(HT == 1 || (DIRECT && !VF && RPW * HT * LPR == kWave), "several heads: whole lists only");
   static_assert(RANK == 0 || (HT == 1 && DIRECT && !VF && !WIDE), "ranking: whole lists of one head");
+  static_assert(PLAN == 0 || (RANK == 0 && HT == 1 && DIRECT && !VF && !WIDE), "plans: whole lists of one head");
   constexpr int kSlots = RANK > 0 ? RANK : 1;       // slots per thread of the ranking
   constexpr int PF = 4;                             // list entries a thread fetches, and score read-modify-writes it starts, early
   constexpr int kRev = NW * U * RPW;                // tokens of one ring revolution of the workgroup
@@ -216,7 +288,7 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
   gchar* const v_base = (gchar*)sqp->v;
   gfloat* const score = (gfloat*)sqp->score;
   // (RANK: the rest of the record, as the ranking needs it)
-  const int step = RANK > 0 ? sqp->step : 0, status_in = RANK > 0 ? sqp->status : 0;
+  const int step = RANK > 0 || PLAN > 0 ? sqp->step : 0, status_in = RANK > 0 ? sqp->status : 0;
   const gint* const pos = RANK > 0 ? (const gint*)sqp->pos : nullptr;
   const BudgetOf budget(*sqp);
   const int n_keep_prefix = RANK > 0 ? sqp->n_keep_prefix : 0;
@@ -753,12 +825,23 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     } else if (accumulate) {
       const float lse2 = M + __log2f(L);
       gfloat* const srow = score + (size_t)head * cap;
+      bool closes = false;                          // PLAN: the sequence closed a row
+      if constexpr (PLAN > 0) {
+        int col = 0;
+        const int W = (int)tail_word(offsetof(PlanTail, W) / 4);
+        if (step >= 1) GridWidth{W, __uint_as_float(tail_word(offsetof(PlanTail, inv_w) / 4))}.row(step - 1, &col);
+        closes = step >= 1 && step <= (int)tail_word(offsetof(PlanTail, total) / 4) && col == W - 1;
+      }
+      auto put = [&](gfloat* at, float sum) {
+        if (PLAN > 0 && closes) __hip_atomic_store(at, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else *at = sum;
+      };
 #pragma unroll
       for (int k = 0; k < PF; ++k) {                // reads were started before the loop
         const int i = tid + k * kAttThreads;
         if (k * kAttThreads < len) {                // (uniform)
           const float sum = pf_old[k] + fast_exp2(s_logit[min(i, len - 1)] - lse2);
-          if (i < len) *(gfloat*)((gchar*)srow + (uint32_t)pf_slot[k] * 4u) = sum;
+          if (i < len) put((gfloat*)((gchar*)srow + (uint32_t)pf_slot[k] * 4u), sum);
         }
       }
       constexpr int B = 4;                          // longer lists: batches of reads, so that their latencies overlap
@@ -773,8 +856,23 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
 #pragma unroll
         for (int k = 0; k < B; ++k) {
           const int i = i0 + k * kAttThreads;
-          if (i < len) srow[slot[k]] = old[k] + fast_exp2(s_logit[i] - lse2);
+          if (i < len) put(srow + slot[k], old[k] + fast_exp2(s_logit[i] - lse2));
         }
+      }
+      if constexpr (PLAN > 0) {
+        if (!closes) return;
+        __shared__ __align__(16) RankShared sh;
+        __shared__ int s_last;
+        gint* const plan = (gint*)tail_address(offsetof(PlanTail, plan)) + 4 * b;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this thread's scores are where every XCD sees them ...
+        __syncthreads();                                       // ... and so are the workgroup's: it may draw its ticket
+        if (tid == 0) s_last = __hip_atomic_fetch_add((int*)plan, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_heads - 1;
+        __syncthreads();
+        if (!s_last) return;
+        const GridWidth grid = {(int)tail_word(offsetof(PlanTail, W) / 4), __uint_as_float(tail_word(offsetof(PlanTail, inv_w) / 4))};
+        plan_row_end<kAttThreads, PLAN>(sh, *sqp, step, n_heads, cap, grid, (int)tail_word(offsetof(PlanTail, R) / 4),
+                                        (int)tail_word(offsetof(PlanTail, recent_m) / 4), plan, (gint*)tail_address(offsetof(PlanTail, keep_map)) + (size_t)b * cap);
+        return;
       }
     }
     // last act on a sequence (one thread; no other workgroup reads step): VF marks the score rows as the
@@ -941,6 +1039,25 @@ hipError_t launch_ranked(const AttendArgs& A, const RankTail& T, const AttendPla
     launch([&](auto... args) { hipExtLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, S>), grid, block, (uint32_t)lds, st, ev_start, ev_stop, 0, args...); });
   else
     launch([&](auto... args) { hipLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, S>), grid, block, lds, st, args...); });
+  return hipGetLastError();
+}
+
+// An attention launch that plans the evictions of row ends (plan_in_attend), S slots per thread.
+template <int EB, int D, int S>
+hipError_t launch_planned(const AttendArgs& A, const PlanTail& T, const AttendPlan& plan, int n_seq, hipStream_t st, hipEvent_t ev_start,
+                          hipEvent_t ev_stop) {
+  constexpr int U = 4, NW = 4, kRev = NW * U * (kWave * 16 / (D * EB));
+  const size_t entries = (size_t)((plan.chunk_max - 1 + kRev - 1) / kRev + 1) * kRev, lds = 2 * entries * sizeof(float);
+  const dim3 grid(1, A.n_heads, n_seq), block(NW * kWave);
+  const uint32_t flags = A.n_heads | 0x10000 | (A.new_f32 ? 0x20000 : 0) | 0x40000 | (uint32_t)(A.head_stride_b >> 36 & 0x1F) << 19 | 1u << 24;
+  auto launch = [&](auto go) {
+    go(lo32(A.seqs), lo32(A.sel_idx), lo32(A.sel_cnt), lo32(A.q), lo32(A.k_new), lo32(A.v_new), hi16s(A.seqs, A.sel_idx), hi16s(A.sel_cnt, A.q), hi16s(A.k_new, A.v_new),
+       flags, (uint32_t)A.cap | (uint32_t)A.sel_cap << 16, A.stride24, (uint32_t)(A.head_stride_b / 16), A.scale_log2, T);
+  };
+  if (ev_start && ev_stop)
+    launch([&](auto... args) { hipExtLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, 0, S>), grid, block, (uint32_t)lds, st, ev_start, ev_stop, 0, args...); });
+  else
+    launch([&](auto... args) { hipLaunchKernelGGL((k_attend<EB, D, 1, U, NW, false, true, false, 0, S>), grid, block, lds, st, args...); });
   return hipGetLastError();
 }
 
@@ -1198,6 +1315,36 @@ hipError_t launch_ranked_attend(const adsa_params& p, const AttendPlan& plan, ad
   // 241 x 128 bf16 9.9 | 9.6, 84 x 242 x 128 fp32 12.5 | 12.2; with two slots a thread, 40 x 237 x 64 in 500 slots, 9.8 | 10.1.
   if (p.cap <= 256) return go(four, one);
   return p.cap <= 512 ? go(eight, one) : go(eight, two);
+}
+
+// Whether adsa_step's attention launch plans the evictions too, which leaves select, attention and move: steps that are too large for
+// one_launch_compact, with 4 waves a list and up to three slots a thread (more rank in larger workgroups).  adsa_step, us with four
+// launches | with three: 64 sequences x 24 heads x 600 slots, no row end 46.7 | 44.9, 2 at one 53.2 | 50.4; 32 x 24, 3 at one 40.8 | 39.1; 100 x 8 x
+// 400, 10 at one 32.1 | 29.4; 200 x 8 x 200, none 25.6 | 23.9, 40 at one 34.7 | 33.6; 300 x 24 x 600, 9 at one 200 | 192.  Where all sequences
+// close a row at once the plan ends no launch sooner and the scores' stores take longer: 40 x 20 x 200 33.9 | 33.6, 100 x 8 x 400 46.0 | 45.9,
+// 64 x 24 x 600 112 | 115, one step of a row's 24.
+bool plan_in_attend(const adsa_params& p, const AttendPlan& plan) {
+  return p.evict_policy == ADSA_EVICT_ROW_END && p.score_mode == ADSA_SCORE_ATTN_MASS && p.q_per_kv <= 1 && !one_launch_compact(p) && plan.n_chunks == 1 &&
+         plan.heads == 1 && plan.waves == 4 && !plan.wide && p.cap <= 768;
+}
+
+hipError_t launch_planned_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,
+                                 int32_t* sel_idx, int32_t* sel_cnt, void* out, float* lse, int32_t* keep_map, char* ws, const Workspace& w, bool new_f32,
+                                 hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const AttendArgs A = attend_args(p, plan, seqs, q, k_new, v_new, sel_idx, sel_cnt, out, lse, ws, w, true, true, kAdvanceNone, new_f32);
+  const PlanTail T = {A.out, A.lse, reinterpret_cast<int32_t*>(ws + w.plan_off), keep_map, p.grid_w, p.win_rows_back, p.grid_h * p.grid_w, kAdvanceNone,
+                      1.0f / (float)p.grid_w, p.win_recent_m, {}};
+  auto go = [&](auto slots) {
+    constexpr int S = decltype(slots)::value;
+    switch (elem_bytes(p) * 1000 + p.head_dim) {
+      case 2064: return launch_planned<2, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 2128: return launch_planned<2, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4064: return launch_planned<4, 64, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      case 4128: return launch_planned<4, 128, S>(A, T, plan, p.n_seq, st, ev_start, ev_stop);
+      default: return hipErrorInvalidValue;
+    }
+  };
+  return p.cap <= 256 ? go(std::integral_constant<int, 1>()) : p.cap <= 512 ? go(std::integral_constant<int, 2>()) : go(std::integral_constant<int, 3>());
 }
 
 }  // namespace adsa

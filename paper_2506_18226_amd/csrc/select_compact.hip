@@ -45,7 +45,7 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : S == 3 && RB == 8 ? 6
   const int status_in = sq.status;
   const BudgetOf budget(sq);                                 // (loaded with the rest of the record, whether it is needed or not)
   rank_clear<NT>(sh);                                        // (while the record is on its way)
-  if (F.b && tid == 0) ((gint*)address(tickets_lo, cnt_tickets_hi >> 16))[4 * b] = 0;       // for this step's k_compact_step
+  if (F.b && tid < 4) ((gint*)address(tickets_lo, cnt_tickets_hi >> 16))[4 * b + tid] = 0;       // for this step's eviction
   if (s < 0 || status_in != 0) { if (tid == 0) { sel_cnt[b] = 0; sq.pending_slot = -1; } return; }
   if (n < 0 || n > cap || s > total) {
     if (tid == 0) { sq.status = status_in | ADSA_SEQ_BAD_STATE; sel_cnt[b] = 0; sq.pending_slot = -1; }
@@ -357,14 +357,20 @@ constexpr int kSliceLanes = 8;
 struct MoveStrides { long long slot_b, head_b; int score_rows; };
 template <int ROWS>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
-                                                              int part_bits, int cap, MoveStrides stride) {
+                                                              int part_bits_advance, int cap, MoveStrides stride) {
+  const int part_bits = part_bits_advance & 15;              // (bit 4: the records advance too, after an attention launch that planned)
   constexpr int kPass = kMoveThreads / kSliceLanes;
   const int b = blockIdx.z, head = blockIdx.x >> part_bits, part = blockIdx.x & ((1 << part_bits) - 1);
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
-  const gseq& sq = ((const gseq*)seqs)[b];
+  gseq& sq = ((gseq*)seqs)[b];
   gchar* const cache = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v);
-  asm volatile("" : : "s"(cache));                           // (asked for together with the plan's words, not after them)
+  const int step = sq.step, status = sq.status;
+  asm volatile("" : : "s"(cache), "s"(step), "s"(status));   // (asked for together with the plan's words, not after them)
   const int n_old = pl.x, first = pl.y;
+  if (part_bits_advance >= 16 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && step >= 0 && status == 0) {   // (no other workgroup uses these)
+    if (pl.z == 0) sq.compacted = 0;
+    sq.step = step + 1;
+  }
   if (pl.z == 0 || first >= n_old) return;
   const int row_in_pass = threadIdx.x / kSliceLanes, lane = threadIdx.x % kSliceLanes;
   gchar* const base = cache + (long long)head * stride.head_b + (part * kSliceLanes + lane) * 16;
@@ -749,21 +755,29 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
 
 static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap; }
 
-hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
-                          const Workspace& w, bool advance_step, hipStream_t st) {
-  int32_t* plan = reinterpret_cast<int32_t*>(ws + w.plan_off);
-  const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
-  hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
-  if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
+static hipError_t launch_move(const adsa_params& p, const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan, int rows_too, bool advance, hipStream_t st) {
   const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);
   constexpr int rows_per_pass = kMoveThreads / kSliceLanes;
   const bool resident = (long long)grid.x * grid.y * grid.z <= 2 * 256;
   auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8>
             : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24>
             : resident ? k_compact_move<32> : k_compact_move<24>;
-  hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, (const adsa_seq*)seqs, (const int32_t*)keep_map,
-                     (const int32_t*)plan, slice_bits(p), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), moved_with_cache(p) ? score_rows(p) : 0});
+  hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, seqs, keep_map,
+                     plan, slice_bits(p) | (advance ? 16 : 0), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), rows_too});
   return hipGetLastError();
+}
+
+hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_map, char* ws,
+                          const Workspace& w, bool advance_step, hipStream_t st) {
+  int32_t* plan = reinterpret_cast<int32_t*>(ws + w.plan_off);
+  const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
+  hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
+  if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
+  return launch_move(p, seqs, keep_map, plan, moved_with_cache(p) ? score_rows(p) : 0, false, st);
+}
+
+hipError_t launch_step_move(const adsa_params& p, adsa_seq* seqs, const int32_t* keep_map, char* ws, const Workspace& w, hipStream_t st) {
+  return launch_move(p, seqs, keep_map, reinterpret_cast<int32_t*>(ws + w.plan_off), score_rows(p), true, st);
 }
 
 }  // namespace adsa

@@ -135,3 +135,31 @@ def test_a_step_in_two_launches_is_select_attend_and_compact(n_seq, n_heads, D, 
         assert ((got["out"] - want["out"]).abs() <= tol * want["out"].abs() + 1e-5).all()
         assert torch.allclose(got["lse"], want["lse"], rtol=1e-6, atol=1e-5)
         assert torch.allclose(got["score"], want["score"], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("n_seq,n_heads,D,dtype,layout,cap,sel_cap,W,R,new_f32,recent_m,launches", [
+    (60, 9, 64, B.BF16, "head_major", 256, 150, 9, 1, True, 0, 3),       # 1 | 2, 2 | 3, 3 slots per thread
+    (30, 9, 128, B.BF16, "slot_major", 257, 200, 11, 2, False, 0, 3),
+    (40, 13, 64, B.BF16, "head_major", 512, 301, 13, 1, False, 0, 3),
+    (45, 12, 64, B.F32, "head_major", 513, 260, 12, 1, False, 0, 3),
+    (33, 8, 128, B.F32, "head_major", 768, 300, 17, 1, False, 0, 3),
+    (20, 27, 64, B.BF16, "head_major", 600, 500, 24, 2, False, 0, 3),    # more score rows than three batches
+    (513, 1, 64, B.BF16, "head_major", 300, 200, 10, 1, False, 0, 3),    # one ticket
+    (300, 2, 64, B.BF16, "head_major", 290, 200, 10, 1, False, 7, 3),    # the 1-D window
+    (70, 8, 64, B.BF16, "head_major", 769, 300, 10, 1, False, 0, 4),
+])
+def test_a_step_that_plans_in_its_attention_is_select_attend_and_compact(n_seq, n_heads, D, dtype, layout, cap, sel_cap, W, R, new_f32, recent_m, launches):
+    """Larger steps: the last workgroup of a sequence that closed a row plans its eviction, from scores that the others have just
+    stored.  The arithmetic is that of the three calls: everything is the same, bit by bit."""
+    lib = B.load_library()
+    for seed in (1, 2, 3):
+        p, st, inputs = make(n_seq, n_heads, D, dtype, layout, cap, sel_cap, W, R, new_f32, seed, recent_m)
+        assert lib.adsa_step_launches(C.byref(p)) == launches
+        flags = B.FLAG_NEW_F32 if new_f32 else 0
+        got, want = (run(p, st, inputs, flags, one) for one in (True, False))
+        assert (want["seqs"]["compacted"] == 1).sum() > n_seq // 5 and (want["seqs"]["step"] == st["seqs"]["step"] + 1).any()
+        assert len(set(want["seqs"]["status"])) >= 4
+        for f in FIELDS:
+            assert np.array_equal(got["seqs"][f], want["seqs"][f]), f
+        for k in ("cnt", "idx", "km", "K", "V", "pos", "score", "out", "lse"):
+            assert torch.equal(got[k], want[k]), k
