@@ -45,7 +45,7 @@ struct Workspace {
                            //                      regions below, the new scores [n_seq][n_heads][cap] of a step in two launches
   size_t part_ml_off;      // float [n_seq][n_heads][n_chunks][2]   (m, l) per chunk
   size_t part_acc_off;     // float [n_seq][n_heads][n_chunks][head_dim]
-  size_t plan_off;         // int32 [n_seq][4]   compaction: old n_res, first moved slot, did, new n_res (k_compact_step, k_step_finish: tickets)
+  size_t plan_off;         // int32 [n_seq][4]   compaction: old n_res, first moved slot, did, new n_res (word 0: tickets where workgroups draw them)
   size_t vcos_off;         // float [n_seq][cap]   inverse V norms of the candidates (0 = not a candidate)
   size_t vcos_u_off;       // float [n_seq][ceil(cap/64)][n_heads*head_dim]   per-tile partial sums of v^
   size_t vcos_s_off;       // float [n_seq][cap]   Eq. 3's S_i of the two-pass computation when score[] holds
@@ -69,7 +69,7 @@ enum : int {
 
 // Kernel launchers (each returns hipGetLastError() of its launch).
 hipError_t launch_workspace_init(char* ws, const Workspace& w, hipStream_t st);
-// tickets: NULL, or the words launch_compact_step counts in, which the launch clears
+// tickets: NULL, or the plan words that launch_compact_step or launch_planned_attend counts in, which the launch clears
 hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx, int32_t* sel_cnt,
                          bool plan_append, int32_t* tickets, hipStream_t st);
 hipError_t launch_vcos(const adsa_params& p, adsa_seq* seqs, bool for_compaction, char* ws,

@@ -8,8 +8,9 @@
 //  k_compact_plan  : Section 4.2 in per-row form: keep flags (prefix, last R rows, top-B of the
 //                    rest), ballot/prefix-sum keep map, in-place move of pos[] and, where they are few, the score rows; or
 //                    Section 4.2 as written (evict the one most redundant candidate when full), closing
-//                    the hole in order or leaving it to the incoming token.
-//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows, and of the score rows where they are many.
+//                    the hole in order or leaving it to the incoming token.  (Larger adsa_step batches: k_attend with PLAN does it.)
+//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows, and of the score rows where they are many or
+//                    the attention launch has planned, whose records it advances.
 //  k_compact_step  : the per-row plan and move of a small decode step in one launch.
 //  k_step_finish   : the same after an attention launch that ranked for itself, with the scores, the record and the query token's
 //                    position, which that launch left alone.
