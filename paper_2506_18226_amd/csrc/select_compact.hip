@@ -526,7 +526,7 @@ __global__ __launch_bounds__(NT) void k_compact_step(
 // The second kernel of a small decode step, after a k_attend that ranked for itself: grid (column slices of K, then of V; sequence).
 // What that launch's workgroups only read is changed here: the scores, which it left in vals ([n_seq][score rows][cap]), and the
 // record; at a row end also what k_compact_step does, on those scores.  plan[b] = { tickets, step or -1 if there is nothing to do,
-// resident slots with the query token's, attended slots }.  No workgroup reads what another one writes: step and count come from the
+// resident slots with the query token's, attended slots }; where none is attended there are no vals.  No workgroup reads what another one writes: step and count come from the
 // plan, scores from vals, and the positions, which the last to draw a ticket moves, are in registers before one is drawn.
 // Most steps close no row: the new scores, the plan and the record are one round trip then, the scores' stores the rest.
 template <int NT, int S, int RB = rank_batch(S)>
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(NT) void k_step_finish(uint32_t seqs_lo, uint32_t m
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & (kWave - 1);
   const int cap = cap_heads_bits & 0xFFFF, n_heads = (cap_heads_bits >> 16) & 0x1FF, part_bits = cap_heads_bits >> 25;
   gint* const plan = (gint*)address(plan_lo, plan_vals_hi & 0xFFFF) + 4 * b;
-  const int s = plan[1], n = plan[2];
+  const int s = plan[1], n = plan[2], attended = plan[3];
   gseq& sq = ((gseq*)address(seqs_lo, seqs_map_hi & 0xFFFF))[b];
   gint* const pos = (gint*)sq.pos;
   gfloat* const score = (gfloat*)sq.score;
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(NT) void k_step_finish(uint32_t seqs_lo, uint32_t m
   if (s < 0) return;
   const int slot_new = s >= 1 ? n - 1 : -1, pos_new = cell.P + s - 1;
   if (!is_row_end(cell, s, total)) {
-    if (head_here) {
+    if (head_here && attended > 0) {                         // (none: step 0 of candidates without a budget; that launch left vals alone)
 #pragma unroll
       for (int u = 0; u < S; ++u)
         if (u * NT + tid < n) elem(score + (size_t)blockIdx.x * cap, u * NT + tid) = val[u];

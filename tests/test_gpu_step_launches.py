@@ -163,3 +163,40 @@ def test_a_step_that_plans_in_its_attention_is_select_attend_and_compact(n_seq, 
             assert np.array_equal(got["seqs"][f], want["seqs"][f]), f
         for k in ("cnt", "idx", "km", "K", "V", "pos", "score", "out", "lse"):
             assert torch.equal(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("n_seq,n_heads,D,dtype,layout,cap,sel_cap,launches", [
+    (9, 4, 64, B.BF16, "head_major", 120, 100, 2),
+    (10, 3, 64, B.F32, "slot_major", 290, 200, 2),
+    (9, 5, 128, B.BF16, "head_major", 700, 500, 2),
+    (2, 20, 64, B.BF16, "head_major", 1024, 700, 2),
+    (12, 9, 64, B.BF16, "head_major", 257, 200, 3),                      # ranked by a launch of its own
+    (60, 9, 64, B.BF16, "head_major", 256, 150, 3),                      # planned by the attention
+])
+def test_a_step_before_the_first_token_leaves_scores_that_nobody_attends(n_seq, n_heads, D, dtype, layout, cap, sel_cap, launches):
+    """Step 0, a condition that is not pinned: its tokens are candidates, and with an effective budget of 0 none is attended.  The record
+    advances; the scores stay, beside sequences that attend some or all of theirs, whatever the workspace holds."""
+    p, st, inputs = make(n_seq, n_heads, D, dtype, layout, cap, sel_cap, 10, 1, False, 1)
+    assert B.load_library().adsa_step_launches(C.byref(p)) == launches
+    none = []
+    for b in range(n_seq):
+        P = (1, 30)[b % 2]
+        num, den, budget, pinned = ((0, 0, 0, 0), (1, P + 1, 7, 0), (1, 2, 0, 0), (0, 0, 0, P))[b // 2 % 4]
+        q = st["seqs"][b]
+        q["n_res"], q["step"], q["grid_origin"], q["n_keep_prefix"], q["status"] = P, 0, P, pinned, 0
+        q["budget"], q["budget_num"], q["budget_den"] = budget, num, den
+        st["pos"][b, :P] = torch.arange(P, dtype=torch.int32)
+        if pinned == 0 and (P * num // den if den else budget) == 0:
+            none.append(b)
+    got, want = (run(p, st, inputs, 0, one) for one in (True, False))
+    some = [b for b in range(n_seq) if b not in none]
+    assert none and (some or n_seq == 2)
+    assert (got["cnt"][none] == 0).all() and (got["out"][none] == 0).all() and (got["cnt"][some] > 0).all()
+    assert torch.equal(got["score"][none], st["score"][none])
+    for f in FIELDS:
+        assert np.array_equal(got["seqs"][f], want["seqs"][f]), f
+    assert (got["seqs"]["step"] == 1).all() and (got["seqs"]["status"] == 0).all()
+    for k in ("cnt", "idx", "km", "K", "V", "pos"):
+        assert torch.equal(got[k], want[k]), k
+    # (fp32 sums over 4 waves or 8: as above)
+    assert torch.allclose(got["score"], want["score"], rtol=1e-5, atol=1e-6)
