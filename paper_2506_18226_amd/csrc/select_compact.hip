@@ -164,7 +164,8 @@ __global__ __launch_bounds__(NT, S >= 8 ? 4 : S == 1 ? 7 : S == 3 && RB == 8 ? 6
 // before the barrier, all destinations are written after it.  (pos has been in registers since the classification.)
 // Rows per batch: as many as leave the kernels around it their residency.  k_compact_plan with 2 slots per thread, us with 8 | 12 |
 // 16 | 24 rows (74 | 94 | 122 | 160 registers): 900 slots, 66 sequences x 24 rows 10.1 | 10.2 | 10.4 | 10.0, 514 x 24
-// 20.8 | 23.4 | 25.3 | 30.1, 516 x 8 12.1 | 14.4 | 15.5 | 23.2, 1538 x 24 53 | 54 | 56 | 66.  (That was with every row in the plan; kMovedWithCache leaves it 11.)
+// 20.8 | 23.4 | 25.3 | 30.1, 516 x 8 12.1 | 14.4 | 15.5 | 23.2, 1538 x 24 53 | 54 | 56 | 66.  (That was with every row in the plan; where
+// kMovedWithCache leaves it up to 11, it asks for other batches.)
 template <int NT, int S, int kRowBatch = S == 2 ? 8 : S <= 3 ? 24 : S == 4 ? 8 : 4>
 __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, int cap, uint32_t moves, const uint32_t (&dest)[S],
                                             const int (&posv)[S]) {
@@ -324,7 +325,11 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
     const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
     if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
-  if (F.rows < kMovedWithCache || cap <= kPlanRowsCap) move_scores<NT, S, S <= 3 ? kMovedWithCache - 1 : 4>(score, pos, F.rows, cap, moves, dest, posv);
+  // (Batches: 11 rows at once where they cost no workgroup its place on the CU, 8 and 4 where they would; a list of up to 128 slots may have
+  // more of them, 24 at once.  With 11 for 2 slots per thread, 90 registers instead of 68, the plan of 516 sequences x 1 row x 900 slots
+  // and its move took 43.4 us instead of 40.1, 1500 x 1 x 400 10.9 instead of 9.5.)
+  if (F.rows < kMovedWithCache) move_scores<NT, S, S == 1 || S == 3 ? kMovedWithCache - 1 : S <= 4 ? 8 : 4>(score, pos, F.rows, cap, moves, dest, posv);
+  else if (S == 1 && cap <= kPlanRowsCap) move_scores<NT, S, 24>(score, pos, F.rows, cap, moves, dest, posv);
   else {
 #pragma unroll
     for (int u = 0; u < S; ++u)

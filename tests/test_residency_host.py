@@ -35,7 +35,7 @@ def registers(code_objects):
 
 @pytest.mark.parametrize("kernel,waves", [       # mangled name and template arguments, waves per SIMD
     (r"k_selectILi256ELi1E", 7), (r"k_selectILi256ELi3ELi8E", 6), (r"k_selectILi512ELi(8|12|16)E", 4),
-    (r"k_compact_planILi256ELi1E", 7), (r"k_attend_gqaILi(64|128)ELi8E", 4),
+    (r"k_compact_planILi256ELi1E", 7), (r"k_compact_planILi(256|512)ELi2E", 6), (r"k_attend_gqaILi(64|128)ELi8E", 4),
     (r"k_compact_moveILi(4|8)E", 8), (r"k_compact_moveILi16E", 4), (r"k_compact_moveILi24E", 3), (r"k_compact_moveILi32E", 2),
 ])
 def test_waves_per_simd(registers, kernel, waves):
