@@ -19,6 +19,8 @@
 // thread), from the one read of the score array to the last write: what crosses threads is a histogram, at most 64
 // keys and one pair of counts per wave.  Both kernels are chains of dependent latencies (record -> scores -> a handful
 // of barriers -> stores) rather than work, so the number of barriers and of memory round trips is what they are built around.
+#include <type_traits>
+
 #include "adsa_rank.h"
 
 namespace adsa {
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
 // of one cache and walks the rows that move in ascending tiles: load survivors -> wait, barrier -> store (a tile's destinations
 // are at most its sources and below the next tile's).  Bound by the copy: ROWS rows per thread in flight, and since nothing
 // reads a row again before the next step's attention, streaming loads and stores.  A tile ends with a wait for its last load, so the
-// best tile is the whole list; but ROWS cost registers (30 with 4 rows, 58 with 8, 106 with 16, 151 with 24, 199 with 32) and most workgroups
+// best tile is the whole list; but ROWS cost registers (30 with 4 rows, 59 with 8, 107 with 16, 151 with 24, 199 with 32) and most workgroups
 // of most steps find nothing to move and are over when they have been launched.  So: as many rows as the capacity needs up to 24, and 32
 // for launches that are resident with them at once, two workgroups per CU.  An eviction, plan included, us with 16 | 24 | 32 rows: full lists,
 // 4 sequences x 32 heads x 4000 slots - | 65.3 | 60.8, 300 x 24 x 1000 585 | 579 | 567, 64 x 16 x 4000 196 | 202 | 195, 162 x 1 x 7631 fp32 114 | 104 | 123;
@@ -359,9 +361,12 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
 // The strides come as a struct, which is not preloaded: each preloaded argument delays the launch of every wave, and 80 000
 // workgroups with nothing to move took 27.4 us with 12 dwords of them, 23.0 with 8.  The record is asked for with the plan's words: one
 // round trip less where rows move (64 x 24 x 696, 4 of them at a row end, 25.2 -> 24.0 us), 0.8 us more for 512 sequences of which none does.
+// SCORES: the score rows move along, and the records may advance.  Up to 16 registers more (36, 64, 114, 163, 215) and a branch between the map and
+// the rows, which moves of cache rows alone do not pay for: us with one form for both | with two (rows left to the plan), 300 sequences x 24
+// rows x 100 slots 41.9 | 40.0, 300 x 16 x 128 35.1 | 32.9, 600 x 1 x 250 15.4 | 15.0, 16 x 16 x 128 fp32 10.9 | 10.2.
 constexpr int kSliceLanes = 8;
 struct MoveStrides { long long slot_b, head_b; int score_rows; };
-template <int ROWS>
+template <int ROWS, bool SCORES>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
                                                               int part_bits_advance, int cap, MoveStrides stride) {
   const int part_bits = part_bits_advance & 15;              // (bit 4: the records advance too, after an attention launch that planned)
@@ -370,10 +375,11 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
   gseq& sq = ((gseq*)seqs)[b];
   gchar* const cache = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v);
-  const int step = sq.step, status = sq.status;
-  asm volatile("" : : "s"(cache), "s"(step), "s"(status));   // (asked for together with the plan's words, not after them)
+  const int step = SCORES ? sq.step : -1, status = SCORES ? sq.status : 0;
+  asm volatile("" : : "s"(cache));                           // (asked for together with the plan's words, not after them)
+  if constexpr (SCORES) asm volatile("" : : "s"(step), "s"(status));
   const int n_old = pl.x, first = pl.y;
-  if (part_bits_advance >= 16 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && step >= 0 && status == 0) {   // (no other workgroup uses these)
+  if (SCORES && part_bits_advance >= 16 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && step >= 0 && status == 0) {   // (no other workgroup uses these)
     if (pl.z == 0) sq.compacted = 0;
     sq.step = step + 1;
   }
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const gint* const map = (const gint*)keep_map + (size_t)b * cap;
   // one workgroup per head also moves the head's score row (score_rows: their number where the plan leaves them, see kMovedWithCache, or 0)
   constexpr int kTile = kPass * ROWS, SLOTS = (kTile + kMoveThreads - 1) / kMoveThreads;
-  const bool scores = blockIdx.y == 0 && part == 0 && head < stride.score_rows;
+  const bool scores = SCORES && blockIdx.y == 0 && part == 0 && head < stride.score_rows;
   gfloat* const score = (gfloat*)sq.score + (size_t)head * cap;
   for (int t0 = first; t0 < n_old; t0 += kTile) {
     uint4 val[ROWS];
@@ -765,9 +771,13 @@ static hipError_t launch_move(const adsa_params& p, const adsa_seq* seqs, const 
   const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);
   constexpr int rows_per_pass = kMoveThreads / kSliceLanes;
   const bool resident = (long long)grid.x * grid.y * grid.z <= 2 * 256;
-  auto move = p.cap <= 4 * rows_per_pass ? k_compact_move<4> : p.cap <= 8 * rows_per_pass ? k_compact_move<8>
-            : p.cap <= 16 * rows_per_pass ? k_compact_move<16> : p.cap <= 24 * rows_per_pass ? k_compact_move<24>
-            : resident ? k_compact_move<32> : k_compact_move<24>;
+  auto of_rows = [&](auto scores) {
+    constexpr bool S = decltype(scores)::value;
+    return p.cap <= 4 * rows_per_pass ? k_compact_move<4, S> : p.cap <= 8 * rows_per_pass ? k_compact_move<8, S>
+         : p.cap <= 16 * rows_per_pass ? k_compact_move<16, S> : p.cap <= 24 * rows_per_pass ? k_compact_move<24, S>
+         : resident ? k_compact_move<32, S> : k_compact_move<24, S>;
+  };
+  auto move = rows_too ? of_rows(std::true_type()) : of_rows(std::false_type());
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, seqs, keep_map,
                      plan, slice_bits(p) | (advance ? 16 : 0), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), rows_too});
   return hipGetLastError();
