@@ -361,25 +361,26 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
 // The strides come as a struct, which is not preloaded: each preloaded argument delays the launch of every wave, and 80 000
 // workgroups with nothing to move took 27.4 us with 12 dwords of them, 23.0 with 8.  The record is asked for with the plan's words: one
 // round trip less where rows move (64 x 24 x 696, 4 of them at a row end, 25.2 -> 24.0 us), 0.8 us more for 512 sequences of which none does.
-// SCORES: the score rows move along, and the records may advance.  Up to 16 registers more (36, 64, 114, 163, 215) and a branch between the map and
+// SCORES: the score rows move along.  Up to 16 registers more (36, 64, 114, 163, 215) and a branch between the map and
 // the rows, which moves of cache rows alone do not pay for: us with one form for both | with two (rows left to the plan), 300 sequences x 24
 // rows x 100 slots 41.9 | 40.0, 300 x 16 x 128 35.1 | 32.9, 600 x 1 x 250 15.4 | 15.0, 16 x 16 x 128 fp32 10.9 | 10.2.
+// ADVANCE: the records advance too, after an attention launch that planned.  The two more words of the record are asked for by these launches
+// alone: with nothing to move, 512 sequences x 24 rows x 696 slots 18.9 | 18.0, 300 x 24 x 1000 14.4 | 13.9, 261 x 48 x 435 20.2 | 19.0.
 constexpr int kSliceLanes = 8;
-struct MoveStrides { long long slot_b, head_b; int score_rows; };
-template <int ROWS, bool SCORES>
+struct MoveStrides { long long slot_b, head_b; };
+template <int ROWS, bool SCORES, bool ADVANCE>
 __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan,
-                                                              int part_bits_advance, int cap, MoveStrides stride) {
-  const int part_bits = part_bits_advance & 15;              // (bit 4: the records advance too, after an attention launch that planned)
+                                                              int part_bits, int cap, MoveStrides stride) {
   constexpr int kPass = kMoveThreads / kSliceLanes;
   const int b = blockIdx.z, head = blockIdx.x >> part_bits, part = blockIdx.x & ((1 << part_bits) - 1);
   const int4 pl = reinterpret_cast<const int4*>(plan)[b];
   gseq& sq = ((gseq*)seqs)[b];
   gchar* const cache = (gchar*)(blockIdx.y == 0 ? sq.k : sq.v);
-  const int step = SCORES ? sq.step : -1, status = SCORES ? sq.status : 0;
+  const int step = ADVANCE ? sq.step : -1, status = ADVANCE ? sq.status : 0;
   asm volatile("" : : "s"(cache));                           // (asked for together with the plan's words, not after them)
-  if constexpr (SCORES) asm volatile("" : : "s"(step), "s"(status));
+  if constexpr (ADVANCE) asm volatile("" : : "s"(step), "s"(status));
   const int n_old = pl.x, first = pl.y;
-  if (SCORES && part_bits_advance >= 16 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && step >= 0 && status == 0) {   // (no other workgroup uses these)
+  if (ADVANCE && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && step >= 0 && status == 0) {   // (no other workgroup uses these)
     if (pl.z == 0) sq.compacted = 0;
     sq.step = step + 1;
   }
@@ -387,9 +388,9 @@ __global__ __launch_bounds__(kMoveThreads) void k_compact_move(const adsa_seq* s
   const int row_in_pass = threadIdx.x / kSliceLanes, lane = threadIdx.x % kSliceLanes;
   gchar* const base = cache + (long long)head * stride.head_b + (part * kSliceLanes + lane) * 16;
   const gint* const map = (const gint*)keep_map + (size_t)b * cap;
-  // one workgroup per head also moves the head's score row (score_rows: their number where the plan leaves them, see kMovedWithCache, or 0)
+  // one workgroup per head also moves the head's score row (attention mass: a row per cache head), where the plan leaves it: see kMovedWithCache
   constexpr int kTile = kPass * ROWS, SLOTS = (kTile + kMoveThreads - 1) / kMoveThreads;
-  const bool scores = SCORES && blockIdx.y == 0 && part == 0 && head < stride.score_rows;
+  const bool scores = SCORES && blockIdx.y == 0 && part == 0;
   gfloat* const score = (gfloat*)sq.score + (size_t)head * cap;
   for (int t0 = first; t0 < n_old; t0 += kTile) {
     uint4 val[ROWS];
@@ -519,7 +520,7 @@ __global__ __launch_bounds__(NT) void k_compact_step(
   __syncthreads();                                           // ... and so has the workgroup: it may draw its ticket
   if (tid == 0) s_last = __hip_atomic_fetch_add((int*)address(tickets_lo, tickets_hi) + 4 * b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
 
-  move_slice<NT, kRows>(kb, vb, n_heads, part_bits, (int)min(sh.first, (uint32_t)n), n, s_map, MoveStrides{slot_stride_b, head_stride_b, 0});
+  move_slice<NT, kRows>(kb, vb, n_heads, part_bits, (int)min(sh.first, (uint32_t)n), n, s_map, MoveStrides{slot_stride_b, head_stride_b});
   __syncthreads();                                           // s_last is there (also when no row moves)
   if (!s_last) return;
 
@@ -755,7 +756,7 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
   auto launch = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, lo32(seqs), lo32(keep_map), lo32(plan), lo32(vals), hi16s(seqs, keep_map), hi16s(plan, vals),
                        (uint32_t)p.cap | (uint32_t)p.n_heads << 16 | (uint32_t)slice_bits(p) << 25, p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,
-                       p.win_recent_m, inv_width(p), MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), 0});
+                       p.win_recent_m, inv_width(p), MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride)});
     return hipGetLastError();
   };
   if (p.cap <= 256) return launch(k_step_finish<256, 1>, 256);
@@ -765,21 +766,25 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
   return hipErrorInvalidValue;
 }
 
+// (Rows of the fused V-cosine form, two a head, never move: slots are reused.)
 static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap; }
 
-static hipError_t launch_move(const adsa_params& p, const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan, int rows_too, bool advance, hipStream_t st) {
+static hipError_t launch_move(const adsa_params& p, const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan, bool scores, bool advance, hipStream_t st) {
   const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);
   constexpr int rows_per_pass = kMoveThreads / kSliceLanes;
   const bool resident = (long long)grid.x * grid.y * grid.z <= 2 * 256;
-  auto of_rows = [&](auto scores) {
-    constexpr bool S = decltype(scores)::value;
-    return p.cap <= 4 * rows_per_pass ? k_compact_move<4, S> : p.cap <= 8 * rows_per_pass ? k_compact_move<8, S>
-         : p.cap <= 16 * rows_per_pass ? k_compact_move<16, S> : p.cap <= 24 * rows_per_pass ? k_compact_move<24, S>
-         : resident ? k_compact_move<32, S> : k_compact_move<24, S>;
+  auto of_rows = [&](auto with_scores, auto with_records) {
+    constexpr bool S = decltype(with_scores)::value, A = decltype(with_records)::value;
+    constexpr int kLeast = S && !A ? 8 : 4, kMost = A ? 24 : 32;                        // (see moved_with_cache and plan_in_attend)
+    return p.cap <= kLeast * rows_per_pass ? k_compact_move<kLeast, S, A> : p.cap <= 8 * rows_per_pass ? k_compact_move<8, S, A>
+         : p.cap <= 16 * rows_per_pass ? k_compact_move<16, S, A> : p.cap <= 24 * rows_per_pass || !resident ? k_compact_move<24, S, A>
+         : k_compact_move<kMost, S, A>;
   };
-  auto move = rows_too ? of_rows(std::true_type()) : of_rows(std::false_type());
+  const std::true_type yes;
+  const std::false_type no;
+  auto move = advance ? of_rows(yes, yes) : scores ? of_rows(yes, no) : of_rows(no, no);
   hipLaunchKernelGGL(move, grid, dim3(kMoveThreads), 0, st, seqs, keep_map,
-                     plan, slice_bits(p) | (advance ? 16 : 0), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride), rows_too});
+                     plan, slice_bits(p), p.cap, MoveStrides{row_bytes(p, p.kv_slot_stride), row_bytes(p, p.kv_head_stride)});
   return hipGetLastError();
 }
 
@@ -789,11 +794,11 @@ hipError_t launch_compact(const adsa_params& p, adsa_seq* seqs, int32_t* keep_ma
   const float* vcos_s = p.score_mode == ADSA_SCORE_VCOS_FUSED ? reinterpret_cast<const float*>(ws + w.vcos_s_off) : nullptr;
   hipError_t e = launch_compact_plan(p, seqs, keep_map, plan, advance_step, vcos_s, st);
   if (e != hipSuccess || p.evict_policy == ADSA_EVICT_REUSE_SLOT) return e;     // slot reuse moves no row
-  return launch_move(p, seqs, keep_map, plan, moved_with_cache(p) ? score_rows(p) : 0, false, st);
+  return launch_move(p, seqs, keep_map, plan, moved_with_cache(p), false, st);
 }
 
 hipError_t launch_step_move(const adsa_params& p, adsa_seq* seqs, const int32_t* keep_map, char* ws, const Workspace& w, hipStream_t st) {
-  return launch_move(p, seqs, keep_map, reinterpret_cast<int32_t*>(ws + w.plan_off), score_rows(p), true, st);
+  return launch_move(p, seqs, keep_map, reinterpret_cast<int32_t*>(ws + w.plan_off), true, true, st);
 }
 
 }  // namespace adsa

@@ -55,4 +55,4 @@ def test_row_moves_preload_eight_dwords(code_objects):
         for kernel in re.findall(r"<\S*k_compact_moveILi\d+E\S*>:\n(.*?)s_branch", text, re.S):
             seen += 1
             assert sum(int(n or 1) for n in re.findall(r"s_load_dword(?:x(\d+))? ", kernel)) <= 8
-    assert seen == 10                                        # (five tile sizes, with and without score rows)
+    assert seen == 13                                        # (five tile sizes; four each with score rows, and with those and the records)
