@@ -352,11 +352,18 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
     float rank[S];
 #pragma unroll
     for (int u = 0; u < S; ++u) { idx[u] = min(u * NT + tid, n - 1); posv[u] = 0; rank[u] = old_score[u] = 0.0f; dest[u] = 0; }
-    if (active && sane && !full && n > 0) {          // (an empty sequence's pointers may be null)
+    const bool reads = active && sane && !full && n > 0;      // (an empty sequence's pointers may be null)
+    if (reads) {
 #pragma unroll
       for (int u = 0; u < S; ++u) { posv[u] = elem(pos, idx[u]); old_score[u] = elem(score + (size_t)head * cap, idx[u]); }
-      rank_values<S, S == 1 ? 24 : 12>(score, n_heads, cap, idx, rank);
     }
+    __builtin_amdgcn_sched_barrier(0);               // (what follows while these are on their way: before them it costs 1 % of a small step)
+    // As in k_select, the ranks need not be read where the budget covers every position that can be a candidate; here every head's workgroup
+    // would read every head's scores.  adsa_step of 1 sequence x 900 tokens x 64 that attends them all, us with three launches | with them
+    // read | with this rule: 24 heads 12.5 | 12.8 | 11.5, 48 heads 12.7 | 14.7 | 11.7, 95 heads 13.6 | 18.8 | 12.1.
+    const uint32_t B = (uint32_t)effective_budget(budget, step);
+    const bool ranked = reads && (int)B < min(n, budget.grid_origin + step - 1 - n_keep_prefix);
+    if (__builtin_expect(ranked, 1)) rank_values<S, S == 1 ? 24 : 12>(score, n_heads, cap, idx, rank);
     const int total = (int)tail_word(offsetof(RankTail, total) / 4);
     uint32_t reject = !active ? 0u : !sane || step > total ? ADSA_SEQ_BAD_STATE : full ? ADSA_SEQ_CACHE_FULL : 0u;
     if (active && reject == 0) {
@@ -375,10 +382,16 @@ __global__ __launch_bounds__(NW * kWave) void k_attend(uint32_t seqs_lo, uint32_
         if (i < n && c != 1) fixedm |= 1u << u;
         if (i == slot_new) old_score[u] = 0.0f;      // a new slot starts at 0
       }
-      const Stats st = block_stats<NT, S>(sh, key, candm, bad);
+      Stats st = block_stats<NT, S>(sh, key, candm, bad);
+      if (__builtin_expect(!ranked && B < st.n_cand, 0)) {                // (uniform) positions were not distinct after all
+        rank_values<S, S == 1 ? 24 : 12>(score, n_heads, cap, idx, rank);
+#pragma unroll
+        for (int u = 0; u < S; ++u) key[u] = order_key(rank[u], true);
+        __syncthreads();
+        st = block_stats<NT, S>(sh, key, candm, bad);
+      }
       if (st.bad) reject = ADSA_SEQ_BAD_STATE;
       else {
-        const uint32_t B = (uint32_t)effective_budget(budget, step);
         uint32_t thr, need_eq, sure = fixedm, eq = 0, count;
         top_threshold<NT, S>(sh, key, candm, st, min(B, st.n_cand), &thr, &need_eq);
 #pragma unroll
@@ -1286,6 +1299,8 @@ hipError_t launch_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq*
 // sequences close one: 1 sequence x 16 heads x 64 fp32, 124 tokens 10.2 | 8.2, 16.0 | 13.5; 7 x 9 x 128 [slot][head][D], 401 tokens 13.5 |
 // 12.2, 17.2 | 15.6; 3 x 24 x 64, 536 tokens 13.7 | 12.4, 28.6 | 23.3; 4 x 20 x 64 in 1000 slots 14.8 | 13.6, 32.4 | 28.8; 95 x 1 x 64
 // 12.8 | 11.3, 24.6 | 20.4; 20 x 16 x 64 [slot][head][D] (320 pairs, 40 groups) 19.3 | 18.5, 38.7 | 34.2.
+// Many heads of one sequence, all of whose workgroups read all score rows, change nothing: 1 x 48 heads x 64, 525 of 1000 slots 15.4 | 14.1, 35.8
+// | 29.4; 1 x 95 19.3 | 18.0, 51.8 | 39.3; 1 x 256 [slot][head][D] 34.6 | 33.5, 113 | 80, 336 of 500 slots 31.0 | 22.0.
 bool rank_in_attend(const adsa_params& p, const AttendPlan& plan, const Workspace& w) {
   return one_launch_compact(p) && p.score_mode == ADSA_SCORE_ATTN_MASS && p.q_per_kv <= 1 && plan.n_chunks == 1 && plan.heads == 1 && !plan.wide &&
          p.cap <= 1024 && sizeof(float) * p.n_seq * p.n_heads * p.cap <= w.plan_off - w.logits_off;

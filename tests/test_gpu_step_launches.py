@@ -200,3 +200,33 @@ def test_a_step_before_the_first_token_leaves_scores_that_nobody_attends(n_seq, 
         assert torch.equal(got[k], want[k]), k
     # (fp32 sums over 4 waves or 8: as above)
     assert torch.allclose(got["score"], want["score"], rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("n_seq,n_heads,D,dtype,layout,cap", [
+    (9, 4, 64, B.BF16, "head_major", 200), (9, 5, 64, B.F32, "slot_major", 400), (9, 3, 64, B.BF16, "head_major", 900)])
+def test_a_step_whose_budget_covers_every_candidate(n_seq, n_heads, D, dtype, layout, cap):
+    """The ranks are not read then, unless positions are not distinct: more candidates than positions they can have, and the budget is no
+    longer all of them.  Beside sequences whose candidates are ranked."""
+    p, st, inputs = make(n_seq, n_heads, D, dtype, layout, cap, cap, 10, 1, False, 1)
+    assert B.load_library().adsa_step_launches(C.byref(p)) == 2
+    rng = np.random.default_rng(cap)
+    P, s, n = 12, 3, cap - 1
+    for b in range(n_seq):
+        q = st["seqs"][b]
+        q["grid_origin"], q["n_keep_prefix"], q["status"], q["budget_num"], q["budget_den"] = P, 0, 0, 0, 0
+        if b % 3 == 2:                                           # 12 positions in all the slots
+            q["step"], q["n_res"], q["budget"] = s, n, P + s - 1
+            st["pos"][b, :n] = torch.from_numpy(np.sort(rng.integers(0, P, n)).astype(np.int32))
+        else:                                                    # distinct ones, all of them or a third attended
+            q["step"], q["n_res"], q["budget"] = n - P + 1, n, n if b % 3 == 0 else cap // 3
+            st["pos"][b, :n] = torch.arange(n, dtype=torch.int32)
+    p.grid_h = 200                                               # (rows enough for the longest of them)
+    got, want = (run(p, st, inputs, 0, one) for one in (True, False))
+    assert (want["seqs"]["status"] == 0).all() and (want["seqs"]["step"] == st["seqs"]["step"] + 1).all()
+    cnt = want["cnt"].cpu().numpy()
+    assert (cnt[0::3] == cap).all() and (cnt[1::3] < cap).all() and (cnt[2::3] == P + s - 1 + 1).all()
+    for f in FIELDS:
+        assert np.array_equal(got["seqs"][f], want["seqs"][f]), f
+    for k in ("cnt", "idx", "km", "K", "V", "pos"):
+        assert torch.equal(got[k], want[k]), k
+    assert torch.allclose(got["score"], want["score"], rtol=1e-5, atol=1e-6)        # (fp32 sums over 4 waves or 8: as above)
