@@ -1334,13 +1334,16 @@ hipError_t launch_ranked_attend(const adsa_params& p, const AttendPlan& plan, ad
 
 // Whether adsa_step's attention launch plans the evictions too, which leaves select, attention and move: steps that are too large for
 // one_launch_compact, with 4 waves a list and up to three slots a thread (more rank in larger workgroups).  adsa_step, us with four
-// launches | with three: 64 sequences x 24 heads x 600 slots, no row end 46.7 | 44.9, 2 at one 53.2 | 50.4; 32 x 24, 3 at one 40.8 | 39.1; 100 x 8 x
-// 400, 10 at one 32.1 | 29.4; 200 x 8 x 200, none 25.6 | 23.9, 40 at one 34.7 | 33.6; 300 x 24 x 600, 9 at one 200 | 192.  Where all sequences
-// close a row at once the plan ends no launch sooner and the scores' stores take longer: 40 x 20 x 200 33.9 | 33.6, 100 x 8 x 400 46.0 | 45.9,
-// 64 x 24 x 600 112 | 115, one step of a row's 24.
+// launches | with three: 64 sequences x 24 heads x 600 slots, no row end 41.6 | 39.9, 2 at one 47.9 | 44.0; 128 x 8 x 250 20.9 | 19.0, 5 at one
+// 25.9 | 23.5; 200 x 8 x 700 43.5 | 41.7, 8 at one 55.2 | 49.4; 160 x 24 x 600 86.9 | 85.3, 6 at one 104 | 98.
+// Where all sequences close a row at once it takes longer from some 1500 pairs on: a sequence's last workgroup to end plans, that is one of the
+// XCD that is behind, which falls further behind for it and draws the next sequence's last ticket too (293 of 381 plans, 883 of 1000).  Up
+// to 4096 pairs that is 3 % of one step of a row's, most of which gain: 64 x 24 x 600 95 | 98, 128 x 24 x 600 168 | 173, 500 x 8 x 250 102 | 106,
+// 250 x 16 x 400 x 128 299 | 298.  Beyond them it is up to 20 %, for 1 to 2 % inside a row: 200 x 48 x 300 240 | 261 and 111 | 109, 400 x 48 x 300
+// 460 | 517 and 210 | 208, 1000 x 24 x 130 276 | 336 and 135 | 132, 1000 x 16 x 300 419 | 466 and 192 | 192.
 bool plan_in_attend(const adsa_params& p, const AttendPlan& plan) {
   return p.evict_policy == ADSA_EVICT_ROW_END && p.score_mode == ADSA_SCORE_ATTN_MASS && p.q_per_kv <= 1 && !one_launch_compact(p) && plan.n_chunks == 1 &&
-         plan.heads == 1 && plan.waves == 4 && !plan.wide && p.cap <= 768;
+         plan.heads == 1 && plan.waves == 4 && !plan.wide && p.cap <= 768 && (long long)p.n_seq * p.n_heads <= 4096;
 }
 
 hipError_t launch_planned_attend(const adsa_params& p, const AttendPlan& plan, adsa_seq* seqs, const void* q, const void* k_new, const void* v_new,

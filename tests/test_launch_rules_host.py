@@ -1,4 +1,5 @@
 """What the attention launch rule promises, over random parameters (host code only)."""
+import ctypes as C
 import random
 
 from paper_2506_18226_amd import binding as B
@@ -56,3 +57,13 @@ def test_32_bit_offsets_end_where_the_unattended_ones_begin():
                           score_mode=B.SCORE_ATTN_MASS, cap=n, layout="slot_major", kv_slot_stride=stride // 2, kv_head_stride=64)
         assert (n - 1) * stride + 128 <= limit if not wide else (n - 1) * stride + 128 > limit
         assert plan_of(p).wide == wide
+
+
+def test_only_steps_of_up_to_4096_pairs_plan_in_their_attention():
+    """The workgroups that plan gather on one XCD, which a row end of a large batch would wait for."""
+    lib = B.load_library()
+    for n_heads, n_seq in ((24, 170), (48, 85), (8, 512), (1, 4096)):
+        for n, launches in ((n_seq, 3), (n_seq + 1, 4)):
+            p = B.make_params(n_seq=n, n_heads=n_heads, head_dim=64, grid_h=40, grid_w=24, win_rows_back=1, win_col_radius=2, dtype=B.BF16,
+                              score_mode=B.SCORE_ATTN_MASS, cap=300, layout="head_major")
+            assert lib.adsa_step_launches(C.byref(p)) == launches, (n, n_heads)
