@@ -9,7 +9,7 @@
 //                    rest), ballot/prefix-sum keep map, in-place move of pos[] and, where they are few, the score rows; or
 //                    Section 4.2 as written (evict the one most redundant candidate when full), closing
 //                    the hole in order or leaving it to the incoming token.  (Larger adsa_step batches: k_attend with PLAN does it.)
-//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows, and of the score rows where they are many or
+//  k_compact_move  : in-place, order-preserving move of the surviving K and V rows, and of the score rows where kMovedWithCache says so or
 //                    the attention launch has planned, whose records it advances.
 //  k_compact_step  : the per-row plan and move of a small decode step in one launch.
 //  k_step_finish   : the same after an attention launch that ranked for itself, with the scores, the record and the query token's
@@ -198,7 +198,11 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
 // 38.7 | 34.7, 3 x 30 x 340 18.6 | 16.6, 52 x 28 x 600 57.1 | 53.3, 20 shapes by 1.05; a step of 64 x 24 x 600 with 2 sequences at a row end
 // 54.0 | 52.6.  Fewer rows and shorter lists cost the plan less than those workgroups: one row, 4 x 9 x 6600 37.2 | 39.1, 443 x 1 x 377 fp32
 // 23.9 | 24.7; 6 rows, 81 x 6 x 253 17.8 | 18.5; 8, a step of 200 x 8 x 250 34.2 | 34.5; 60 slots, 83 x 43 fp32 37.0 | 39.2, 406 x 12 30.2 | 31.4.
-constexpr int kMovedWithCache = 12, kPlanRowsCap = 128;
+// With many sequences the plan launch is no chain that the chip idles through any more, and finds the rows it has just ranked in its L2.  All at a
+// row end, as the layers of one model are, 400 sequences x 16 x 300 102 | 106, 1000 x 16 x 300 239 | 253, 800 x 12 x 300 147 | 153, 192 x 16 x 300 by
+// 1.03, 700 x 12 x 480 by 1.02, but 128 x 16 x 300 by 1.01 and 128 x 24 x 300 by 0.99.  (One in 20 at a row end: the move stays ahead, 128 x 24 x 300 by 1.11,
+// 400 x 24 x 300 by 1.07.)
+constexpr int kMovedWithCache = 12, kPlanRowsCap = 128, kPlanRowsSeqs = 128;
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
 template <int NT, int S, int RB = rank_batch(S)>
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), cap = (int)cap_arg;
   gseq& sq = ((gseq*)address(seqs_lo, seqs_map_hi & 0xFFFF))[b];
   gint* const plan = (gint*)address(plan_lo, plan_vs_hi & 0xFFFF);
-  const RankFlags F(flags);                                  // a: advance the step
+  const RankFlags F(flags);                                  // a: advance the step; b: the move takes the score rows along
   const bool advance_step = F.a;
   gint* const pos = (gint*)sq.pos;
   gfloat* const score = (gfloat*)sq.score;
@@ -327,11 +331,12 @@ __global__ __launch_bounds__(NT, S == 1 ? 7 : 1) void k_compact_plan(
     const unsigned long long gone = __ballot(((in >> u) & 1u) && !kept);
     if (gone != 0 && lane == 0) atomicMin(&sh.first, (uint32_t)(u * NT + wave_id() * kWave + __ffsll((long long)gone) - 1));
   }
-  // (Batches: 11 rows at once where they cost no workgroup its place on the CU, 8 and 4 where they would; a list of up to 128 slots may have
-  // more of them, 24 at once.  With 11 for 2 slots per thread, 90 registers instead of 68, the plan of 516 sequences x 1 row x 900 slots
-  // and its move took 43.4 us instead of 40.1, 1500 x 1 x 400 10.9 instead of 9.5.)
-  if (F.rows < kMovedWithCache) move_scores<NT, S, S == 1 || S == 3 ? kMovedWithCache - 1 : S <= 4 ? 8 : 4>(score, pos, F.rows, cap, moves, dest, posv);
-  else if (S == 1 && cap <= kPlanRowsCap) move_scores<NT, S, 24>(score, pos, F.rows, cap, moves, dest, posv);
+  // (Batches: for fewer than 12 rows 11 at once where they cost no workgroup its place on the CU, 8 and 4 where they would; for more 24 where
+  // they do not.  With 11 for 2 slots per thread, 90 registers instead of 68, the plan of 516 sequences x 1 row x 900 slots and its move took
+  // 43.4 us instead of 40.1, 1500 x 1 x 400 10.9 instead of 9.5.)
+  constexpr int kFew = S == 1 || S == 3 ? kMovedWithCache - 1 : S <= 4 ? 8 : 4, kMany = S == 1 || S == 3 ? 24 : kFew;
+  if (!F.b && (kFew == kMany || F.rows < kMovedWithCache)) move_scores<NT, S, kFew>(score, pos, F.rows, cap, moves, dest, posv);
+  else if (!F.b) move_scores<NT, S, kMany>(score, pos, F.rows, cap, moves, dest, posv);
   else {
 #pragma unroll
     for (int u = 0; u < S; ++u)
@@ -693,6 +698,9 @@ hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx,
   ADSA_SELECT(512, 16, 1);
 }
 
+// (Rows of the fused V-cosine form, two a head, never move: slots are reused.)
+static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap && p.n_seq <= kPlanRowsSeqs; }
+
 // k_compact_plan: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (32.7 with keys in LDS), 512 x 48 rows x 632 of the
 // fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).  It needs more registers than
 // k_select (512x8 and 512x12 above 128), so above 3072 slots the workgroups of 1024 threads stay ahead at any number of
@@ -703,7 +711,7 @@ static hipError_t launch_compact_plan(const adsa_params& p, adsa_seq* seqs, int3
                                       bool advance_step, const float* vcos_s, hipStream_t st) {
 #define ADSA_PLAN(...)                                                                                                                          \
   ADSA_RANK_LAUNCH(k_compact_plan, ADSA_SHAPE(__VA_ARGS__), lo32(seqs), lo32(keep_map), lo32(plan), lo32(vcos_s), hi16s(seqs, keep_map),          \
-                   hi16s(plan, vcos_s), (uint32_t)p.cap, rank_flags(p, advance_step, false), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back,     \
+                   hi16s(plan, vcos_s), (uint32_t)p.cap, rank_flags(p, advance_step, moved_with_cache(p)), p.grid_h * p.grid_w, p.grid_w, p.win_rows_back, \
                    p.win_recent_m, inv_width(p), p.n_heads * p.head_dim)
   if (p.cap <= 256) ADSA_PLAN(256, 1);
   if (p.cap <= 512) ADSA_PLAN(256, 2);
@@ -765,9 +773,6 @@ hipError_t launch_step_finish(const adsa_params& p, adsa_seq* seqs, int32_t* kee
   if (p.cap <= 1024) return launch(k_step_finish<512, 2>, 512);
   return hipErrorInvalidValue;
 }
-
-// (Rows of the fused V-cosine form, two a head, never move: slots are reused.)
-static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap; }
 
 static hipError_t launch_move(const adsa_params& p, const adsa_seq* seqs, const int32_t* keep_map, const int32_t* plan, bool scores, bool advance, hipStream_t st) {
   const dim3 grid(p.n_heads << slice_bits(p), 2, p.n_seq);

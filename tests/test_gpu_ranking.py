@@ -222,3 +222,30 @@ def test_score_rows_move_with_the_cache_rows(heads, cap, D, layout):
             want, now = before[name][b].clone(), getattr(batch, name)[b].cpu()
             want.narrow(axis, 0, n).copy_(before[name][b].index_select(axis, kept))
             assert torch.equal(now.narrow(axis, 0, n), want.narrow(axis, 0, n)), (b, name)
+
+
+@pytest.mark.parametrize("rows", [11, 12, 26])
+@pytest.mark.parametrize("cap", [200, 400, 700, 1500])
+def test_many_sequences_move_their_scores_like_few(cap, rows):
+    """From 129 sequences on the plan of an eviction moves all score rows itself: as the cache move does for a small batch."""
+    P, W, few = cap % 16 + 16, 16, 3
+    s = cap - P
+    wl = WL.get_workload("xl", n_heads=rows, head_dim=64, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
+    g = torch.Generator().manual_seed(cap + rows)
+    score = torch.randint(0, 40, (few, rows, cap), generator=g).float() / 8
+    got = []
+    for n_seq in (few, 129):
+        batch = LayerBatch(params_for(wl, n_seq, cap, score_mode=B.SCORE_ATTN_MASS), DEV)
+        at = torch.arange(n_seq) % few
+        batch.pos.copy_(torch.arange(cap, dtype=torch.int32).expand(n_seq, cap))
+        batch.score.copy_(score[at])
+        h = batch.seqs_host
+        h["n_res"], h["step"], h["grid_origin"], h["n_keep_prefix"] = cap, s, P, P
+        h["budget"] = [0, s // 3, s - 2 * W - 1] * (n_seq // few)
+        batch.upload_seqs()
+        batch.compact()
+        torch.cuda.synchronize()
+        got.append([x.cpu() for x in (batch.keep_map, torch.from_numpy(batch.read_seqs()["n_res"].copy()), batch.score, batch.pos)])
+    for a, b in zip(*got):
+        assert torch.equal(a[at], b)
+    assert len(set(got[0][1].tolist())) == few
