@@ -130,10 +130,10 @@ hipError_t vcos_prepare_kernels();
 extern "C" {
 struct adsa_launch_plan {
   int32_t chunks, waves, heads;       // attention: chunks per list, waves and heads per workgroup
-  int32_t one_launch_eviction;        // adsa_step's row-end eviction is k_compact_step
+  int32_t eviction;                   // a row end of adsa_step: 0 k_compact_plan and _move, 1 k_compact_step, 2 k_step_finish, 3 the attention and _move
   int32_t vcos_split, vcos_tile;      // V-cosine passes
   int32_t wide;                       // attention: the form with 64-bit offsets
 };
 int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out);
-int adsa_step_launches(const adsa_params* p);      // kernels of an adsa_step that evicts by rows and ranks by attention mass: 2, 3 or 4; else 0
+int adsa_step_launches(const adsa_params* p);      // kernels of an adsa_step that evicts by rows and has no pass over V: 2, 3 or 4; else 0
 }

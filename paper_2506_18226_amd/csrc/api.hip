@@ -389,15 +389,17 @@ int adsa_plan_of(const adsa_params* p, adsa_launch_plan* out) {
   if (rc) return rc;
   const AttendPlan a = make_attend_plan(eff);
   const VcosPlan v = make_vcos_plan(eff);
-  *out = {a.n_chunks, a.waves, a.heads, one_launch_compact(eff) ? 1 : 0, v.split ? 1 : 0, v.tile, a.wide ? 1 : 0};
+  const int eviction = rank_in_attend(eff, a, make_workspace(eff, a)) ? 2 : one_launch_compact(eff) ? 1 : plan_in_attend(eff, a) ? 3 : 0;
+  *out = {a.n_chunks, a.waves, a.heads, eviction, v.split ? 1 : 0, v.tile, a.wide ? 1 : 0};
   return ADSA_OK;
 }
 
 int adsa_step_launches(const adsa_params* p) {
   adsa_params eff;
-  if (resolve_params(p, &eff) != ADSA_OK || eff.evict_policy != ADSA_EVICT_ROW_END || eff.score_mode != ADSA_SCORE_ATTN_MASS) return 0;
-  const AttendPlan plan = make_attend_plan(eff);
-  return rank_in_attend(eff, plan, make_workspace(eff, plan)) ? 2 : one_launch_compact(eff) || plan_in_attend(eff, plan) ? 3 : 4;
+  adsa_launch_plan plan;
+  if (resolve_params(p, &eff) != ADSA_OK || eff.evict_policy != ADSA_EVICT_ROW_END || is_vcos(eff) || adsa_plan_of(p, &plan) != ADSA_OK) return 0;
+  const int split = plan.chunks > 1 ? 1 : 0;                // (k_attend_finish)
+  return split + (plan.eviction == 2 ? 2 : plan.eviction == 0 ? 4 : 3);
 }
 
 int adsa_profile_enable(int on) {

@@ -81,7 +81,7 @@ def oracle_step_phases(cfg, st, s, q, k_new, v_new):
 class LaunchPlan(C.Structure):
     """What the library's launch rules decide for a parameter set (csrc/adsa_internal.h): tests ask for it where they claim to
     take a certain way."""
-    _fields_ = [(n, C.c_int32) for n in ("chunks", "waves", "heads", "one_launch_eviction", "vcos_split", "vcos_tile", "wide")]
+    _fields_ = [(n, C.c_int32) for n in ("chunks", "waves", "heads", "eviction", "vcos_split", "vcos_tile", "wide")]
 
 
 def plan_of(params) -> LaunchPlan:

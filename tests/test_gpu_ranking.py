@@ -75,14 +75,14 @@ def test_empty_sequences_touch_no_memory():
     (1, 1, 64, "bf16", 70, "head_major"), (3, 4, 64, "f32", 257, "slot_major"), (2, 3, 128, "bf16", 513, "head_major"),
     (2, 2, 128, "f32", 800, "slot_major"), (1, 5, 64, "bf16", 1025, "head_major"), (16, 32, 64, "bf16", 90, "head_major"),
     (17, 32, 64, "bf16", 90, "head_major"), (1, 2, 64, "bf16", 2049, "head_major")])
-def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, layout):
-    """adsa_step, whose eviction is one launch for small batches, against the split-phase calls on a copy of the same state: the
+def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, layout, score_mode=None):
+    """adsa_step, whose eviction has four forms by the size of the step, against the split-phase calls on a copy of the same state: the
     sequences close a row, stand inside one, are inactive, rejected or empty; everything either of them writes is the same."""
     W, P, R = 10, 7, 1
     H = (cap - P) // W + 3
     rng = np.random.default_rng(cap)
     wl = WL.get_workload("tiny", n_heads=h, head_dim=D, grid_h=H, grid_w=W, prefix_len=P, win_rows_back=R, win_col_radius=2, dtype=dtype)
-    batches = [LayerBatch(params_for(wl, n_seq, cap, layout=layout), DEV) for _ in range(2)]
+    batches = [LayerBatch(params_for(wl, n_seq, cap, score_mode=score_mode, layout=layout), DEV) for _ in range(2)]
     rows = ((cap - P) // W - 1) * W                          # whole rows that fit
     for b in range(n_seq):
         s = rows if b % 4 != 1 else rows - 3                 # this step's query token closes the row, or does not
@@ -90,7 +90,7 @@ def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, 
         k, v = (WL.quantise(wl, rng.standard_normal((n, h, D), dtype=np.float32)) for _ in range(2))
         score = rng.random((h, n)).astype(np.float32)
         for batch in batches:
-            batch.set_sequence(b, k=k, v=v, pos=np.arange(n, dtype=np.int32), score=score, step=s, grid_origin=P,
+            batch.set_sequence(b, k=k, v=v, pos=np.arange(n, dtype=np.int32), score=score[:B.score_rows(batch.params)], step=s, grid_origin=P,
                                budget=(5, s, s // 2, s - 3 * W)[b % 4])
             if b == 5:
                 batch.seqs_host[b]["step"] = -1              # inactive
@@ -99,8 +99,11 @@ def test_a_step_evicts_as_select_attend_and_compact_do(n_seq, h, D, dtype, cap, 
             if b == 7:
                 batch.seqs_host[b]["n_res"], batch.seqs_host[b]["step"] = 0, 0
     one, two = batches
-    # above 1024 workgroups and above 2048 slots adsa_step's eviction is the same two launches as adsa_compact's
-    assert plan_of(one.params).one_launch_eviction == (n_seq <= 16 and cap <= 2048)
+    # above 2048 slots adsa_step's eviction is the same two launches as adsa_compact's; above 1024 workgroups the attention plans it; up to 1024
+    # slots, for whole lists and where the workspace has room for the scores it is k_step_finish; k_compact_step otherwise
+    plan = plan_of(one.params)
+    own = score_mode is None and n_seq <= 3 and cap <= 1024 and plan.chunks == 1
+    assert plan.eviction == (0 if cap > 2048 else 3 if n_seq > 16 else 2 if own else 1)
     for batch in batches:
         batch.seqs_host["compacted"] = 1
         batch.upload_seqs()
@@ -188,6 +191,12 @@ def test_more_sequences_than_compute_units_rank_like_few(cap):
 @pytest.mark.parametrize("cap", [256, 512, 768, 1024, 2048])
 def test_a_step_evicts_lists_that_fill_its_tile(cap):
     test_a_step_evicts_as_select_attend_and_compact_do(2, 3, 64, "bf16", cap, "head_major")
+
+
+@pytest.mark.parametrize("cap", [256, 512, 768, 1024])
+def test_a_step_of_given_scores_evicts_lists_that_fill_its_tile(cap):
+    """Scores of the caller's leave these lists to k_compact_step."""
+    test_a_step_evicts_as_select_attend_and_compact_do(2, 3, 64, "bf16", cap, "head_major", B.SCORE_EXT_LARGEST)
 
 
 @pytest.mark.parametrize("heads", [11, 12, 13])
