@@ -284,7 +284,8 @@ int adsa_step_static(const adsa_params* p, adsa_seq* seqs, const void* q, const 
                      int32_t* keep_map, uint32_t flags, void* stream);
 
 /* Timing hook for benchmarks: when enabled, adsa_attend/adsa_step attach a start and a stop HIP
-   event to every attention-kernel dispatch on the caller's stream.  adsa_profile_read
+   event to every attention-kernel dispatch on the caller's stream (in adsa_step, where that kernel ranks for itself or plans
+   evictions, those are part of it; kernels that merge split lists are not).  adsa_profile_read
    synchronises those events and returns, through its arguments, the number of timed launches and
    their summed duration in milliseconds since the last adsa_profile_enable(1); [host] pointers.
    adsa_profile_enable(0) switches the hook off and destroys its events.  Process-wide state, not thread-safe. */

@@ -223,7 +223,8 @@ __device__ __forceinline__ T elem(const ADSA_GLOBAL T* base, uint32_t i) { retur
 
 // v[u] = sum over the score rows of slot idx[u], ascending row order, plain fp32 adds.  The loads of all slots and of two
 // batches of rows are in flight together: one memory round trip for up to 2 * RB + 1 rows.
-// SHARED: by loads that see what other workgroups of the same launch have stored with scope agent, whichever XCD they ran on.
+// SHARED: by loads that see what other workgroups of the same launch have stored with scope agent, whichever XCD they ran on.  All reads
+// of score[] in such a launch have to be these: a plain one may find an older line in its own L2.
 template <bool SHARED>
 __device__ __forceinline__ float score_at(const gfloat* row, uint32_t i) {
   if constexpr (SHARED) return __hip_atomic_load((const gfloat*)((const gchar*)row + i * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -2,7 +2,7 @@
 // attention over the selected slots, plus the cache append (Section 4.2) and the per-head
 // attention-mass update, in ONE launch.
 //
-//  k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE> : grid (token chunk, HT heads, sequence), NW waves.
+//  k_attend<EB, D, HT, U, NW, VF, DIRECT, WIDE, RANK, PLAN> : grid (token chunk, HT heads, sequence), NW waves.
 //    HT = 1: a 16-byte-per-lane streaming load of one wave covers RPW = 64 / (D*EB/16) consecutive tokens of ONE head.
 //    That holds for [slot][head][D] caches too: a row is 128 bytes or more, whole cache lines, so a workgroup that
 //    walks one head's rows at a stride fetches nothing it does not use.  But it visits every page of the sequence for its
@@ -12,12 +12,19 @@
 //    registers, fp32, log2 domain.  The lane groups of a wave merge in registers (DPP and 16-/32-lane
 //    swaps), the waves through one small LDS record each.
 //    With one chunk per (sequence, head) the workgroup writes out / lse itself and adds the probabilities it produced
-//    to its OWN head's row of score[]: no workgroup ever talks to another one.
+//    to its OWN head's row of score[].  Except with PLAN no workgroup ever talks to another one of its launch.
 //    With several chunks, each writes a partial and the scaled logits to the workspace and a second kernel,
 //    k_attend_finish, merges them and updates the scores.
 //    VF (ADSA_SCORE_VCOS_FUSED): every V row that streams through also yields its head's share of |v|^2
 //    and of v.u (u = running sum of the candidates' normalised V, Eq. 2-3), stored per (head, slot): the
 //    next eviction ranks from them instead of re-reading V.
+//    RANK: the ranking of a small decode step too.  The workgroup leaves score[], pos and the record as they are and writes the new scores of
+//    its head, of all resident slots, to the workspace; k_step_finish, the next kernel, puts them in place.
+//    PLAN: the eviction plans of larger steps too, by the last workgroup of a sequence that closed a row, from scores that the sequence's other
+//    workgroups have just stored, on any XCD.  What orders this is the hardware alone: score[] is stored and loaded with scope agent, past
+//    the L2s; a thread's stores are acknowledged (s_waitcnt vmcnt(0)) and its workgroup's threads have met before the relaxed ticket
+//    is drawn, and nothing is loaded before the last one has come back.  A plain store or load of score[] of such a sequence, in the
+//    update or in plan_row_end, would be a race; pos, the record and the list come from earlier launches and are read plainly.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
