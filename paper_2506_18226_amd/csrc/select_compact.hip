@@ -198,11 +198,12 @@ __device__ __forceinline__ void move_scores(gfloat* score, gint* pos, int rows, 
 // 38.7 | 34.7, 3 x 30 x 340 18.6 | 16.6, 52 x 28 x 600 57.1 | 53.3, 20 shapes by 1.05; a step of 64 x 24 x 600 with 2 sequences at a row end
 // 54.0 | 52.6.  Fewer rows and shorter lists cost the plan less than those workgroups: one row, 4 x 9 x 6600 37.2 | 39.1, 443 x 1 x 377 fp32
 // 23.9 | 24.7; 6 rows, 81 x 6 x 253 17.8 | 18.5; 8, a step of 200 x 8 x 250 34.2 | 34.5; 60 slots, 83 x 43 fp32 37.0 | 39.2, 406 x 12 30.2 | 31.4.
-// With many sequences the plan launch is no chain that the chip idles through any more, and finds the rows it has just ranked in its L2.  All at a
-// row end, as the layers of one model are, 400 sequences x 16 x 300 102 | 106, 1000 x 16 x 300 239 | 253, 800 x 12 x 300 147 | 153, 192 x 16 x 300 by
-// 1.03, 700 x 12 x 480 by 1.02, but 128 x 16 x 300 by 1.01 and 128 x 24 x 300 by 0.99.  (One in 20 at a row end: the move stays ahead, 128 x 24 x 300 by 1.11,
-// 400 x 24 x 300 by 1.07.)
-constexpr int kMovedWithCache = 12, kPlanRowsCap = 128, kPlanRowsSeqs = 128;
+// With more than 128 sequences the plan launch is no chain that the chip idles through any more, and finds the rows it has just ranked in its L2:
+// there it keeps fewer than 24 rows, and all of them in caches of 257 to 384 slots, which the move takes in a tile of 512.  All sequences at a
+// row end, as the layers of one model are, plan | move: 400 sequences x 16 x 300 102 | 106, 1000 x 16 x 300 239 | 253, 800 x 12 x 300 147 | 153; by (plan /
+// move) 400 x 24 x 300 0.98, 700 x 12 x 480 0.98, 700 x 20 x 450 0.98, but 128 x 16 x 300 1.01, 400 x 24 x 512 1.04, 400 x 32 x 600 1.02, 160 x 24 x 700 1.03,
+// 512 x 24 x 696 1.01.  (One in 20 at a row end: the move is ahead everywhere, by 1.02 to 1.2.)
+constexpr int kMovedWithCache = 12, kPlanRowsCap = 128, kPlanRowsSeqs = 128, kManyRows = 24;
 
 // plan[b] = { old n_res, first slot that moves, did compact, new n_res }
 template <int NT, int S, int RB = rank_batch(S)>
@@ -699,7 +700,10 @@ hipError_t launch_select(const adsa_params& p, adsa_seq* seqs, int32_t* sel_idx,
 }
 
 // (Rows of the fused V-cosine form, two a head, never move: slots are reused.)
-static bool moved_with_cache(const adsa_params& p) { return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap && p.n_seq <= kPlanRowsSeqs; }
+static bool moved_with_cache(const adsa_params& p) {
+  return score_rows(p) >= kMovedWithCache && p.cap > kPlanRowsCap &&
+         (p.n_seq <= kPlanRowsSeqs || (score_rows(p) >= kManyRows && (p.cap <= 256 || p.cap > 384)));
+}
 
 // k_compact_plan: 512 sequences x 24 rows x 696 slots at a row end 15.3 us (32.7 with keys in LDS), 512 x 48 rows x 632 of the
 // fused V-cosine form 13.6 us (36.9: its loop over the heads waited for every pair of rows).  It needs more registers than

@@ -235,9 +235,10 @@ def test_score_rows_move_with_the_cache_rows(heads, cap, D, layout):
 
 
 @pytest.mark.parametrize("rows", [11, 12, 26])
-@pytest.mark.parametrize("cap", [200, 400, 700, 1500])
+@pytest.mark.parametrize("cap", [120, 200, 300, 400, 700, 1500])
 def test_many_sequences_move_their_scores_like_few(cap, rows):
-    """From 129 sequences on the plan of an eviction moves all score rows itself: as the cache move does for a small batch."""
+    """From 129 sequences on the plan of an eviction moves fewer than 24 score rows itself, and in caches of 257 to 384 slots all of them: as the
+    cache move does for a small batch."""
     P, W, few = cap % 16 + 16, 16, 3
     s = cap - P
     wl = WL.get_workload("xl", n_heads=rows, head_dim=64, grid_h=s // W, grid_w=W, prefix_len=P, win_rows_back=1, win_col_radius=2)
